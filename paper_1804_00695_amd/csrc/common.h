@@ -253,14 +253,25 @@ __device__ __forceinline__ int dpp_move(int v)
     return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
 }
 
+// DPP broadcasts of the last lane of a 16-lane row to the next row (row_bcast:15,
+// written to rows 1 and 3) and of lane 31 to the upper half (row_bcast:31):
+// they carry a row's prefix into the rows after it.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_bcast(int v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
+}
+
 template <int G, typename T>
 __device__ __forceinline__ T group_sum(T v)
 {
-    if constexpr (G <= 16 && sizeof(T) == 4 && T(-1) < T(0)) {
+    if constexpr (sizeof(T) == 4 && T(-1) < T(0)) {
         if constexpr (G >= 2) v += dpp_move<0xB1>(v);    // quad_perm [1,0,3,2]: lane ^ 1
         if constexpr (G >= 4) v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]: lane ^ 2
         if constexpr (G >= 8) v += dpp_move<0x141>(v);   // row_half_mirror: the other quad of 8
         if constexpr (G >= 16) v += dpp_move<0x140>(v);  // row_mirror: the other half of 16
+        if constexpr (G >= 32) v += __shfl_xor(v, 16, G);
+        if constexpr (G >= 64) v += __shfl_xor(v, 32, G);
         return v;
     } else {
 #pragma unroll
@@ -274,6 +285,7 @@ template <int G>
 __device__ __forceinline__ int group_total(int v, int incl)
 {
     if constexpr (G <= 16) return group_sum<G>(v);
+    else if constexpr (G == 64) return __builtin_amdgcn_readlane(incl, 63);
     else return __shfl(incl, G - 1, G);
 }
 
@@ -301,21 +313,15 @@ __device__ __forceinline__ int group_rank(int key, int lane)
 template <int G>
 __device__ __forceinline__ int group_scan_incl(int v, int lane)
 {
-    if constexpr (G <= 16) {
-        int y;
-        if constexpr (G >= 2) { y = dpp_move<0x111>(v); if (lane >= 1) v += y; }   // row_shr:1
-        if constexpr (G >= 4) { y = dpp_move<0x112>(v); if (lane >= 2) v += y; }   // row_shr:2
-        if constexpr (G >= 8) { y = dpp_move<0x114>(v); if (lane >= 4) v += y; }   // row_shr:4
-        if constexpr (G >= 16) { y = dpp_move<0x118>(v); if (lane >= 8) v += y; }  // row_shr:8
-        return v;
-    } else {
-#pragma unroll
-        for (int o = 1; o < G; o <<= 1) {
-            const int y = __shfl_up(v, o, G);
-            if (lane >= o) v += y;
-        }
-        return v;
-    }
+    int y;
+    const int l16 = lane & 15;
+    if constexpr (G >= 2) { y = dpp_move<0x111>(v); if (l16 >= 1) v += y; }   // row_shr:1
+    if constexpr (G >= 4) { y = dpp_move<0x112>(v); if (l16 >= 2) v += y; }   // row_shr:2
+    if constexpr (G >= 8) { y = dpp_move<0x114>(v); if (l16 >= 4) v += y; }   // row_shr:4
+    if constexpr (G >= 16) { y = dpp_move<0x118>(v); if (l16 >= 8) v += y; }  // row_shr:8
+    if constexpr (G >= 32) v += dpp_bcast<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+    if constexpr (G >= 64) v += dpp_bcast<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+    return v;
 }
 
 // Row at position pos of perm, or -1 (and an error bit) when the position or
