@@ -248,6 +248,13 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(
 {
     constexpr int kNumDepth = NumShape<G, CAP, PACK, MULTI, FLAT>::DEPTH;
     constexpr bool PF = NumShape<G, CAP, PACK, MULTI, FLAT>::PF;
+    // Where a wave owns a row, rows of B are long (the host picks G from their
+    // mean length) and often longer than G: a staged chunk is cut into steps
+    // of at most G entries of one row of B each, so that every step takes the
+    // batched path. (One step at a time through a long row chains load, lookup
+    // and load per 64 entries: numeric phase of the restriction times the
+    // 81-point elasticity operator on 48^3 nodes 1050 us, in steps 711 us.)
+    constexpr bool LONG = G == kWave && !FLAT;
     static_assert(FLAT || G % kNumDepth == 0, "the staged entries are read kNumDepth at a time");
     constexpr int W = kWave / G;
     constexpr int XW = FLAT ? num_flat_words(G) : 0;
@@ -358,10 +365,19 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(
         const int pe_w = skip ? ps : pe;
         // stage a chunk: (q0, q1, a) of its entry pc + lane, from the B row
         // pointers as loaded; FLAT: the group's pair offsets and pair count
+        int eq0 = 0, eq1 = 0;   // LONG: this lane's entry of the chunk
+        double ea = 0.0;
         auto stage = [&](int q0r, int q1r, double a) -> int {
             const int sq0 = q0r - b_off, sq1 = q1r - b_off;
-            par[lane] = make_int4(sq0, sq1, __double2loint(a), __double2hiint(a));
             int tot = 0;
+            if constexpr (LONG) {
+                eq0 = sq0;
+                eq1 = sq1;
+                ea = a;
+                asm volatile("" : "+v"(ea));   // waited for here, not where the two ways join
+                return tot;
+            }
+            par[lane] = make_int4(sq0, sq1, __double2loint(a), __double2hiint(a));
             if constexpr (FLAT) {
                 const int np = sq1 > sq0 ? sq1 - sq0 : 0;
                 const int incl = group_scan_incl<G>(np, lane);
@@ -460,32 +476,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(
                     }
                 }
             }
-            for (int u0 = 0; u0 < n; u0 += kNumDepth) {
-                // issue the B loads of kNumDepth steps, then accumulate them in order.
-                // The staged entries are read together (all G are written every
-                // chunk, those past the row as empty ranges, and G is a multiple of
-                // kNumDepth).
-                int2 qr[kNumDepth];
-#pragma unroll
-                for (int d = 0; d < kNumDepth; ++d) qr[d] = *(const int2 *)(par + u0 + d);
-                bool longs = false;   // a step whose row of B is longer than G
-#pragma unroll
-                for (int d = 0; d < kNumDepth; ++d) longs |= qr[d].y - qr[d].x > G;
-                if (__ballot(longs)) {
-                    // one step at a time, each through all of its row of B: its
-                    // entries have distinct columns, so the order is kept
-#pragma unroll 1
-                    for (int d = 0; d < kNumDepth; ++d) {
-                        const int4 pr = par[u0 + d];
-                        const double a = __hiloint2double(pr.w, pr.z);
-                        for (int q = pr.x + lane; q < pr.y; q += G) {
-                            const int pos = tab.lookup(logcap, bci[q]);
-                            if (pos >= 0) atomicAdd(acc + pos, a * bval[q]);
-                            else bad = true;
-                        }
-                    }
-                    continue;
-                }
+            // kNumDepth staged steps, no row of B longer than G: their B loads are
+            // issued together, then accumulated in step order
+            auto batch = [&](int u0, const int2 (&qr)[kNumDepth]) {
                 int jv[kNumDepth];
                 double bv[kNumDepth], av[kNumDepth];
                 // lanes past their row of B load the all-ones dummy instead
@@ -519,6 +512,56 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(
                     if (posv[d] >= 0) atomicAdd(acc + posv[d], av[d] * bv[d]);
                     else if (posv[d] == -1) bad = true;
                 }
+            };
+            if constexpr (LONG) {
+                // the chunk's steps, G staged at a time: a lane writes those of its
+                // own entry (an empty row of B has none)
+                const int ns = eq1 > eq0 ? (eq1 - eq0 + G - 1) / G : 0;
+                const int incl = group_scan_incl<G>(ns, lane);
+                const int steps = group_total<G>(ns, incl);
+                const int st = incl - ns;
+                for (int s0 = 0; s0 < steps; s0 += G) {
+                    const int nst = min(G, steps - s0);
+                    const int x1 = min(st + ns, s0 + G);
+                    for (int x = max(st, s0); x < x1; ++x)
+                        par[x - s0] = make_int4(eq0 + (x - st) * G, eq1, __double2loint(ea), __double2hiint(ea));
+                    if (lane >= nst) par[lane] = make_int4(0, 0, 0, 0);
+                    nwave_sync();
+                    for (int u0 = 0; u0 < nst; u0 += kNumDepth) {
+                        int2 qr[kNumDepth];
+#pragma unroll
+                        for (int d = 0; d < kNumDepth; ++d) qr[d] = *(const int2 *)(par + u0 + d);
+                        batch(u0, qr);
+                    }
+                    nwave_sync();
+                }
+            }
+            for (int u0 = 0; !LONG && u0 < n; u0 += kNumDepth) {
+                // The staged entries are read together (all G are written every
+                // chunk, those past the row as empty ranges, and G is a multiple of
+                // kNumDepth).
+                int2 qr[kNumDepth];
+#pragma unroll
+                for (int d = 0; d < kNumDepth; ++d) qr[d] = *(const int2 *)(par + u0 + d);
+                bool longs = false;   // a step whose row of B is longer than G
+#pragma unroll
+                for (int d = 0; d < kNumDepth; ++d) longs |= qr[d].y - qr[d].x > G;
+                if (__ballot(longs)) {
+                    // one step at a time, each through all of its row of B: its
+                    // entries have distinct columns, so the order is kept
+#pragma unroll 1
+                    for (int d = 0; d < kNumDepth; ++d) {
+                        const int4 pr = par[u0 + d];
+                        const double a = __hiloint2double(pr.w, pr.z);
+                        for (int q = pr.x + lane; q < pr.y; q += G) {
+                            const int pos = tab.lookup(logcap, bci[q]);
+                            if (pos >= 0) atomicAdd(acc + pos, a * bval[q]);
+                            else bad = true;
+                        }
+                    }
+                    continue;
+                }
+                batch(u0, qr);
             }
             nwave_sync();
         }
