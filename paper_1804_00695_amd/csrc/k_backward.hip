@@ -641,8 +641,11 @@ void launch_backward(const Batch &b, const Sched &sc, const double *wval, double
     case 64: launch_bwd_class<64, kFillCap[1]>(b, sc, 1, dA, dB, s); break;
     default: launch_bwd_class<32, kFillCap[1]>(b, sc, 1, dA, dB, s); break;
     }
-    if (G >= 64) launch_bwd_class<64, kFillCap[2]>(b, sc, 2, dA, dB, s);
-    else launch_bwd_class<32, kFillCap[2]>(b, sc, 2, dA, dB, s);
+    // the pairs are flattened, so lanes are filled whatever the rows of B: from
+    // the 1024-slot class on, a whole wave per row (one row's LDS per wave)
+    // keeps the most waves resident (300000 rows of about 160 outputs: 32
+    // lanes 1250-1365 us, 64 lanes 841-911 us)
+    launch_bwd_class<64, kFillCap[2]>(b, sc, 2, dA, dB, s);
     launch_bwd_class<64, kFillCap[3]>(b, sc, 3, dA, dB, s);
     launch_bwd_class<64, kFillCap[4]>(b, sc, 4, dA, dB, s);
     constexpr int NWW = nw_bwd(bwd_win_bytes(kBwdWinCap), 1);
