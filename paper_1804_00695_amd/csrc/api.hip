@@ -227,11 +227,13 @@ spgemm_status prepare_batch(int32_t nbatch, const spgemm_csr *A, const spgemm_cs
         key.push_back((uint64_t)B[t].nnz);
         key.push_back(C ? (uint64_t)(uintptr_t)C[t].row_ptr : 0ull);
     }
-    if (!upload) return nbatch == 1 ? SPGEMM_OK : SPGEMM_ERR_INVALID_ARG;
+    // a single product goes to the kernels by value, its entry counts included
+    if (nbatch == 1) return SPGEMM_OK;
+    if (!upload) return SPGEMM_ERR_INVALID_ARG;
     hipError_t e = hipSuccess;
     e = hipMemcpyAsync(ws + out.layout.nnz_tab, out.nnz_tab.data(), sizeof(int64_t) * out.nnz_tab.size(),
                        hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && nbatch > 1) {
+    if (e == hipSuccess) {
         e = hipMemcpyAsync(ws + out.layout.probs, out.probs.data(), sizeof(Prob) * nbatch, hipMemcpyHostToDevice, s);
         if (e == hipSuccess)
             e = hipMemcpyAsync(ws + out.layout.abase, out.abase.data(), sizeof(int32_t) * (nbatch + 1),
@@ -250,6 +252,45 @@ int choose_group(double avg)
     return pow2_group(avg);
 }
 
+// CSR checks of the operands, queued; the kernels behind them return at once
+// when they fail (bad_csr). B is not checked again when every B_t is A_t itself.
+static void queue_validate(const BatchHost &bh, char *ws, uint32_t *err, hipStream_t s)
+{
+    bool same = true;
+    for (int t = 0; t < bh.batch.nprob && same; ++t) {
+        const Prob &q = bh.probs[t];
+        same = q.arp == q.brp && q.aci == q.bci && q.nrows == q.krows && q.ncols == q.krows &&
+               q.a_off == q.b_off && bh.nnz_tab[2 * t] == bh.nnz_tab[2 * t + 1];
+    }
+    const int64_t *tab = bh.batch.nprob > 1 ? (const int64_t *)(ws + bh.layout.nnz_tab) : nullptr;
+    launch_validate(bh.batch, same ? 0 : 2, tab, bh.nnz_tab[0], bh.nnz_tab[1], err, s);
+}
+
+// Waits for a count pass: error word and nnz of every product, in one copy
+// (the header, which begins with the error word, and the totals behind it).
+static spgemm_status read_counts(BatchHost &bh, char *ws, int64_t *nnz_host, hipStream_t s)
+{
+    const Layout &L = bh.layout;
+    const int np = bh.batch.nprob;
+    static_assert(kHdrErr == 0 && kHdrBytes % sizeof(int64_t) == 0, "read as one block");
+    const size_t words = (L.totals - L.hdr) / sizeof(int64_t);
+    std::vector<int64_t> got(words + (size_t)np, 0);
+    hipError_t e = hipMemcpyAsync(got.data(), ws + L.hdr, sizeof(int64_t) * got.size(), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_fail(e);
+    uint32_t err = 0;
+    std::memcpy(&err, got.data(), sizeof(err));
+    if (err & kErrBadCsr) return err_status(err);
+    int64_t *tot = got.data() + words;
+    // products with no rows never write their total
+    for (int t = 0; t < np; ++t)
+        if (bh.probs[t].nrows == 0) tot[t] = 0;
+    if (nnz_host) std::memcpy(nnz_host, tot, sizeof(int64_t) * (size_t)np);
+    for (int t = 0; t < np; ++t)
+        if (tot[t] >= 0x7fffffffLL) return SPGEMM_ERR_INDEX_OVERFLOW;
+    return err_status(err);
+}
+
 // Symbolic count or fill over a prepared batch.
 spgemm_status run_symbolic(BatchHost &bh, char *ws, int fill, int64_t *nnz_host, hipStream_t s)
 {
@@ -260,28 +301,21 @@ spgemm_status run_symbolic(BatchHost &bh, char *ws, int fill, int64_t *nnz_host,
         reuse = fill && g_memo.valid && g_memo.ws == ws && g_memo.key == bh.key;
         if (g_memo.ws == ws) g_memo.valid = false;
     }
+    // few columns: dense bitmaps in place of compression, binning and hash
+    // tables (the test knobs that choose a path or class keep those)
+    const bool bits = symbit_fits(bh.batch) && !g_opt.force_spill && g_opt.force_class < 0;
     if (fill && !reuse) L.has_scratch = false;   // nothing to expand: recompute every row
     Sched sc = make_sched(ws, L);
     reset_header(ws, L, s);
-    if (!fill && g_opt.validate) {
-        launch_validate(bh.batch, 0, (const int64_t *)(ws + L.nnz_tab), sc.err, s);
-        // B is checked by the same rules as A: skip it when every B_t is A_t itself
-        bool same = true;
-        for (int t = 0; t < bh.batch.nprob && same; ++t) {
-            const Prob &q = bh.probs[t];
-            same = q.arp == q.brp && q.aci == q.bci && q.nrows == q.krows && q.ncols == q.krows &&
-                   q.a_off == q.b_off && bh.nnz_tab[2 * t] == bh.nnz_tab[2 * t + 1];
-        }
-        if (!same) launch_validate(bh.batch, 1, (const int64_t *)(ws + L.nnz_tab), sc.err, s);
-        spgemm_status st = check_launch();
-        if (st != SPGEMM_OK) return st;
-        st = read_errors(ws, L, s);
-        if (st != SPGEMM_OK) return st;
+    if (!fill && g_opt.validate) queue_validate(bh, ws, sc.err, s);
+    if (bits) {
+        launch_symbit(bh.batch, sc, fill, s);
+    } else {
+        if (!reuse) launch_compress(bh.batch, sc.err, s);
+        launch_bin(bh.batch, fill ? kModeFill : kModeCount, sc, bin_force(), nullptr, s);
+        if (fill) launch_sym_expand(bh.batch, sc, s);
+        launch_symbolic(bh.batch, sc, fill, choose_group(bh.avg_a), s);
     }
-    if (!reuse) launch_compress(bh.batch, s);
-    launch_bin(bh.batch, fill ? kModeFill : kModeCount, sc, bin_force(), nullptr, s);
-    if (fill) launch_sym_expand(bh.batch, sc, s);
-    launch_symbolic(bh.batch, sc, fill, choose_group(bh.avg_a), s);
     spgemm_status st = check_launch();
     if (st != SPGEMM_OK) return st;
     if (fill) {
@@ -293,25 +327,17 @@ spgemm_status run_symbolic(BatchHost &bh, char *ws, int fill, int64_t *nnz_host,
     }
     for (int t = 0; t < bh.batch.nprob; ++t)
         if (bh.probs[t].nrows == 0) launch_fill_i32(bh.probs[t].crp, 0, 1, s);
-    int64_t *prefix = (int64_t *)(ws + L.prefix);
-    launch_scan(sc.val, bh.batch.na, (int64_t *)(ws + L.tiles), prefix, s);
-    launch_write_rowptr(bh.batch, prefix, (int64_t *)(ws + L.totals), sc.err, s);
+    if (bits && bh.batch.na > 0 && bh.batch.na <= kRowptrSmallRows) {
+        launch_rowptr_small(bh.batch, sc.val, (int64_t *)(ws + L.totals), sc.err, s);
+    } else {
+        int64_t *prefix = (int64_t *)(ws + L.prefix);
+        launch_scan(sc.val, bh.batch.na, (int64_t *)(ws + L.tiles), prefix, s);
+        launch_write_rowptr(bh.batch, prefix, (int64_t *)(ws + L.totals), sc.err, s);
+    }
     st = check_launch();
     if (st != SPGEMM_OK) return st;
-    std::vector<int64_t> tot(bh.batch.nprob, 0);
-    uint32_t err = 0;
-    hipError_t e = hipMemcpyAsync(tot.data(), ws + L.totals, sizeof(int64_t) * tot.size(), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&err, ws + L.hdr + kHdrErr, sizeof(err), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(e);
-    // products with no rows never write their total
-    for (int t = 0; t < bh.batch.nprob; ++t)
-        if (bh.probs[t].nrows == 0) tot[t] = 0;
-    if (nnz_host) std::memcpy(nnz_host, tot.data(), sizeof(int64_t) * tot.size());
-    for (int t = 0; t < bh.batch.nprob; ++t)
-        if (tot[t] >= 0x7fffffffLL) return SPGEMM_ERR_INDEX_OVERFLOW;
-    st = err_status(err);
-    if (st == SPGEMM_OK) {
+    st = read_counts(bh, ws, nnz_host, s);
+    if (st == SPGEMM_OK && !bits) {
         std::lock_guard<std::mutex> lk(g_memo_mu);
         g_memo.ws = ws; g_memo.key = bh.key; g_memo.valid = true;
     }
@@ -464,7 +490,7 @@ spgemm_status spgemm_compress(const spgemm_csr *B, uint32_t *words, int32_t *cou
     b.p0.bwc = count;
     b.p0.ncols = B->ncols;
     b.p0.krows = B->nrows;
-    launch_compress(b, stream);
+    launch_compress(b, nullptr, stream);
     return check_launch();
 }
 

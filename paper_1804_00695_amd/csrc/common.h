@@ -124,6 +124,15 @@ __device__ __forceinline__ MLS_G T *gpw(T *p)
     return (MLS_G T *)(p);
 }
 
+// Whether the CSR check that ran before on this stream refused the operands:
+// every kernel queued behind it that follows their indices, or that works on
+// what such a kernel would have written, returns at once then, so the host
+// reads the verdict back once, with the result. err may be NULL (no check).
+__device__ __forceinline__ bool bad_csr(const uint32_t *err)
+{
+    return err && (*gp(err) & kErrBadCsr) != 0u;
+}
+
 __device__ __forceinline__ int find_prob(const int32_t *base, int nprob, int g)
 {
     // largest t with base[t] <= g

@@ -74,11 +74,19 @@ __device__ __forceinline__ void validate_group_rows(unsigned long long mm, int l
     }
 }
 
-__global__ __launch_bounds__(kWG) void k_validate(Batch b, int which, const int64_t *nnz_tab, uint32_t *err)
+// which = 0: the A rows; 1: the B rows; 2: the A rows by the first a_blocks
+// workgroups, the B rows by the others.
+__global__ __launch_bounds__(kWG) void k_validate(Batch b, int which, const int64_t *nnz_tab, int64_t nnz_a,
+                                                  int64_t nnz_b, int a_blocks, uint32_t *err)
 {
     const int lane = threadIdx.x & 63;
+    int blk = (int)blockIdx.x;
+    if (which == 2) {
+        which = blk < a_blocks ? 0 : 1;
+        if (which) blk -= a_blocks;
+    }
     const int total = which == 0 ? b.na : b.nb;
-    const int g = blockIdx.x * kWG + threadIdx.x;
+    const int g = blk * kWG + (int)threadIdx.x;
     bool bad = false, longrow = false, midrow = false;
     const int32_t *ci_row = nullptr;   // entries of this thread's row (long rows)
     int len = 0, ncols = 0;
@@ -93,7 +101,7 @@ __global__ __launch_bounds__(kWG) void k_validate(Batch b, int which, const int6
         const int off = which == 0 ? P.a_off : P.b_off;
         ncols = which == 0 ? P.k_hi : P.ncols;
         const int nrows = which == 0 ? P.nrows : P.krows;
-        const int64_t nnz = gp(nnz_tab)[2 * t + which];
+        const int64_t nnz = nnz_tab ? gp(nnz_tab)[2 * t + which] : (which == 0 ? nnz_a : nnz_b);
         const int s = rp[i], e = rp[i + 1];
         if (i == 0 && s != off) bad = true;
         if (i == nrows - 1 && (int64_t)e - off != nnz) bad = true;
@@ -231,8 +239,9 @@ __device__ __forceinline__ void compress_group_rows(unsigned long long mm, int l
     }
 }
 
-__global__ __launch_bounds__(kWG) void k_compress(Batch b)
+__global__ __launch_bounds__(kWG) void k_compress(Batch b, const uint32_t *err)
 {
+    if (bad_csr(err)) return;
     __shared__ uint32_t s_set[kWG / kWave][kWave + 1];
     __shared__ uint32_t s_msk[kWG / kWave][kWave + 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -448,6 +457,7 @@ __global__ __launch_bounds__(kWG) void k_bin(Batch b, int mode, Sched sc, int fo
     __shared__ int s_long[kBinMaxLong];
     __shared__ int s_nlong;
     __shared__ int64_t s_red[kWG / kWave];
+    if (bad_csr(sc.err)) return;
     if (threadIdx.x < kNumBins) cnt[threadIdx.x] = 0;
     if (threadIdx.x == 0) { tsum = 0; s_nlong = 0; }
     __syncthreads();
@@ -572,6 +582,7 @@ __global__ __launch_bounds__(kScanWG) void k_bin_scan(Sched sc, int nb)
 {
     static_assert(kNumBins * kScanHalves <= kScanWG / kWave, "a wave per bin and half");
     __shared__ int s_tot[kNumBins * kScanHalves];
+    if (bad_csr(sc.err)) return;
     MLS_G int32_t *blk = gpw(sc.blk_cnt);
     const int stride = sc.nblk;
     const int nblk = nb < stride ? nb : stride;
@@ -628,6 +639,7 @@ __global__ __launch_bounds__(kWG) void k_scatter(int na, Sched sc, int nb, int f
     __shared__ int s_wcnt[kWG / kWave][kNumBins];
     __shared__ int s_base[kNumBins];
     __shared__ int s_tot[kNumBins];
+    if (bad_csr(sc.err)) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int me = (int)blockIdx.x;
     if (fold) {
@@ -770,6 +782,7 @@ __global__ void k_scan_apply(const int32_t *val, int n, const int64_t *tile_off,
 // Row pointers of every product from the global prefix; totals[t] = nnz(C_t).
 __global__ void k_write_rowptr(Batch b, const int64_t *prefix, int64_t *totals, uint32_t *err)
 {
+    if (bad_csr(err)) return;
     int g = blockIdx.x * blockDim.x + threadIdx.x;
     const int t = b.nprob == 1 ? 0 : find_prob_rows(b.abase, b.nprob, g - (int)(threadIdx.x & 63), g);
     if (g >= b.na) return;
@@ -804,19 +817,21 @@ void launch_fill_f64(double *p, double v, int64_t n, hipStream_t s)
     hipLaunchKernelGGL(k_fill_f64, dim3(grid), dim3(kWG), 0, s, p, v, n);
 }
 
-void launch_validate(const Batch &b, int which, const int64_t *nnz_tab, uint32_t *err, hipStream_t s)
+void launch_validate(const Batch &b, int which, const int64_t *nnz_tab, int64_t nnz_a, int64_t nnz_b, uint32_t *err,
+                     hipStream_t s)
 {
-    int n = which == 0 ? b.na : b.nb;
-    if (n <= 0) return;
+    const int a_blocks = which == 1 ? 0 : nblk(b.na, kWG), b_blocks = which == 0 ? 0 : nblk(b.nb, kWG);
+    if (a_blocks + b_blocks <= 0) return;
     ProfScope ps("validate", s);
-    hipLaunchKernelGGL(k_validate, dim3(nblk(n, kWG)), dim3(kWG), 0, s, b, which, nnz_tab, err);
+    hipLaunchKernelGGL(k_validate, dim3(a_blocks + b_blocks), dim3(kWG), 0, s, b, which, nnz_tab, nnz_a, nnz_b,
+                       a_blocks, err);
 }
 
-void launch_compress(const Batch &b, hipStream_t s)
+void launch_compress(const Batch &b, const uint32_t *err, hipStream_t s)
 {
     if (b.nb <= 0) return;
     ProfScope ps("compress", s);
-    hipLaunchKernelGGL(k_compress, dim3(nblk(b.nb, kWG)), dim3(kWG), 0, s, b);
+    hipLaunchKernelGGL(k_compress, dim3(nblk(b.nb, kWG)), dim3(kWG), 0, s, b, err);
 }
 
 void launch_bin(const Batch &b, int mode, const Sched &sc, int force, unsigned long long *total,

@@ -1,0 +1,347 @@
+// k_symbit.hip -- symbolic phase (Sec. 2.1) of products whose C has few
+// columns: the union of the rows B_k, k in row i of A, as a dense bitmap over
+// C's columns in LDS, one wave per row and straight from B's column indices.
+// No compression of B, no binning and no hash tables: the count pass is one
+// launch over the rows and one over the rows set aside, the fill pass the
+// same two, and columns come out of the bitmap in ascending order.
+//
+// What bounds it: latency for small products (each launch of the binned path
+// costs its 2-20 us run or at least 4.7 us of stream time, and there are 14
+// in a count pass), LDS atomics for large ones. Whole products, binned path
+// against this one: 64x64 Laplacian square 273 / 143 us, 3000 x 2000 x 2500
+// random rows 372 / 144 us, R-MAT 16 square 12.9 / 9.6 ms.
+#include <cstdio>
+
+#include "common.h"
+#include "launch.h"
+#include "profile.h"
+
+namespace mls {
+
+constexpr int kBitTile = 4 * kWave;        // words a wave reads per step of a bitmap scan (16 bytes per lane)
+constexpr int kBitRowWork = 4096;          // multiply-adds of a row one wave takes; longer rows are set aside
+constexpr int kBitLongWG = 512;            // threads per set-aside row
+constexpr int kBitPieceLanes = 16;         // lanes per piece of a row of B in those
+constexpr int kBitPiece = 4 * kBitPieceLanes;   // columns per piece: four loads in flight per lane
+
+__device__ __forceinline__ void bit_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// ORs columns j (those >= 0) into the wave's bitmap of `words` words.
+__device__ __forceinline__ void bit_set(uint32_t *bm, int words, int j, bool ok, bool &bad)
+{
+    if (!ok) return;
+    if ((uint32_t)j < 32u * (uint32_t)words) atomicOr(bm + (j >> 5), 1u << (j & 31));
+    else bad = true;
+}
+
+// Rows of at most 64 entries of A and kBitRowWork multiply-adds, one per wave
+// (rows dealt round-robin: their sizes vary); the others go to the list in
+// sc.perm, counted in the spill bin's count.
+template <bool FILL>
+__global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_bm[];   // words per wave, a multiple of kBitTile
+    if (bad_csr(sc.err)) return;
+    const int lane = threadIdx.x & 63, wave = (int)(threadIdx.x >> 6);
+    uint32_t *bm = s_bm + wave * words;
+    const Prob &P = b.p0;
+    const MLS_G int32_t *__restrict__ arp = gp(P.arp);
+    const MLS_G int32_t *__restrict__ aci = gp(P.aci);
+    const MLS_G int32_t *__restrict__ brp = gp(P.brp);
+    const MLS_G int32_t *__restrict__ bci = gp(P.bci);
+    const MLS_G int32_t *__restrict__ crp = gp(P.crp);
+    MLS_G int32_t *__restrict__ cci = gpw(P.cci);
+    for (int x = 4 * lane; x < words; x += kBitTile) *(uint4 *)(bm + x) = make_uint4(0u, 0u, 0u, 0u);
+    bit_sync();
+    bool bad = false;
+    const int stride = (int)gridDim.x * (kWG / kWave);
+    int g = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (kWG / kWave) + wave);
+    for (; g < b.na; g += stride) {
+        const int s = arp[g] - P.a_off, e = arp[g + 1] - P.a_off;
+        const int cs = FILL ? crp[g] - P.c_off : 0, ce = FILL ? crp[g + 1] - P.c_off : 0;
+        const int len = e - s;
+        int q0 = 0, n = 0;
+        if (lane < len) {
+            const int k = aci[s + lane];
+            if (k >= P.k_lo && k < P.k_hi) {
+                q0 = brp[k - P.k_lo] - P.b_off;
+                n = brp[k - P.k_lo + 1] - P.b_off - q0;
+            }
+        }
+        const int incl = group_scan_incl<kWave>(n, lane);
+        const int total = group_total<kWave>(n, incl);
+        if (len > kWave || total > kBitRowWork) {
+            if (lane == 0) {
+                const int at = atomicAdd(sc.bin_count + kBinSpill, 1);
+                if (at < b.na) gpw(sc.perm)[at] = g;
+            }
+            continue;
+        }
+        // the (entry, position in B_k) pairs, flattened, four per lane in flight;
+        // a pair's entry is the last one that starts at or before it, found by
+        // bisecting the lanes' first pairs
+        const int first = incl - n;
+        int top = 1;
+        while (top < len) top <<= 1;
+        for (int base = 0; base < total; base += 4 * kWave) {
+            int jv[4];
+            bool ok[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int pp = base + u * kWave + lane;
+                int at = 0;
+                for (int step = top >> 1; step > 0; step >>= 1) {
+                    const int c = at + step;
+                    const int f = __shfl(first, c & 63, kWave);
+                    if (c < len && f <= pp) at = c;
+                }
+                const int qa = __shfl(q0, at, kWave), fa = __shfl(first, at, kWave);
+                ok[u] = pp < total;
+                jv[u] = *(ok[u] ? bci + (qa + (pp - fa)) : (const MLS_G int32_t *)k_zeros4);
+                if (base + (u + 1) * kWave >= total) {
+#pragma unroll
+                    for (int v = u + 1; v < 4; ++v) ok[v] = false;
+                    break;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) bit_set(bm, words, jv[u], ok[u], bad);
+        }
+        bit_sync();
+        // the bitmap in column order, cleared for the next row as it is read
+        int c = 0, at = cs;
+        for (int x0 = 0; x0 < words; x0 += kBitTile) {
+            const int x = x0 + 4 * lane;
+            const uint4 w = *(const uint4 *)(bm + x);
+            const bool any = (w.x | w.y | w.z | w.w) != 0u;
+            if (!__ballot(any)) continue;
+            if (any) *(uint4 *)(bm + x) = make_uint4(0u, 0u, 0u, 0u);
+            const int pc = __popc(w.x) + __popc(w.y) + __popc(w.z) + __popc(w.w);
+            if constexpr (!FILL) {
+                c += pc;
+            } else {
+                const int in = group_scan_incl<kWave>(pc, lane);
+                int pos = at + in - pc;
+                at += group_total<kWave>(pc, in);
+                const uint32_t wv[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    uint32_t m = wv[d];
+                    while (m) {
+                        if (pos < ce) cci[pos] = (x + d) * 32 + (__ffs(m) - 1);
+                        else bad = true;
+                        ++pos;
+                        m &= m - 1u;
+                    }
+                }
+            }
+        }
+        if constexpr (FILL) {
+            if (at != ce) bad = true;
+        } else {
+            c = group_sum<kWave>(c);
+            if (lane == 0) gpw(sc.val)[g] = c;
+        }
+        bit_sync();
+    }
+    if (bad) atomicOr(sc.err, kErrStructure);
+}
+
+// The rows set aside, a workgroup each: their rows of B are cut into pieces
+// of kBitPiece columns, dealt to groups of kBitPieceLanes lanes.
+template <bool FILL>
+__global__ __launch_bounds__(kBitLongWG) void k_bit_long(Batch b, Sched sc, int words)
+{
+    constexpr int NT = kBitLongWG, NWV = NT / kWave;
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_bm[];   // words
+    __shared__ int s_first[NT + 1], s_q0[NT], s_n[NT], s_red[NWV];
+    __shared__ int s_row;
+    const int n_rows = min(gp(sc.bin_count)[kBinSpill], b.na);
+    if ((int)blockIdx.x >= n_rows) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const Prob &P = b.p0;
+    const MLS_G int32_t *__restrict__ aci = gp(P.aci);
+    const MLS_G int32_t *__restrict__ brp = gp(P.brp);
+    const MLS_G int32_t *__restrict__ bci = gp(P.bci);
+    MLS_G int32_t *__restrict__ cci = gpw(P.cci);
+    // exclusive scan over the workgroup; returns the thread's prefix, all = the total
+    auto scan = [&](int v, int &all) -> int {
+        const int incl = group_scan_incl<kWave>(v, lane);
+        if (lane == kWave - 1) s_red[wave] = incl;
+        __syncthreads();
+        int before = 0;
+        all = 0;
+#pragma unroll
+        for (int x = 0; x < NWV; ++x) {
+            before += x < wave ? s_red[x] : 0;
+            all += s_red[x];
+        }
+        __syncthreads();
+        return before + incl - v;
+    };
+    bool bad = false;
+    for (;;) {
+        if (tid == 0) s_row = atomicAdd(sc.task_cursor + kBinSpill * kXcd, 1);
+        __syncthreads();
+        const int r = s_row;
+        if (r >= n_rows) break;
+        const int g = bin_row(sc.perm, sc.err, b.na, r);
+        for (int x = tid; x < words; x += NT) s_bm[x] = 0u;
+        const int s = g >= 0 ? gp(P.arp)[g] - P.a_off : 0, e = g >= 0 ? gp(P.arp)[g + 1] - P.a_off : 0;
+        for (int pb = s; pb < e; pb += NT) {
+            int q0 = 0, n = 0;
+            if (pb + tid < e) {
+                const int k = aci[pb + tid];
+                if (k >= P.k_lo && k < P.k_hi) {
+                    q0 = brp[k - P.k_lo] - P.b_off;
+                    n = brp[k - P.k_lo + 1] - P.b_off - q0;
+                }
+            }
+            int all;
+            s_first[tid] = scan((n + kBitPiece - 1) / kBitPiece, all);
+            s_q0[tid] = q0;
+            s_n[tid] = n;
+            if (tid == 0) s_first[NT] = all;
+            __syncthreads();
+            const int gl = tid % kBitPieceLanes;
+            for (int p = tid / kBitPieceLanes; p < all; p += NT / kBitPieceLanes) {
+                int lo = 0, hi = NT - 1;   // largest entry whose first piece is at or before p
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (s_first[mid] <= p) lo = mid; else hi = mid - 1;
+                }
+                const int off = (p - s_first[lo]) * kBitPiece + gl;
+                const MLS_G int32_t *src = bci + s_q0[lo];
+                const int nn = s_n[lo];
+                int jv[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int o = off + u * kBitPieceLanes;
+                    jv[u] = *(o < nn ? src + o : (const MLS_G int32_t *)k_zeros4);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) bit_set(s_bm, words, jv[u], off + u * kBitPieceLanes < nn, bad);
+            }
+            __syncthreads();
+        }
+        if (s >= e) __syncthreads();   // (the bitmap is cleared)
+        // thread tid owns a run of consecutive words
+        const int run = (words + NT - 1) / NT;
+        const int x0 = tid * run, x1 = min(x0 + run, words);
+        int c = 0;
+        for (int x = x0; x < x1; ++x) c += __popc(s_bm[x]);
+        int all;
+        const int before = scan(c, all);
+        if constexpr (FILL) {
+            const int cs = g >= 0 ? gp(P.crp)[g] - P.c_off : 0, ce = g >= 0 ? gp(P.crp)[g + 1] - P.c_off : 0;
+            int pos = cs + before;
+            for (int x = x0; x < x1; ++x) {
+                uint32_t m = s_bm[x];
+                while (m) {
+                    if (pos < ce) cci[pos] = x * 32 + (__ffs(m) - 1);
+                    else bad = true;
+                    ++pos;
+                    m &= m - 1u;
+                }
+            }
+            if (cs + all != ce) bad = true;
+        } else if (tid == 0 && g >= 0) {
+            gpw(sc.val)[g] = all;
+        }
+        __syncthreads();
+    }
+    if (bad) atomicOr(sc.err, kErrStructure);
+}
+
+// Row pointers and nnz(C) of one product of few rows from the rows' counts,
+// one workgroup, 8 rows per thread and step (three launches otherwise).
+constexpr int kRowptrWG = 1024;
+constexpr int kRowptrPer = 8;
+
+__global__ __launch_bounds__(kRowptrWG) void k_rowptr_small(Batch b, const int32_t *val, int64_t *total, uint32_t *err)
+{
+    __shared__ int64_t s_red[kRowptrWG / kWave];
+    if (bad_csr(err)) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    MLS_G int32_t *crp = gpw(b.p0.crp);
+    int64_t carry = 0;
+    for (int r0 = 0; r0 < b.na; r0 += kRowptrWG * kRowptrPer) {
+        const int r = r0 + (int)threadIdx.x * kRowptrPer;
+        int v[kRowptrPer];
+        int sum = 0;   // at most 8 rows of at most 65536 columns
+#pragma unroll
+        for (int d = 0; d < kRowptrPer; ++d) {
+            v[d] = r + d < b.na ? gp(val)[r + d] : 0;
+            sum += v[d];
+        }
+        const int incl = group_scan_incl<kWave>(sum, lane);
+        if (lane == kWave - 1) s_red[wave] = incl;
+        __syncthreads();
+        int64_t off = carry + incl - sum, all = 0;
+        for (int w = 0; w < kRowptrWG / kWave; ++w) {
+            off += w < wave ? s_red[w] : 0;
+            all += s_red[w];
+        }
+#pragma unroll
+        for (int d = 0; d < kRowptrPer; ++d) {
+            off += v[d];
+            if (r + d < b.na) {
+                if (off >= 0x7fffffffLL) atomicOr(err, kErrOverflow);
+                crp[r + d + 1] = (int32_t)(off >= 0x7fffffffLL ? 0x7fffffffLL : off);
+            }
+        }
+        carry += all;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        crp[0] = 0;
+        *gpw(total) = carry;
+    }
+}
+
+// ---------------------------------------------------------------------------
+
+bool symbit_fits(const Batch &b)
+{
+    return b.nprob == 1 && b.p0.ncols <= kBitMaxCols;
+}
+
+void launch_symbit(const Batch &b, const Sched &sc, int fill, hipStream_t s)
+{
+    if (b.na <= 0) return;
+    int words = (b.p0.ncols + 31) / 32;
+    words = (words + kBitTile - 1) / kBitTile * kBitTile;
+    if (words < kBitTile) words = kBitTile;
+    const size_t wave_bytes = (size_t)words * 4;
+    static int cus = device_cu_count();
+    const int nw = kWG / kWave;
+    // as many workgroups as stay resident (160 KB of LDS, 32 waves per CU)
+    int per_cu = (int)(163840 / (nw * wave_bytes));
+    per_cu = per_cu > 8 ? 8 : (per_cu < 1 ? 1 : per_cu);
+    const int want = (b.na + nw - 1) / nw;
+    const int grid = want < cus * per_cu ? want : cus * per_cu;
+    int long_per_cu = (int)(163840 / (wave_bytes + 16384));
+    long_per_cu = long_per_cu > 4 ? 4 : (long_per_cu < 1 ? 1 : long_per_cu);
+    const int long_grid = b.na < cus * long_per_cu ? b.na : cus * long_per_cu;
+    ProfScope ps(fill ? "sym_bit_fill" : "sym_bit_count", s);
+    if (fill) {
+        hipLaunchKernelGGL(k_bit_rows<true>, dim3(grid), dim3(kWG), nw * wave_bytes, s, b, sc, words);
+        hipLaunchKernelGGL(k_bit_long<true>, dim3(long_grid), dim3(kBitLongWG), wave_bytes, s, b, sc, words);
+    } else {
+        hipLaunchKernelGGL(k_bit_rows<false>, dim3(grid), dim3(kWG), nw * wave_bytes, s, b, sc, words);
+        hipLaunchKernelGGL(k_bit_long<false>, dim3(long_grid), dim3(kBitLongWG), wave_bytes, s, b, sc, words);
+    }
+}
+
+void launch_rowptr_small(const Batch &b, const int32_t *val, int64_t *total, uint32_t *err, hipStream_t s)
+{
+    ProfScope ps("rowptr_small", s);
+    hipLaunchKernelGGL(k_rowptr_small, dim3(1), dim3(kRowptrWG), 0, s, b, val, total, err);
+}
+
+}  // namespace mls

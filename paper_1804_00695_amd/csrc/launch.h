@@ -12,8 +12,13 @@ enum { kModeCount = 0, kModeFill = 1, kModeNumeric = 2, kModeWork = 3 };
 
 void launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 void launch_fill_f64(double *p, double v, int64_t n, hipStream_t s);
-void launch_validate(const Batch &b, int which, const int64_t *nnz_tab, uint32_t *err, hipStream_t s);
-void launch_compress(const Batch &b, hipStream_t s);
+// CSR checks: which = 0 A, 1 B, 2 both in one launch. The entry counts come
+// from nnz_tab (device, two per product), or, when it is NULL (one product),
+// from nnz_a and nnz_b.
+void launch_validate(const Batch &b, int which, const int64_t *nnz_tab, int64_t nnz_a, int64_t nnz_b, uint32_t *err,
+                     hipStream_t s);
+// err (may be NULL): the error word of a CSR check queued before.
+void launch_compress(const Batch &b, const uint32_t *err, hipStream_t s);
 void launch_bin(const Batch &b, int mode, const Sched &sc, int force, unsigned long long *total,
                 hipStream_t s);
 int scan_tiles(int n);
@@ -23,6 +28,16 @@ void launch_write_rowptr(const Batch &b, const int64_t *prefix, int64_t *totals,
 // Symbolic phase: count (fill == 0) or fill (fill == 1) over the binned rows.
 // G = lanes per row for the LDS classes.
 void launch_symbolic(const Batch &b, const Sched &sc, int fill, int G, hipStream_t s);
+
+// Symbolic phase by dense bitmaps: one product of at most kBitMaxCols columns.
+// A wave's bitmap then takes at most 8 KB of LDS, which leaves 20 waves per
+// CU resident; each doubling halves them.
+constexpr int kBitMaxCols = 65536;
+bool symbit_fits(const Batch &b);
+void launch_symbit(const Batch &b, const Sched &sc, int fill, hipStream_t s);
+// Row pointers and nnz(C) of one product in one launch (few rows).
+constexpr int kRowptrSmallRows = 65536;
+void launch_rowptr_small(const Batch &b, const int32_t *val, int64_t *total, uint32_t *err, hipStream_t s);
 
 // Fill pass from the count pass's scratch words (rows with scnt >= 0).
 void launch_sym_expand(const Batch &b, const Sched &sc, hipStream_t s);

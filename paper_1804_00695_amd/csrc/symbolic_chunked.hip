@@ -131,7 +131,6 @@ extern "C" spgemm_status spgemm_symbolic_chunked(const spgemm_csr *A, const spge
     int32_t *d_bwc = (int32_t *)(ws + R.bwc);
     char *stage = ws + R.stage;
     hipError_t e = hipSuccess;
-    int64_t nnz_tab[2] = {0, 0};
     auto h2d = [&](void *dst, const void *src, size_t bytes) {
         if (bytes && e == hipSuccess) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
     };
@@ -159,16 +158,13 @@ extern "C" spgemm_status spgemm_symbolic_chunked(const spgemm_csr *A, const spge
         q.ncols = B->ncols;
         q.b_off = (int32_t)q0;
         if (g_opt.validate) {
-            nnz_tab[0] = 0;
-            nnz_tab[1] = q1 - q0;
             reset_header(ws, L, s);
-            h2d(ws + L.nnz_tab, nnz_tab, sizeof(nnz_tab));
             if (e != hipSuccess) return fail();
-            launch_validate(bt, 1, (const int64_t *)(ws + L.nnz_tab), (uint32_t *)(ws + L.hdr + kHdrErr), s);
-            spgemm_status st = sync_errors(ws, L, s);   // also keeps nnz_tab alive until the copy is done
+            launch_validate(bt, 1, nullptr, 0, q1 - q0, (uint32_t *)(ws + L.hdr + kHdrErr), s);
+            spgemm_status st = sync_errors(ws, L, s);
             if (st != SPGEMM_OK) return st;
         }
-        launch_compress(bt, s);
+        launch_compress(bt, nullptr, s);
         spgemm_status st = check_launch();
         if (st != SPGEMM_OK) return st;
         e = hipStreamSynchronize(s);   // the stage is reused by the next part
@@ -212,11 +208,8 @@ extern "C" spgemm_status spgemm_symbolic_chunked(const spgemm_csr *A, const spge
         q.k_hi = B->nrows;
         reset_header(ws, L, s);
         if (g_opt.validate) {
-            nnz_tab[0] = a1 - a0;
-            nnz_tab[1] = 0;
-            h2d(ws + L.nnz_tab, nnz_tab, sizeof(nnz_tab));
             if (e != hipSuccess) return fail();
-            launch_validate(bt, 0, (const int64_t *)(ws + L.nnz_tab), (uint32_t *)(ws + L.hdr + kHdrErr), s);
+            launch_validate(bt, 0, nullptr, a1 - a0, 0, (uint32_t *)(ws + L.hdr + kHdrErr), s);
             spgemm_status st = sync_errors(ws, L, s);
             if (st != SPGEMM_OK) return st;
         }

@@ -88,14 +88,14 @@ spgemm_status spgemm_tc(const spgemm_csr *L, int64_t *counts, int64_t *total_hos
     reset_header(ws, Lay, s);
     launch_fill_i32((int32_t *)counts, 0, 2 * (int64_t)L->nrows, s);
     if (g_opt.validate) {
-        launch_validate(bh.batch, 0, (const int64_t *)(ws + Lay.nnz_tab), sc.err, s);
+        launch_validate(bh.batch, 0, nullptr, L->nnz, 0, sc.err, s);
         st = check_launch();
         if (st != SPGEMM_OK) return st;
         st = read_errors(ws, Lay, s);
         if (st != SPGEMM_OK) return st;
     }
     unsigned long long *tot = (unsigned long long *)(ws + Lay.hdr + kHdrTotal);
-    launch_compress(bh.batch, s);
+    launch_compress(bh.batch, sc.err, s);
     launch_tc_bin(bh.batch, sc, bin_force(), s);
     launch_tc(bh.batch, sc, counts, tot, (uint32_t *)(ws + Lay.spill), Lay.spill_slots, Lay.spill_words, s);
     st = check_launch();

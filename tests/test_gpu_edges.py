@@ -51,3 +51,59 @@ def test_long_rows_of_b(cls, len_b):
         check(A, B)
     finally:
         mls.set_option(mls._abi.OPT_GROUP_SIZE, 0)
+
+
+def rows_of(lengths, ncols, seed):
+    g = synth.rng(seed)
+    rows = [np.sort(g.choice(ncols, n, replace=False)) for n in lengths]
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    ci = np.concatenate(rows).astype(np.int32) if rows else np.zeros(0, np.int32)
+    return synth.Csr(len(lengths), ncols, rp, ci, g.standard_normal(int(rp[-1])))
+
+
+# the bitmap symbolic path (C of at most 65536 columns) and the binned one
+# (more columns, or the class knob): rows of 0, 1, 63..65 and more entries of
+# A, 4096 and 4097 multiply-adds (the most one wave takes), rows of B shorter
+# and longer than a piece, first and last columns
+@pytest.mark.parametrize("binned", [False, True])
+@pytest.mark.parametrize("ncols", [1, 31, 32, 33, 8191, 8192, 8193, 65535, 65536, 65537])
+def test_symbolic_columns(ncols, binned):
+    lens_b = [min(n, ncols) for n in [0, 1, 2, 15, 16, 17, 63, 64, 65, 127, 256, 1000, 5000] * 8]
+    B = rows_of(lens_b, ncols, ncols)
+    if B.nnz and ncols > 1:
+        last = int(B.row_ptr[5 * 13]) - 1   # a row of B that ends in the last column
+        B.col_idx[last] = ncols - 1
+        B.col_idx[int(B.row_ptr[4 * 13 + 1])] = 0
+    A = rows_of([0, 1, 5, 63, 64, 65, 104, 0, 2, 33], 104, 7)
+    mls.set_option(mls._abi.OPT_FORCE_CLASS, 0 if binned else -1)
+    try:
+        check(A, B)
+    finally:
+        mls.set_option(mls._abi.OPT_FORCE_CLASS, -1)
+
+
+@pytest.mark.parametrize("work", [63, 64, 65, 255, 256, 257, 4095, 4096, 4097])
+def test_symbolic_row_work(work):
+    B = rows_of([work // 2, work - work // 2, 0, 1], 9000, work)
+    check(rows_of([2, 3, 4, 1], 4, 1), B)
+
+
+# a refused operand leaves the outputs alone and the next call unharmed,
+# whichever factor it is and whichever path would have run
+@pytest.mark.parametrize("binned", [False, True])
+@pytest.mark.parametrize("which", ["A", "B"])
+def test_refused_then_accepted(which, binned):
+    A, B = synth.poisson_csr(3000, 500, 6.0, 1), synth.poisson_csr(500, 700, 6.0, 2)
+    dA, dB = mls.DeviceCsr.from_host(A), mls.DeviceCsr.from_host(B)
+    M = dA if which == "A" else dB
+    mls.set_option(mls._abi.OPT_FORCE_CLASS, 0 if binned else -1)
+    try:
+        for at, value in ((7, -3), (M.nnz - 1, 1 << 30), (11, int(M.col_idx[10]))):
+            keep = int(M.col_idx[at])
+            M.col_idx[at] = value
+            with pytest.raises(mls.SpgemmError):
+                mls.symbolic(dA, dB)
+            M.col_idx[at] = keep
+        check(A, B)
+    finally:
+        mls.set_option(mls._abi.OPT_FORCE_CLASS, -1)
