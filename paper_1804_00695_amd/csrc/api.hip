@@ -349,6 +349,12 @@ spgemm_status run_numeric(BatchHost &bh, char *ws, hipStream_t s)
     memo_forget(ws);
     const Layout &L = bh.layout;
     Sched sc = make_sched(ws, L);
+    // few rows: two launches in all (the test knobs that choose classes, lanes
+    // or table layouts keep the launches by class)
+    if (small_rows_fit(bh.batch) && bin_force() < 0 && !g_opt.group_size) {
+        launch_numeric_small(bh.batch, sc, s);
+        return check_launch();
+    }
     reset_header(ws, L, s);
     launch_bin(bh.batch, kModeNumeric, sc, bin_force(), nullptr, s);
     launch_numeric(bh.batch, sc, choose_group(bh.avg_b), s);
@@ -548,11 +554,11 @@ spgemm_status spgemm_check_errors(void *ws, size_t ws_bytes, hipStream_t stream)
     std::memset(&L, 0, sizeof(L));
     L.hdr = 0;
     spgemm_status st = read_errors((char *)ws, L, stream);
-    if (st == SPGEMM_OK || st == SPGEMM_ERR_BAD_CSR || st == SPGEMM_ERR_INDEX_OVERFLOW ||
+    // (a word that is 0 already needs no clearing)
+    if (st == SPGEMM_ERR_BAD_CSR || st == SPGEMM_ERR_INDEX_OVERFLOW ||
         st == SPGEMM_ERR_STRUCTURE) {
         launch_fill_i32((int32_t *)((char *)ws + kHdrErr), 0, 1, stream);
-        spgemm_status st2 = check_launch();
-        if (st == SPGEMM_OK) st = st2;
+        (void)check_launch();   // the word's own verdict is the call's
     }
     return st;
 }

@@ -89,8 +89,11 @@ spgemm_status spgemm_backward(const spgemm_csr *A, const spgemm_csr *B, const sp
     if (st != SPGEMM_OK) return st;
     char *ws = (char *)ws_v;
     Sched sc = make_sched(ws, bh.layout);
-    if (dA) launch_fill_f64(dA, 0.0, A->nnz, s);
-    if (dB) launch_fill_f64(dB, 0.0, B->nnz, s);
+    launch_zero2_f64(dA, A->nnz, dB, B->nnz, s);
+    if (small_rows_fit(bh.batch) && bin_force() < 0 && !g_opt.group_size) {
+        launch_backward_small(bh.batch, sc, dA, dB, s);
+        return check_launch();
+    }
     reset_header(ws, bh.layout, s);
     launch_bin(bh.batch, kModeNumeric, sc, bin_force(), nullptr, s);
     launch_backward(bh.batch, sc, W->values, dA, dB, choose_group(bh.avg_b), s);

@@ -100,6 +100,8 @@ struct Sched {
 
 constexpr int kScratchWords = 64;
 
+static_assert(kBinSpill == kNumClasses, "the spill bin follows the classes");
+
 // Rows per binning block: every binning kernel assigns rows [b * kBinRowsPerWG,
 // (b + 1) * kBinRowsPerWG) to workgroup b and leaves the block's row count per
 // bin in blk_cnt, so that the bin scan and the scatter need no global atomics.
@@ -376,6 +378,40 @@ __device__ __forceinline__ int bin_start(const int32_t *bin_count, int bin)
     return s;
 }
 
+// One launch for every class of the numeric (or adjoint) phase: which part
+// (class 0..4, or kNumClasses for the spill windows) this workgroup serves, -1
+// for none, with its index and the number of workgroups of that part. The
+// launch's workgroups are divided in proportion to the parts' rows over `per`,
+// the rows (windows) a workgroup of the part takes at once; every part with
+// rows gets at least one.
+__device__ __forceinline__ int part_of_block(const Sched &sc, const int (&per)[kNumClasses + 1], int &vblk, int &vgrid)
+{
+    int want[kNumClasses + 1], all = 0, parts = 0, at = 0;
+    for (int c = 0; c <= kNumClasses; ++c) {
+        int n = gp(sc.bin_count)[c];
+        if (c == kBinSpill && n > 0) n = gp(sc.wstart)[n];
+        want[c] = (n + per[c] - 1) / per[c];
+        all += want[c];
+        parts += n > 0;
+    }
+    const int grid = (int)gridDim.x, blk = (int)blockIdx.x;
+    const int share = grid > parts ? grid - parts : 0;   // beyond one each
+    int sum = 0;
+    for (int c = 0; c <= kNumClasses; ++c) {
+        if (want[c] == 0) continue;
+        const int lo = at + (int)((int64_t)share * sum / all);
+        sum += want[c];
+        ++at;
+        const int hi = at + (int)((int64_t)share * sum / all);
+        if (blk >= lo && blk < hi) {
+            vblk = blk - lo;
+            vgrid = hi - lo;
+            return c;
+        }
+    }
+    return -1;
+}
+
 // Per-wave task schedule. Tasks of a bin are split into one contiguous slab
 // per XCD (workgroup w runs on XCD w % 8, and the CUs of an XCD share one L2).
 // Inside a slab, waves take blocks of kTaskBlock tasks from a per-XCD counter;
@@ -401,15 +437,19 @@ struct TaskIter {
     bool first;
 };
 
-__device__ __forceinline__ TaskIter task_iter(int ntasks, int waves_per_wg, int log_chunk = -1)
+// vblk, vgrid: the workgroup's index among those of its bin and their number
+// (the launch's own, unless one launch serves several bins).
+__device__ __forceinline__ TaskIter task_iter(int ntasks, int waves_per_wg, int log_chunk, int vblk, int vgrid)
 {
-    const int x = (int)(blockIdx.x % kXcd);
+    // (fewer workgroups than XCDs: as many slabs)
+    const int nx = log_chunk < 0 && vgrid < kXcd ? vgrid : kXcd;
+    const int x = vblk % nx;
     TaskIter it;
     it.x = x;
     it.lc = log_chunk;
     if (log_chunk < 0) {
-        it.lo = (int)(((int64_t)ntasks * x) / kXcd);
-        it.hi = (int)(((int64_t)ntasks * (x + 1)) / kXcd);
+        it.lo = (int)(((int64_t)ntasks * x) / nx);
+        it.hi = (int)(((int64_t)ntasks * (x + 1)) / nx);
     } else {
         // local tasks of XCD x: the full chunks x, x + 8, ... and the
         // partial last chunk when it falls on x
@@ -419,16 +459,21 @@ __device__ __forceinline__ TaskIter task_iter(int ntasks, int waves_per_wg, int 
         it.lo = 0;
         it.hi = (full << log_chunk) + (nch % kXcd == x ? rem : 0);
     }
-    const int wgs_x = ((int)gridDim.x - x + kXcd - 1) / kXcd;   // workgroups on this XCD
+    const int wgs_x = (vgrid - x + nx - 1) / nx;   // workgroups on this XCD
     it.S = wgs_x * waves_per_wg;
     if (it.S < 1) it.S = 1;
     it.cur = 0;
     it.left = 0;
     // in [0, S); read from the first lane so that the compiler keeps it, and
     // every task index derived from it, in scalar registers
-    it.wid = (int)(blockIdx.x / kXcd) * waves_per_wg + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    it.wid = (vblk / nx) * waves_per_wg + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     it.first = true;
     return it;
+}
+
+__device__ __forceinline__ TaskIter task_iter(int ntasks, int waves_per_wg, int log_chunk = -1)
+{
+    return task_iter(ntasks, waves_per_wg, log_chunk, (int)blockIdx.x, (int)gridDim.x);
 }
 
 __device__ __forceinline__ int task_global(const TaskIter &it, int t)
@@ -457,7 +502,7 @@ __device__ __forceinline__ int next_task_wave(int32_t *cursor, int ntasks, TaskI
             it.first = false;
         } else {
             if ((int64_t)it.lo + (int64_t)it.S * kTaskBlock >= it.hi) return -1;   // no block past the first S
-            if ((threadIdx.x & 63) == 0) blk = atomicAdd(cursor + blockIdx.x % kXcd, 1);
+            if ((threadIdx.x & 63) == 0) blk = atomicAdd(cursor + it.x, 1);
             blk = __builtin_amdgcn_readlane(blk, 0) + it.S;
         }
         const int64_t base = (int64_t)it.lo + (int64_t)(blk / it.S) * it.S * kTaskBlock + blk % it.S;

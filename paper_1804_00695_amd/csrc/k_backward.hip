@@ -37,10 +37,10 @@ __device__ __forceinline__ void bwd_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-constexpr int nw_bwd(int row_bytes, int rows_per_wave)
+constexpr int nw_bwd(int row_bytes, int rows_per_wave, int lds = 65536)
 {
     int per_wave = row_bytes * rows_per_wave;
-    int nw = 65536 / per_wave;
+    int nw = lds / per_wave;
     return nw > 4 ? 4 : (nw < 1 ? 1 : nw);
 }
 
@@ -112,15 +112,15 @@ constexpr int bwd_row_bytes(int CAP, int G, bool PACK)
 }
 
 // Waves per workgroup that keep the most waves resident on a CU (160 KB of
-// LDS, 32 waves), given the LDS of one wave.
-constexpr int nw_bwd_best(int wave_bytes)
+// LDS, 32 waves), given the LDS of one wave and the most a workgroup may have.
+constexpr int nw_bwd_best(int wave_bytes, int lds)
 {
     int best = 1, best_w = 0;
     for (int nw = 1; nw <= 4; ++nw) {
         int wgs = 163840 / (nw * wave_bytes);
         int w = wgs * nw;
         if (w > 32) w = 32;
-        if (65536 < nw * wave_bytes) w = 0;   // a workgroup's static LDS stays within 64 KB
+        if (lds < nw * wave_bytes) w = 0;   // a workgroup's LDS stays within lds
         if (w >= best_w) { best = nw; best_w = w; }
     }
     return best;
@@ -181,18 +181,35 @@ __device__ __forceinline__ void bwd_first_b(const Prob &P, BwdFirst &f)
     f.q1 = pb[1];
 }
 
-template <int G, int CAP, bool PACK>
-__global__ __launch_bounds__(kWG) void k_bwd_lds(Batch b, Sched sc, int bin, double *dA, double *dB)
+template <int G, int CAP, bool PACK, int MAXLDS = 65536>
+struct BwdShape {
+    static constexpr int W = kWave / G;
+    static constexpr int NW = nw_bwd_best(bwd_row_bytes(CAP, G, PACK) * W, MAXLDS);
+    static constexpr int WV = PACK ? CAP / 2 : CAP;   // W values per row: by position, or by slot
+    static constexpr int LDS_WV = NW * W * CAP * 4;
+    static constexpr int LDS_PA = LDS_WV + NW * W * WV * 8;
+    static constexpr int LDS_DA = LDS_PA + NW * W * G * 8;
+    static constexpr int LDS_POFF = LDS_DA + NW * W * G * 8;
+    static constexpr int LDS_PQ = LDS_POFF + NW * W * (G + 4) * 4;
+    static constexpr int LDS = LDS_PQ + NW * W * G * 4;
+};
+
+// The rows of one bin on the workgroups vblk of vgrid; lds: BwdShape::LDS bytes
+// of this workgroup.
+template <int G, int CAP, bool PACK, int MAXLDS>
+__device__ __forceinline__ void bwd_lds_rows(const Batch &b, const Sched &sc, int bin, double *dA, double *dB,
+                                             char *lds, int vblk, int vgrid)
 {
-    constexpr int W = kWave / G;
-    constexpr int NW = nw_bwd_best(bwd_row_bytes(CAP, G, PACK) * W);
-    constexpr int WV = PACK ? CAP / 2 : CAP;   // W values per row: by position, or by slot
-    __shared__ __attribute__((aligned(16))) int s_key[NW * W * CAP];
-    __shared__ double s_wv[NW * W * WV];
-    __shared__ double s_pa[NW * W * G];
-    __shared__ double s_da[NW * W * G];
-    __shared__ int s_pq[NW * W * G];
-    __shared__ __attribute__((aligned(16))) int s_poff[NW * W * (G + 4)];   // read four at a time
+    using Shape = BwdShape<G, CAP, PACK, MAXLDS>;
+    constexpr int W = Shape::W;
+    constexpr int NW = Shape::NW;
+    constexpr int WV = Shape::WV;
+    int *s_key = (int *)lds;
+    double *s_wv = (double *)(lds + Shape::LDS_WV);
+    double *s_pa = (double *)(lds + Shape::LDS_PA);
+    double *s_da = (double *)(lds + Shape::LDS_DA);
+    int *s_poff = (int *)(lds + Shape::LDS_POFF);   // read four at a time
+    int *s_pq = (int *)(lds + Shape::LDS_PQ);
 
     const int wave = threadIdx.x >> 6;
     if (wave >= NW) return;
@@ -219,7 +236,7 @@ __global__ __launch_bounds__(kWG) void k_bwd_lds(Batch b, Sched sc, int bin, dou
     const int n_bin = gp(sc.bin_count)[bin];
     const int start = bin_start(sc.bin_count, bin);
     const int ntasks = (n_bin + W - 1) / W;
-    TaskIter it = task_iter(ntasks, NW);
+    TaskIter it = task_iter(ntasks, NW, -1, vblk, vgrid);
     // Three rows of a slot are in flight: the row after next has its perm
     // entry loading, the next row its metadata, then its first chunk (entries
     // of A_i while this row's W_i is hashed, their B row bounds after this
@@ -413,6 +430,13 @@ __global__ __launch_bounds__(kWG) void k_bwd_lds(Batch b, Sched sc, int bin, dou
     }
 }
 
+template <int G, int CAP, bool PACK>
+__global__ __launch_bounds__(kWG) void k_bwd_lds(Batch b, Sched sc, int bin, double *dA, double *dB)
+{
+    __shared__ __attribute__((aligned(16))) char s_mem[BwdShape<G, CAP, PACK>::LDS];
+    bwd_lds_rows<G, CAP, PACK, 65536>(b, sc, bin, dA, dB, s_mem, (int)blockIdx.x, (int)gridDim.x);
+}
+
 __device__ __forceinline__ int bsearch_w(const MLS_G int32_t *cols, int n, int j)
 {
     int lo = 0, hi = n;
@@ -445,17 +469,29 @@ constexpr int bwd_win_bytes(int CAP) { return CAP * 12 + kWave * 16 + (kWave + 1
 // A window's (entry, B position) pairs are flattened, 64 per step: each pair
 // adds a_ik W_ij into dB with a device atomic and W_ij b_kj into its entry's
 // dA part in LDS; the parts go to dA with one device atomic per entry.
-template <int CAP>
-__global__ __launch_bounds__(kWG) void k_bwd_win(Batch b, Sched sc, double *dA, double *dB)
+template <int CAP, int MAXLDS = 65536>
+struct BwdWinShape {
+    static constexpr int NW = nw_bwd(bwd_win_bytes(CAP), 1, MAXLDS);
+    static constexpr int LDS_WV = NW * CAP * 4;
+    static constexpr int LDS_PAR = LDS_WV + NW * CAP * 8;
+    static constexpr int LDS_DA = LDS_PAR + NW * kWave * 16;
+    static constexpr int LDS_POFF = LDS_DA + NW * kWave * 8;
+    static constexpr int LDS = LDS_POFF + NW * (kWave + 1) * 4;
+};
+
+// lds: BwdWinShape::LDS bytes of this workgroup
+template <int CAP, int MAXLDS>
+__device__ __forceinline__ void bwd_win_rows(const Batch &b, const Sched &sc, double *dA, double *dB, char *lds)
 {
+    using Shape = BwdWinShape<CAP, MAXLDS>;
     constexpr int G = kWave;
     constexpr int M = CAP / 2;
-    constexpr int NW = nw_bwd(bwd_win_bytes(CAP), 1);
-    __shared__ __attribute__((aligned(16))) int s_key[NW * CAP];
-    __shared__ double s_wv[NW * CAP];
-    __shared__ int4 s_par[NW * G];        // staged entries: (first B position, -, a)
-    __shared__ int s_poff[NW * (G + 1)];  // first pair of each staged entry, then the total
-    __shared__ double s_da[NW * G];
+    constexpr int NW = Shape::NW;
+    int *s_key = (int *)lds;
+    double *s_wv = (double *)(lds + Shape::LDS_WV);
+    int4 *s_par = (int4 *)(lds + Shape::LDS_PAR);    // staged entries: (first B position, -, a)
+    double *s_da = (double *)(lds + Shape::LDS_DA);
+    int *s_poff = (int *)(lds + Shape::LDS_POFF);    // first pair of each staged entry, then the total
 
     const int wave = threadIdx.x >> 6;
     if (wave >= NW) return;
@@ -597,6 +633,48 @@ __global__ __launch_bounds__(kWG) void k_bwd_win(Batch b, Sched sc, double *dA, 
     }
 }
 
+template <int CAP>
+__global__ __launch_bounds__(kWG) void k_bwd_win(Batch b, Sched sc, double *dA, double *dB)
+{
+    __shared__ __attribute__((aligned(16))) char s_mem[BwdWinShape<CAP>::LDS];
+    bwd_win_rows<CAP, 65536>(b, sc, dA, dB, s_mem);
+}
+
+// Products of few rows: every class and the spill windows in one launch, the
+// rows of the largest class as windows (as the numeric phase's k_num_all, with
+// the same saving: 5000 random rows of 36 outputs 52 -> 23 us).
+constexpr int kBwdAllLds = 24576;
+
+using BwdAll0 = BwdShape<8, kFillCap[0], true, kBwdAllLds>;
+using BwdAll1 = BwdShape<32, kFillCap[1], true, kBwdAllLds>;
+using BwdAll2 = BwdShape<64, kFillCap[2], true, kBwdAllLds>;
+using BwdAll3 = BwdShape<64, kFillCap[3], true, kBwdAllLds>;
+using BwdAllW = BwdWinShape<kBwdWinCap, kBwdAllLds>;
+static_assert(BwdAll0::LDS <= kBwdAllLds && BwdAll1::LDS <= kBwdAllLds && BwdAll2::LDS <= kBwdAllLds &&
+              BwdAll3::LDS <= kBwdAllLds && BwdAllW::LDS <= kBwdAllLds, "one LDS buffer for every part");
+
+__global__ __launch_bounds__(kWG) void k_bwd_all(Batch b, Sched sc, double *dA, double *dB)
+{
+    __shared__ __attribute__((aligned(16))) char s_mem[kBwdAllLds];
+    const int per[kNumClasses + 1] = {BwdAll0::W * BwdAll0::NW, BwdAll1::W * BwdAll1::NW, BwdAll2::NW, BwdAll3::NW,
+                                      1, BwdAllW::NW};
+    int vblk, vgrid;
+    switch (part_of_block(sc, per, vblk, vgrid)) {
+    case 0: bwd_lds_rows<8, kFillCap[0], true, kBwdAllLds>(b, sc, 0, dA, dB, s_mem, vblk, vgrid); break;
+    case 1: bwd_lds_rows<32, kFillCap[1], true, kBwdAllLds>(b, sc, 1, dA, dB, s_mem, vblk, vgrid); break;
+    case 2: bwd_lds_rows<64, kFillCap[2], true, kBwdAllLds>(b, sc, 2, dA, dB, s_mem, vblk, vgrid); break;
+    case 3: bwd_lds_rows<64, kFillCap[3], true, kBwdAllLds>(b, sc, 3, dA, dB, s_mem, vblk, vgrid); break;
+    case kNumClasses: bwd_win_rows<kBwdWinCap, kBwdAllLds>(b, sc, dA, dB, s_mem); break;
+    }
+}
+
+void launch_backward_small(const Batch &b, const Sched &sc, double *dA, double *dB, hipStream_t s)
+{
+    launch_bin_small(b, sc, kBwdWinCap / 2, s);
+    ProfScope ps("bwd_all", s);
+    hipLaunchKernelGGL(k_bwd_all, dim3(small_rows_grid(b.na)), dim3(kWG), 0, s, b, sc, dA, dB);
+}
+
 template <typename K>
 static int bwd_grid(K kernel, int threads)
 {
@@ -610,8 +688,7 @@ static int bwd_grid(K kernel, int threads)
 template <int G, int CAP, bool PACK>
 static void launch_bwd_variant(const Batch &b, const Sched &sc, int bin, double *dA, double *dB, hipStream_t s)
 {
-    constexpr int W = kWave / G;
-    constexpr int NW = nw_bwd_best(bwd_row_bytes(CAP, G, PACK) * W);
+    constexpr int NW = BwdShape<G, CAP, PACK>::NW;
     static int grid = bwd_grid(k_bwd_lds<G, CAP, PACK>, NW * kWave);
     static char name[64];
     if (!name[0]) snprintf(name, sizeof(name), "bwd_lds_G%d_C%d%s", G, CAP, PACK ? "_p" : "");
@@ -648,7 +725,7 @@ void launch_backward(const Batch &b, const Sched &sc, const double *wval, double
     launch_bwd_class<64, kFillCap[2]>(b, sc, 2, dA, dB, s);
     launch_bwd_class<64, kFillCap[3]>(b, sc, 3, dA, dB, s);
     launch_bwd_class<64, kFillCap[4]>(b, sc, 4, dA, dB, s);
-    constexpr int NWW = nw_bwd(bwd_win_bytes(kBwdWinCap), 1);
+    constexpr int NWW = BwdWinShape<kBwdWinCap>::NW;
     static int win_grid = bwd_grid(k_bwd_win<kBwdWinCap>, NWW * kWave);
     ProfScope ps("bwd_spill", s);
     hipLaunchKernelGGL(k_win_scan, dim3(1), dim3(kWG), 0, s, b, sc, kBwdWinCap / 2);

@@ -49,10 +49,10 @@ __device__ __forceinline__ void nwave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-constexpr int nw_num(int row_bytes, int rows_per_wave)
+constexpr int nw_num(int row_bytes, int rows_per_wave, int lds = 65536)
 {
     int per_wave = row_bytes * rows_per_wave;
-    int nw = 65536 / per_wave;
+    int nw = lds / per_wave;
     return nw > 4 ? 4 : (nw < 1 ? 1 : nw);
 }
 
@@ -221,11 +221,12 @@ constexpr int lds_waves_per_simd(int wg_bytes, int nw)
     return w > 8 ? 8 : (w < 1 ? 1 : w);
 }
 
-template <int G, int CAP, bool PACK, bool MULTI, bool FLAT>
+// MAXLDS: LDS bytes of a workgroup that set how many waves it has (1 to 4)
+template <int G, int CAP, bool PACK, bool MULTI, bool FLAT, int MAXLDS = 65536>
 struct NumShape {
     static constexpr int W = kWave / G;
     static constexpr int XW = FLAT ? num_flat_words(G) : 0;
-    static constexpr int NW = nw_num(num_row_bytes(CAP, G, PACK) + 4 * XW, W);
+    static constexpr int NW = nw_num(num_row_bytes(CAP, G, PACK) + 4 * XW, W, MAXLDS);
     static constexpr int OCC = lds_waves_per_simd(NW * W * (num_row_bytes(CAP, G, PACK) + 4 * XW), NW);
     // where LDS already limits a SIMD to 4 waves, registers are free for
     // twice the steps in flight
@@ -240,14 +241,22 @@ struct NumShape {
     // most 5 waves per SIMD); otherwise a row loads its first chunk when it
     // starts
     static constexpr bool PF = !MULTI && OCC_R <= 5;
+    // LDS of a workgroup: tables (and FLAT pair offsets), staged entries of A
+    // (q0, q1, a), accumulators
+    static constexpr int TW = PACK ? CAP : 2 * CAP;   // table words per row
+    static constexpr int LDS_PAR = (NW * W * (TW + XW) * 4 + 15) / 16 * 16;
+    static constexpr int LDS_ACC = LDS_PAR + NW * W * G * 16;
+    static constexpr int LDS = LDS_ACC + NW * W * (CAP / 2) * 8;
 };
 
-template <int G, int CAP, bool PACK, bool MULTI, bool FLAT>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(
-    NumShape<G, CAP, PACK, MULTI, FLAT>::OCC_R))) void k_num_lds(Batch b, Sched sc, int bin)
+// The rows of one bin on the workgroups vblk of vgrid; lds: NumShape::LDS bytes
+// of this workgroup.
+template <int G, int CAP, bool PACK, bool MULTI, bool FLAT, int MAXLDS>
+__device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, int bin, char *lds, int vblk, int vgrid)
 {
-    constexpr int kNumDepth = NumShape<G, CAP, PACK, MULTI, FLAT>::DEPTH;
-    constexpr bool PF = NumShape<G, CAP, PACK, MULTI, FLAT>::PF;
+    using Shape = NumShape<G, CAP, PACK, MULTI, FLAT, MAXLDS>;
+    constexpr int kNumDepth = Shape::DEPTH;
+    constexpr bool PF = Shape::PF;
     // Where a wave owns a row, rows of B are long (the host picks G from their
     // mean length) and often longer than G: a staged chunk is cut into steps
     // of at most G entries of one row of B each, so that every step takes the
@@ -258,11 +267,11 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(
     static_assert(FLAT || G % kNumDepth == 0, "the staged entries are read kNumDepth at a time");
     constexpr int W = kWave / G;
     constexpr int XW = FLAT ? num_flat_words(G) : 0;
-    constexpr int NW = nw_num(num_row_bytes(CAP, G, PACK) + 4 * XW, W);
-    constexpr int TW = PACK ? CAP : 2 * CAP;   // table words per row
-    __shared__ __attribute__((aligned(16))) uint32_t s_tab[NW * W * (TW + XW)];
-    __shared__ double s_acc[NW * W * (CAP / 2)];
-    __shared__ int4 s_par[NW * W * G];   // staged entries of row i of A: (q0, q1, a)
+    constexpr int NW = Shape::NW;
+    constexpr int TW = Shape::TW;
+    uint32_t *s_tab = (uint32_t *)lds;
+    int4 *s_par = (int4 *)(lds + Shape::LDS_PAR);
+    double *s_acc = (double *)(lds + Shape::LDS_ACC);
 
     const int wave = threadIdx.x >> 6;
     if (wave >= NW) return;
@@ -279,7 +288,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(
     const int n_bin = gp(sc.bin_count)[bin];
     const int start = bin_start(sc.bin_count, bin);
     const int ntasks = (n_bin + W - 1) / W;
-    TaskIter it = task_iter(ntasks, NW);
+    TaskIter it = task_iter(ntasks, NW, -1, vblk, vgrid);
     // Rows of a slot overlap: with PF three are in flight (the row after next
     // has its perm entry loading; the next row its metadata, then its first
     // chunk: A entries during this row's insert and steps, B row pointers
@@ -589,6 +598,14 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
+template <int G, int CAP, bool PACK, bool MULTI, bool FLAT>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(
+    NumShape<G, CAP, PACK, MULTI, FLAT>::OCC_R))) void k_num_lds(Batch b, Sched sc, int bin)
+{
+    __shared__ __attribute__((aligned(16))) char s_mem[NumShape<G, CAP, PACK, MULTI, FLAT>::LDS];
+    num_lds_rows<G, CAP, PACK, MULTI, FLAT, 65536>(b, sc, bin, s_mem, (int)blockIdx.x, (int)gridDim.x);
+}
+
 // first position in cols[lo, hi) whose column is >= j
 __device__ __forceinline__ int lower_col(const MLS_G int32_t *cols, int lo, int hi, int j)
 {
@@ -656,18 +673,32 @@ constexpr int win_bytes(int CAP, bool PACK)
 // same output, so the adds are applied in rounds: in each round the lowest
 // pending lane of every output position adds (an LDS min over lane ids
 // finds it), which keeps every c_ij's terms in ascending k.
-template <int CAP, bool PACK, bool MULTI>
-__global__ __launch_bounds__(kWG) void k_num_win(Batch b, Sched sc)
+template <int CAP, bool PACK, int MAXLDS = 65536>
+struct WinShape {
+    static constexpr int M = CAP / 2;   // positions of C per window
+    static constexpr int NW = nw_num(win_bytes(CAP, PACK), 1, MAXLDS);
+    static constexpr int TW = PACK ? CAP : 2 * CAP;
+    static constexpr int LDS_PAR = NW * TW * 4;
+    static constexpr int LDS_ACC = LDS_PAR + NW * kWave * 16;
+    static constexpr int LDS_OWN = LDS_ACC + NW * M * 8;
+    static constexpr int LDS_POFF = LDS_OWN + NW * M * 4;
+    static constexpr int LDS = LDS_POFF + NW * (kWave + 1) * 4;
+};
+
+// lds: WinShape::LDS bytes of this workgroup
+template <int CAP, bool PACK, bool MULTI, int MAXLDS>
+__device__ __forceinline__ void num_win_rows(const Batch &b, const Sched &sc, char *lds)
 {
+    using Shape = WinShape<CAP, PACK, MAXLDS>;
     constexpr int G = kWave;
-    constexpr int M = CAP / 2;   // positions of C per window
-    constexpr int NW = nw_num(win_bytes(CAP, PACK), 1);
-    constexpr int TW = PACK ? CAP : 2 * CAP;
-    __shared__ __attribute__((aligned(16))) uint32_t s_tab[NW * TW];
-    __shared__ double s_acc[NW * M];
-    __shared__ int4 s_par[NW * G];        // staged entries: (first B position, -, a)
-    __shared__ int s_poff[NW * (G + 1)];  // first pair of each staged entry, then the total
-    __shared__ int s_own[NW * M];
+    constexpr int M = Shape::M;
+    constexpr int NW = Shape::NW;
+    constexpr int TW = Shape::TW;
+    uint32_t *s_tab = (uint32_t *)lds;
+    int4 *s_par = (int4 *)(lds + Shape::LDS_PAR);    // staged entries: (first B position, -, a)
+    double *s_acc = (double *)(lds + Shape::LDS_ACC);
+    int *s_own = (int *)(lds + Shape::LDS_OWN);
+    int *s_poff = (int *)(lds + Shape::LDS_POFF);    // first pair of each staged entry, then the total
 
     const int wave = threadIdx.x >> 6;
     if (wave >= NW) return;
@@ -816,6 +847,48 @@ __global__ __launch_bounds__(kWG) void k_num_win(Batch b, Sched sc)
     }
 }
 
+template <int CAP, bool PACK, bool MULTI>
+__global__ __launch_bounds__(kWG) void k_num_win(Batch b, Sched sc)
+{
+    __shared__ __attribute__((aligned(16))) char s_mem[WinShape<CAP, PACK>::LDS];
+    num_win_rows<CAP, PACK, MULTI, 65536>(b, sc, s_mem);
+}
+
+// Products of few rows: every class and the spill windows in one launch, the
+// workgroups divided among the bins by their work (each bin with rows gets at
+// least one). The classes' own launches cost at least 4.7 us of stream time
+// each, empty or not, and seven of them (with the window scan) are saved. A
+// workgroup has as many waves per class as kAllLds holds, and the rows of the
+// largest class (33 KB each) run as windows, so that five workgroups (20
+// waves, what the registers allow) stay resident per CU, as in the launches
+// by class. Numeric phase of 5000 random rows of 36 outputs 46 -> 22 us, of
+// the 64x64 Laplacian square 36 -> 15 us.
+constexpr int kAllLds = 24576;
+
+using NumAll0 = NumShape<8, kFillCap[0], true, false, true, kAllLds>;
+using NumAll1 = NumShape<32, kFillCap[1], true, false, false, kAllLds>;
+using NumAll2 = NumShape<64, kFillCap[2], true, false, false, kAllLds>;
+using NumAll3 = NumShape<64, kFillCap[3], true, false, false, kAllLds>;
+using NumAllW = WinShape<kNumWinCap, true, kAllLds>;
+static_assert(NumAll0::LDS <= kAllLds && NumAll1::LDS <= kAllLds && NumAll2::LDS <= kAllLds &&
+              NumAll3::LDS <= kAllLds && NumAllW::LDS <= kAllLds, "one LDS buffer for every part");
+
+__global__ __launch_bounds__(kWG) void k_num_all(Batch b, Sched sc)
+{
+    __shared__ __attribute__((aligned(16))) char s_mem[kAllLds];
+    // rows (windows) per workgroup of each part
+    const int per[kNumClasses + 1] = {NumAll0::W * NumAll0::NW, NumAll1::W * NumAll1::NW, NumAll2::NW, NumAll3::NW,
+                                      1, NumAllW::NW};
+    int vblk, vgrid;
+    switch (part_of_block(sc, per, vblk, vgrid)) {
+    case 0: num_lds_rows<8, kFillCap[0], true, false, true, kAllLds>(b, sc, 0, s_mem, vblk, vgrid); break;
+    case 1: num_lds_rows<32, kFillCap[1], true, false, false, kAllLds>(b, sc, 1, s_mem, vblk, vgrid); break;
+    case 2: num_lds_rows<64, kFillCap[2], true, false, false, kAllLds>(b, sc, 2, s_mem, vblk, vgrid); break;
+    case 3: num_lds_rows<64, kFillCap[3], true, false, false, kAllLds>(b, sc, 3, s_mem, vblk, vgrid); break;
+    case kNumClasses: num_win_rows<kNumWinCap, true, false, kAllLds>(b, sc, s_mem); break;
+    }
+}
+
 // ---------------------------------------------------------------------------
 
 template <typename K>
@@ -831,9 +904,7 @@ static int persistent_grid_n(K kernel, int threads)
 template <int G, int CAP, bool PACK, bool MULTI, bool FLAT>
 static void launch_num_variant(const Batch &b, const Sched &sc, int bin, hipStream_t s)
 {
-    constexpr int W = kWave / G;
-    constexpr int XW = FLAT ? num_flat_words(G) : 0;
-    constexpr int NW = nw_num(num_row_bytes(CAP, G, PACK) + 4 * XW, W);
+    constexpr int NW = NumShape<G, CAP, PACK, MULTI, FLAT>::NW;
     static int grid = persistent_grid_n(k_num_lds<G, CAP, PACK, MULTI, FLAT>, NW * kWave);
     static char name[64];
     if (!name[0])
@@ -863,7 +934,7 @@ static void launch_num_class(const Batch &b, const Sched &sc, int bin, hipStream
 template <int CAP, bool PACK, bool MULTI>
 static void launch_num_win(const Batch &b, const Sched &sc, hipStream_t s)
 {
-    constexpr int NW = nw_num(win_bytes(CAP, PACK), 1);
+    constexpr int NW = WinShape<CAP, PACK>::NW;
     static int grid = persistent_grid_n(k_num_win<CAP, PACK, MULTI>, NW * kWave);
     static char name[64];
     if (!name[0]) snprintf(name, sizeof(name), "num_spill_C%d%s%s", CAP, PACK ? "_p" : "", MULTI ? "_b" : "");
@@ -900,6 +971,25 @@ void launch_numeric_groups(const Batch &b, const Sched &sc, int G1, int G2, hipS
     launch_num_class<64, kFillCap[3]>(b, sc, 3, s);
     launch_num_class<64, kFillCap[4]>(b, sc, 4, s);
     launch_num_spill(b, sc, s);
+}
+
+bool small_rows_fit(const Batch &b)
+{
+    return b.nprob == 1 && b.na > 0 && b.na <= kSmallRows && b.max_ncols > 0 &&
+           (uint32_t)b.max_ncols <= PackBits<kFillCap[4]>::kMaxCols;
+}
+
+int small_rows_grid(int na)
+{
+    const int want = na / 2 + kNumBins;   // two rows per workgroup in the larger classes
+    return want < kSmallGrid ? want : kSmallGrid;
+}
+
+void launch_numeric_small(const Batch &b, const Sched &sc, hipStream_t s)
+{
+    launch_bin_small(b, sc, kNumWinCap / 2, s);
+    ProfScope ps("num_all", s);
+    hipLaunchKernelGGL(k_num_all, dim3(small_rows_grid(b.na)), dim3(kWG), 0, s, b, sc);
 }
 
 void launch_numeric(const Batch &b, const Sched &sc, int G, hipStream_t s)

@@ -24,6 +24,13 @@ __global__ void k_fill_f64(double *p, double v, int64_t n)
     for (; i < n; i += stride) p[i] = v;
 }
 
+__global__ void k_zero2_f64(double *p, int64_t n, double *q, int64_t m)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (; i < n + m; i += stride) *(i < n ? p + i : q + (i - n)) = 0.0;
+}
+
 // ---------------------------------------------------------------------------
 // Per-row helpers: one thread per short row, the whole wave per long row.
 
@@ -700,6 +707,102 @@ __global__ __launch_bounds__(kWG) void k_scatter(int na, Sched sc, int nb, int f
     }
 }
 
+// Numeric binning of one product of few rows by one workgroup, in place of the
+// header fill, the binning, the scatter and the window scan: sizes from C's
+// row pointers, counts per bin and wave, then each wave's rows placed in
+// ascending order (wave w takes the rows [w * span, (w + 1) * span), read
+// again from the cache: classes kept in registers spilled). The launch that
+// follows has no part for the largest class: its rows join the spill bin.
+// Latency bound: 4096 rows take 4 iterations, 20480 take 20.
+constexpr int kSmallWG = 1024;
+
+__device__ __forceinline__ int small_class(int nc)
+{
+    const int c = class_of(kModeNumeric, nc, -1);
+    return c == kNumClasses - 1 ? kBinSpill : c;
+}
+
+__global__ __launch_bounds__(kSmallWG) void k_bin_small(Batch b, Sched sc, int m)
+{
+    constexpr int NW = kSmallWG / kWave;
+    __shared__ int s_cnt[NW][kNumBins];
+    __shared__ int s_red[NW];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const MLS_G int32_t *crp = gp(b.p0.crp);
+    if (tid == 0) *gpw(sc.err) = 0u;
+    if (tid < kNumBins * kXcd) gpw(sc.task_cursor)[tid] = 0;
+    const int span = ((b.na + NW - 1) / NW + kWave - 1) / kWave * kWave;
+    const int r0 = wave * span, r1 = min(b.na, r0 + span);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int n[kNumBins];
+#pragma unroll
+    for (int c = 0; c < kNumBins; ++c) n[c] = 0;
+#pragma unroll 4
+    for (int r = r0; r < r1; r += kWave) {
+        const int i = r + lane;
+        const int nc = i < r1 ? crp[i + 1] - crp[i] : 0;
+        const int cls = i < r1 ? small_class(nc) : -1;
+        if (i < r1) gpw(sc.val)[i] = nc;
+#pragma unroll
+        for (int c = 0; c < kNumBins; ++c) n[c] += __popcll(__ballot(cls == c));
+    }
+    if (lane == 0) {
+#pragma unroll
+        for (int c = 0; c < kNumBins; ++c) s_cnt[wave][c] = n[c];
+    }
+    __syncthreads();
+    int at[kNumBins], before = 0, spill0 = 0, nspill = 0;
+#pragma unroll
+    for (int c = 0; c < kNumBins; ++c) {
+        int mine = 0, all = 0;
+        for (int w = 0; w < NW; ++w) {
+            mine += w < wave ? s_cnt[w][c] : 0;
+            all += s_cnt[w][c];
+        }
+        at[c] = before + mine;
+        if (c == kBinSpill) { spill0 = before; nspill = all; }
+        before += all;
+        if (tid == 0) gpw(sc.bin_count)[c] = all;
+    }
+#pragma unroll 4
+    for (int r = r0; r < r1; r += kWave) {
+        const int i = r + lane;
+        const int cls = i < r1 ? small_class(crp[i + 1] - crp[i]) : -1;
+#pragma unroll
+        for (int c = 0; c < kNumBins; ++c) {
+            const unsigned long long mm = __ballot(cls == c);
+            if (cls == c) gpw(sc.perm)[at[c] + __popcll(mm & below)] = i;
+            at[c] += __popcll(mm);
+        }
+    }
+    if (nspill == 0) return;
+    __threadfence_block();
+    __syncthreads();
+    // windows of the spill rows, as k_win_scan numbers them
+    MLS_G int32_t *ws = gpw(sc.wstart);
+    int carry = 0;
+    for (int q0 = 0; q0 < nspill; q0 += kSmallWG) {
+        const int q = q0 + tid;
+        int c = 0;
+        if (q < nspill) {
+            const int i = __hip_atomic_load(sc.perm + spill0 + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            c = (crp[i + 1] - crp[i] + m - 1) / m;
+        }
+        const int incl = group_scan_incl<kWave>(c, lane);
+        if (lane == kWave - 1) s_red[wave] = incl;
+        __syncthreads();
+        int off = carry, all = 0;
+        for (int w = 0; w < NW; ++w) {
+            off += w < wave ? s_red[w] : 0;
+            all += s_red[w];
+        }
+        if (q < nspill) ws[q] = off + incl - c;
+        carry += all;
+        __syncthreads();
+    }
+    if (tid == 0) ws[nspill] = carry;
+}
+
 // ---------------------------------------------------------------------------
 // Exclusive scan of the per-row counts into int64 prefixes, then the int32
 // row pointers of each product.
@@ -817,6 +920,16 @@ void launch_fill_f64(double *p, double v, int64_t n, hipStream_t s)
     hipLaunchKernelGGL(k_fill_f64, dim3(grid), dim3(kWG), 0, s, p, v, n);
 }
 
+void launch_zero2_f64(double *p, int64_t n, double *q, int64_t m, hipStream_t s)
+{
+    if (!p) n = 0;
+    if (!q) m = 0;
+    if (n + m <= 0) return;
+    int grid = nblk(n + m, kWG);
+    if (grid > 4096) grid = 4096;
+    hipLaunchKernelGGL(k_zero2_f64, dim3(grid), dim3(kWG), 0, s, p, n, q, m);
+}
+
 void launch_validate(const Batch &b, int which, const int64_t *nnz_tab, int64_t nnz_a, int64_t nnz_b, uint32_t *err,
                      hipStream_t s)
 {
@@ -854,6 +967,12 @@ void launch_scatter(int na, const Sched &sc, hipStream_t s)
     const int fold = nb <= kFoldBlocks;
     if (!fold) hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(kScanWG), 0, s, sc, nb);
     hipLaunchKernelGGL(k_scatter, dim3(nb), dim3(kWG), 0, s, na, sc, nb, fold);
+}
+
+void launch_bin_small(const Batch &b, const Sched &sc, int m, hipStream_t s)
+{
+    ProfScope ps("bin_small", s);
+    hipLaunchKernelGGL(k_bin_small, dim3(1), dim3(kSmallWG), 0, s, b, sc, m);
 }
 
 int scan_tiles(int n) { return nblk(n > 0 ? n : 1, kScanTile); }

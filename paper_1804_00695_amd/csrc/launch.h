@@ -12,6 +12,8 @@ enum { kModeCount = 0, kModeFill = 1, kModeNumeric = 2, kModeWork = 3 };
 
 void launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 void launch_fill_f64(double *p, double v, int64_t n, hipStream_t s);
+// Both arrays in one launch (either may be NULL or empty).
+void launch_zero2_f64(double *p, int64_t n, double *q, int64_t m, hipStream_t s);
 // CSR checks: which = 0 A, 1 B, 2 both in one launch. The entry counts come
 // from nnz_tab (device, two per product), or, when it is NULL (one product),
 // from nnz_a and nnz_b.
@@ -45,6 +47,23 @@ void launch_sym_expand(const Batch &b, const Sched &sc, hipStream_t s);
 // Windows of the spill bin's rows, ceil(size / m) per row: sc.wstart[r] = the
 // first window of the r-th spill row, sc.wstart[n] = their total (one workgroup).
 __global__ void k_win_scan(Batch b, Sched sc, int m);
+
+// Products of at most kSmallRows rows (one product, columns that fit the
+// packed tables): the numeric phase as two launches, one workgroup that bins
+// the rows (those of the largest class with the spill rows), clears the
+// scheduling counters (and the error word, which it owns) and numbers the
+// windows of `m` positions, and one launch for every class. Up to 20480 rows:
+// beyond, the one workgroup that bins takes longer than the launches it saves
+// (random rows of 36 outputs, numeric / adjoint in us by class and in two
+// launches: 12000 rows 55/57 and 32/39, 20000 rows 50/58 and 46/55, 32000
+// rows 66/77 and 67/80).
+constexpr int kSmallRows = 20480;
+constexpr int kSmallGrid = 1280;   // five workgroups per CU
+bool small_rows_fit(const Batch &b);
+int small_rows_grid(int na);
+void launch_bin_small(const Batch &b, const Sched &sc, int m, hipStream_t s);
+void launch_numeric_small(const Batch &b, const Sched &sc, hipStream_t s);
+void launch_backward_small(const Batch &b, const Sched &sc, double *dA, double *dB, hipStream_t s);
 
 // Numeric phase (row-range fused multiply-add) over the binned rows.
 void launch_numeric(const Batch &b, const Sched &sc, int G, hipStream_t s);

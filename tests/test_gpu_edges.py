@@ -107,3 +107,32 @@ def test_refused_then_accepted(which, binned):
         check(A, B)
     finally:
         mls.set_option(mls._abi.OPT_FORCE_CLASS, -1)
+
+
+# few rows run in two launches (the default) or by class (any forced lane
+# count); around the limit of 20480 rows, with every bin present or alone, and
+# fewer workgroups than XCDs
+@pytest.mark.parametrize("rows", [1, 2, 63, 64, 65, 1023, 1025, 20479, 20480, 20481])
+def test_few_rows(rows):
+    g = synth.rng(rows)
+    lens = np.zeros(rows, np.int64)
+    lens[g.integers(0, rows, rows // 2 + 1)] = g.integers(1, 12, rows // 2 + 1)
+    for at, n in enumerate([30, 33, 128, 129, 500, 513, 1020, 1030, 2040, 2060, 4000]):
+        if rows > 600:
+            lens[(at * 53 + 7) % rows] = n      # C's rows are as long: B's rows are single columns
+    n = 5000
+    A = rows_of(lens, n, rows)
+    B = synth.Csr(n, n, np.arange(n + 1, dtype=np.int32),
+                  g.permutation(n).astype(np.int32), g.standard_normal(n))
+    R = check(A, B)
+    W = synth.Csr(R.nrows, R.ncols, R.row_ptr, R.col_idx, synth.normal_values(R.nnz, 3))
+    gA, gB = mls.backward(*[mls.DeviceCsr.from_host(M) for M in (A, B, W)])
+    rA, rB, aA, aB = oracle.backward(A, B, W)
+    assert np.all(np.abs(gA.cpu().numpy() - rA) <= 1e-10 * aA)
+    assert np.all(np.abs(gB.cpu().numpy() - rB) <= 1e-10 * aB)
+
+
+@pytest.mark.parametrize("row_len", [20, 100, 400, 900, 1500, 3000])
+def test_few_rows_one_bin(row_len):
+    A = rows_of([row_len] * 9, 6000, row_len)
+    check(A, synth.poisson_csr(6000, 50000, 1.3, 9))
