@@ -52,6 +52,7 @@ struct BatchHost {
     std::vector<Prob> probs;
     std::vector<int32_t> abase, bbase;
     std::vector<int64_t> nnz_tab;
+    int64_t za = 0, zb = 0;     // entries of all A and of all B
     double avg_a = 1.0, avg_b = 1.0;
     std::vector<uint64_t> key;  // operands and shapes of the call, verbatim
 };
@@ -63,6 +64,10 @@ Layout make_layout(int64_t nprob, int64_t na, int64_t nb, int64_t zb, int64_t ma
 Sched make_sched(char *ws, const Layout &L);
 void reset_header(char *ws, const Layout &L, hipStream_t s);
 spgemm_status read_errors(char *ws, const Layout &L, hipStream_t s);
+spgemm_status read_header_total(char *ws, const Layout &L, int64_t *total_host, hipStream_t s);
+// Copies a few bytes of device memory to the host behind the work queued on s
+// and waits for them.
+spgemm_status read_back(void *dst, const void *src, size_t bytes, hipStream_t s);
 // upload = false skips the host-to-device copies of the descriptor tables
 // (only a single product's numeric phase can do without them: it passes its
 // descriptor by value and never reads the entry-count table).

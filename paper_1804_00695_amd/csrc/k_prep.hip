@@ -32,355 +32,265 @@ __global__ void k_zero2_f64(double *p, int64_t n, double *q, int64_t m)
 }
 
 // ---------------------------------------------------------------------------
-// Per-row helpers: one thread per short row, the whole wave per long row.
+// Entry streams: the rows of a wave (rw consecutive ones, rw a power of two up
+// to 64) hold one contiguous run of entries, which the wave walks 64 at a time
+// whatever the rows' lengths, with the loads of a tile of kTileSteps steps in
+// flight. A bit per entry of the tile tells where a (non-empty) row starts.
+constexpr int kTileSteps = 8;
+constexpr int kTileEntries = kTileSteps * kWave;
+
+__device__ __forceinline__ void prep_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// Row starts of the tile [tb, tb + kTileEntries) from the lanes' rows [s, e),
+// as a bitmap in flags (kTileEntries bits).
+__device__ __forceinline__ void tile_starts(uint32_t *flags, int lane, int tb, int s, int e)
+{
+    static_assert(kTileEntries / 32 <= kWave, "one word per lane");
+    if (lane < kTileEntries / 32) flags[lane] = 0u;
+    prep_sync();
+    const int at = s - tb;
+    if (s < e && (uint32_t)at < (uint32_t)kTileEntries) atomicOr(flags + (at >> 5), 1u << (at & 31));
+    prep_sync();
+}
+
+// Lane l's value from lane l - 1; lane 0 gets `first` (DPP wave shift).
+__device__ __forceinline__ int lane_before(int v, int first)
+{
+    return __builtin_amdgcn_update_dpp(first, v, 0x138, 0xF, 0xF, false);
+}
 
 // CSR checks over the A rows (which = 0) or B rows (which = 1) of a batch:
 // row_ptr[0] == 0, non-decreasing, row_ptr[n] == nnz, columns in range and
-// strictly increasing. Column indices outside [0, nnz) are never read.
-// One thread per row walks rows of up to kShortRow entries; rows of up to 16
-// (32) entries are checked by 16 (32) lanes each, four (two) at a time; the
-// wave checks longer rows together, one at a time, 64 entries per step.
-constexpr int kShortRow = 4;
-constexpr int kLongAhead = 4;   // long rows: steps of 64 entries whose loads are issued together
-
-// 64 / GL rows per step, GL lanes per row (rows of at most GL entries); mm
-// holds the lanes that own such rows. A row's verdict goes to its owner lane.
-template <int GL>
-__device__ __forceinline__ void validate_group_rows(unsigned long long mm, int lane, int len, int ncols,
-                                                    const int32_t *ci_row, bool &bad)
-{
-    constexpr int NG = kWave / GL;
-    constexpr uint32_t kAll = GL == 32 ? 0xffffffffu : ((1u << GL) - 1u);
-    const int grp = lane / GL, gl = lane % GL;
-    while (mm) {
-        int pick = -1;
-#pragma unroll
-        for (int j = 0; j < NG; ++j) {
-            const int r = mm ? __ffsll((long long)mm) - 1 : -1;
-            if (mm) mm &= mm - 1ull;
-            if (j == grp) pick = r;
-        }
-        // every lane takes part in the shuffles (a group without a row reads lane 0)
-        const int from = pick >= 0 ? pick : 0;
-        int n = __shfl(len, from, kWave);
-        if (pick < 0) n = 0;
-        const int nc = __shfl(ncols, from, kWave);
-        const uint64_t pa = ((uint64_t)(uint32_t)__shfl((int)((uint64_t)ci_row >> 32), from, kWave) << 32) |
-                            (uint32_t)__shfl((int)(uint64_t)ci_row, from, kWave);
-        const bool valid = gl < n;
-        const int cq = valid ? ((const MLS_G int32_t *)pa)[gl] : 0;
-        int prev = __shfl_up(cq, 1, GL);
-        if (gl == 0) prev = -1;
-        const bool bl = valid && (cq < 0 || cq >= nc || cq <= prev);
-        const unsigned long long bb = __ballot(bl);
-#pragma unroll
-        for (int j = 0; j < NG; ++j) {
-            const int pj = __shfl(pick, j * GL, kWave);
-            if (((uint32_t)(bb >> (j * GL)) & kAll) && lane == pj) bad = true;
-        }
-    }
-}
-
-// which = 0: the A rows; 1: the B rows; 2: the A rows by the first a_blocks
-// workgroups, the B rows by the others.
+// strictly increasing. Column indices outside [0, nnz) are never read: a wave
+// whose row pointers fail reads no entries.
+// which = 2: the A rows by the first a_blocks workgroups, the B rows by the
+// others. Bound by the reads of the columns: 27-point stencil 128^3 54 us (223
+// MB, 4.1 TB/s), R-MAT 18's L 21 us. (112 and 74 us with rows dealt to 1, 16,
+// 32 or 64 lanes by length, rows of more than 32 entries one after the other.)
 __global__ __launch_bounds__(kWG) void k_validate(Batch b, int which, const int64_t *nnz_tab, int64_t nnz_a,
-                                                  int64_t nnz_b, int a_blocks, uint32_t *err)
+                                                  int64_t nnz_b, int a_blocks, int rw_a, int rw_b, uint32_t *err)
 {
+    __shared__ uint32_t s_flags[kWG / kWave][kTileEntries / 32];
     const int lane = threadIdx.x & 63;
+    uint32_t *flags = s_flags[threadIdx.x >> 6];
     int blk = (int)blockIdx.x;
     if (which == 2) {
         which = blk < a_blocks ? 0 : 1;
         if (which) blk -= a_blocks;
     }
     const int total = which == 0 ? b.na : b.nb;
-    const int g = blk * kWG + (int)threadIdx.x;
-    bool bad = false, longrow = false, midrow = false;
-    const int32_t *ci_row = nullptr;   // entries of this thread's row (long rows)
-    int len = 0, ncols = 0;
+    const int rw = which == 0 ? rw_a : rw_b;
+    const int g0 = (blk * (kWG / kWave) + (int)(threadIdx.x >> 6)) * rw, g = g0 + lane;
     const int32_t *base = which == 0 ? b.abase : b.bbase;
-    const int t_row = b.nprob == 1 ? 0 : find_prob_rows(base, b.nprob, g - lane, g);
-    if (g < total) {
-        const int t = t_row;
+    const bool row = lane < rw && g < total;
+    const int gw = g0 < total ? g0 : total - 1;
+    const int t = b.nprob == 1 ? 0 : find_prob_rows(base, b.nprob, gw, row ? g : gw);
+    bool bad = false;
+    const int32_t *ci = nullptr;
+    int s = 0, e = 0, ncols = 0;
+    if (row) {
         const Prob P = get_prob_any(b, t);
         const int i = g - (b.nprob == 1 ? 0 : gp(base)[t]);
         const MLS_G int32_t *rp = gp(which == 0 ? P.arp : P.brp);
-        const int32_t *ci = which == 0 ? P.aci : P.bci;
         const int off = which == 0 ? P.a_off : P.b_off;
+        ci = which == 0 ? P.aci : P.bci;
         ncols = which == 0 ? P.k_hi : P.ncols;
         const int nrows = which == 0 ? P.nrows : P.krows;
         const int64_t nnz = nnz_tab ? gp(nnz_tab)[2 * t + which] : (which == 0 ? nnz_a : nnz_b);
-        const int s = rp[i], e = rp[i + 1];
+        s = rp[i];
+        e = rp[i + 1];
         if (i == 0 && s != off) bad = true;
         if (i == nrows - 1 && (int64_t)e - off != nnz) bad = true;
         if (e < s || s < off || (int64_t)e - off > nnz) bad = true;
-        if (!bad) {
-            len = e - s;
-            ci_row = ci + (s - off);
-            if (len <= kShortRow) {
-                const MLS_G int32_t *c = gp(ci_row);
-                int prev = -1, q = 0;
-                for (; q + 4 <= len; q += 4) {
-                    const int c0 = c[q], c1 = c[q + 1], c2 = c[q + 2], c3 = c[q + 3];
-                    bad |= c0 <= prev || c1 <= c0 || c2 <= c1 || c3 <= c2 || c0 < 0 || c3 >= ncols;
-                    prev = c3;
-                }
-                for (; q < len; ++q) {
-                    const int cq = c[q];
-                    bad |= cq <= prev || cq < 0 || cq >= ncols;
-                    prev = cq;
-                }
-            } else if (len <= kWave / 2) {
-                midrow = true;
-            } else {
-                longrow = true;
-            }
-        }
+        s -= off;
+        e -= off;
     }
-    // rows of kShortRow + 1 .. 16 entries four per step (16 lanes each), of
-    // 17 .. 32 entries two per step (32 lanes each)
-    validate_group_rows<16>(__ballot(midrow && len <= 16), lane, len, ncols, ci_row, bad);
-    validate_group_rows<32>(__ballot(midrow && len > 16), lane, len, ncols, ci_row, bad);
-    unsigned long long lm = __ballot(longrow);
-    while (lm) {
-        const int src = __ffsll((long long)lm) - 1;
-        lm &= lm - 1ull;
-        const int n = __builtin_amdgcn_readlane(len, src);
-        const int nc = __builtin_amdgcn_readlane(ncols, src);
-        const uint64_t pa = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)((uint64_t)ci_row >> 32), src) << 32) |
-                            (uint32_t)__builtin_amdgcn_readlane((int)(uint64_t)ci_row, src);
+    if (__ballot(bad)) {
+        if (lane == 0) atomicOr(err, kErrBadCsr);
+        return;
+    }
+    // the wave's rows of one product at a time (almost always all of them):
+    // their pointers are consistent, so their entries are contiguous
+    unsigned long long todo = __ballot(row);
+    while (todo) {
+        const int l0 = __ffsll((long long)todo) - 1;
+        const int t0 = __builtin_amdgcn_readlane(t, l0);
+        const unsigned long long seg = __ballot(row && t == t0);
+        const int l1 = 63 - __clzll((long long)seg);
+        todo &= ~seg;
+        const bool mine = row && t == t0;
+        const int nc = __builtin_amdgcn_readlane(ncols, l0);
+        const int q0 = __builtin_amdgcn_readlane(s, l0), q1 = __builtin_amdgcn_readlane(e, l1);
+        const uint64_t pa = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)((uint64_t)ci >> 32), l0) << 32) |
+                            (uint32_t)__builtin_amdgcn_readlane((int)(uint64_t)ci, l0);
         const MLS_G int32_t *c = (const MLS_G int32_t *)pa;
         int carry = -1;
-        bool bl = false;
-        for (int q4 = 0; q4 < n; q4 += kLongAhead * kWave) {
-            // the loads of kLongAhead steps first
-            int cqv[kLongAhead];
+        for (int tb = q0; tb < q1; tb += kTileEntries) {
+            int cv[kTileSteps];
 #pragma unroll
-            for (int u = 0; u < kLongAhead; ++u) {
-                const int q = q4 + u * kWave + lane;
-                cqv[u] = q < n ? c[q] : 0;
+            for (int u = 0; u < kTileSteps; ++u) {
+                const int q = tb + u * kWave + lane;
+                cv[u] = *(q < q1 ? c + q : (const MLS_G int32_t *)k_zeros4);
             }
+            tile_starts(flags, lane, tb, mine ? s : 0, mine ? e : 0);
 #pragma unroll
-            for (int u = 0; u < kLongAhead; ++u) {
-                const int q0 = q4 + u * kWave;
-                if (q0 >= n) break;
-                const bool valid = q0 + lane < n;
-                const int cq = cqv[u];
-                int prev = __shfl_up(cq, 1, kWave);
-                if (lane == 0) prev = carry;
-                if (valid && (cq < 0 || cq >= nc || cq <= prev)) bl = true;
-                carry = __shfl(cq, kWave - 1, kWave);
+            for (int u = 0; u < kTileSteps; ++u) {
+                const int q = tb + u * kWave + lane;
+                const bool start = ((flags[2 * u + (lane >> 5)] >> (lane & 31)) & 1u) != 0u;
+                const int prev = lane_before(cv[u], carry);
+                bad |= q < q1 && (cv[u] < 0 || cv[u] >= nc || (!start && cv[u] <= prev));
+                carry = __builtin_amdgcn_readlane(cv[u], 63);
             }
+            prep_sync();
         }
-        if (__ballot(bl)) bad = bad || lane == src;
     }
-    if (bad) atomicOr(err, kErrBadCsr);
+    if (__ballot(bad) && lane == 0) atomicOr(err, kErrBadCsr);
 }
 
 // Column compression of every B row (set = col >> 5, mask bit = col & 31),
-// padded layout: the words of row k start at B's entry offset of row k.
-// One thread per row walks rows of up to kCompressShort entries; rows of up to
-// 16 (32) entries take 16 (32) lanes each, four (two) at a time; the wave takes
-// longer rows together, 64 entries per step: a lane starts a word where its set differs
-// from the previous entry's, masks are OR-ed in LDS, and the last word of a
-// step stays open (it may continue in the next step).
-constexpr int kCompressShort = 4;   // longest row a single thread compresses
-
-// 64 / GL rows per step, GL lanes per row (rows of at most GL entries); mm
-// holds the lanes that own such rows; wset / wmsk: the wave's 64 LDS slots.
-template <int GL>
-__device__ __forceinline__ void compress_group_rows(unsigned long long mm, int lane, int len, const int32_t *ci_row,
-                                                    uint2 *out_row, int32_t *cnt_ptr, uint32_t *wset, uint32_t *wmsk)
-{
-    constexpr int NG = kWave / GL;
-    constexpr uint32_t kAll = GL == 32 ? 0xffffffffu : ((1u << GL) - 1u);
-    constexpr uint32_t kNone = 0xffffffffu;
-    const int grp = lane / GL, gl = lane % GL;
-    while (mm) {
-        int pick = -1;
-#pragma unroll
-        for (int j = 0; j < NG; ++j) {
-            const int r = mm ? __ffsll((long long)mm) - 1 : -1;
-            if (mm) mm &= mm - 1ull;
-            if (j == grp) pick = r;
-        }
-        // every lane takes part in the shuffles (a group without a row reads lane 0)
-        const int from = pick >= 0 ? pick : 0;
-        int n = __shfl(len, from, kWave);
-        if (pick < 0) n = 0;
-        const uint64_t pc_ = ((uint64_t)(uint32_t)__shfl((int)((uint64_t)ci_row >> 32), from, kWave) << 32) |
-                             (uint32_t)__shfl((int)(uint64_t)ci_row, from, kWave);
-        const uint64_t po_ = ((uint64_t)(uint32_t)__shfl((int)((uint64_t)out_row >> 32), from, kWave) << 32) |
-                             (uint32_t)__shfl((int)(uint64_t)out_row, from, kWave);
-        const uint64_t pn_ = ((uint64_t)(uint32_t)__shfl((int)((uint64_t)cnt_ptr >> 32), from, kWave) << 32) |
-                             (uint32_t)__shfl((int)(uint64_t)cnt_ptr, from, kWave);
-        const bool valid = gl < n;
-        const uint32_t cv = valid ? (uint32_t)((const MLS_G int32_t *)pc_)[gl] : 0u;
-        const uint32_t set = valid ? (cv >> 5) : kNone;
-        uint32_t prev = __shfl_up(set, 1, GL);
-        if (gl == 0) prev = kNone;
-        const bool head = valid && set != prev;
-        const uint32_t hm = (uint32_t)(__ballot(head) >> (GL * grp)) & kAll;
-        const int lw = __popc(hm & ((2u << gl) - 1u)) - 1;   // word of this entry (entry 0 is a head)
-        uint32_t *hs = wset + GL * grp;
-        uint32_t *hk = wmsk + GL * grp;
-        hk[gl] = 0u;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        if (valid) {
-            atomicOr(&hk[lw], 1u << (cv & 31u));
-            if (head) hs[lw] = set;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        const int nh = __popc(hm);
-        if (gl < nh) {
-            u32x2 w; w.x = hs[gl]; w.y = hk[gl];
-            ((MLS_G u32x2 *)po_)[gl] = w;
-        }
-        if (pick >= 0 && gl == 0) gpw((int32_t *)pn_)[0] = nh;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    }
-}
-
-__global__ __launch_bounds__(kWG) void k_compress(Batch b, const uint32_t *err)
+// padded layout: the words of row k start at B's entry offset of row k. An
+// entry starts a word (is a head) where a row starts or its set differs from
+// the entry before; the masks of a step's words are OR-ed in LDS, and the last
+// word of a step stays open (it may continue in the next one). With H the
+// heads of the wave's stream before a head, its word goes to q - H of the
+// latest row start, plus H. Bound by reads and writes: 27-point stencil 128^3
+// 136 us (about 0.39 GB); R-MAT 18's L, whose long rows are neighbours, 77 us,
+// by its waves' longest runs. (179 and 199 us row by row as above; 155 and 186
+// us as a stream of 64 rows per wave and one LDS exchange per step.)
+__global__ __launch_bounds__(kWG) void k_compress(Batch b, int rw, const uint32_t *err)
 {
     if (bad_csr(err)) return;
-    __shared__ uint32_t s_set[kWG / kWave][kWave + 1];
-    __shared__ uint32_t s_msk[kWG / kWave][kWave + 1];
+    constexpr int NWV = kWG / kWave;
+    __shared__ uint32_t s_flags[NWV][kTileEntries / 32];
+    __shared__ uint32_t s_msk[NWV][kTileEntries + kWave];   // masks of a tile's words, 0 the one left open
+    __shared__ int s_heads[NWV][kWave + 1];   // heads before the k-th non-empty row
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t *wset = s_set[wave];
-    uint32_t *wmsk = s_msk[wave];
-    const uint32_t kNone = 0xffffffffu;
-    const int g = blockIdx.x * kWG + threadIdx.x;
-    bool longrow = false, midrow = false;
-    const int32_t *ci_row = nullptr;
-    uint2 *out_row = nullptr;
-    int32_t *cnt_ptr = nullptr;
-    int len = 0;
-    const int t_row = b.nprob == 1 ? 0 : find_prob_rows(b.bbase, b.nprob, g - (int)(threadIdx.x & 63), g);
-    if (g < b.nb) {
-        const int t = t_row;
+    uint32_t *flags = s_flags[wave], *wmsk = s_msk[wave];
+    int *heads = s_heads[wave];
+    constexpr uint32_t kNone = 0xffffffffu;
+    const int g0 = ((int)blockIdx.x * NWV + wave) * rw, g = g0 + lane;
+    const bool row = lane < rw && g < b.nb;
+    const int gw = g0 < b.nb ? g0 : b.nb - 1;
+    const int t = b.nprob == 1 ? 0 : find_prob_rows(b.bbase, b.nprob, gw, row ? g : gw);
+    const int32_t *ci = nullptr;
+    uint2 *bw = nullptr;
+    int32_t *cnt = nullptr;
+    int s = 0, e = 0;
+    if (row) {
         const Prob P = get_prob_any(b, t);
         const int k = g - (b.nprob == 1 ? 0 : gp(b.bbase)[t]);
-        const int s0 = gp(P.brp)[k] - P.b_off;
-        len = gp(P.brp)[k + 1] - P.b_off - s0;
-        ci_row = P.bci + s0;
-        out_row = P.bw + s0;
-        cnt_ptr = P.bwc + k;
-        if (len <= kCompressShort) {
-            const MLS_G int32_t *c = gp(ci_row);
-            MLS_G u32x2 *out = (MLS_G u32x2 *)out_row;
-            uint32_t cur = kNone, msk = 0;
-            int nout = 0;
-            for (int q0 = 0; q0 < len; q0 += 4) {
-                int cq[4];
-#pragma unroll
-                for (int d = 0; d < 4; ++d) cq[d] = q0 + d < len ? c[q0 + d] : -1;
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    if (cq[d] < 0) continue;
-                    const uint32_t set = (uint32_t)cq[d] >> 5;
-                    if (set != cur) {
-                        if (cur != kNone) { u32x2 w; w.x = cur; w.y = msk; out[nout++] = w; }
-                        cur = set;
-                        msk = 0;
-                    }
-                    msk |= 1u << (cq[d] & 31);
-                }
-            }
-            if (cur != kNone) { u32x2 w; w.x = cur; w.y = msk; out[nout++] = w; }
-            gpw(cnt_ptr)[0] = nout;
-        } else if (len <= kWave / 2) {
-            midrow = true;
-        } else {
-            longrow = true;
-        }
+        s = gp(P.brp)[k] - P.b_off;
+        e = gp(P.brp)[k + 1] - P.b_off;
+        ci = P.bci;
+        bw = P.bw;
+        cnt = P.bwc + k;
     }
-    // rows of kCompressShort + 1 .. 16 entries four per step (16 lanes each),
-    // of 17 .. 32 entries two per step (32 lanes each)
-    compress_group_rows<16>(__ballot(midrow && len <= 16), lane, len, ci_row, out_row, cnt_ptr, wset, wmsk);
-    compress_group_rows<32>(__ballot(midrow && len > 16), lane, len, ci_row, out_row, cnt_ptr, wset, wmsk);
-    unsigned long long lm = __ballot(longrow);
-    while (lm) {
-        const int src = __ffsll((long long)lm) - 1;
-        lm &= lm - 1ull;
-        const int n = __builtin_amdgcn_readlane(len, src);
+    for (int x = lane; x < kTileEntries + kWave; x += kWave) wmsk[x] = 0u;
+    const unsigned long long upto = lane == 63 ? ~0ull : (2ull << lane) - 1ull;   // lanes 0 .. lane
+    unsigned long long todo = __ballot(row);
+    while (todo) {
+        const int l0 = __ffsll((long long)todo) - 1;
+        const int t0 = __builtin_amdgcn_readlane(t, l0);
+        const bool mine = row && t == t0;
+        const unsigned long long seg = __ballot(mine);
+        const int l1 = 63 - __clzll((long long)seg);
+        todo &= ~seg;
         auto rl64 = [&](const void *p) {
             const uint64_t v = (uint64_t)p;
-            return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), src) << 32) |
-                   (uint32_t)__builtin_amdgcn_readlane((int)v, src);
+            return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l0) << 32) |
+                   (uint32_t)__builtin_amdgcn_readlane((int)v, l0);
         };
-        const MLS_G int32_t *c = (const MLS_G int32_t *)rl64(ci_row);
-        MLS_G u32x2 *out = (MLS_G u32x2 *)rl64(out_row);
-        int32_t *cp = (int32_t *)rl64(cnt_ptr);
-        uint32_t carry_set = kNone, carry_msk = 0;
-        int nout = 0;
-        uint32_t cvv[kLongAhead];
-        for (int c0 = 0; c0 < n; c0 += kWave) {
-            const int u = (c0 / kWave) % kLongAhead;
-            if (u == 0) {   // the loads of the next kLongAhead steps
+        const MLS_G int32_t *c = (const MLS_G int32_t *)rl64(ci);
+        MLS_G u32x2 *out = (MLS_G u32x2 *)rl64(bw);
+        const int q0 = __builtin_amdgcn_readlane(s, l0), q1 = __builtin_amdgcn_readlane(e, l1);
+        const unsigned long long full = __ballot(mine && s < e);
+        // the open word (set, mask, its place), the latest row start's q - H,
+        // and the heads and row starts of the stream so far
+        uint32_t open_set = kNone, open_msk = 0u;
+        int open_pos = 0, shift = 0, nheads = 0, nrows = 0;
+        for (int tb = q0; tb < q1; tb += kTileEntries) {
+            uint32_t cv[kTileSteps];
 #pragma unroll
-                for (int v = 0; v < kLongAhead; ++v) {
-                    const int qv = c0 + v * kWave + lane;
-                    cvv[v] = qv < n ? (uint32_t)c[qv] : 0u;
+            for (int u = 0; u < kTileSteps; ++u) {
+                const int q = tb + u * kWave + lane;
+                cv[u] = (uint32_t)*(q < q1 ? c + q : (const MLS_G int32_t *)k_zeros4);
+            }
+            tile_starts(flags, lane, tb, mine ? s : 0, mine ? e : 0);
+            // the tile's heads and their words' masks: every step's ORs before
+            // any of their results is read
+            int lw[kTileSteps], at[kTileSteps];   // at < 0: no head
+            int th = 0;                           // heads of the tile so far
+            uint32_t carry = open_set, last_set = open_set;
+            int last_pos = open_pos;
+#pragma unroll
+            for (int u = 0; u < kTileSteps; ++u) {
+                lw[u] = 0;
+                at[u] = -1;
+                if (tb + u * kWave >= q1) continue;
+                const int q = tb + u * kWave + lane;
+                const bool valid = q < q1;
+                const bool start = valid && ((flags[2 * u + (lane >> 5)] >> (lane & 31)) & 1u) != 0u;
+                const uint32_t set = valid ? cv[u] >> 5 : kNone;
+                const uint32_t prev = (uint32_t)lane_before((int)set, (int)carry);
+                const bool head = valid && (start || set != prev);
+                const unsigned long long hm = __ballot(head), sm = __ballot(start);
+                lw[u] = th + __popcll(hm & upto);     // the entry's word in the tile
+                const int h = nheads + lw[u] - 1;     // heads before the entry's own
+                if (start) heads[nrows + __popcll(sm & upto) - 1] = h;
+                // q - H of the latest row start at or before this lane
+                const unsigned long long sb = sm & upto;
+                const int sh = __shfl(q - h, sb ? 63 - __clzll((long long)sb) : 0, kWave);
+                const int place = (sb ? sh : shift) + h;
+                if (head) at[u] = place;
+                if (valid) atomicOr(&wmsk[lw[u]], 1u << (cv[u] & 31u));
+                if (hm) {
+                    const int lh = 63 - __clzll((long long)hm);
+                    last_set = (uint32_t)__builtin_amdgcn_readlane((int)set, lh);
+                    last_pos = __builtin_amdgcn_readlane(place, lh);
                 }
+                if (sm) shift = __builtin_amdgcn_readlane(q - h, 63 - __clzll((long long)sm));
+                carry = (uint32_t)__builtin_amdgcn_readlane((int)set, 63);
+                th += __popcll(hm);
+                nrows += __popcll(sm);
             }
-            const int q = c0 + lane;
-            const bool valid = q < n;
-            uint32_t cv = 0u;
+            prep_sync();
+            // word 0 continues the open word, words 1 .. th - 1 are complete,
+            // word th stays open
+            if (th > 0 && open_set != kNone && lane == 0) {
+                u32x2 w; w.x = open_set; w.y = open_msk | wmsk[0];
+                out[open_pos] = w;
+            }
+            if (th == 0) open_msk |= (uint32_t)__builtin_amdgcn_readfirstlane((int)wmsk[0]);
+            else open_msk = (uint32_t)__builtin_amdgcn_readfirstlane((int)wmsk[th]);
+            open_set = last_set;
+            open_pos = last_pos;
+            nheads += th;
 #pragma unroll
-            for (int v = 0; v < kLongAhead; ++v)
-                if (v == u) cv = cvv[v];
-            cv = valid ? cv : 0u;
-            const uint32_t set = valid ? (cv >> 5) : kNone;
-            uint32_t prev = __shfl_up(set, 1, kWave);
-            if (lane == 0) prev = carry_set;
-            const bool head = valid && set != prev;
-            const unsigned long long hm = __ballot(head);
-            const int lw = __popcll(hm & ((2ull << lane) - 1ull));   // 0 = continues the open word
-            wmsk[lane] = 0u;
-            if (lane == 0) wmsk[kWave] = 0u;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            if (valid) {
-                atomicOr(&wmsk[lw], 1u << (cv & 31u));
-                if (head) wset[lw] = set;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            const int nh = __popcll(hm);
-            // word 0 continues the open word; words 1..nh-1 are complete; word nh stays open
-            if (nh > 0 && carry_set != kNone && lane == 0) {
-                u32x2 w; w.x = carry_set; w.y = carry_msk | wmsk[0];
-                out[nout] = w;
-            }
-            const int base_out = nout + (carry_set != kNone ? 1 : 0);
-            if (lane >= 1 && lane < nh) {
-                u32x2 w; w.x = wset[lane]; w.y = wmsk[lane];
-                out[base_out + lane - 1] = w;
-            }
-            if (nh > 0) {
-                nout += (carry_set != kNone ? 1 : 0) + nh - 1;
-                carry_set = wset[nh];
-                carry_msk = wmsk[nh];
-            } else {
-                carry_msk |= wmsk[0];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            for (int u = 0; u < kTileSteps; ++u)
+                if (at[u] >= 0 && lw[u] < th) {
+                    u32x2 w; w.x = cv[u] >> 5; w.y = wmsk[lw[u]];
+                    out[at[u]] = w;
+                }
+            prep_sync();
+            for (int x = lane; x <= th; x += kWave) wmsk[x] = 0u;
+            prep_sync();
         }
-        if (carry_set != kNone) {
-            if (lane == 0) { u32x2 w; w.x = carry_set; w.y = carry_msk; out[nout] = w; }
-            ++nout;
+        if (open_set != kNone && lane == 0) {
+            u32x2 w; w.x = open_set; w.y = open_msk;
+            out[open_pos] = w;
         }
-        if (lane == 0) gpw(cp)[0] = nout;
+        if (lane == 0) heads[nrows] = nheads;
+        prep_sync();
+        if (mine) {
+            const int o = __popcll(full & upto) - 1;   // this row's rank among the non-empty ones
+            gpw(cnt)[0] = s < e ? heads[o + 1] - heads[o] : 0;
+        }
+        prep_sync();
     }
 }
 
@@ -930,21 +840,34 @@ void launch_zero2_f64(double *p, int64_t n, double *q, int64_t m, hipStream_t s)
     hipLaunchKernelGGL(k_zero2_f64, dim3(grid), dim3(kWG), 0, s, p, n, q, m);
 }
 
+// Rows per wave of the entry streams: about a tile of entries (512) on
+// average, at least 8 rows. Few rows also bound the run of entries that falls
+// to one wave where long rows lie next to each other.
+static int stream_rows(int64_t rows, int64_t nnz)
+{
+    int rw = 64;
+    while (rw > 8 && (int64_t)rw * nnz > kTileEntries * rows) rw >>= 1;
+    return rw;
+}
+
 void launch_validate(const Batch &b, int which, const int64_t *nnz_tab, int64_t nnz_a, int64_t nnz_b, uint32_t *err,
                      hipStream_t s)
 {
-    const int a_blocks = which == 1 ? 0 : nblk(b.na, kWG), b_blocks = which == 0 ? 0 : nblk(b.nb, kWG);
+    constexpr int nw = kWG / kWave;
+    const int rw_a = stream_rows(b.na, nnz_a), rw_b = stream_rows(b.nb, nnz_b);
+    const int a_blocks = which == 1 ? 0 : nblk(b.na, nw * rw_a), b_blocks = which == 0 ? 0 : nblk(b.nb, nw * rw_b);
     if (a_blocks + b_blocks <= 0) return;
     ProfScope ps("validate", s);
     hipLaunchKernelGGL(k_validate, dim3(a_blocks + b_blocks), dim3(kWG), 0, s, b, which, nnz_tab, nnz_a, nnz_b,
-                       a_blocks, err);
+                       a_blocks, rw_a, rw_b, err);
 }
 
-void launch_compress(const Batch &b, const uint32_t *err, hipStream_t s)
+void launch_compress(const Batch &b, int64_t nnz_b, const uint32_t *err, hipStream_t s)
 {
     if (b.nb <= 0) return;
     ProfScope ps("compress", s);
-    hipLaunchKernelGGL(k_compress, dim3(nblk(b.nb, kWG)), dim3(kWG), 0, s, b, err);
+    const int rw = stream_rows(b.nb, nnz_b);
+    hipLaunchKernelGGL(k_compress, dim3(nblk(b.nb, kWG / kWave * rw)), dim3(kWG), 0, s, b, rw, err);
 }
 
 void launch_bin(const Batch &b, int mode, const Sched &sc, int force, unsigned long long *total,

@@ -287,6 +287,7 @@ __global__ __launch_bounds__(kWG) void k_tc_spill(Batch b, Sched sc, int64_t *co
 __global__ __launch_bounds__(kWG) void k_tc_bin(Batch b, Sched sc, int force)
 {
     __shared__ int cnt[kNumBins];
+    if (bad_csr(sc.err)) return;
     if (threadIdx.x < kNumBins) cnt[threadIdx.x] = 0;
     __syncthreads();
     const Prob P = b.p0;

@@ -16,11 +16,12 @@ void launch_fill_f64(double *p, double v, int64_t n, hipStream_t s);
 void launch_zero2_f64(double *p, int64_t n, double *q, int64_t m, hipStream_t s);
 // CSR checks: which = 0 A, 1 B, 2 both in one launch. The entry counts come
 // from nnz_tab (device, two per product), or, when it is NULL (one product),
-// from nnz_a and nnz_b.
+// from nnz_a and nnz_b (which are the batch's totals otherwise).
 void launch_validate(const Batch &b, int which, const int64_t *nnz_tab, int64_t nnz_a, int64_t nnz_b, uint32_t *err,
                      hipStream_t s);
-// err (may be NULL): the error word of a CSR check queued before.
-void launch_compress(const Batch &b, const uint32_t *err, hipStream_t s);
+// nnz_b: entries of all B. err (may be NULL): the error word of a CSR check
+// queued before.
+void launch_compress(const Batch &b, int64_t nnz_b, const uint32_t *err, hipStream_t s);
 void launch_bin(const Batch &b, int mode, const Sched &sc, int force, unsigned long long *total,
                 hipStream_t s);
 int scan_tiles(int n);

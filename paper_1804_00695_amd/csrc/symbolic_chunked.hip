@@ -164,7 +164,7 @@ extern "C" spgemm_status spgemm_symbolic_chunked(const spgemm_csr *A, const spge
             spgemm_status st = sync_errors(ws, L, s);
             if (st != SPGEMM_OK) return st;
         }
-        launch_compress(bt, nullptr, s);
+        launch_compress(bt, q1 - q0, nullptr, s);
         spgemm_status st = check_launch();
         if (st != SPGEMM_OK) return st;
         e = hipStreamSynchronize(s);   // the stage is reused by the next part

@@ -87,25 +87,16 @@ spgemm_status spgemm_tc(const spgemm_csr *L, int64_t *counts, int64_t *total_hos
     Sched sc = make_sched(ws, Lay);
     reset_header(ws, Lay, s);
     launch_fill_i32((int32_t *)counts, 0, 2 * (int64_t)L->nrows, s);
-    if (g_opt.validate) {
-        launch_validate(bh.batch, 0, nullptr, L->nnz, 0, sc.err, s);
-        st = check_launch();
-        if (st != SPGEMM_OK) return st;
-        st = read_errors(ws, Lay, s);
-        if (st != SPGEMM_OK) return st;
-    }
+    // (the kernels behind a failed check return at once; its verdict comes
+    // back with the total)
+    if (g_opt.validate) launch_validate(bh.batch, 0, nullptr, L->nnz, 0, sc.err, s);
     unsigned long long *tot = (unsigned long long *)(ws + Lay.hdr + kHdrTotal);
-    launch_compress(bh.batch, sc.err, s);
+    launch_compress(bh.batch, L->nnz, sc.err, s);
     launch_tc_bin(bh.batch, sc, bin_force(), s);
     launch_tc(bh.batch, sc, counts, tot, (uint32_t *)(ws + Lay.spill), Lay.spill_slots, Lay.spill_words, s);
     st = check_launch();
     if (st != SPGEMM_OK) return st;
-    unsigned long long t = 0;
-    hipError_t e = hipMemcpyAsync(&t, tot, sizeof(t), hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return hip_fail(e);
-    st = read_errors(ws, Lay, s);
-    if (total_host) *total_host = (int64_t)t;
-    return st;
+    return read_header_total(ws, Lay, total_host, s);
 }
 
 }  // extern "C"

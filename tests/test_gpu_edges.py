@@ -136,3 +136,55 @@ def test_few_rows(rows):
 def test_few_rows_one_bin(row_len):
     A = rows_of([row_len] * 9, 6000, row_len)
     check(A, synth.poisson_csr(6000, 50000, 1.3, 9))
+
+
+# the entry streams of validation and compression: tiles of 512 entries, steps
+# of 64, rows of every length around them, empty rows, words that end with
+# their row, a step or a tile, and batches whose products end inside a wave
+@pytest.mark.parametrize("lens", [[0], [1] * 200, [63, 64, 65] * 40, [511, 512, 513, 0, 1] * 5, [5, 0, 0, 700, 2] * 30,
+                                  [27] * 130, [3000, 1, 0, 2]])
+def test_compress_streams(lens):
+    for ncols in (3001, 100000):
+        M = rows_of(lens, ncols, len(lens))
+        if M.nnz > 40 and ncols == 3001:
+            M.col_idx[M.row_ptr[0]:M.row_ptr[1]] = np.arange(lens[0])   # full words
+        words, count = mls.compress(mls.DeviceCsr.from_host(M))
+        w = words.cpu().numpy().view(np.uint32).reshape(-1, 2)
+        count = count.cpu().numpy()
+        for k in range(M.nrows):
+            c = M.row(k)[0]
+            sets = np.unique(c >> 5)
+            assert count[k] == len(sets)
+            got = w[M.row_ptr[k]:M.row_ptr[k] + len(sets)]
+            assert np.array_equal(got[:, 0], sets)
+            masks = [np.bitwise_or.reduce(np.uint32(1) << (c[c >> 5 == x] & 31).astype(np.uint32)) for x in sets]
+            assert np.array_equal(got[:, 1], np.array(masks, np.uint32))
+
+
+@pytest.mark.parametrize("where", [0, 63, 64, 511, 512, 513, 1023, 1300])
+@pytest.mark.parametrize("kind", ["equal", "smaller", "negative", "past"])
+def test_validate_streams(where, kind):
+    M = synth.poisson_csr(200, 70000, 7.0, 4)
+    starts = set(int(x) for x in M.row_ptr)
+    at = where if where not in starts else where + 1
+    if at in starts:
+        at += 1
+    D = mls.DeviceCsr.from_host(M)
+    E = mls.DeviceCsr.from_host(synth.poisson_csr(70000, 66000, 1.0, 5))
+    mls.symbolic(D, E)
+    prev = int(M.col_idx[at - 1])
+    D.col_idx[at] = {"equal": prev, "smaller": prev - 1, "negative": -1, "past": 70000}[kind]
+    with pytest.raises(mls.SpgemmError):
+        mls.symbolic(D, E)
+
+
+def test_batch_products_inside_a_wave():
+    As = [synth.poisson_csr(m, 90, 9.0, m) for m in (1, 5, 30, 64, 3, 200, 17)]
+    Bs = [synth.poisson_csr(90, 66000 + 7 * i, 40.0, 50 + i) for i in range(len(As))]
+    dev = mls.DeviceCsr.from_host
+    dA, dB = [dev(M) for M in As], [dev(M) for M in Bs]
+    Cs = mls.batch_numeric(dA, dB, mls.batch_symbolic(dA, dB))
+    for A, B, C in zip(As, Bs, Cs):
+        R, _ = oracle.spgemm(A, B)
+        rp, ci, v = C.numpy()
+        assert np.array_equal(rp, R.row_ptr) and np.array_equal(ci, R.col_idx) and np.array_equal(v, R.values)
