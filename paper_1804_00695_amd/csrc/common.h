@@ -167,6 +167,24 @@ __device__ __forceinline__ int find_prob_wave(const int32_t *base, int nprob, in
     return t + (63 - __clzll(m));
 }
 
+// Largest r in [0, n) with at[r] <= u (at ascending, at[0] <= u, n >= 1), for a
+// u that is the same in every lane, all lanes active: 64 candidates per step,
+// three dependent loads for n = 20000 in place of fifteen.
+__device__ __forceinline__ int find_last_wave(const MLS_G int32_t *at, int n, int u)
+{
+    const int lane = (int)(threadIdx.x & 63);
+    int lo = 0;
+    while (n > 1) {
+        const int step = (n + kWave - 1) / kWave;
+        const int c = lane * step;
+        const int v = at[lo + (c < n ? c : 0)];
+        const int k = 63 - __clzll((long long)__ballot(c < n && v <= u));   // lane 0 always holds
+        lo += k * step;
+        n = min(step, n - k * step);
+    }
+    return lo;
+}
+
 // Product of row g when consecutive rows are spread over a wave (g = g_w +
 // lane, g_w uniform): the product of the wave's first row serves every lane
 // whose row lies before that product's end, the others search on their own.
@@ -438,11 +456,12 @@ struct TaskIter {
 };
 
 // vblk, vgrid: the workgroup's index among those of its bin and their number
-// (the launch's own, unless one launch serves several bins).
+// (the launch's own, unless one launch serves several bins: FEW, when they may
+// be fewer than the XCDs and cut as many slabs).
+template <bool FEW>
 __device__ __forceinline__ TaskIter task_iter(int ntasks, int waves_per_wg, int log_chunk, int vblk, int vgrid)
 {
-    // (fewer workgroups than XCDs: as many slabs)
-    const int nx = log_chunk < 0 && vgrid < kXcd ? vgrid : kXcd;
+    const int nx = FEW && vgrid < kXcd ? vgrid : kXcd;
     const int x = vblk % nx;
     TaskIter it;
     it.x = x;
@@ -473,7 +492,7 @@ __device__ __forceinline__ TaskIter task_iter(int ntasks, int waves_per_wg, int 
 
 __device__ __forceinline__ TaskIter task_iter(int ntasks, int waves_per_wg, int log_chunk = -1)
 {
-    return task_iter(ntasks, waves_per_wg, log_chunk, (int)blockIdx.x, (int)gridDim.x);
+    return task_iter<false>(ntasks, waves_per_wg, log_chunk, (int)blockIdx.x, (int)gridDim.x);
 }
 
 __device__ __forceinline__ int task_global(const TaskIter &it, int t)

@@ -236,7 +236,7 @@ __device__ __forceinline__ void bwd_lds_rows(const Batch &b, const Sched &sc, in
     const int n_bin = gp(sc.bin_count)[bin];
     const int start = bin_start(sc.bin_count, bin);
     const int ntasks = (n_bin + W - 1) / W;
-    TaskIter it = task_iter(ntasks, NW, -1, vblk, vgrid);
+    TaskIter it = task_iter<MAXLDS != 65536>(ntasks, NW, -1, vblk, vgrid);
     // Three rows of a slot are in flight: the row after next has its perm
     // entry loading, the next row its metadata, then its first chunk (entries
     // of A_i while this row's W_i is hashed, their B row bounds after this
@@ -459,7 +459,6 @@ __device__ __forceinline__ int lower_col_w(const MLS_G int32_t *cols, int lo, in
 
 constexpr int kBwdWinCap = 1024;   // table slots of a spill window (CAP / 2 positions of W_i)
 constexpr int kBwdWinDepth = 2;    // batches of 64 pairs whose B loads are issued together
-constexpr int kBwdWinBlock = 4;    // consecutive windows a wave takes per counter grab
 
 // LDS of one spill window: hash keys and W values, staged entries, their
 // first pair, and the entries' dA parts
@@ -521,115 +520,104 @@ __device__ __forceinline__ void bwd_win_rows(const Batch &b, const Sched &sc, do
     if (nwin == 0) return;
     int32_t *cursor = sc.task_cursor + kBinSpill * kXcd;
     for (;;) {
-        int u0 = 0;
-        if (lane == 0) u0 = atomicAdd(cursor, 1) * kBwdWinBlock;
-        u0 = __builtin_amdgcn_readlane(u0, 0);
-        if (u0 >= nwin) break;
-        int r = 0;   // largest r with wst[r] <= u0: the row holding window u0
-        {
-            int hi = n_bin - 1;
-            while (r < hi) {
-                const int mid = (r + hi + 1) >> 1;
-                if (wst[mid] <= u0) r = mid; else hi = mid - 1;
+        int u = 0;
+        if (lane == 0) u = atomicAdd(cursor, 1);
+        u = __builtin_amdgcn_readlane(u, 0);
+        if (u >= nwin) break;
+        const int r = find_last_wave(wst, n_bin, u);   // the row holding window u
+        const int i = bin_row(sc.perm, sc.err, b.na, start + r);
+        if (i < 0) continue;
+        const int nw = gp(sc.val)[i];
+        const int c0 = (u - wst[r]) * M;
+        const int ws0 = wrp[i] + c0;
+        const int n = min(M, nw - c0);
+        const bool narrow = nw > M;
+        // open below for the row's first window and above for its last, so
+        // that a column outside the whole row still fails the lookup
+        const int jlo = c0 == 0 ? INT_MIN : wci[ws0];
+        const int jhi = c0 + n == nw ? INT_MAX : wci[ws0 + n - 1];
+        int logcap = ilog2_ceil(2 * n);
+        if (logcap < 5) logcap = 5;
+        const int cap = 1 << logcap;
+        for (int h = lane; h < cap; h += G) key[h] = -1;
+        bwd_sync();
+        for (int e0 = lane; e0 < n; e0 += G * kBwdInsDepth) {
+            int jv[kBwdInsDepth];
+            double wj[kBwdInsDepth];
+#pragma unroll
+            for (int u = 0; u < kBwdInsDepth; ++u) {
+                const int e = e0 + u * G;
+                jv[u] = -1;
+                wj[u] = 0.0;
+                if (e < n) { jv[u] = wci[ws0 + e]; wj[u] = wval[ws0 + e]; }
             }
+#pragma unroll
+            for (int u = 0; u < kBwdInsDepth; ++u)
+                if (jv[u] >= 0) w_insert(key, wv, logcap, jv[u], wj[u]);
         }
-        const int u1 = min(u0 + kBwdWinBlock, nwin);
-        for (int u = u0; u < u1; ++u) {
-            while (wst[r + 1] <= u) ++r;
-            const int i = bin_row(sc.perm, sc.err, b.na, start + r);
-            if (i < 0) continue;
-            const int nw = gp(sc.val)[i];
-            const int c0 = (u - wst[r]) * M;
-            const int ws0 = wrp[i] + c0;
-            const int n = min(M, nw - c0);
-            const bool narrow = nw > M;
-            // open below for the row's first window and above for its last, so
-            // that a column outside the whole row still fails the lookup
-            const int jlo = c0 == 0 ? INT_MIN : wci[ws0];
-            const int jhi = c0 + n == nw ? INT_MAX : wci[ws0 + n - 1];
-            int logcap = ilog2_ceil(2 * n);
-            if (logcap < 5) logcap = 5;
-            const int cap = 1 << logcap;
-            for (int h = lane; h < cap; h += G) key[h] = -1;
-            bwd_sync();
-            for (int e0 = lane; e0 < n; e0 += G * kBwdInsDepth) {
-                int jv[kBwdInsDepth];
-                double wj[kBwdInsDepth];
-#pragma unroll
-                for (int u = 0; u < kBwdInsDepth; ++u) {
-                    const int e = e0 + u * G;
-                    jv[u] = -1;
-                    wj[u] = 0.0;
-                    if (e < n) { jv[u] = wci[ws0 + e]; wj[u] = wval[ws0 + e]; }
+        bwd_sync();
+        bool bad = false;
+        const int ps = arp[i], pe = arp[i + 1];
+        for (int pc = ps; pc < pe; pc += G) {
+            int sq0 = 0, sq1 = 0;
+            double sa = 0.0;
+            if (pc + lane < pe) {
+                const int k = aci[pc + lane];
+                sa = aval[pc + lane];
+                sq0 = brp[k];
+                sq1 = brp[k + 1];
+                if (narrow && sq1 - sq0 > 32) {
+                    if (jlo != INT_MIN) sq0 = lower_col_w(bci, sq0, sq1, jlo);
+                    if (jhi != INT_MAX) sq1 = lower_col_w(bci, sq0, sq1, jhi + 1);
                 }
-#pragma unroll
-                for (int u = 0; u < kBwdInsDepth; ++u)
-                    if (jv[u] >= 0) w_insert(key, wv, logcap, jv[u], wj[u]);
             }
+            const int np = sq1 > sq0 ? sq1 - sq0 : 0;
+            int incl = group_scan_incl<G>(np, lane);
+            const int total = group_total<G>(np, incl);
+            poff[lane] = incl - np;
+            if (lane == 0) poff[G] = total;
+            par[lane] = make_int4(sq0, 0, __double2loint(sa), __double2hiint(sa));
+            da[lane] = 0.0;
             bwd_sync();
-            bool bad = false;
-            const int ps = arp[i], pe = arp[i + 1];
-            for (int pc = ps; pc < pe; pc += G) {
-                int sq0 = 0, sq1 = 0;
-                double sa = 0.0;
-                if (pc + lane < pe) {
-                    const int k = aci[pc + lane];
-                    sa = aval[pc + lane];
-                    sq0 = brp[k];
-                    sq1 = brp[k + 1];
-                    if (narrow && sq1 - sq0 > 32) {
-                        if (jlo != INT_MIN) sq0 = lower_col_w(bci, sq0, sq1, jlo);
-                        if (jhi != INT_MAX) sq1 = lower_col_w(bci, sq0, sq1, jhi + 1);
-                    }
-                }
-                const int np = sq1 > sq0 ? sq1 - sq0 : 0;
-                int incl = group_scan_incl<G>(np, lane);
-                const int total = group_total<G>(np, incl);
-                poff[lane] = incl - np;
-                if (lane == 0) poff[G] = total;
-                par[lane] = make_int4(sq0, 0, __double2loint(sa), __double2hiint(sa));
-                da[lane] = 0.0;
-                bwd_sync();
-                for (int base = 0; base < total; base += G * kBwdWinDepth) {
-                    int ev[kBwdWinDepth], qv[kBwdWinDepth], jv[kBwdWinDepth];
-                    double bv[kBwdWinDepth], av[kBwdWinDepth];
+            for (int base = 0; base < total; base += G * kBwdWinDepth) {
+                int ev[kBwdWinDepth], qv[kBwdWinDepth], jv[kBwdWinDepth];
+                double bv[kBwdWinDepth], av[kBwdWinDepth];
 #pragma unroll
-                    for (int d = 0; d < kBwdWinDepth; ++d) {
-                        jv[d] = -1; ev[d] = 0; qv[d] = 0; bv[d] = 0.0; av[d] = 0.0;
-                        const int pp = base + d * G + lane;
-                        if (pp < total) {
-                            int lo = 0, hi = G - 1;   // largest e with poff[e] <= pp
-                            while (lo < hi) {
-                                const int mid = (lo + hi + 1) >> 1;
-                                if (poff[mid] <= pp) lo = mid; else hi = mid - 1;
-                            }
-                            const int4 pr = par[lo];
-                            ev[d] = lo;
-                            qv[d] = pr.x + (pp - poff[lo]);
-                            av[d] = __hiloint2double(pr.w, pr.z);
-                            jv[d] = bci[qv[d]];
-                            bv[d] = bval[qv[d]];
+                for (int d = 0; d < kBwdWinDepth; ++d) {
+                    jv[d] = -1; ev[d] = 0; qv[d] = 0; bv[d] = 0.0; av[d] = 0.0;
+                    const int pp = base + d * G + lane;
+                    if (pp < total) {
+                        int lo = 0, hi = G - 1;   // largest e with poff[e] <= pp
+                        while (lo < hi) {
+                            const int mid = (lo + hi + 1) >> 1;
+                            if (poff[mid] <= pp) lo = mid; else hi = mid - 1;
                         }
-                    }
-                    int jw[kBwdWinDepth], sl[kBwdWinDepth];
-                    double w[kBwdWinDepth];
-#pragma unroll
-                    for (int d = 0; d < kBwdWinDepth; ++d) jw[d] = (jv[d] >= jlo && jv[d] <= jhi) ? jv[d] : -1;
-                    w_lookup_n<kBwdWinDepth>(key, wv, logcap, jw, sl, w);
-#pragma unroll
-                    for (int d = 0; d < kBwdWinDepth; ++d) {
-                        if (sl[d] == -1) bad = true;
-                        if (sl[d] < 0) continue;
-                        if (dA) atomicAdd(da + ev[d], w[d] * bv[d]);
-                        if (dB) atomicAdd(dB + qv[d], av[d] * w[d]);
+                        const int4 pr = par[lo];
+                        ev[d] = lo;
+                        qv[d] = pr.x + (pp - poff[lo]);
+                        av[d] = __hiloint2double(pr.w, pr.z);
+                        jv[d] = bci[qv[d]];
+                        bv[d] = bval[qv[d]];
                     }
                 }
-                bwd_sync();
-                if (dA && pc + lane < pe && da[lane] != 0.0) atomicAdd(dA + pc + lane, da[lane]);
-                bwd_sync();
+                int jw[kBwdWinDepth], sl[kBwdWinDepth];
+                double w[kBwdWinDepth];
+#pragma unroll
+                for (int d = 0; d < kBwdWinDepth; ++d) jw[d] = (jv[d] >= jlo && jv[d] <= jhi) ? jv[d] : -1;
+                w_lookup_n<kBwdWinDepth>(key, wv, logcap, jw, sl, w);
+#pragma unroll
+                for (int d = 0; d < kBwdWinDepth; ++d) {
+                    if (sl[d] == -1) bad = true;
+                    if (sl[d] < 0) continue;
+                    if (dA) atomicAdd(da + ev[d], w[d] * bv[d]);
+                    if (dB) atomicAdd(dB + qv[d], av[d] * w[d]);
+                }
             }
-            if (bad) atomicOr(sc.err, kErrStructure);
+            bwd_sync();
+            if (dA && pc + lane < pe && da[lane] != 0.0) atomicAdd(dA + pc + lane, da[lane]);
+            bwd_sync();
         }
+        if (bad) atomicOr(sc.err, kErrStructure);
     }
 }
 

@@ -35,7 +35,7 @@ namespace mls {
 
 constexpr int kNumDepth = 4;   // steps whose B loads are issued together (8 where LDS caps occupancy at 4)
 constexpr int kNumWinCap = 1024;   // table slots of a spill window (CAP / 2 positions)
-constexpr int kWinDepth = 2;       // spill window: batches of 64 pairs whose B loads are issued together
+constexpr int kWinDepth = 8;       // spill window: steps of 64 pairs whose B loads are issued together
 constexpr bool kNumFlat = true;    // flattened pairs for the classes of at most kNumFlatMaxG lanes per row
 constexpr int kNumFlatMaxG = 8;
 
@@ -205,6 +205,102 @@ __device__ __forceinline__ void first_b(const Prob &P, FirstChunk &f)
     f.r1 = pb[1];
 }
 
+// Wave-wide flattened steps: the (entry, B position) pairs of a staged chunk,
+// entry-major (so in ascending k), 64 per step whatever the rows of B, D steps
+// with their loads in flight. The chunk's non-empty entries are compacted in
+// par: (first B position - first pair, -, a). A bit per pair tells where an
+// entry starts, so a lane's entry is a count of the bits up to it; eb holds
+// the entries that started before the tile, less one. Lanes of a step that
+// belong to different entries may hit the same output: they add entry by
+// entry (one wave's LDS adds take effect in program order), which keeps every
+// c_ij's terms in ascending k. Columns outside [jlo, jhi] are another
+// window's. Returns whether a column was not found.
+template <int D, typename TAB>
+__device__ __forceinline__ bool flat_tile(const TAB &tab, int logcap, double *acc, const int4 *par, uint32_t *flags,
+                                          int lane, int base, int first, bool nonempty, int total, int &eb,
+                                          const MLS_G int32_t *bci, const MLS_G double *bval, int jlo, int jhi)
+{
+    if (lane < 2 * D) flags[lane] = 0u;
+    nwave_sync();
+    const int at = first - base;
+    if (nonempty && (uint32_t)at < (uint32_t)(kWave * D)) atomicOr(flags + (at >> 5), 1u << (at & 31));
+    nwave_sync();
+    int jv[D], rel[D], more[D];
+    double av[D], bv[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        const uint2 m = *(const uint2 *)(flags + 2 * d);
+        const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)m.x);
+        const uint32_t m1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)m.y);
+        const uint64_t starts = ((uint64_t)m1 << 32) | m0, after = starts >> 1;   // after: lanes 1 and up
+        rel[d] = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(after >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)after, 0u));
+        more[d] = __popcll(after);
+        const int e0 = eb + (int)(starts & 1u);
+        const int pp = base + d * kWave + lane;
+        const bool ok = pp < total;
+        const int4 pr = par[e0 + rel[d]];
+        const int q = pr.x + pp;
+        const MLS_G int32_t *pj = ok ? bci + q : (const MLS_G int32_t *)k_num_void;
+        const MLS_G double *pv = ok ? bval + q : (const MLS_G double *)k_num_void;
+        jv[d] = *pj;
+        bv[d] = *pv;
+        av[d] = __hiloint2double(pr.w, pr.z);
+        eb = e0 + more[d];
+    }
+    // every load is issued before the first use of a loaded column
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (jv[d] < jlo || jv[d] > jhi) jv[d] = -1;
+    int posv[D];
+    tab.template lookup_n<D>(logcap, jv, posv);
+#pragma unroll
+    for (int d = 0; d < D; ++d) asm volatile("" ::"v"(bv[d]));
+    bool bad = false;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        bad |= posv[d] == -1;
+        const double t = av[d] * bv[d];
+        for (int r = 0; r <= more[d]; ++r)
+            if (posv[d] >= 0 && rel[d] == r) atomicAdd(acc + posv[d], t);
+    }
+    return bad;
+}
+
+constexpr int kFlatWords = 16;   // start bits of a tile of 8 steps
+
+template <int DEPTH, typename TAB>
+__device__ __forceinline__ bool flat_chunk(const TAB &tab, int logcap, double *acc, int4 *par, uint32_t *flags,
+                                           int lane, int q0, int q1, double a, const MLS_G int32_t *bci,
+                                           const MLS_G double *bval, int jlo, int jhi)
+{
+    static_assert(2 * DEPTH <= kFlatWords, "start bits");
+    const int np = q1 > q0 ? q1 - q0 : 0;
+    const int incl = group_scan_incl<kWave>(np, lane);
+    const int total = group_total<kWave>(np, incl);
+    const int first = incl - np;
+    const unsigned long long ne = __ballot(np > 0);
+    if (np > 0)
+        par[__popcll(ne & ((1ull << lane) - 1ull))] = make_int4(q0 - first, 0, __double2loint(a), __double2hiint(a));
+    bool bad = false;
+    int eb = -1;
+    for (int base = 0; base < total;) {
+        // (the tail in smaller tiles: a step past the pairs costs as much as any)
+        const int steps = (total - base + kWave - 1) / kWave;
+        if (steps > DEPTH / 2) {
+            bad |= flat_tile<DEPTH>(tab, logcap, acc, par, flags, lane, base, first, np > 0, total, eb, bci, bval,
+                                    jlo, jhi);
+            base += DEPTH * kWave;
+        } else {
+            bad |= flat_tile<2>(tab, logcap, acc, par, flags, lane, base, first, np > 0, total, eb, bci, bval, jlo,
+                                jhi);
+            base += 2 * kWave;
+        }
+    }
+    nwave_sync();
+    return bad;
+}
+
 // FLAT: the (entry, B position) pairs of a staged chunk are flattened, G at a
 // time, one per lane (for rows of B shorter than G, which would leave lanes
 // idle); the adds of a step go in rounds by the number of lower lanes with
@@ -225,7 +321,7 @@ constexpr int lds_waves_per_simd(int wg_bytes, int nw)
 template <int G, int CAP, bool PACK, bool MULTI, bool FLAT, int MAXLDS = 65536>
 struct NumShape {
     static constexpr int W = kWave / G;
-    static constexpr int XW = FLAT ? num_flat_words(G) : 0;
+    static constexpr int XW = FLAT ? num_flat_words(G) : (G == kWave ? kFlatWords : 0);
     static constexpr int NW = nw_num(num_row_bytes(CAP, G, PACK) + 4 * XW, W, MAXLDS);
     static constexpr int OCC = lds_waves_per_simd(NW * W * (num_row_bytes(CAP, G, PACK) + 4 * XW), NW);
     // where LDS already limits a SIMD to 4 waves, registers are free for
@@ -257,16 +353,17 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
     using Shape = NumShape<G, CAP, PACK, MULTI, FLAT, MAXLDS>;
     constexpr int kNumDepth = Shape::DEPTH;
     constexpr bool PF = Shape::PF;
-    // Where a wave owns a row, rows of B are long (the host picks G from their
-    // mean length) and often longer than G: a staged chunk is cut into steps
-    // of at most G entries of one row of B each, so that every step takes the
-    // batched path. (One step at a time through a long row chains load, lookup
-    // and load per 64 entries: numeric phase of the restriction times the
-    // 81-point elasticity operator on 48^3 nodes 1050 us, in steps 711 us.)
+    // Where a wave owns a row, its pairs are flattened over the 64 lanes
+    // (flat_chunk): rows of B are long there (the host picks G from their mean
+    // length), and one entry of A per step would leave lanes idle or, past 64
+    // entries, chain a load, a lookup and a load per step. Numeric phase of the
+    // restriction times the 81-point elasticity operator on 48^3 nodes: 1050 us
+    // with one step at a time, 711 us in steps of one entry,
+    // 611 us flattened.
     constexpr bool LONG = G == kWave && !FLAT;
     static_assert(FLAT || G % kNumDepth == 0, "the staged entries are read kNumDepth at a time");
     constexpr int W = kWave / G;
-    constexpr int XW = FLAT ? num_flat_words(G) : 0;
+    constexpr int XW = Shape::XW;
     constexpr int NW = Shape::NW;
     constexpr int TW = Shape::TW;
     uint32_t *s_tab = (uint32_t *)lds;
@@ -283,12 +380,12 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
     PosTab<CAP, PACK, (G >= 32 ? 2 : 4)> tab{s_tab + rs * TW};
     double *acc = s_acc + rs * (CAP / 2);
     int4 *par = s_par + rs * G;
-    int *poff = (int *)(s_tab + NW * W * TW) + rs * XW;   // FLAT only: staged pair offsets
+    int *poff = (int *)(s_tab + NW * W * TW) + rs * XW;   // FLAT: staged pair offsets, LONG: start bits
 
     const int n_bin = gp(sc.bin_count)[bin];
     const int start = bin_start(sc.bin_count, bin);
     const int ntasks = (n_bin + W - 1) / W;
-    TaskIter it = task_iter(ntasks, NW, -1, vblk, vgrid);
+    TaskIter it = task_iter<MAXLDS != 65536>(ntasks, NW, -1, vblk, vgrid);
     // Rows of a slot overlap: with PF three are in flight (the row after next
     // has its perm entry loading; the next row its metadata, then its first
     // chunk: A entries during this row's insert and steps, B row pointers
@@ -522,29 +619,9 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
                     else if (posv[d] == -1) bad = true;
                 }
             };
-            if constexpr (LONG) {
-                // the chunk's steps, G staged at a time: a lane writes those of its
-                // own entry (an empty row of B has none)
-                const int ns = eq1 > eq0 ? (eq1 - eq0 + G - 1) / G : 0;
-                const int incl = group_scan_incl<G>(ns, lane);
-                const int steps = group_total<G>(ns, incl);
-                const int st = incl - ns;
-                for (int s0 = 0; s0 < steps; s0 += G) {
-                    const int nst = min(G, steps - s0);
-                    const int x1 = min(st + ns, s0 + G);
-                    for (int x = max(st, s0); x < x1; ++x)
-                        par[x - s0] = make_int4(eq0 + (x - st) * G, eq1, __double2loint(ea), __double2hiint(ea));
-                    if (lane >= nst) par[lane] = make_int4(0, 0, 0, 0);
-                    nwave_sync();
-                    for (int u0 = 0; u0 < nst; u0 += kNumDepth) {
-                        int2 qr[kNumDepth];
-#pragma unroll
-                        for (int d = 0; d < kNumDepth; ++d) qr[d] = *(const int2 *)(par + u0 + d);
-                        batch(u0, qr);
-                    }
-                    nwave_sync();
-                }
-            }
+            if constexpr (LONG)
+                bad |= flat_chunk<kNumDepth>(tab, logcap, acc, par, (uint32_t *)poff, lane, eq0, eq1, ea, bci, bval,
+                                             INT_MIN, INT_MAX);
             for (int u0 = 0; !LONG && u0 < n; u0 += kNumDepth) {
                 // The staged entries are read together (all G are written every
                 // chunk, those past the row as empty ranges, and G is a multiple of
@@ -658,21 +735,25 @@ __global__ __launch_bounds__(kWG) void k_win_scan(Batch b, Sched sc, int m)
     if (threadIdx.x == 0) ws[n] = s_carry;
 }
 
-constexpr int kWinBlock = 2;   // consecutive windows a wave takes per counter grab
+// Consecutive windows a wave takes per counter grab: one, so that heavy rows'
+// windows spread over all waves, unless there are so many that the grabs (14
+// ns each, one address) would bound the launch. R-MAT squares of 16384 / 65536
+// rows, 40000 / 330000 windows: one each 638 us / 4.62 ms, two 792 us / 3.92 ms.
+constexpr int kWinMany = 131072;
 
-// LDS of one spill window: table, accumulators, staged entries, their first
-// pair and the per-position lane marks of the ordered adds
+// LDS of one spill window: table, accumulators, staged entries and the start
+// bits of their pairs
 constexpr int win_bytes(int CAP, bool PACK)
 {
-    return CAP * (PACK ? 4 : 8) + (CAP / 2) * 8 + kWave * 16 + (kWave + 1) * 4 + (CAP / 2) * 4;
+    return CAP * (PACK ? 4 : 8) + (CAP / 2) * 8 + kWave * 16 + kFlatWords * 4;
 }
 
-// A window's terms are flattened: the (entry, B position) pairs of a staged
-// chunk of A's row, entry-major (so in ascending k), are taken 64 at a time,
-// one per lane, with coalesced loads of B. Two lanes of a batch may hit the
-// same output, so the adds are applied in rounds: in each round the lowest
-// pending lane of every output position adds (an LDS min over lane ids
-// finds it), which keeps every c_ij's terms in ascending k.
+// A window streams the whole row of A, its rows of B narrowed to the window's
+// columns, as flattened pairs (flat_chunk). What bounds it: every window
+// stages the whole row of A, with two binary searches in B per entry and
+// window. R-MAT 16 square, whole numeric phase: 6.85 ms with a binary search
+// per pair for its entry and the adds ordered by an LDS minimum per output
+// position, 3.9 ms so.
 template <int CAP, bool PACK, int MAXLDS = 65536>
 struct WinShape {
     static constexpr int M = CAP / 2;   // positions of C per window
@@ -680,9 +761,8 @@ struct WinShape {
     static constexpr int TW = PACK ? CAP : 2 * CAP;
     static constexpr int LDS_PAR = NW * TW * 4;
     static constexpr int LDS_ACC = LDS_PAR + NW * kWave * 16;
-    static constexpr int LDS_OWN = LDS_ACC + NW * M * 8;
-    static constexpr int LDS_POFF = LDS_OWN + NW * M * 4;
-    static constexpr int LDS = LDS_POFF + NW * (kWave + 1) * 4;
+    static constexpr int LDS_FLAGS = LDS_ACC + NW * M * 8;
+    static constexpr int LDS = LDS_FLAGS + NW * kFlatWords * 4;
 };
 
 // lds: WinShape::LDS bytes of this workgroup
@@ -697,8 +777,7 @@ __device__ __forceinline__ void num_win_rows(const Batch &b, const Sched &sc, ch
     uint32_t *s_tab = (uint32_t *)lds;
     int4 *s_par = (int4 *)(lds + Shape::LDS_PAR);    // staged entries: (first B position, -, a)
     double *s_acc = (double *)(lds + Shape::LDS_ACC);
-    int *s_own = (int *)(lds + Shape::LDS_OWN);
-    int *s_poff = (int *)(lds + Shape::LDS_POFF);    // first pair of each staged entry, then the total
+    uint32_t *flags = (uint32_t *)(lds + Shape::LDS_FLAGS) + (threadIdx.x >> 6) * kFlatWords;
 
     const int wave = threadIdx.x >> 6;
     if (wave >= NW) return;
@@ -706,8 +785,6 @@ __device__ __forceinline__ void num_win_rows(const Batch &b, const Sched &sc, ch
     PosTab<CAP, PACK, 2> tab{s_tab + wave * TW};
     double *acc = s_acc + wave * M;
     int4 *par = s_par + wave * G;
-    int *poff = s_poff + wave * (G + 1);
-    int *own = s_own + wave * M;
 
     const int n_bin = gp(sc.bin_count)[kBinSpill];
     const int start = bin_start(sc.bin_count, kBinSpill);
@@ -717,21 +794,15 @@ __device__ __forceinline__ void num_win_rows(const Batch &b, const Sched &sc, ch
     // windows are consecutive and long) for per-XCD slabs
     if (nwin == 0) return;
     int32_t *cursor = sc.task_cursor + kBinSpill * kXcd;
+    const int block = nwin > kWinMany ? 2 : 1;
     ProbCache pcache;
     for (;;) {
         int u0 = 0;
-        if (lane == 0) u0 = atomicAdd(cursor, 1) * kWinBlock;
+        if (lane == 0) u0 = atomicAdd(cursor, 1) * block;
         u0 = __builtin_amdgcn_readlane(u0, 0);
         if (u0 >= nwin) break;
-        int r = 0;   // largest r with wst[r] <= u0: the row holding window u0
-        {
-            int hi = n_bin - 1;
-            while (r < hi) {
-                const int mid = (r + hi + 1) >> 1;
-                if (wst[mid] <= u0) r = mid; else hi = mid - 1;
-            }
-        }
-        const int u1 = min(u0 + kWinBlock, nwin);
+        int r = find_last_wave(wst, n_bin, u0);   // the row holding window u0
+        const int u1 = min(u0 + block, nwin);
         for (int u = u0; u < u1; ++u) {
             while (wst[r + 1] <= u) ++r;
             const int g = bin_row(sc.perm, sc.err, b.na, start + r);
@@ -786,59 +857,7 @@ __device__ __forceinline__ void num_win_rows(const Batch &b, const Sched &sc, ch
                         }
                     }
                 }
-                const int np = sq1 > sq0 ? sq1 - sq0 : 0;
-                int incl = group_scan_incl<G>(np, lane);
-                const int total = group_total<G>(np, incl);
-                poff[lane] = incl - np;
-                if (lane == 0) poff[G] = total;
-                par[lane] = make_int4(sq0, 0, __double2loint(sa), __double2hiint(sa));
-                nwave_sync();
-                for (int base = 0; base < total; base += G * kWinDepth) {
-                    // kWinDepth batches of 64 pairs: loads first, then lookups,
-                    // then the ordered adds batch by batch
-                    int jv[kWinDepth];
-                    double tv[kWinDepth];
-#pragma unroll
-                    for (int d = 0; d < kWinDepth; ++d) {
-                        jv[d] = -1;
-                        tv[d] = 0.0;
-                        const int pp = base + d * G + lane;
-                        if (pp < total) {
-                            int lo = 0, hi = G - 1;   // largest e with poff[e] <= pp
-                            while (lo < hi) {
-                                const int mid = (lo + hi + 1) >> 1;
-                                if (poff[mid] <= pp) lo = mid; else hi = mid - 1;
-                            }
-                            const int4 pr = par[lo];
-                            const int q = pr.x + (pp - poff[lo]);
-                            jv[d] = bci[q];
-                            tv[d] = __hiloint2double(pr.w, pr.z) * bval[q];
-                        }
-                    }
-                    int jw[kWinDepth], posv[kWinDepth];
-#pragma unroll
-                    for (int d = 0; d < kWinDepth; ++d) jw[d] = (jv[d] >= jlo && jv[d] <= jhi) ? jv[d] : -1;
-                    tab.template lookup_n<kWinDepth>(logcap, jw, posv);
-#pragma unroll
-                    for (int d = 0; d < kWinDepth; ++d)
-                        if (posv[d] == -1) bad = true;
-#pragma unroll
-                    for (int d = 0; d < kWinDepth; ++d) {
-                        bool pend = posv[d] >= 0;
-                        while (__ballot(pend)) {
-                            if (pend) own[posv[d]] = G;
-                            nwave_sync();
-                            if (pend) atomicMin(own + posv[d], lane);
-                            nwave_sync();
-                            if (pend && own[posv[d]] == lane) {
-                                atomicAdd(acc + posv[d], tv[d]);
-                                pend = false;
-                            }
-                            nwave_sync();
-                        }
-                    }
-                }
-                nwave_sync();
+                bad |= flat_chunk<kWinDepth>(tab, logcap, acc, par, flags, lane, sq0, sq1, sa, bci, bval, jlo, jhi);
             }
             if (bad) atomicOr(sc.err, kErrStructure);
             for (int e = lane; e < n; e += G) cval[cs + e] = acc[e];
