@@ -77,10 +77,10 @@ spgemm_status spgemm_backward(const spgemm_csr *A, const spgemm_csr *B, const sp
         int32_t *tci = (int32_t *)(w + d.tci);
         double *tv = (double *)(w + d.tv);
         if (dB)
-            launch_transpose(A->nrows, A->ncols, A->row_ptr, A->col_idx, A->values, trp, tci, tv,
+            launch_transpose(A->nrows, A->ncols, A->nnz, A->row_ptr, A->col_idx, A->values, trp, tci, tv,
                              (int32_t *)(w + d.cursor), (int64_t *)(w + d.tiles), (int64_t *)(w + d.prefix),
                              (int32_t *)(w + d.cnt), s);
-        launch_backward_det(A->nrows, B->nrows, A->row_ptr, A->col_idx, B->row_ptr, B->col_idx, B->values,
+        launch_backward_det(A->nrows, B->nrows, B->nnz, W->nnz, A->row_ptr, A->col_idx, B->row_ptr, B->col_idx, B->values,
                             W->row_ptr, W->col_idx, W->values, trp, tci, tv, dA, dB, (uint32_t *)w, s);
         return check_launch();
     }
@@ -121,7 +121,7 @@ spgemm_status spgemm_transpose(const spgemm_csr *M, spgemm_csr *T, void *ws_v, s
     int32_t *cursor = (int32_t *)(w + a);
     int64_t *tiles = (int64_t *)(w + 2 * a);
     int64_t *prefix = (int64_t *)(w + 2 * a + al(8 * (size_t)scan_tiles(M->ncols)));
-    launch_transpose(M->nrows, M->ncols, M->row_ptr, M->col_idx, M->values, T->row_ptr, T->col_idx,
+    launch_transpose(M->nrows, M->ncols, M->nnz, M->row_ptr, M->col_idx, M->values, T->row_ptr, T->col_idx,
                      M->values ? T->values : nullptr, cursor, tiles, prefix, cnt, s);
     return check_launch();
 }

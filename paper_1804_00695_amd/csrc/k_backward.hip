@@ -730,92 +730,266 @@ void launch_backward(const Batch &b, const Sched &sc, const double *wval, double
 // columns (no LDS table, no atomics on the outputs); a triple whose column j
 // is missing from W_i sets the structure error.
 
-constexpr int kDetLanes = 8;   // lanes per row; a lane takes every 8th entry
+// G lanes own a row of A (of B): rows of W of up to kDetStage * G columns are
+// staged in LDS and searched there, longer ones in place. Bound by latency:
+// what a lane searches is a handful of columns, in rows of W that arrive in one
+// coalesced pass each. (Searching every column in global memory made 6 to 8
+// dependent gathers per term: 200003 rows, Poisson(8), dA 612 and dB 411 us;
+// so 253 and 283 us, near what the lines of B and W that the gathers touch take
+// from the last-level cache: about 0.6 and 1.4 GB.)
+constexpr int kDetStage = 16;   // columns of W_i per lane
+constexpr int kDetAhead = 4;    // terms of a lane searched together
 
-__global__ __launch_bounds__(kWG) void k_bwd_det_da(int32_t m, const int32_t *arp, const int32_t *aci,
+// Four entries from p on, p >= end giving none that is used: one wide load
+// (element-aligned) where four more entries of the array follow, else one at a
+// time. end: entries of the whole array.
+typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double f64x4u __attribute__((ext_vector_type(4), aligned(8)));
+
+__device__ __forceinline__ void load4(const MLS_G int32_t *a, int64_t p, int64_t end, int (&v)[4])
+{
+    if (p + 4 <= end) {
+        const i32x4u w = *(const MLS_G i32x4u *)(a + p);
+        v[0] = w.x; v[1] = w.y; v[2] = w.z; v[3] = w.w;
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = p + u < end ? a[p + u] : 0;
+    }
+}
+
+__device__ __forceinline__ void load4(const MLS_G double *a, int64_t p, int64_t end, double (&v)[4])
+{
+    if (p + 4 <= end) {
+        const f64x4u w = *(const MLS_G f64x4u *)(a + p);
+        v[0] = w.x; v[1] = w.y; v[2] = w.z; v[3] = w.w;
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = p + u < end ? a[p + u] : 0.0;
+    }
+}
+
+// first position in the n ascending columns c (in LDS) whose column is >= j,
+// for D columns at once; top: the largest power of two <= n
+template <int D>
+__device__ __forceinline__ void det_lower(const int *c, int n, int top, const int (&j)[D], int (&at)[D])
+{
+#pragma unroll
+    for (int d = 0; d < D; ++d) at[d] = 0;
+    for (int step = top; step > 0; step >>= 1) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int x = at[d] + step;
+            if (x <= n && c[x - 1] < j[d]) at[d] = x;
+        }
+    }
+}
+
+__device__ __forceinline__ int det_top(int n) { return n > 0 ? 1 << (31 - __clz(n)) : 0; }
+
+template <int G>
+__global__ __launch_bounds__(kWG) void k_bwd_det_da(int32_t m, int64_t nnz_b, int64_t nnz_w, const int32_t *arp, const int32_t *aci,
                                                     const int32_t *brp, const int32_t *bci, const double *bval,
                                                     const int32_t *wrp, const int32_t *wci, const double *wval,
                                                     double *dA, uint32_t *err)
 {
-    const int64_t g = (int64_t)blockIdx.x * kWG + threadIdx.x;
-    const int64_t i = g / kDetLanes;
-    if (i >= m) return;
-    const int l = (int)(g % kDetLanes);
-    const int ws = gp(wrp)[i], wn = gp(wrp)[i + 1] - ws;
+    constexpr int CAP = kDetStage * G;
+    __shared__ __attribute__((aligned(16))) int s_c[kWG / G][CAP];
+    const int grp = threadIdx.x / G, l = threadIdx.x % G;
+    const int64_t i = (int64_t)blockIdx.x * (kWG / G) + grp;
+    const bool row = i < m;
+    const int ws = row ? gp(wrp)[i] : 0, wn = row ? gp(wrp)[i + 1] - ws : 0;
     const MLS_G int32_t *wc = gp(wci) + ws;
     const MLS_G double *wv = gp(wval) + ws;
+    int *c = s_c[grp];
+    const bool staged = wn <= CAP;
+    if (staged) {
+        for (int x = 4 * l; x < wn; x += 4 * G) {
+            int w[4];
+            load4(gp(wci), (int64_t)ws + x, nnz_w, w);
+            *(int4 *)(c + x) = make_int4(w[0], w[1], w[2], w[3]);
+        }
+    }
+    bwd_sync();
+    if (!row) return;
+    const int top = det_top(wn);
     bool bad = false;
     const int pe = gp(arp)[i + 1];
-    for (int p = gp(arp)[i] + l; p < pe; p += kDetLanes) {
+    for (int p = gp(arp)[i] + l; p < pe; p += G) {
         const int k = gp(aci)[p];
         const int qs = gp(brp)[k], qe = gp(brp)[k + 1];
         double sum = 0.0;
-        int lo = 0;   // the columns of B_k ascend, so each search starts past the last hit
-        for (int q = qs; q < qe; ++q) {
-            const int j = gp(bci)[q];
-            lo = lower_col_w(wc, lo, wn, j);
-            if (lo >= wn || wc[lo] != j) { bad = true; break; }
-            sum += wv[lo] * gp(bval)[q];
+        if (staged) {
+            for (int q = qs; q < qe; q += kDetAhead) {
+                int j[kDetAhead], at[kDetAhead];
+                double bv[kDetAhead];
+                load4(gp(bci), q, nnz_b, j);
+                load4(gp(bval), q, nnz_b, bv);
+                det_lower<kDetAhead>(c, wn, top, j, at);
+                double w[kDetAhead];
+                bool hit[kDetAhead];
+#pragma unroll
+                for (int u = 0; u < kDetAhead; ++u) {
+                    hit[u] = q + u < qe && at[u] < wn && c[at[u]] == j[u];
+                    bad |= q + u < qe && !hit[u];
+                    w[u] = *(hit[u] ? wv + at[u] : (const MLS_G double *)k_zeros4);
+                }
+#pragma unroll
+                for (int u = 0; u < kDetAhead; ++u)   // terms in ascending j
+                    if (hit[u]) sum += w[u] * bv[u];
+            }
+        } else {
+            int lo = 0;   // the columns of B_k ascend, so each search starts past the last hit
+            for (int q = qs; q < qe; ++q) {
+                const int j = gp(bci)[q];
+                lo = lower_col_w(wc, lo, wn, j);
+                if (lo >= wn || wc[lo] != j) { bad = true; break; }
+                sum += wv[lo] * gp(bval)[q];
+            }
         }
         gpw(dA)[p] = sum;
     }
     if (bad) atomicOr(err, kErrStructure);
 }
 
-__global__ __launch_bounds__(kWG) void k_bwd_det_db(int32_t kb, const int32_t *trp, const int32_t *tci,
+// A lane holds kDetOwn entries of B_k (one per G), and the group walks the rows
+// i of column k of A in ascending order; the next row of W loads while the
+// current one is searched.
+constexpr int kDetOwn = 2;
+
+template <int G>
+__global__ __launch_bounds__(kWG) void k_bwd_det_db(int32_t kb, int64_t nnz_w, const int32_t *trp, const int32_t *tci,
                                                     const double *tv, const int32_t *brp, const int32_t *bci,
                                                     const int32_t *wrp, const int32_t *wci, const double *wval,
                                                     double *dB, uint32_t *err)
 {
-    const int64_t g = (int64_t)blockIdx.x * kWG + threadIdx.x;
-    const int64_t k = g / kDetLanes;
-    if (k >= kb) return;
-    const int l = (int)(g % kDetLanes);
+    constexpr int CAP = kDetStage * G;
+    constexpr int NV = kDetStage / 4;   // wide loads of a row of W per lane
+    __shared__ __attribute__((aligned(16))) int s_c[kWG / G][CAP];
+    const int grp = threadIdx.x / G, l = threadIdx.x % G;
+    const int64_t k = (int64_t)blockIdx.x * (kWG / G) + grp;
+    if (k >= kb) return;   // whole groups: a group exchanges with itself alone
+    int *c = s_c[grp];
     const int rs = gp(trp)[k], re = gp(trp)[k + 1];
+    const int qs = gp(brp)[k], qe = gp(brp)[k + 1];
     bool bad = false;
-    const int qe = gp(brp)[k + 1];
-    for (int q = gp(brp)[k] + l; q < qe; q += kDetLanes) {
-        const int j = gp(bci)[q];
-        double sum = 0.0;
-        for (int r = rs; r < re; ++r) {   // rows i of column k of A, ascending
-            const int i = gp(tci)[r];
-            const int ws = gp(wrp)[i], wn = gp(wrp)[i + 1] - ws;
-            const int pos = lower_col_w(gp(wci) + ws, 0, wn, j);
-            if (pos >= wn || gp(wci)[ws + pos] != j) { bad = true; break; }
-            sum += gp(tv)[r] * gp(wval)[ws + pos];
+    for (int q0 = qs; q0 < qe; q0 += G * kDetOwn) {
+        int j[kDetOwn];
+        double sum[kDetOwn];
+#pragma unroll
+        for (int u = 0; u < kDetOwn; ++u) {
+            const int q = q0 + u * G + l;
+            j[u] = q < qe ? gp(bci)[q] : -1;
+            sum[u] = 0.0;
         }
-        gpw(dB)[q] = sum;
+        // the term found last: added once the next row's loads are queued
+        double pa = 0.0, pw[kDetOwn];
+        bool ph[kDetOwn];
+#pragma unroll
+        for (int u = 0; u < kDetOwn; ++u) { pw[u] = 0.0; ph[u] = false; }
+        for (int rb = rs; rb < re; rb += G) {   // rows i of column k of A, ascending, G located together
+            const bool in = rb + l < re;
+            const int i = in ? gp(tci)[rb + l] : 0;
+            const double al = in ? gp(tv)[rb + l] : 0.0;
+            const int wsl = gp(wrp)[i], wnl = in ? gp(wrp)[i + 1] - wsl : 0;
+            const int nr = min(G, re - rb);
+            int w[NV][4];
+            int w0 = __shfl(wsl, 0, G), n = __shfl(wnl, 0, G);
+            auto next_row = [&]() {   // the row's columns x, 4 at a time, lane by lane
+#pragma unroll
+                for (int x = 0; x < NV; ++x)
+                    if (4 * (x * G + l) < n) load4(gp(wci), (int64_t)w0 + 4 * (x * G + l), nnz_w, w[x]);
+            };
+            next_row();
+            for (int y = 0; y < nr; ++y) {
+                const double a = __shfl(al, y, G);
+                const int cw0 = w0, cn = n;
+#pragma unroll
+                for (int x = 0; x < NV; ++x)
+                    if (4 * (x * G + l) < cn)
+                        *(int4 *)(c + 4 * (x * G + l)) = make_int4(w[x][0], w[x][1], w[x][2], w[x][3]);
+                bwd_sync();
+                w0 = __shfl(wsl, y + 1 < nr ? y + 1 : 0, G);
+                n = y + 1 < nr ? __shfl(wnl, y + 1 < nr ? y + 1 : 0, G) : 0;
+                next_row();
+                int at[kDetOwn];
+                if (cn <= CAP) {
+                    det_lower<kDetOwn>(c, cn, det_top(cn), j, at);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < kDetOwn; ++u) at[u] = lower_col_w(gp(wci) + cw0, 0, cn, j[u]);
+                }
+                double v[kDetOwn];
+                bool hit[kDetOwn];
+#pragma unroll
+                for (int u = 0; u < kDetOwn; ++u) {
+                    hit[u] = j[u] >= 0 && at[u] < cn && (cn <= CAP ? c[at[u] < CAP ? at[u] : 0] : gp(wci)[cw0 + at[u]]) == j[u];
+                    bad |= j[u] >= 0 && !hit[u];
+                    v[u] = *(hit[u] ? gp(wval) + cw0 + at[u] : (const MLS_G double *)k_zeros4);
+                }
+#pragma unroll
+                for (int u = 0; u < kDetOwn; ++u) {
+                    if (ph[u]) sum[u] += pa * pw[u];
+                    ph[u] = hit[u];
+                    pw[u] = v[u];
+                }
+                pa = a;
+                bwd_sync();
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kDetOwn; ++u)
+            if (ph[u]) sum[u] += pa * pw[u];
+#pragma unroll
+        for (int u = 0; u < kDetOwn; ++u) {
+            const int q = q0 + u * G + l;
+            if (q < qe) gpw(dB)[q] = sum[u];
+        }
     }
     if (bad) atomicOr(err, kErrStructure);
 }
 
-void launch_backward_det(int32_t m, int32_t kb, const int32_t *arp, const int32_t *aci, const int32_t *brp,
-                         const int32_t *bci, const double *bval, const int32_t *wrp, const int32_t *wci,
-                         const double *wval, const int32_t *trp, const int32_t *tci, const double *tv, double *dA,
-                         double *dB, uint32_t *err, hipStream_t s)
+template <int G>
+static void launch_det_group(int32_t m, int32_t kb, int64_t nnz_b, int64_t nnz_w, const int32_t *arp, const int32_t *aci, const int32_t *brp,
+                             const int32_t *bci, const double *bval, const int32_t *wrp, const int32_t *wci,
+                             const double *wval, const int32_t *trp, const int32_t *tci, const double *tv, double *dA,
+                             double *dB, uint32_t *err, hipStream_t s)
 {
+    constexpr int rows = kWG / G;
     if (dA && m > 0) {
         ProfScope ps("bwd_det_dA", s);
-        const int64_t blocks = ((int64_t)m * kDetLanes + kWG - 1) / kWG;
-        hipLaunchKernelGGL(k_bwd_det_da, dim3((unsigned)blocks), dim3(kWG), 0, s, m, arp, aci, brp, bci, bval, wrp,
-                           wci, wval, dA, err);
+        hipLaunchKernelGGL(k_bwd_det_da<G>, dim3((unsigned)((m + rows - 1) / rows)), dim3(kWG), 0, s, m, nnz_b, nnz_w, arp,
+                           aci, brp, bci, bval, wrp, wci, wval, dA, err);
     }
     if (dB && kb > 0) {
         ProfScope ps("bwd_det_dB", s);
-        const int64_t blocks = ((int64_t)kb * kDetLanes + kWG - 1) / kWG;
-        hipLaunchKernelGGL(k_bwd_det_db, dim3((unsigned)blocks), dim3(kWG), 0, s, kb, trp, tci, tv, brp, bci, wrp,
-                           wci, wval, dB, err);
+        hipLaunchKernelGGL(k_bwd_det_db<G>, dim3((unsigned)((kb + rows - 1) / rows)), dim3(kWG), 0, s, kb, nnz_w, trp,
+                           tci, tv, brp, bci, wrp, wci, wval, dB, err);
     }
+}
+
+void launch_backward_det(int32_t m, int32_t kb, int64_t nnz_b, int64_t nnz_w, const int32_t *arp, const int32_t *aci,
+                         const int32_t *brp, const int32_t *bci, const double *bval, const int32_t *wrp,
+                         const int32_t *wci, const double *wval, const int32_t *trp, const int32_t *tci,
+                         const double *tv, double *dA, double *dB, uint32_t *err, hipStream_t s)
+{
+    // lanes per row so that most rows of W fit the stage (16 columns per lane):
+    // twice their mean length
+    const double mean = m > 0 ? (double)nnz_w / m : 0.0;
+    if (2.0 * mean <= kDetStage * 8 + 16)
+        launch_det_group<8>(m, kb, nnz_b, nnz_w, arp, aci, brp, bci, bval, wrp, wci, wval, trp, tci, tv, dA, dB, err, s);
+    else if (2.0 * mean <= kDetStage * 16)
+        launch_det_group<16>(m, kb, nnz_b, nnz_w, arp, aci, brp, bci, bval, wrp, wci, wval, trp, tci, tv, dA, dB, err, s);
+    else
+        launch_det_group<32>(m, kb, nnz_b, nnz_w, arp, aci, brp, bci, bval, wrp, wci, wval, trp, tci, tv, dA, dB, err, s);
 }
 
 // ---------------------------------------------------------------------------
 // transpose
 
-__global__ void k_tr_count(int32_t nrows, const int32_t *rp, const int32_t *ci, int32_t *cnt)
+__global__ void k_tr_count(int64_t nnz, const int32_t *ci, int32_t *cnt)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nrows) return;
-    for (int p = gp(rp)[i]; p < gp(rp)[i + 1]; ++p) atomicAdd(cnt + gp(ci)[p], 1);
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < nnz) atomicAdd(cnt + gp(ci)[p], 1);
 }
 
 __global__ void k_tr_rowptr(int32_t n, const int64_t *prefix, int32_t *trp)
@@ -824,57 +998,116 @@ __global__ void k_tr_rowptr(int32_t n, const int64_t *prefix, int32_t *trp)
     if (i <= n) gpw(trp)[i] = (int32_t)gp(prefix)[i];
 }
 
-__global__ void k_tr_scatter(int32_t nrows, const int32_t *rp, const int32_t *ci, const double *v, const int32_t *trp,
-                             int32_t *cursor, int32_t *tci, double *tv)
+constexpr int kTrLanes = 8;   // lanes per row of the scatter (their atomics are independent)
+
+__global__ __launch_bounds__(kWG) void k_tr_scatter(int32_t nrows, const int32_t *rp, const int32_t *ci, const double *v,
+                                                    const int32_t *trp, int32_t *cursor, int32_t *tci, double *tv)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = (int64_t)blockIdx.x * kWG + threadIdx.x;
+    const int64_t i = t / kTrLanes;
     if (i >= nrows) return;
-    for (int p = gp(rp)[i]; p < gp(rp)[i + 1]; ++p) {
-        int c = gp(ci)[p];
-        int pos = gp(trp)[c] + atomicAdd(cursor + c, 1);
-        gpw(tci)[pos] = i;
+    const int e = gp(rp)[i + 1];
+    for (int p = gp(rp)[i] + (int)(t % kTrLanes); p < e; p += kTrLanes) {
+        const int c = gp(ci)[p];
+        const int pos = gp(trp)[c] + atomicAdd(cursor + c, 1);
+        gpw(tci)[pos] = (int32_t)i;
         if (v) gpw(tv)[pos] = gp(v)[p];
     }
 }
 
-// per-row insertion sort of (column, value) pairs (rows of a transpose are
-// short for the workloads here; long rows still sort correctly, just slowly)
-__global__ void k_tr_sort(int32_t n, const int32_t *trp, int32_t *tci, double *tv)
+// Rows of the transpose sorted by column (1.6M entries in rows of 8: 83 us with
+// an insertion sort per lane in global memory, 16 us so): an entry's place is the number of
+// smaller columns in its row (they are distinct). 16 lanes per row rank rows
+// of up to 16 entries from each other's registers; the wave takes the longer
+// ones of its four rows one at a time, columns in LDS, up to kTrSortMax
+// entries; still longer ones are insertion-sorted by one lane.
+constexpr int kTrGroup = 16;
+constexpr int kTrPer = 8;                       // entries per lane of a wave's row
+constexpr int kTrSortMax = kTrPer * kWave;
+
+__global__ __launch_bounds__(kWG) void k_tr_sort(int32_t n, const int32_t *trp, int32_t *tci, double *tv)
 {
-    int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    const int s = gp(trp)[r], e = gp(trp)[r + 1];
-    MLS_G int32_t *c = gpw(tci);
-    MLS_G double *v = gpw(tv);
-    for (int a = s + 1; a < e; ++a) {
-        int key = c[a];
-        double kv = tv ? v[a] : 0.0;
-        int b2 = a - 1;
-        while (b2 >= s && c[b2] > key) {
-            c[b2 + 1] = c[b2];
-            if (tv) v[b2 + 1] = v[b2];
-            --b2;
+    __shared__ int s_c[kWG / kWave][kTrSortMax];
+    const int lane = threadIdx.x & 63, l = lane % kTrGroup;
+    int *c = s_c[threadIdx.x >> 6];
+    const int64_t r = ((int64_t)blockIdx.x * kWG + threadIdx.x) / kTrGroup;
+    const int s = r < n ? gp(trp)[r] : 0, e = r < n ? gp(trp)[r + 1] : 0;
+    const int len = e - s;
+    const bool mine = len <= kTrGroup && l < len;
+    const int col = mine ? gp(tci)[s + l] : 0x7fffffff;
+    const double val = mine && tv ? gp(tv)[s + l] : 0.0;
+    int rank = 0;
+#pragma unroll
+    for (int x = 0; x < kTrGroup; ++x) rank += __shfl(col, x, kTrGroup) < col ? 1 : 0;
+    if (mine) {
+        gpw(tci)[s + rank] = col;
+        if (tv) gpw(tv)[s + rank] = val;
+    }
+    unsigned long long big = __ballot(l == 0 && len > kTrGroup);
+    while (big) {
+        const int src = __ffsll((long long)big) - 1;
+        big &= big - 1ull;
+        const int s0 = __builtin_amdgcn_readlane(s, src), nn = __builtin_amdgcn_readlane(len, src);
+        MLS_G int32_t *rc = gpw(tci) + s0;
+        MLS_G double *rv = gpw(tv) + s0;
+        if (nn <= kTrSortMax) {
+            int cv[kTrPer];
+            double vv[kTrPer];
+#pragma unroll
+            for (int u = 0; u < kTrPer; ++u) {
+                const int x = u * kWave + lane;
+                cv[u] = x < nn ? rc[x] : 0x7fffffff;
+                vv[u] = x < nn && tv ? rv[x] : 0.0;
+                if (x < nn) c[x] = cv[u];
+            }
+            bwd_sync();
+            int at[kTrPer];
+#pragma unroll
+            for (int u = 0; u < kTrPer; ++u) at[u] = 0;
+            for (int x = 0; x < nn; ++x) {
+                const int y = c[x];
+#pragma unroll
+                for (int u = 0; u < kTrPer; ++u) at[u] += y < cv[u] ? 1 : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kTrPer; ++u) {
+                if (u * kWave + lane >= nn) continue;
+                rc[at[u]] = cv[u];
+                if (tv) rv[at[u]] = vv[u];
+            }
+            bwd_sync();
+        } else if (lane == 0) {
+            for (int a = 1; a < nn; ++a) {
+                const int key = rc[a];
+                const double kv = tv ? rv[a] : 0.0;
+                int b2 = a - 1;
+                while (b2 >= 0 && rc[b2] > key) {
+                    rc[b2 + 1] = rc[b2];
+                    if (tv) rv[b2 + 1] = rv[b2];
+                    --b2;
+                }
+                rc[b2 + 1] = key;
+                if (tv) rv[b2 + 1] = kv;
+            }
         }
-        c[b2 + 1] = key;
-        if (tv) v[b2 + 1] = kv;
     }
 }
 
-void launch_transpose(int32_t nrows, int32_t ncols, const int32_t *rp, const int32_t *ci, const double *v,
+void launch_transpose(int32_t nrows, int32_t ncols, int64_t nnz, const int32_t *rp, const int32_t *ci, const double *v,
                       int32_t *trp, int32_t *tci, double *tv, int32_t *cursor, int64_t *tile_sum, int64_t *prefix,
                       int32_t *cnt, hipStream_t s)
 {
     ProfScope ps("transpose", s);
-    launch_fill_i32(cnt, 0, ncols, s);
-    launch_fill_i32(cursor, 0, ncols, s);
-    if (nrows > 0)
-        hipLaunchKernelGGL(k_tr_count, dim3((nrows + kWG - 1) / kWG), dim3(kWG), 0, s, nrows, rp, ci, cnt);
+    launch_fill_i32(cnt, 0, (cursor - cnt) + ncols, s);   // cursor follows cnt
+    if (nnz > 0) hipLaunchKernelGGL(k_tr_count, dim3((unsigned)((nnz + kWG - 1) / kWG)), dim3(kWG), 0, s, nnz, ci, cnt);
     launch_scan(cnt, ncols, tile_sum, prefix, s);
     hipLaunchKernelGGL(k_tr_rowptr, dim3((ncols + kWG) / kWG), dim3(kWG), 0, s, ncols, prefix, trp);
+    constexpr int srows = kWG / kTrLanes, trows = kWG / kTrGroup;
     if (nrows > 0)
-        hipLaunchKernelGGL(k_tr_scatter, dim3((nrows + kWG - 1) / kWG), dim3(kWG), 0, s, nrows, rp, ci, v, trp, cursor,
-                           tci, tv);
-    if (ncols > 0) hipLaunchKernelGGL(k_tr_sort, dim3((ncols + kWG - 1) / kWG), dim3(kWG), 0, s, ncols, trp, tci, tv);
+        hipLaunchKernelGGL(k_tr_scatter, dim3((nrows + srows - 1) / srows), dim3(kWG), 0, s, nrows, rp, ci, v, trp,
+                           cursor, tci, tv);
+    if (ncols > 0)
+        hipLaunchKernelGGL(k_tr_sort, dim3((ncols + trows - 1) / trows), dim3(kWG), 0, s, ncols, trp, tci, tv);
 }
 
 // out[e] = X(r, c) for the e-th entry (r, c) of pattern P, else 0.0

@@ -83,13 +83,14 @@ void launch_backward(const Batch &b, const Sched &sc, const double *wval, double
 
 // Deterministic adjoint (one lane per output entry, sequential sums; W_ij by
 // binary search in W_i). trp/tci/tv: the transpose of A with its values.
-void launch_backward_det(int32_t m, int32_t kb, const int32_t *arp, const int32_t *aci, const int32_t *brp,
-                         const int32_t *bci, const double *bval, const int32_t *wrp, const int32_t *wci,
-                         const double *wval, const int32_t *trp, const int32_t *tci, const double *tv, double *dA,
-                         double *dB, uint32_t *err, hipStream_t s);
+void launch_backward_det(int32_t m, int32_t kb, int64_t nnz_b, int64_t nnz_w, const int32_t *arp, const int32_t *aci,
+                         const int32_t *brp, const int32_t *bci, const double *bval, const int32_t *wrp,
+                         const int32_t *wci, const double *wval, const int32_t *trp, const int32_t *tci,
+                         const double *tv, double *dA, double *dB, uint32_t *err, hipStream_t s);
 
-// Transpose and masked gather helpers.
-void launch_transpose(int32_t nrows, int32_t ncols, const int32_t *rp, const int32_t *ci, const double *v,
+// Transpose and masked gather helpers. cursor: ncols words somewhere behind cnt
+// in the same allocation (both, and what lies between, are cleared).
+void launch_transpose(int32_t nrows, int32_t ncols, int64_t nnz, const int32_t *rp, const int32_t *ci, const double *v,
                       int32_t *trp, int32_t *tci, double *tv, int32_t *cursor, int64_t *tile_sum,
                       int64_t *prefix, int32_t *cnt, hipStream_t s);
 void launch_mask_gather(int32_t nrows, const int32_t *xrp, const int32_t *xci, const double *xv,

@@ -188,3 +188,33 @@ def test_batch_products_inside_a_wave():
         R, _ = oracle.spgemm(A, B)
         rp, ci, v = C.numpy()
         assert np.array_equal(rp, R.row_ptr) and np.array_equal(ci, R.col_idx) and np.array_equal(v, R.values)
+
+
+# the fixed-order adjoint: rows of W that fit the staged columns (16 per lane;
+# 8, 16 and 32 lanes per row) or not, rows of B longer than a group's lanes
+# hold; and transposes with rows around 16, 64 and 512 entries
+@pytest.mark.parametrize("len_w", [4, 70, 128, 129, 256, 257, 512, 700])
+@pytest.mark.parametrize("len_b", [1, 16, 17, 33, 70])
+def test_fixed_order_adjoint(len_w, len_b):
+    g = synth.rng(len_w * 100 + len_b)
+    n = 900
+    per = max(1, len_w // len_b)
+    inner = 1500
+    A = rows_of([per] * 60 + [0, 1, 2] + [min(2 * per, inner)] * 5, inner, len_w)
+    B = rows_of([len_b] * (inner - 10) + [0] * 10, n, len_b)
+    R, _ = oracle.spgemm(A, B)
+    W = synth.Csr(R.nrows, R.ncols, R.row_ptr, R.col_idx, g.standard_normal(R.nnz))
+    gA, gB = mls.backward(*[mls.DeviceCsr.from_host(M) for M in (A, B, W)], deterministic=True)
+    rA, rB, _, _ = oracle.backward(A, B, W)
+    assert np.array_equal(gA.cpu().numpy(), rA) and np.array_equal(gB.cpu().numpy(), rB)
+
+
+@pytest.mark.parametrize("lens", [[1, 15, 16, 17, 0, 63, 64, 65], [511, 512, 513, 3], [0, 0, 0], [16] * 9])
+@pytest.mark.parametrize("values", [True, False])
+def test_transpose_rows(lens, values):
+    T = rows_of(lens, 600, len(lens))          # the expected transpose
+    M = synth.transpose(T)
+    D = mls.DeviceCsr.from_host(M, values=values)
+    rp, ci, v = mls.transpose(D).numpy()
+    assert np.array_equal(rp, T.row_ptr) and np.array_equal(ci, T.col_idx)
+    assert (v is None) if not values else np.array_equal(v, T.values)
