@@ -390,7 +390,8 @@ spgemm_status spgemm_batch_numeric(int32_t nbatch, const spgemm_csr *A, const sp
  * tune_cache_path is not NULL, read from and appended to that text file
  * (lines "batch <nbatch> <rows of A> <rows of B> <nnz A> <nnz C> <device>
  * <g1> <g2> <floor>"; unreadable lines are ignored), so that other processes
- * on the same kind of GPU skip the search. Tuning synchronises the stream. */
+ * on the same kind of GPU skip the search. Creating a plan synchronises the
+ * stream (the rows of every bin are read back: empty bins are not launched). */
 typedef struct spgemm_batch_plan spgemm_batch_plan;
 spgemm_status spgemm_batch_plan_create(int32_t nbatch, const spgemm_csr *A, const spgemm_csr *B,
                                        spgemm_csr *C, int32_t group_size, int32_t use_graph,

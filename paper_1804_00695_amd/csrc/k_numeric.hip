@@ -975,21 +975,26 @@ static void launch_num_spill(const Batch &b, const Sched &sc, hipStream_t s)
     }
 }
 
-void launch_numeric_groups(const Batch &b, const Sched &sc, int G1, int G2, hipStream_t s)
+void launch_numeric_groups(const Batch &b, const Sched &sc, int G1, int G2, const int32_t *n_bin, hipStream_t s)
 {
     if (b.na <= 0) return;
-    launch_num_class<8, kFillCap[0]>(b, sc, 0, s);
-    switch (G1) {
-    case 8: launch_num_class<8, kFillCap[1]>(b, sc, 1, s); break;
-    case 16: launch_num_class<16, kFillCap[1]>(b, sc, 1, s); break;
-    case 64: launch_num_class<64, kFillCap[1]>(b, sc, 1, s); break;
-    default: launch_num_class<32, kFillCap[1]>(b, sc, 1, s); break;
+    auto rows = [&](int bin) { return !n_bin || n_bin[bin] > 0; };
+    if (rows(0)) launch_num_class<8, kFillCap[0]>(b, sc, 0, s);
+    if (rows(1)) {
+        switch (G1) {
+        case 8: launch_num_class<8, kFillCap[1]>(b, sc, 1, s); break;
+        case 16: launch_num_class<16, kFillCap[1]>(b, sc, 1, s); break;
+        case 64: launch_num_class<64, kFillCap[1]>(b, sc, 1, s); break;
+        default: launch_num_class<32, kFillCap[1]>(b, sc, 1, s); break;
+        }
     }
-    if (G2 >= 64) launch_num_class<64, kFillCap[2]>(b, sc, 2, s);
-    else launch_num_class<32, kFillCap[2]>(b, sc, 2, s);
-    launch_num_class<64, kFillCap[3]>(b, sc, 3, s);
-    launch_num_class<64, kFillCap[4]>(b, sc, 4, s);
-    launch_num_spill(b, sc, s);
+    if (rows(2)) {
+        if (G2 >= 64) launch_num_class<64, kFillCap[2]>(b, sc, 2, s);
+        else launch_num_class<32, kFillCap[2]>(b, sc, 2, s);
+    }
+    if (rows(3)) launch_num_class<64, kFillCap[3]>(b, sc, 3, s);
+    if (rows(4)) launch_num_class<64, kFillCap[4]>(b, sc, 4, s);
+    if (rows(kBinSpill)) launch_num_spill(b, sc, s);
 }
 
 bool small_rows_fit(const Batch &b)
@@ -1013,7 +1018,7 @@ void launch_numeric_small(const Batch &b, const Sched &sc, hipStream_t s)
 
 void launch_numeric(const Batch &b, const Sched &sc, int G, hipStream_t s)
 {
-    launch_numeric_groups(b, sc, G, G >= 64 ? 64 : 32, s);
+    launch_numeric_groups(b, sc, G, G >= 64 ? 64 : 32, nullptr, s);
 }
 
 }  // namespace mls

@@ -68,8 +68,10 @@ void launch_backward_small(const Batch &b, const Sched &sc, double *dA, double *
 
 // Numeric phase (row-range fused multiply-add) over the binned rows.
 void launch_numeric(const Batch &b, const Sched &sc, int G, hipStream_t s);
-// The same with the lanes per row of the first (G1) and second (G2) LDS classes given.
-void launch_numeric_groups(const Batch &b, const Sched &sc, int G1, int G2, hipStream_t s);
+// The same with the lanes per row of the first (G1) and second (G2) LDS classes
+// given, and, where the caller knows them, the rows of every bin (n_bin, host):
+// bins without rows are not launched.
+void launch_numeric_groups(const Batch &b, const Sched &sc, int G1, int G2, const int32_t *n_bin, hipStream_t s);
 
 // Triangle counting over the binned rows of L (A = B = L in the batch).
 void launch_tc(const Batch &b, const Sched &sc, int64_t *counts, unsigned long long *total,
