@@ -246,6 +246,9 @@ spgemm_status prepare_batch(int32_t nbatch, const spgemm_csr *A, const spgemm_cs
         Prob &P = out.probs[t];
         P.arp = A[t].row_ptr; P.aci = A[t].col_idx; P.aval = A[t].values;
         P.brp = B[t].row_ptr; P.bci = B[t].col_idx; P.bval = B[t].values;
+        // a step on an empty row of B may read B's first entry (and ignore it):
+        // with no entries at all, any device memory serves
+        if (B[t].nnz == 0) { P.bci = (const int32_t *)ws; P.bval = (const double *)ws; }
         if (need_bw) {
             P.bw = (uint2 *)(ws + out.layout.bw) + eb;
             P.bwc = (int32_t *)(ws + out.layout.bwc) + out.bbase[t];

@@ -259,10 +259,16 @@ __device__ __forceinline__ Prob get_prob_any(const Batch &b, int t)
     return get_prob_batch(b, t);
 }
 
-// Multiplicative (Fibonacci) hashing of a 32-bit key into 2^logcap slots.
+// Multiplicative (Fibonacci) hashing of a key's low 24 bits (a column, or a set
+// of 32): the product modulo 2^24 spreads consecutive keys by the golden
+// ratio, its top bits are the slot. The 24-bit multiply runs at full rate, the
+// 32-bit one at a quarter of it. Keys that differ above bit 24 alone share
+// their home slot.
+constexpr uint32_t kHashMul = 0x9E3779u;
+
 __device__ __forceinline__ uint32_t hslot(uint32_t key, int logcap)
 {
-    return (key * 0x9E3779B1u) >> (32 - logcap);
+    return __builtin_amdgcn_ubfe(__umul24(key, kHashMul), 24 - logcap, logcap);
 }
 
 __device__ __forceinline__ int ilog2_ceil(int x)
@@ -318,24 +324,23 @@ __device__ __forceinline__ int group_total(int v, int incl)
     else return __shfl(incl, G - 1, G);
 }
 
-// number of lower lanes of the group (G <= 16) whose key equals this lane's
-template <int O, int G>
-__device__ __forceinline__ void group_rank_step(int key, int lane, int &r)
+// at, or last where !ok (ok: at <= last). Written as a select on an opaque copy:
+// as a plain minimum, the compiler would redo the comparison where ok is used
+// next, behind the loads, and keep both operands in registers until then
+// (which spilled).
+__device__ __forceinline__ int or_last(bool ok, int at, int last)
 {
-    if constexpr (O < G) {
-        const int y = dpp_move<0x110 + O>(key);   // row_shr:O
-        r += (lane >= O && y == key) ? 1 : 0;
-        group_rank_step<O + 1, G>(key, lane, r);
-    }
+    asm("" : "+v"(at));
+    return ok ? at : last;
 }
 
-template <int G>
-__device__ __forceinline__ int group_rank(int key, int lane)
+// OR over the 8 lanes of a group
+__device__ __forceinline__ uint32_t group_or8(uint32_t v)
 {
-    static_assert(G <= 16, "one DPP row");
-    int r = 0;
-    group_rank_step<1, G>(key, lane, r);
-    return r;
+    v |= (uint32_t)dpp_move<0xB1>((int)v);    // quad_perm [1,0,3,2]: lane ^ 1
+    v |= (uint32_t)dpp_move<0x4E>((int)v);    // quad_perm [2,3,0,1]: lane ^ 2
+    v |= (uint32_t)dpp_move<0x141>((int)v);   // row_half_mirror: the other quad of 8
+    return v;
 }
 
 // inclusive prefix sum over the group; lane = position in the group

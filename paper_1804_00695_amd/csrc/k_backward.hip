@@ -27,9 +27,6 @@ namespace mls {
 
 constexpr int kBwdUnroll = 4;
 
-// all ones: read as a column it is -1 (no entry)
-__device__ __attribute__((aligned(8))) int32_t k_bwd_void[2] = {-1, -1};
-
 __device__ __forceinline__ void bwd_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -104,11 +101,13 @@ __device__ __forceinline__ void w_lookup_n(const int *key, const double *wv, int
 
 // LDS of one row: W_i's hash (wide: key and value per slot; packed: a
 // column -> position table and the values by position), the staged entries
-// of A (first B position, a_ik, their dA sums) and the staged entries' first
-// pairs
+// of A (B position, a_ik, their dA sums) and, for groups of 32 or 64 lanes, the
+// start bits of a tile of pairs
+constexpr int bwd_flag_words(int G) { return G >= 32 ? G * kBwdUnroll / 32 : 0; }
+
 constexpr int bwd_row_bytes(int CAP, int G, bool PACK)
 {
-    return (PACK ? CAP * 4 + (CAP / 2) * 8 : CAP * 12) + G * 20 + (G + 4) * 4;
+    return (PACK ? CAP * 4 + (CAP / 2) * 8 : CAP * 12) + G * 20 + bwd_flag_words(G) * 4;
 }
 
 // Waves per workgroup that keep the most waves resident on a CU (160 KB of
@@ -189,8 +188,8 @@ struct BwdShape {
     static constexpr int LDS_WV = NW * W * CAP * 4;
     static constexpr int LDS_PA = LDS_WV + NW * W * WV * 8;
     static constexpr int LDS_DA = LDS_PA + NW * W * G * 8;
-    static constexpr int LDS_POFF = LDS_DA + NW * W * G * 8;
-    static constexpr int LDS_PQ = LDS_POFF + NW * W * (G + 4) * 4;
+    static constexpr int LDS_FLAGS = LDS_DA + NW * W * G * 8;
+    static constexpr int LDS_PQ = LDS_FLAGS + NW * W * bwd_flag_words(G) * 4;
     static constexpr int LDS = LDS_PQ + NW * W * G * 4;
 };
 
@@ -208,7 +207,7 @@ __device__ __forceinline__ void bwd_lds_rows(const Batch &b, const Sched &sc, in
     double *s_wv = (double *)(lds + Shape::LDS_WV);
     double *s_pa = (double *)(lds + Shape::LDS_PA);
     double *s_da = (double *)(lds + Shape::LDS_DA);
-    int *s_poff = (int *)(lds + Shape::LDS_POFF);   // read four at a time
+    uint32_t *s_flags = (uint32_t *)(lds + Shape::LDS_FLAGS);   // start bits, read four words at a time
     int *s_pq = (int *)(lds + Shape::LDS_PQ);
 
     const int wave = threadIdx.x >> 6;
@@ -222,7 +221,7 @@ __device__ __forceinline__ void bwd_lds_rows(const Batch &b, const Sched &sc, in
     double *pa = s_pa + rs * G;
     double *da = s_da + rs * G;
     int *pq = s_pq + rs * G;
-    int *poff = s_poff + rs * (G + 4);
+    uint32_t *flags = s_flags + rs * bwd_flag_words(G);   // groups of 32 or 64 lanes
 
     const Prob P = b.p0;
     const MLS_G int32_t *__restrict__ aci = gp(P.aci);
@@ -262,11 +261,10 @@ __device__ __forceinline__ void bwd_lds_rows(const Batch &b, const Sched &sc, in
         const int nw = m.nw, ws0 = m.ws0, ps = m.ps, pe = m.pe;
         int logcap = ilog2_ceil(2 * nw);
         if (logcap < 5) logcap = 5;
-        const int cap = 1 << logcap;
         if constexpr (PACK) {
-            ptab.clear(cap, lane, G);
+            ptab.open(nw, lane, G);
         } else {
-            for (int h = lane; h < cap; h += G) key[h] = -1;
+            for (int h = lane; h < 1 << logcap; h += G) key[h] = -1;
         }
         // this row's first chunk was located during the previous row
         int ka = f.ka;
@@ -287,7 +285,7 @@ __device__ __forceinline__ void bwd_lds_rows(const Batch &b, const Sched &sc, in
             for (int u = 0; u < kBwdInsDepth; ++u) {
                 if (jv[u] < 0) continue;
                 if constexpr (PACK) {
-                    ptab.insert(logcap, jv[u], e0 + u * G);
+                    ptab.insert(jv[u], e0 + u * G);
                     wv[e0 + u * G] = wj[u];
                 } else {
                     w_insert(key, wv, logcap, jv[u], wj[u]);
@@ -300,16 +298,22 @@ __device__ __forceinline__ void bwd_lds_rows(const Batch &b, const Sched &sc, in
         // scans (cross-lane shuffles) run with every lane present
         int nch = (pe - ps + G - 1) / G;
         for (int o = 32; o >= 1; o >>= 1) nch = max(nch, __shfl_xor(nch, o, kWave));
-        // stage a chunk: its entries' first B positions, pair offsets, a_ik
-        // and zeroed dA sums; returns the chunk's pair count
+        // stage a chunk: its non-empty entries compacted (first B position - first
+        // pair, a_ik and zeroed dA sums); returns the chunk's pair count
+        int first = 0, rank = 0;   // this lane's entry: its first pair, its place
+        bool any = false;
         auto stage = [&](int q0, int q1, double a) -> int {
             const int np = q1 > q0 ? q1 - q0 : 0;
             const int incl = group_scan_incl<G>(np, lane);
             const int tot = group_total<G>(np, incl);
-            poff[lane] = incl - np;
-            if (lane == 0) poff[G] = tot;
-            pq[lane] = q0;
-            pa[lane] = a;
+            first = incl - np;
+            any = np > 0;
+            const unsigned long long ne = __ballot(any) >> (slot * G);
+            rank = __popcll(ne & ((1ull << lane) - 1ull));
+            if (any) {
+                pq[rank] = q0 - first;
+                pa[rank] = a;
+            }
             da[lane] = 0.0;
             return tot;
         };
@@ -333,17 +337,6 @@ __device__ __forceinline__ void bwd_lds_rows(const Batch &b, const Sched &sc, in
                 sa = *(on ? aval + pc + G + lane : (const MLS_G double *)k_zeros4);
             }
             bwd_sync();
-            // groups of at most 16 lanes keep the pair offsets in registers: a
-            // pair's entry is the last one whose offset is at most its index
-            constexpr int RG = G <= 16 ? G : 4;
-            int pofv[RG];
-            if constexpr (G <= 16) {
-#pragma unroll
-                for (int x = 0; x < G; x += 4) {
-                    const int4 v = *(const int4 *)(poff + x);
-                    pofv[x] = v.x; pofv[x + 1] = v.y; pofv[x + 2] = v.z; pofv[x + 3] = v.w;
-                }
-            }
             // the dB adds of a batch are issued after the next batch's loads:
             // the wait for those loads then does not include them (the
             // counter covers loads and atomics in issue order)
@@ -351,62 +344,88 @@ __device__ __forceinline__ void bwd_lds_rows(const Batch &b, const Sched &sc, in
             double dv[kBwdUnroll];
 #pragma unroll
             for (int d = 0; d < kBwdUnroll; ++d) { dq[d] = -1; dv[d] = 0.0; }
+            int eb = -1;   // entries started before the tile, less one
             for (int base = 0; base < total; base += G * kBwdUnroll) {
+                // a bit per pair of the tile where an entry starts: a pair's entry is
+                // the count of the bits up to it (from DPP ORs for groups of up to 16
+                // lanes, through LDS for wider ones)
+                constexpr int NB = G * kBwdUnroll / 32;   // words of bits
+                uint32_t m[NB];
+                const int at0 = first - base;
+                if constexpr (G <= 16) {
+#pragma unroll
+                    for (int x = 0; x < NB; ++x) {
+                        const int at = at0 - 32 * x;
+                        m[x] = group_or8(any && (uint32_t)at < 32u ? 1u << at : 0u);
+                        if constexpr (G == 16) m[x] |= (uint32_t)dpp_move<0x140>((int)m[x]);   // the other half of 16
+                    }
+                } else {
+                    if (lane < NB) flags[lane] = 0u;
+                    bwd_sync();
+                    if (any && (uint32_t)at0 < 32u * NB) atomicOr(flags + (at0 >> 5), 1u << (at0 & 31));
+                    bwd_sync();
+#pragma unroll
+                    for (int x = 0; x < NB; x += 4) {
+                        const uint4 v = *(const uint4 *)(flags + x);
+                        m[x] = v.x; m[x + 1] = v.y; m[x + 2] = v.z; m[x + 3] = v.w;
+                    }
+                    bwd_sync();
+                }
                 int qv[kBwdUnroll], ev[kBwdUnroll], jv[kBwdUnroll];
+                bool ok[kBwdUnroll];
                 double bv[kBwdUnroll];
-                // loads without branches (pairs past the chunk read the all-ones
-                // dummy: column -1), all issued before any use
+                // loads without branches (past the pairs, the last one again), all
+                // issued before any use
 #pragma unroll
                 for (int d = 0; d < kBwdUnroll; ++d) {
                     const int pp = base + d * G + lane;
-                    int lo, po;
-                    if constexpr (G <= 16) {
-                        lo = -1;
-                        po = 0;
-#pragma unroll
-                        for (int x = 0; x < G; ++x) {
-                            const bool le = pofv[x] <= pp;
-                            lo += le ? 1 : 0;
-                            po = le ? pofv[x] : po;
-                        }
+                    int en;
+                    if constexpr (G == 64) {
+                        const uint64_t mm = ((uint64_t)m[2 * d + 1] << 32) | m[2 * d];
+                        en = eb + __popcll(mm & (lane == 63 ? ~0ull : (2ull << lane) - 1ull));
+                        eb += __popcll(mm);
                     } else {
-                        lo = 0;
-                        int hi = G - 1;   // largest e with poff[e] <= pp
-                        while (lo < hi) {
-                            const int mid = (lo + hi + 1) >> 1;
-                            if (poff[mid] <= pp) lo = mid; else hi = mid - 1;
-                        }
-                        po = poff[lo];
+                        const int sh = d * G % 32;
+                        const uint32_t w = m[d * G / 32];
+                        en = eb + __popc(w & ((2u << (sh + lane)) - 1u));
+                        if (sh + G == 32) eb += __popc(w);
                     }
-                    const bool ok = pp < total;
-                    ev[d] = lo;
-                    qv[d] = pq[lo] + (pp - po);
-                    const MLS_G int32_t *pj = ok ? bci + qv[d] : (const MLS_G int32_t *)k_bwd_void;
-                    const MLS_G double *pv = ok ? bval + qv[d] : (const MLS_G double *)k_bwd_void;
-                    jv[d] = *pj;
-                    bv[d] = *pv;
+                    ok[d] = pp < total;
+                    ev[d] = en;
+                    qv[d] = pq[en] + or_last(ok[d], pp, total - 1);
+                    jv[d] = bci[(uint32_t)qv[d]];
+                    bv[d] = bval[(uint32_t)qv[d]];
                 }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int d = 0; d < kBwdUnroll; ++d)
                     if (dq[d] >= 0) atomicAdd(dB + dq[d], dv[d]);
-                int sl[kBwdUnroll];
+                bool hit[kBwdUnroll];
                 double w[kBwdUnroll];
                 if constexpr (PACK) {
                     // positions in W_i's row, then the values by position
-                    ptab.template lookup_n<kBwdUnroll>(logcap, jv, sl);
+                    uint32_t pos[kBwdUnroll];
+                    ptab.template lookup_n<kBwdUnroll>(jv, ok, pos);
 #pragma unroll
-                    for (int d = 0; d < kBwdUnroll; ++d) w[d] = wv[sl[d] >= 0 ? sl[d] : 0];
+                    for (int d = 0; d < kBwdUnroll; ++d) {
+                        hit[d] = ok[d] && pos[d] <= ptab.kMaxPos;
+                        w[d] = wv[hit[d] ? pos[d] : 0u];
+                    }
                 } else {
+                    int sl[kBwdUnroll];
+#pragma unroll
+                    for (int d = 0; d < kBwdUnroll; ++d) jv[d] = ok[d] ? jv[d] : -1;
                     w_lookup_n<kBwdUnroll>(key, wv, logcap, jv, sl, w);
+#pragma unroll
+                    for (int d = 0; d < kBwdUnroll; ++d) hit[d] = sl[d] >= 0;
                 }
 #pragma unroll
                 for (int d = 0; d < kBwdUnroll; ++d) asm volatile("" ::"v"(bv[d]));
 #pragma unroll
                 for (int d = 0; d < kBwdUnroll; ++d) {
-                    if (sl[d] == -1) bad = true;
+                    bad |= ok[d] && !hit[d];
                     dq[d] = -1;
-                    if (sl[d] < 0) continue;
+                    if (!hit[d]) continue;
                     if (dA) atomicAdd(da + ev[d], w[d] * bv[d]);
                     if (dB) { dq[d] = qv[d]; dv[d] = pa[ev[d]] * w[d]; }
                 }
@@ -415,7 +434,7 @@ __device__ __forceinline__ void bwd_lds_rows(const Batch &b, const Sched &sc, in
             for (int d = 0; d < kBwdUnroll; ++d)
                 if (dq[d] >= 0) atomicAdd(dB + dq[d], dv[d]);
             bwd_sync();
-            if (dA && pc + lane < pe) gdA[pc + lane] = da[lane];
+            if (dA && pc + lane < pe) gdA[pc + lane] = any ? da[rank] : 0.0;
             bwd_sync();
         }
         // the next row's B row bounds (its entries of A arrived during the pairs)

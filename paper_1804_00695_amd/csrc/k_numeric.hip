@@ -39,9 +39,6 @@ constexpr int kWinDepth = 8;       // spill window: steps of 64 pairs whose B lo
 constexpr bool kNumFlat = true;    // flattened pairs for the classes of at most kNumFlatMaxG lanes per row
 constexpr int kNumFlatMaxG = 8;
 
-// all ones: read as a column it is -1 (no entry)
-__device__ __attribute__((aligned(8))) int32_t k_num_void[2] = {-1, -1};
-
 __device__ __forceinline__ void nwave_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -65,7 +62,7 @@ template <int G>
 constexpr int ins_depth() { return G >= 32 ? 2 : 4; }
 
 template <int G, typename TAB>
-__device__ __forceinline__ void insert_row(TAB &tab, double *acc, int logcap,
+__device__ __forceinline__ void insert_row(TAB &tab, double *acc,
                                            const MLS_G int32_t *__restrict__ cols,
                                            const MLS_G double *__restrict__ vals, int off, int n, int lane,
                                            bool accumulate)
@@ -73,7 +70,7 @@ __device__ __forceinline__ void insert_row(TAB &tab, double *acc, int logcap,
     constexpr int kInsDepth = ins_depth<G>();
     if constexpr (kInsDepth == 1) {
         for (int e = lane; e < n; e += G) {
-            tab.insert(logcap, cols[off + e], e);
+            tab.insert(cols[off + e], e);
             acc[e] = accumulate ? vals[off + e] : 0.0;
         }
         return;
@@ -87,7 +84,7 @@ __device__ __forceinline__ void insert_row(TAB &tab, double *acc, int logcap,
         }
 #pragma unroll
         for (int u = 0; u < kInsDepth; ++u)
-            if (jv[u] >= 0) tab.insert(logcap, jv[u], e0 + u * G);
+            if (jv[u] >= 0) tab.insert(jv[u], e0 + u * G);
         if (accumulate) {
             double v[kInsDepth];
 #pragma unroll
@@ -191,7 +188,7 @@ struct FirstChunk {
 __device__ __forceinline__ void first_a(const Prob &P, const RowMeta &m, int lane, FirstChunk &f)
 {
     const bool on = m.ps + lane < m.pe;
-    const MLS_G int32_t *pk = on ? gp(P.aci) + m.ps + lane : (const MLS_G int32_t *)k_num_void;
+    const MLS_G int32_t *pk = on ? gp(P.aci) + m.ps + lane : (const MLS_G int32_t *)k_ones4;
     const MLS_G double *pa = on ? gp(P.aval) + m.ps + lane : (const MLS_G double *)k_zeros4;
     f.ka = *pk;
     f.sa = *pa;
@@ -216,7 +213,7 @@ __device__ __forceinline__ void first_b(const Prob &P, FirstChunk &f)
 // c_ij's terms in ascending k. Columns outside [jlo, jhi] are another
 // window's. Returns whether a column was not found.
 template <int D, typename TAB>
-__device__ __forceinline__ bool flat_tile(const TAB &tab, int logcap, double *acc, const int4 *par, uint32_t *flags,
+__device__ __forceinline__ bool flat_tile(const TAB &tab, double *acc, const int4 *par, uint32_t *flags,
                                           int lane, int base, int first, bool nonempty, int total, int &eb,
                                           const MLS_G int32_t *bci, const MLS_G double *bval, int jlo, int jhi)
 {
@@ -226,6 +223,7 @@ __device__ __forceinline__ bool flat_tile(const TAB &tab, int logcap, double *ac
     if (nonempty && (uint32_t)at < (uint32_t)(kWave * D)) atomicOr(flags + (at >> 5), 1u << (at & 31));
     nwave_sync();
     int jv[D], rel[D], more[D];
+    bool ok[D];
     double av[D], bv[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -237,32 +235,30 @@ __device__ __forceinline__ bool flat_tile(const TAB &tab, int logcap, double *ac
         more[d] = __popcll(after);
         const int e0 = eb + (int)(starts & 1u);
         const int pp = base + d * kWave + lane;
-        const bool ok = pp < total;
+        ok[d] = pp < total;
         const int4 pr = par[e0 + rel[d]];
-        const int q = pr.x + pp;
-        const MLS_G int32_t *pj = ok ? bci + q : (const MLS_G int32_t *)k_num_void;
-        const MLS_G double *pv = ok ? bval + q : (const MLS_G double *)k_num_void;
-        jv[d] = *pj;
-        bv[d] = *pv;
+        const uint32_t q = (uint32_t)(pr.x + or_last(ok[d], pp, total - 1));   // (past the pairs: the last one again)
+        jv[d] = bci[q];
+        bv[d] = bval[q];
         av[d] = __hiloint2double(pr.w, pr.z);
         eb = e0 + more[d];
     }
     // every load is issued before the first use of a loaded column
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int d = 0; d < D; ++d)
-        if (jv[d] < jlo || jv[d] > jhi) jv[d] = -1;
-    int posv[D];
-    tab.template lookup_n<D>(logcap, jv, posv);
+    for (int d = 0; d < D; ++d) ok[d] = ok[d] && jv[d] >= jlo && jv[d] <= jhi;
+    uint32_t posv[D];
+    tab.template lookup_n<D>(jv, ok, posv);
 #pragma unroll
     for (int d = 0; d < D; ++d) asm volatile("" ::"v"(bv[d]));
     bool bad = false;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        bad |= posv[d] == -1;
+        const bool hit = ok[d] && posv[d] <= TAB::kMaxPos;
+        bad |= ok[d] && !hit;
         const double t = av[d] * bv[d];
         for (int r = 0; r <= more[d]; ++r)
-            if (posv[d] >= 0 && rel[d] == r) atomicAdd(acc + posv[d], t);
+            if (hit && rel[d] == r) atomicAdd(acc + posv[d], t);
     }
     return bad;
 }
@@ -270,7 +266,7 @@ __device__ __forceinline__ bool flat_tile(const TAB &tab, int logcap, double *ac
 constexpr int kFlatWords = 16;   // start bits of a tile of 8 steps
 
 template <int DEPTH, typename TAB>
-__device__ __forceinline__ bool flat_chunk(const TAB &tab, int logcap, double *acc, int4 *par, uint32_t *flags,
+__device__ __forceinline__ bool flat_chunk(const TAB &tab, double *acc, int4 *par, uint32_t *flags,
                                            int lane, int q0, int q1, double a, const MLS_G int32_t *bci,
                                            const MLS_G double *bval, int jlo, int jhi)
 {
@@ -288,11 +284,11 @@ __device__ __forceinline__ bool flat_chunk(const TAB &tab, int logcap, double *a
         // (the tail in smaller tiles: a step past the pairs costs as much as any)
         const int steps = (total - base + kWave - 1) / kWave;
         if (steps > DEPTH / 2) {
-            bad |= flat_tile<DEPTH>(tab, logcap, acc, par, flags, lane, base, first, np > 0, total, eb, bci, bval,
+            bad |= flat_tile<DEPTH>(tab, acc, par, flags, lane, base, first, np > 0, total, eb, bci, bval,
                                     jlo, jhi);
             base += DEPTH * kWave;
         } else {
-            bad |= flat_tile<2>(tab, logcap, acc, par, flags, lane, base, first, np > 0, total, eb, bci, bval, jlo,
+            bad |= flat_tile<2>(tab, acc, par, flags, lane, base, first, np > 0, total, eb, bci, bval, jlo,
                                 jhi);
             base += 2 * kWave;
         }
@@ -303,10 +299,7 @@ __device__ __forceinline__ bool flat_chunk(const TAB &tab, int logcap, double *a
 
 // FLAT: the (entry, B position) pairs of a staged chunk are flattened, G at a
 // time, one per lane (for rows of B shorter than G, which would leave lanes
-// idle); the adds of a step go in rounds by the number of lower lanes with
-// the same output position, so the terms still arrive in ascending k. The
-// staged pair offsets follow the tables in LDS.
-constexpr int num_flat_words(int G) { return G; }
+// idle).
 
 // Waves per SIMD that the LDS of one workgroup (NW waves) leaves resident:
 // 160 KB per CU, 4 SIMDs, at most 8 waves each.
@@ -321,7 +314,7 @@ constexpr int lds_waves_per_simd(int wg_bytes, int nw)
 template <int G, int CAP, bool PACK, bool MULTI, bool FLAT, int MAXLDS = 65536>
 struct NumShape {
     static constexpr int W = kWave / G;
-    static constexpr int XW = FLAT ? num_flat_words(G) : (G == kWave ? kFlatWords : 0);
+    static constexpr int XW = G == kWave && !FLAT ? kFlatWords : 0;   // start bits of a wave's pairs
     static constexpr int NW = nw_num(num_row_bytes(CAP, G, PACK) + 4 * XW, W, MAXLDS);
     static constexpr int OCC = lds_waves_per_simd(NW * W * (num_row_bytes(CAP, G, PACK) + 4 * XW), NW);
     // where LDS already limits a SIMD to 4 waves, registers are free for
@@ -337,7 +330,7 @@ struct NumShape {
     // most 5 waves per SIMD); otherwise a row loads its first chunk when it
     // starts
     static constexpr bool PF = !MULTI && OCC_R <= 5;
-    // LDS of a workgroup: tables (and FLAT pair offsets), staged entries of A
+    // LDS of a workgroup: tables (and start bits), staged entries of A
     // (q0, q1, a), accumulators
     static constexpr int TW = PACK ? CAP : 2 * CAP;   // table words per row
     static constexpr int LDS_PAR = (NW * W * (TW + XW) * 4 + 15) / 16 * 16;
@@ -380,7 +373,7 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
     PosTab<CAP, PACK, (G >= 32 ? 2 : 4)> tab{s_tab + rs * TW};
     double *acc = s_acc + rs * (CAP / 2);
     int4 *par = s_par + rs * G;
-    int *poff = (int *)(s_tab + NW * W * TW) + rs * XW;   // FLAT: staged pair offsets, LONG: start bits
+    uint32_t *flags = s_tab + NW * W * TW + rs * XW;   // LONG only
 
     const int n_bin = gp(sc.bin_count)[bin];
     const int start = bin_start(sc.bin_count, bin);
@@ -428,10 +421,7 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
         const RowMeta m = row_final<MULTI>(b, mr);
         const Prob P = prob_of<MULTI>(b, m.t);
         const int nc = m.nc;
-        int logcap = ilog2_ceil(2 * nc);
-        if (logcap < 5) logcap = 5;
-        const int cap = 1 << logcap;
-        tab.clear(cap, lane, G);
+        tab.open(nc, lane, G);
         // descriptor fields into registers once per row, as global pointers
         const MLS_G int32_t *__restrict__ aci = gp(P.aci);
         const MLS_G double *__restrict__ aval = gp(P.aval);
@@ -459,7 +449,7 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
             skip = pe - ps <= G && (bal & gm) == 0ull;
         }
         nwave_sync();
-        if (!skip) insert_row<G>(tab, acc, logcap, cci, cval, cs, nc, lane, accumulate);
+        if (!skip) insert_row<G>(tab, acc, cci, cval, cs, nc, lane, accumulate);
         nwave_sync();
         if constexpr (!PF) {
             mr_n = row_issue<MULTI>(b, sc, bin_row_checked(sc.err, b.na, g_x, h_x), pc);
@@ -473,6 +463,8 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
         // pointers as loaded; FLAT: the group's pair offsets and pair count
         int eq0 = 0, eq1 = 0;   // LONG: this lane's entry of the chunk
         double ea = 0.0;
+        int fe_first = 0;       // FLAT: first pair of this lane's entry, if it has any
+        bool fe_any = false;
         auto stage = [&](int q0r, int q1r, double a) -> int {
             const int sq0 = q0r - b_off, sq1 = q1r - b_off;
             int tot = 0;
@@ -483,12 +475,21 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
                 asm volatile("" : "+v"(ea));   // waited for here, not where the two ways join
                 return tot;
             }
-            par[lane] = make_int4(sq0, sq1, __double2loint(a), __double2hiint(a));
             if constexpr (FLAT) {
+                // the non-empty entries compacted: (first B position - first pair, -, a)
                 const int np = sq1 > sq0 ? sq1 - sq0 : 0;
                 const int incl = group_scan_incl<G>(np, lane);
-                tot = group_total<G>(np, incl);
-                poff[lane] = incl - np;
+                tot = group_total<G>(np, incl) - 1;
+                fe_first = incl - np;
+                fe_any = np > 0;
+                const uint32_t ne = (uint32_t)(__ballot(fe_any) >> (slot * G)) & 0xffu;
+                if (fe_any)
+                    par[__popc(ne & ((1u << lane) - 1u))] =
+                        make_int4(sq0 - fe_first, 0, __double2loint(a), __double2hiint(a));
+            } else {
+                // (first, last B position, a); an empty row of B is (1, 0)
+                const bool any = sq1 > sq0;
+                par[lane] = make_int4(any ? sq0 : 1, any ? sq1 - 1 : 0, __double2loint(a), __double2hiint(a));
             }
             return tot;
         };
@@ -496,7 +497,7 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
         // previous row (unused when the row has no chunk), the later ones in
         // the chunk loop: no loaded value reaches a point where the two ways
         // join, where its wait would also cover the loads issued since
-        int total = stage(f.r0, f.r1, f.sa);
+        int last = stage(f.r0, f.r1, f.sa);   // FLAT: the chunk's last pair
         // PF: the next row's first A entries load during this row's steps
         RowMeta mn{};
         Prob Pn{};
@@ -511,7 +512,7 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
                 // during the previous chunk
                 const bool in = ka >= k_lo && ka < k_hi;
                 const MLS_G int32_t *pb = in ? brp + (ka - k_lo) : (const MLS_G int32_t *)k_zeros4;
-                total = stage(pb[0], pb[1], sa);
+                last = stage(pb[0], pb[1], sa);
             }
             nwave_sync();
             // the next chunk's entries of A are in flight during this chunk's
@@ -525,56 +526,51 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
             }
             const int n = FLAT ? 0 : min(G, pe - pc);
             if constexpr (FLAT) {
-                // the group's pair offsets in registers: a pair's entry is the
-                // last one whose offset is at most the pair's index
-                static_assert(G % 4 == 0 && G <= 16, "offsets read four at a time");
-                int pofv[G];
-#pragma unroll
-                for (int x = 0; x < G; x += 4) {
-                    const int4 v = *(const int4 *)(poff + x);
-                    pofv[x] = v.x; pofv[x + 1] = v.y; pofv[x + 2] = v.z; pofv[x + 3] = v.w;
-                }
-                for (int base = 0; base < total; base += G * kNumDepth) {
-                    int jv[kNumDepth];
+                // kNumDepth * 8 pairs per tile, one bit per pair where an entry
+                // starts (OR-ed over the group by DPP): a pair's entry is the count
+                // of the bits up to it. Lanes of a step that belong to different
+                // entries may hit the same output: they add entry by entry, so the
+                // terms arrive in ascending k (one wave's LDS adds take effect in
+                // program order).
+                static_assert(G == 8 && (kNumDepth == 4 || kNumDepth == 8), "a tile of 32 or 64 pairs");
+                int eb = -1;   // entries started before the tile, less one
+                for (int base = 0; base <= last; base += G * kNumDepth) {
+                    int jv[kNumDepth], rel[kNumDepth];
+                    bool ok[kNumDepth];
                     double av[kNumDepth], bv[kNumDepth];
-                    // loads without branches (pairs past the chunk read the
-                    // all-ones dummy: column -1), all issued before any use
 #pragma unroll
-                    for (int d = 0; d < kNumDepth; ++d) {
-                        const int pp = base + d * G + lane;
-                        int lo = -1, po = 0;
+                    for (int h = 0; h < kNumDepth / 4; ++h) {
+                        const int at = fe_first - base - 32 * h;
+                        uint32_t m = fe_any && (uint32_t)at < 32u ? 1u << at : 0u;
+                        m = group_or8(m);
 #pragma unroll
-                        for (int x = 0; x < G; ++x) {
-                            const bool le = pofv[x] <= pp;
-                            lo += le ? 1 : 0;
-                            po = le ? pofv[x] : po;
+                        for (int d4 = 0; d4 < 4; ++d4) {
+                            const int d = 4 * h + d4;
+                            const int pp = base + d * G + lane;
+                            const int e0 = eb + __popc(m & ((2u << (8 * d4)) - 1u));   // the step's first lane's entry
+                            const int en = eb + __popc(m & ((2u << (8 * d4 + lane)) - 1u));
+                            rel[d] = en - e0;
+                            ok[d] = pp <= last;
+                            const int4 pr = par[en];   // (past the pairs: the last entry's last pair again)
+                            const uint32_t q = (uint32_t)(pr.x + or_last(ok[d], pp, last));
+                            jv[d] = bci[q];
+                            bv[d] = bval[q];
+                            av[d] = __hiloint2double(pr.w, pr.z);
                         }
-                        const int4 pr = par[lo];
-                        const int q = pr.x + (pp - po);
-                        const bool ok = pp < total;
-                        const MLS_G int32_t *pj = ok ? bci + q : (const MLS_G int32_t *)k_num_void;
-                        const MLS_G double *pv = ok ? bval + q : (const MLS_G double *)k_num_void;
-                        jv[d] = *pj;
-                        bv[d] = *pv;
-                        av[d] = __hiloint2double(pr.w, pr.z);
+                        eb += __popc(m);
                     }
+                    // (every load before the first use of a loaded column)
                     __builtin_amdgcn_sched_barrier(0);
-                    int posv[kNumDepth];
-                    tab.template lookup_n<kNumDepth>(logcap, jv, posv);
+                    uint32_t posv[kNumDepth];
+                    tab.template lookup_n<kNumDepth>(jv, ok, posv);
 #pragma unroll
                     for (int d = 0; d < kNumDepth; ++d) asm volatile("" ::"v"(bv[d]));
 #pragma unroll
-                    for (int d = 0; d < kNumDepth; ++d)
-                        if (posv[d] == -1) bad = true;
-                    // lanes of a step holding the same output add in lane (= term)
-                    // order: a lane's round is the number of lower lanes of its
-                    // group with the same position, and one wave's LDS adds take
-                    // effect in program order
-#pragma unroll
                     for (int d = 0; d < kNumDepth; ++d) {
-                        const int rank = group_rank<G>(posv[d], lane);
-                        const int rk = posv[d] >= 0 ? rank : -1;
+                        const bool hit = ok[d] && posv[d] <= tab.kMaxPos;
+                        bad |= ok[d] && !hit;
                         const double t = av[d] * bv[d];
+                        const int rk = hit ? rel[d] : -1;
                         for (int rr = 0;; ++rr) {
                             if (rk == rr) atomicAdd(acc + posv[d], t);
                             if (!__ballot(rk > rr)) break;
@@ -586,17 +582,18 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
             // issued together, then accumulated in step order
             auto batch = [&](int u0, const int2 (&qr)[kNumDepth]) {
                 int jv[kNumDepth];
+                bool ok[kNumDepth];
                 double bv[kNumDepth], av[kNumDepth];
-                // lanes past their row of B load the all-ones dummy instead
-                // (column -1: no lookup, no add), so no branch surrounds the loads
+                // lanes past their row of B load its last entry again (B's first for
+                // an empty row; neither looked up nor added), so no branch
+                // surrounds the loads
 #pragma unroll
                 for (int d = 0; d < kNumDepth; ++d) {
                     const int q = qr[d].x + lane;
-                    const bool ok = q < qr[d].y;
-                    const MLS_G int32_t *pj = ok ? bci + q : (const MLS_G int32_t *)k_num_void;
-                    const MLS_G double *pv = ok ? bval + q : (const MLS_G double *)k_num_void;
-                    jv[d] = *pj;
-                    bv[d] = *pv;
+                    ok[d] = q <= qr[d].y;
+                    const uint32_t qi = (uint32_t)or_last(ok[d], q, qr[d].y);
+                    jv[d] = bci[qi];
+                    bv[d] = bval[qi];
                 }
                 // keep the scheduler from hoisting uses of the loaded columns
                 // above the later loads (each would wait for a load)
@@ -607,20 +604,21 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
                 // order; within a step the lanes hold distinct columns of B_k, so
                 // no two lanes add to the same slot and every slot gets its terms
                 // in ascending k. The LDS fp64 add rounds like a plain add.
-                int posv[kNumDepth];
-                tab.template lookup_n<kNumDepth>(logcap, jv, posv);
+                uint32_t posv[kNumDepth];
+                tab.template lookup_n<kNumDepth>(jv, ok, posv);
                 // every loaded value is consumed on every path (an empty asm
                 // use), so no load is left pending into the next batch
 #pragma unroll
                 for (int d = 0; d < kNumDepth; ++d) asm volatile("" ::"v"(bv[d]));
 #pragma unroll
                 for (int d = 0; d < kNumDepth; ++d) {
-                    if (posv[d] >= 0) atomicAdd(acc + posv[d], av[d] * bv[d]);
-                    else if (posv[d] == -1) bad = true;
+                    const bool hit = ok[d] && posv[d] <= tab.kMaxPos;
+                    bad |= ok[d] && !hit;
+                    if (hit) atomicAdd(acc + posv[d], av[d] * bv[d]);
                 }
             };
             if constexpr (LONG)
-                bad |= flat_chunk<kNumDepth>(tab, logcap, acc, par, (uint32_t *)poff, lane, eq0, eq1, ea, bci, bval,
+                bad |= flat_chunk<kNumDepth>(tab, acc, par, flags, lane, eq0, eq1, ea, bci, bval,
                                              INT_MIN, INT_MAX);
             for (int u0 = 0; !LONG && u0 < n; u0 += kNumDepth) {
                 // The staged entries are read together (all G are written every
@@ -631,7 +629,7 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
                 for (int d = 0; d < kNumDepth; ++d) qr[d] = *(const int2 *)(par + u0 + d);
                 bool longs = false;   // a step whose row of B is longer than G
 #pragma unroll
-                for (int d = 0; d < kNumDepth; ++d) longs |= qr[d].y - qr[d].x > G;
+                for (int d = 0; d < kNumDepth; ++d) longs |= qr[d].y - qr[d].x >= G;
                 if (__ballot(longs)) {
                     // one step at a time, each through all of its row of B: its
                     // entries have distinct columns, so the order is kept
@@ -639,9 +637,9 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
                     for (int d = 0; d < kNumDepth; ++d) {
                         const int4 pr = par[u0 + d];
                         const double a = __hiloint2double(pr.w, pr.z);
-                        for (int q = pr.x + lane; q < pr.y; q += G) {
-                            const int pos = tab.lookup(logcap, bci[q]);
-                            if (pos >= 0) atomicAdd(acc + pos, a * bval[q]);
+                        for (int q = pr.x + lane; q <= pr.y; q += G) {
+                            const uint32_t pos = tab.lookup(bci[q]);
+                            if (pos <= tab.kMaxPos) atomicAdd(acc + pos, a * bval[q]);
                             else bad = true;
                         }
                     }
@@ -833,11 +831,9 @@ __device__ __forceinline__ void num_win_rows(const Batch &b, const Sched &sc, ch
             // a column outside the whole row still fails the lookup
             const int jlo = c0 == 0 ? INT_MIN : cci[cs];
             const int jhi = c0 + n == nc ? INT_MAX : cci[cs + n - 1];
-            int logcap = ilog2_ceil(2 * n);
-            if (logcap < 5) logcap = 5;
-            tab.clear(1 << logcap, lane, G);
+            tab.open(n, lane, G);
             nwave_sync();
-            insert_row<G>(tab, acc, logcap, cci, cval, cs, n, lane, accumulate);
+            insert_row<G>(tab, acc, cci, cval, cs, n, lane, accumulate);
             nwave_sync();
             bool bad = false;
             for (int pc = ps; pc < pe; pc += G) {
@@ -857,7 +853,7 @@ __device__ __forceinline__ void num_win_rows(const Batch &b, const Sched &sc, ch
                         }
                     }
                 }
-                bad |= flat_chunk<kWinDepth>(tab, logcap, acc, par, flags, lane, sq0, sq1, sa, bci, bval, jlo, jhi);
+                bad |= flat_chunk<kWinDepth>(tab, acc, par, flags, lane, sq0, sq1, sa, bci, bval, jlo, jhi);
             }
             if (bad) atomicOr(sc.err, kErrStructure);
             for (int e = lane; e < n; e += G) cval[cs + e] = acc[e];
