@@ -343,6 +343,23 @@ __device__ __forceinline__ uint32_t group_or8(uint32_t v)
     return v;
 }
 
+// OR over the group of G consecutive lanes
+template <int G>
+__device__ __forceinline__ uint32_t group_or(uint32_t v)
+{
+    static_assert(G == 8 || G == 16 || G == 32 || G == 64, "group size");
+    v = group_or8(v);
+    if constexpr (G >= 16) v |= (uint32_t)dpp_move<0x140>((int)v);   // row_mirror: the other 8 of 16
+    if constexpr (G >= 32) {
+        // the other row of 16 of a pair: each takes the odd row of one copy for the even row of the other
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        v = r[0] | r[1];
+    }
+    if constexpr (G == 64)
+        v = (uint32_t)__builtin_amdgcn_readlane((int)v, 0) | (uint32_t)__builtin_amdgcn_readlane((int)v, 32);
+    return v;
+}
+
 // inclusive prefix sum over the group; lane = position in the group
 template <int G>
 __device__ __forceinline__ int group_scan_incl(int v, int lane)

@@ -1,9 +1,9 @@
 // k_symbolic.hip -- symbolic phase (Sec. 2.1): for every row i of C the union
 // of the compressed column sets of the rows B_k, k in row i of A.
 //
-// LDS path: G lanes own one row; the lanes walk the entries of row i of A
-// (one k per lane) and OR every (set, mask) word of compressed B_k into an
-// open-addressing hash table in LDS keyed by set. Count pass: rownnz =
+// LDS path: G lanes own one row; they take G entries of row i of A at a time,
+// lay the (set, mask) words of their compressed B_k end to end and OR them, G
+// words per step, into an open-addressing hash table in LDS keyed by set. Count pass: rownnz =
 // sum of popcounts. Fill pass: the occupied (set, mask) pairs are compacted,
 // sorted by set in LDS (bitonic network), and their bits expand into
 // ascending columns at offsets from a scan of the popcounts.
@@ -22,10 +22,13 @@
 namespace mls {
 
 constexpr uint32_t kEmptyKey = 0xffffffffu;
-constexpr int kSymBatch = 6;   // words of one B_k row loaded before they are inserted (measured)
-// fewer where 32 or more lanes own a row (their count kernels run at 6 waves per SIMD)
-template <int G, bool FILL>
-constexpr int sym_batch() { return (!FILL && (G >= 32 || G <= 8)) ? 4 : kSymBatch; }
+// Words per lane loaded before they are inserted. More in a batch's count: its
+// kernels run at fewer waves per SIMD and its rows have few words, most of
+// which one tile then takes (20 Galerkin setups, 64- and 256-slot rows: 140 and
+// 67 us with 4, 128 and 47 with these; a single random product of 300k rows
+// loses, 141 -> 159 and 83 -> 91 us, and past 16 lanes registers spill).
+template <int G, bool FILL, bool MULTI>
+constexpr int sym_batch() { return !FILL && MULTI ? (G == 8 ? 8 : (G == 16 ? 6 : 4)) : 4; }
 
 __device__ __forceinline__ void wave_sync()
 {
@@ -43,15 +46,21 @@ constexpr int nw_for(int row_bytes, int rows_per_wave)
 
 // OR mask m into the slot of set s, given the word k read from its home slot
 // h (possibly before other lanes' inserts: an empty slot is claimed with a
-// compare-and-swap, whose result is the slot's current key)
+// compare-and-swap, whose result is the slot's current key). Every set has its
+// own odd step through the table: a row's word bound, which sizes the table,
+// is also its number of sets where no two rows of B share one, and a table
+// close to full then takes far fewer probes than with a step of one (256- and
+// 512-slot tables of a random product of 200k rows, 16 entries in a row of A
+// and 24 in one of B: 199 + 2062 -> 94 + 996 us).
 __device__ __forceinline__ void set_insert_at(uint32_t *key, uint32_t *msk, int logcap, uint32_t s, uint32_t m,
                                               uint32_t h, uint32_t k, uint32_t *err)
 {
     const uint32_t cmask = (1u << logcap) - 1u;
+    const uint32_t step = hslot(s * 5u, logcap) | 1u;
     for (uint32_t probe = 0; probe <= cmask; ++probe) {
         if (k == kEmptyKey) k = atomicCAS(key + h, kEmptyKey, s);
         if (k == kEmptyKey || k == s) { atomicOr(msk + h, m); return; }
-        h = (h + 1u) & cmask;
+        h = (h + step) & cmask;
         k = __hip_atomic_load(key + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     atomicOr(err, kErrTable);
@@ -134,6 +143,53 @@ __device__ __forceinline__ void sym_first_b(const Batch &b, const SymRow &m, Sym
     f.nw = *(in ? gp(P.bwc) + kl : zero);
 }
 
+// What bounds the count: instruction issue and the latency of the words' loads.
+// A lane per row of B (which this replaces) read a line per lane and load, and
+// its longest row of B held up the group; end to end, a load reads the words of
+// few rows. 27-point stencil square on 128^3, 256- and 512-slot rows: 1520 and
+// 414 us so, 1057 and 334 us now (with 32 instead of 16 lanes for the first,
+// and the table read back four slots a lane without loops over them).
+//
+// One tile of a chunk's word sequence, SB words per lane, loads in flight
+// together: lane l of the group takes words base + d * G + l. A bit per word
+// tells where an entry starts (OR-ed over the group without LDS), so a word's
+// entry is the count of the bits up to it. Words past the sequence (ok false)
+// load its last one.
+template <int G, int SB>
+__device__ __forceinline__ void word_tile(const MLS_G u32x2 *bw, int lane, int base, int total, int first,
+                                          bool nonempty, int qd, int &eb, u32x2 (&wd)[SB], bool (&ok)[SB])
+{
+    static_assert(SB * G % 32 == 0, "whole 32-bit words of start bits");
+    constexpr int SW = G < 32 ? 32 / G : 1;   // steps per word of start bits
+    constexpr int WS = G > 32 ? G / 32 : 1;   // words of start bits per step
+#pragma unroll
+    for (int h = 0; h < SB / SW; ++h) {
+        uint32_t m[WS];
+#pragma unroll
+        for (int x = 0; x < WS; ++x) {
+            const int at = first - base - 32 * (WS * h + x);
+            m[x] = group_or<G>(nonempty && (uint32_t)at < 32u ? 1u << at : 0u);
+        }
+#pragma unroll
+        for (int d4 = 0; d4 < SW; ++d4) {
+            const int d = SW * h + d4;
+            int en = eb;
+            if constexpr (WS == 1) {
+                en += __popc(m[0] & ((2u << (G * d4 + lane)) - 1u));
+            } else {
+                en += __popc(m[0] & (lane < 31 ? (2u << lane) - 1u : ~0u));
+                en += lane >= 32 ? __popc(m[1] & ((2u << (lane - 32)) - 1u)) : 0;
+            }
+            const int pp = base + d * G + lane;
+            ok[d] = pp < total;
+            const int q = __builtin_amdgcn_ds_bpermute(en * 4, qd) + min(pp, total - 1);
+            wd[d] = bw[q];
+        }
+#pragma unroll
+        for (int x = 0; x < WS; ++x) eb += __popc(m[x]);
+    }
+}
+
 // Waves per SIMD that the count kernel's LDS leaves resident (160 KB per CU,
 // 4 SIMDs), at most 6 for 64 lanes per row and 5 otherwise, one fewer for
 // batches (registers for the batched inserts and the row pipeline, without
@@ -154,7 +210,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(FILL ? 1 : 
 void k_sym_lds(Batch b, Sched sc, int bin)
 {
     constexpr int W = kWave / G;
-    constexpr int SB = sym_batch<G, FILL>();
+    constexpr int SB = sym_batch<G, FILL, MULTI>();
     constexpr int ROWB = FILL ? CAP * 12 : CAP * 8;
     constexpr int NW = nw_for(ROWB, W);
     constexpr int LIST = FILL ? CAP / 2 : 1;
@@ -218,15 +274,10 @@ void k_sym_lds(Batch b, Sched sc, int bin)
         int logcap = ilog2_ceil(FILL ? 2 * size : size);
         if (logcap < 5) logcap = 5;
         const int cap = 1 << logcap;
-        // table passes touch 4 slots per lane per access when the table is large enough
-        const bool vec = cap >= 4 * G;
-        if (vec) {
-            for (int h = 4 * lane; h < cap; h += 4 * G) {
-                *(uint4 *)(key + h) = make_uint4(kEmptyKey, kEmptyKey, kEmptyKey, kEmptyKey);
-                *(uint4 *)(msk + h) = make_uint4(0u, 0u, 0u, 0u);
-            }
-        } else {
-            for (int h = lane; h < cap; h += G) { key[h] = kEmptyKey; msk[h] = 0u; }
+        // (table passes touch 4 slots per lane per access)
+        for (int h = 4 * lane; h < cap; h += 4 * G) {
+            *(uint4 *)(key + h) = make_uint4(kEmptyKey, kEmptyKey, kEmptyKey, kEmptyKey);
+            *(uint4 *)(msk + h) = make_uint4(0u, 0u, 0u, 0u);
         }
         if (FILL && lane == 0) s_cnt[rs] = 0;
         wave_sync();
@@ -237,54 +288,64 @@ void k_sym_lds(Batch b, Sched sc, int bin)
             const MLS_G int32_t *__restrict__ bwc = gp(P.bwc);
             const int b_off = P.b_off, k_lo = P.k_lo, k_hi = P.k_hi;
             const int ps = m.ps, pe = m.pe;
-            for (int p = ps + lane; p < pe; p += G) {
-                int q0, nw;
-                if (p == ps + lane) {   // first chunk: B row located during the previous row
-                    q0 = f.q0 - b_off;
-                    nw = f.nw;
-                } else {
-                    const int k = aci[p];
-                    if (k < k_lo || k >= k_hi) continue;
-                    const int kl = k - k_lo;
-                    q0 = brp[kl] - b_off;
-                    nw = bwc[kl];
-                }
-                const MLS_G u32x2 *w = bw + q0;
-                // each lane starts at its own word of the row and wraps around:
-                // neighbouring rows of B share most sets, and lanes ORing the same
-                // set in one instruction would be serialized by the LDS
-                const int rot = nw > 0 ? lane % nw : 0;
-                for (int x = 0; x < nw; x += SB) {
+            // the B row of the lane's entry: the first chunk's was located during
+            // the previous row, a later one's is while the chunk before it runs
+            int q0 = f.q0 - b_off, nw = f.nw;
+            for (int pc = ps; pc < pe; pc += G) {
+                const int pn = pc + G + lane;
+                const int kn = *(pn < pe ? aci + pn : (const MLS_G int32_t *)k_ones4);
+                int q0n = 0, nwn = 0;
+                // the chunk's words in one sequence, entry after entry: the first
+                // word of an entry with words, less its place in the sequence, in
+                // lane r of the group for the r-th such entry
+                const int incl = group_scan_incl<G>(nw, lane);
+                const int total = group_total<G>(nw, incl);
+                const int first = incl - nw;
+                const unsigned long long lt = (1ull << lane) - 1ull;
+                const unsigned long long ne = __ballot(nw > 0) >> (slot * G);
+                const unsigned long long em = __ballot(nw <= 0) >> (slot * G);
+                constexpr unsigned long long kAll = G == kWave ? ~0ull : (1ull << (G & 63)) - 1ull;
+                const int rank = nw > 0 ? __popcll(ne & lt) : __popcll(ne & kAll) + __popcll(em & lt);
+                const int qd = __builtin_amdgcn_ds_permute((slot * G + rank) * 4, q0 - first);
+                int eb = slot * G - 1;   // lane of the last entry that started before the tile
+                for (int base = 0; base < total; base += SB * G) {
                     u32x2 wd[SB];
-#pragma unroll
-                    for (int d = 0; d < SB; ++d)
-                        if (x + d < nw) {
-                            int e = x + d + rot;
-                            if (e >= nw) e -= nw;
-                            wd[d] = w[e];
-                        }
+                    bool ok[SB];
+                    word_tile<G, SB>(bw, lane, base, total, first, nw > 0, qd, eb, wd, ok);
+                    if (base == 0) {
+                        const bool in = kn >= k_lo && kn < k_hi;
+                        q0n = *(in ? brp + (kn - k_lo) : (const MLS_G int32_t *)k_zeros4);
+                        nwn = *(in ? bwc + (kn - k_lo) : (const MLS_G int32_t *)k_zeros4);
+                    }
                     // the home slots of all the words are read before any is
                     // updated, so their LDS latencies overlap
                     uint32_t hv[SB], kv[SB];
 #pragma unroll
-                    for (int d = 0; d < SB; ++d) hv[d] = x + d < nw ? hslot(wd[d].x, logcap) : 0u;
-#pragma unroll
-                    for (int d = 0; d < SB; ++d)
+                    for (int d = 0; d < SB; ++d) {
+                        hv[d] = hslot(wd[d].x, logcap);
                         kv[d] = __hip_atomic_load(key + hv[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
                     // empty home slots claimed together, then the ORs; a word
                     // whose home slot holds another set probes on
 #pragma unroll
                     for (int d = 0; d < SB; ++d)
-                        if (x + d < nw && kv[d] == kEmptyKey) kv[d] = atomicCAS(key + hv[d], kEmptyKey, wd[d].x);
+                        if (ok[d] && kv[d] == kEmptyKey) kv[d] = atomicCAS(key + hv[d], kEmptyKey, wd[d].x);
 #pragma unroll
                     for (int d = 0; d < SB; ++d) {
-                        if (x + d >= nw) continue;
+                        if (!ok[d]) continue;
                         if (kv[d] == kEmptyKey || kv[d] == wd[d].x)
                             atomicOr(msk + hv[d], wd[d].y);
                         else
                             set_insert_at(key, msk, logcap, wd[d].x, wd[d].y, hv[d], kv[d], sc.err);
                     }
                 }
+                if (total <= 0) {
+                    const bool in = kn >= k_lo && kn < k_hi;
+                    q0n = *(in ? brp + (kn - k_lo) : (const MLS_G int32_t *)k_zeros4);
+                    nwn = *(in ? bwc + (kn - k_lo) : (const MLS_G int32_t *)k_zeros4);
+                }
+                q0 = q0n - b_off;
+                nw = nwn;
             }
         }
         wave_sync();
@@ -297,42 +358,30 @@ void k_sym_lds(Batch b, Sched sc, int bin)
             // one pass over the table: popcount of the union, and the occupied
             // (set, mask) words compacted in slot order into the row's scratch
             // slot for the fill pass (the first kScratchWords of them; a row
-            // with more is marked and rebuilt there); each lane owns 4 (vec)
-            // or 1 consecutive slots per step
-            const int per = vec ? 4 : 1;
+            // with more is marked and rebuilt there); each lane owns 4
+            // consecutive slots per step
             MLS_G u32x2 *dst = sc.scr ? (MLS_G u32x2 *)sc.scr + (int64_t)g * kScratchWords : nullptr;
             int c = 0, base = 0;
-            for (int h0 = 0; h0 < cap; h0 += per * G) {
-                const int h = h0 + per * lane;
-                uint32_t kk[4], mm[4];
-                int nl = 0;
+            for (int h0 = 0; h0 < cap; h0 += 4 * G) {
+                const int h = h0 + 4 * lane;
+                uint4 k4 = make_uint4(kEmptyKey, kEmptyKey, kEmptyKey, kEmptyKey), m4 = make_uint4(0u, 0u, 0u, 0u);
                 if (h < cap) {
-                    if (vec) {
-                        const uint4 k4 = *(const uint4 *)(key + h);
-                        const uint4 m4 = *(const uint4 *)(msk + h);
-                        kk[0] = k4.x; kk[1] = k4.y; kk[2] = k4.z; kk[3] = k4.w;
-                        mm[0] = m4.x; mm[1] = m4.y; mm[2] = m4.z; mm[3] = m4.w;
-                    } else {
-                        kk[0] = key[h]; mm[0] = msk[h];
-                    }
-                    for (int x = 0; x < per; ++x) {
-                        nl += kk[x] != kEmptyKey;
-                        c += __popc(mm[x]);
-                    }
+                    k4 = *(const uint4 *)(key + h);
+                    m4 = *(const uint4 *)(msk + h);
                 }
+                const int n0 = k4.x != kEmptyKey, n1 = k4.y != kEmptyKey;
+                const int n2 = k4.z != kEmptyKey, n3 = k4.w != kEmptyKey;
+                const int nl = n0 + n1 + n2 + n3;
+                c += __popc(m4.x) + __popc(m4.y) + __popc(m4.z) + __popc(m4.w);
                 // exclusive prefix of nl over the group
                 const int incl = group_scan_incl<G>(nl, lane);
                 const int tot = group_total<G>(nl, incl);
                 if (sc.scr && active && nl) {
-                    int w = base + incl - nl;
-                    for (int x = 0; x < per; ++x)
-                        if (kk[x] != kEmptyKey) {
-                            if (w < kScratchWords) {
-                                u32x2 v; v.x = kk[x]; v.y = mm[x];
-                                dst[w] = v;
-                            }
-                            ++w;
-                        }
+                    const int w0 = base + incl - nl, w1 = w0 + n0, w2 = w1 + n1, w3 = w2 + n2;
+                    if (n0 && w0 < kScratchWords) { u32x2 v; v.x = k4.x; v.y = m4.x; dst[w0] = v; }
+                    if (n1 && w1 < kScratchWords) { u32x2 v; v.x = k4.y; v.y = m4.y; dst[w1] = v; }
+                    if (n2 && w2 < kScratchWords) { u32x2 v; v.x = k4.z; v.y = m4.z; dst[w2] = v; }
+                    if (n3 && w3 < kScratchWords) { u32x2 v; v.x = k4.w; v.y = m4.w; dst[w3] = v; }
                 }
                 base += tot;
             }
@@ -821,10 +870,11 @@ static void launch_sym_all(const Batch &b, const Sched &sc, int G, hipStream_t s
     constexpr int C3 = FILL ? kFillCap[3] : kCountCap[3];
     constexpr int C4 = FILL ? kFillCap[4] : kCountCap[4];
     launch_sym_class<8, C0, FILL>(b, sc, 0, s);
-    // the 256-slot count class runs with half the lanes per row (measured
-    // faster on the 27-point stencil square, 1.88 -> 1.82 ms, and on the
-    // Galerkin products)
-    switch (!FILL && G >= 32 ? G / 2 : G) {
+    // Batches count the 256-slot class with half the lanes per row: finding a
+    // row's product is work per row, and their rows of B are short (20 Galerkin
+    // setups: 134 us with 16 lanes, 197 with 32). A single product does not
+    // (27-point stencil square on 128^3: 1222 us with 16 lanes, 1076 with 32).
+    switch (!FILL && b.nprob > 1 && G >= 32 ? G / 2 : G) {
     case 8: launch_sym_class<8, C1, FILL>(b, sc, 1, s); break;
     case 16: launch_sym_class<16, C1, FILL>(b, sc, 1, s); break;
     case 64: launch_sym_class<64, C1, FILL>(b, sc, 1, s); break;

@@ -218,3 +218,36 @@ def test_transpose_rows(lens, values):
     rp, ci, v = mls.transpose(D).numpy()
     assert np.array_equal(rp, T.row_ptr) and np.array_equal(ci, T.col_idx)
     assert (v is None) if not values else np.array_equal(v, T.values)
+
+
+# wide symbolic tables: rows of A around one and several chunks of a group's
+# lanes, rows of B from empty to several tiles of words, for every group size;
+# spread: one column per word and no set shared (tables at their word bound),
+# else full words shared by all rows of B; last: a word at either end of C
+@pytest.mark.parametrize("batch", [False, True])
+@pytest.mark.parametrize("spread", [False, True])
+@pytest.mark.parametrize("group", [8, 16, 32, 64])
+def test_symbolic_word_sequences(group, spread, batch):
+    ncols = 400000 if spread else 66000
+    lens_b = [0, 1, 3, 0, 0, 17, 64, 2, 0, 130, 1, 1, 5, 33, 0, 700] * 9
+    g = synth.rng(group)
+    lo = 0 if spread else 33000
+    rows = [lo + np.sort(g.choice(ncols - lo if spread else 2000, n, replace=False)) for n in lens_b]
+    rows[1] = np.array([0, ncols - 1])
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    B = synth.Csr(144, ncols, rp, np.concatenate(rows).astype(np.int32), g.standard_normal(int(rp[-1])))
+    A = rows_of([0, 1, 2, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 100, 128, 129, 144, 0] * 2, 144, 3)
+    mls.set_option(mls._abi.OPT_GROUP_SIZE, group)
+    try:
+        if not batch:
+            check(A, B)
+            return
+        A2 = rows_of([1, 0, 5, 30, 3], 144, 4)
+        dA, dB = [mls.DeviceCsr.from_host(M) for M in (A, A2, A)], [mls.DeviceCsr.from_host(B)] * 3
+        for M, C in zip((A, A2, A), mls.batch_numeric(dA, dB, mls.batch_symbolic(dA, dB))):
+            rp, ci, v = C.numpy()
+            R, _ = oracle.spgemm(M, B)
+            assert np.array_equal(rp, R.row_ptr) and np.array_equal(ci, R.col_idx)
+            assert np.array_equal(v, R.values)
+    finally:
+        mls.set_option(mls._abi.OPT_GROUP_SIZE, 0)
