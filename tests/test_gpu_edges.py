@@ -251,3 +251,24 @@ def test_symbolic_word_sequences(group, spread, batch):
             assert np.array_equal(v, R.values)
     finally:
         mls.set_option(mls._abi.OPT_GROUP_SIZE, 0)
+
+
+# rows of C of more words than the count keeps, their sets even, in one clump
+# with a word far away on either side (buckets past the counted limit), or in
+# buckets of exactly that limit and one more
+@pytest.mark.parametrize("clump", [32, 33, 65, 127, 128, 129, 500, 1000, 2000])
+@pytest.mark.parametrize("group", [16, 32, 64])
+def test_symbolic_fill_clumps(clump, group):
+    ncols, g = 8000000, synth.rng(clump)
+    rows = [32 * (100000 + np.arange(clump)), np.array([0]), np.array([ncols - 1]),
+            np.sort(g.choice(ncols, 70, replace=False)), 32 * 100000 + np.arange(200)]
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    B = synth.Csr(5, ncols, rp, np.concatenate(rows).astype(np.int32), g.standard_normal(int(rp[-1])))
+    lists = [[0], [0, 1], [0, 2], [0, 1, 2], [0, 3], [3], [1, 2, 3], [3, 4], [0, 1, 2, 3, 4]]
+    rpa = np.concatenate([[0], np.cumsum([len(r) for r in lists])]).astype(np.int32)
+    A = synth.Csr(len(lists), 5, rpa, np.concatenate(lists).astype(np.int32), g.standard_normal(int(rpa[-1])))
+    mls.set_option(mls._abi.OPT_GROUP_SIZE, group)
+    try:
+        check(A, B)
+    finally:
+        mls.set_option(mls._abi.OPT_GROUP_SIZE, 0)
