@@ -93,8 +93,8 @@ struct Sched {
     // and the fill pass expands them instead of recomputing the union
     uint2 *scr;             // nullptr when the workspace has no room for it
     int32_t *scnt;
-    // numeric / adjoint spill path: first window of each spill row (position
-    // in the spill bin), then the total; per-row scratch of na + 1 entries
+    // numeric / adjoint spill path: first task of each spill row (position in
+    // the spill bin), then the total; per-row scratch of na + 1 entries
     int32_t *wstart;
 };
 
@@ -417,6 +417,16 @@ __device__ __forceinline__ int bin_start(const int32_t *bin_count, int bin)
     for (int c = 0; c < bin; ++c) s += bin_count[c];
     return s;
 }
+
+// Windows of a spill row that a wave of the numeric phase takes in turn: where
+// one window ends in a row of B the next one starts (kept for kWinCarry
+// entries of A), which saves it a search; rows of more entries take one window
+// at a time, as theirs are long and have to spread over all waves. R-MAT 16
+// square, windows of rows of up to 64 and 448 entries: 4 and 2 in turn 2.78 ms,
+// 2 and 2 2.92 ms, 8 and 4 2.75 ms; R-MAT 15 with 12 entries per row: 1.61,
+// 1.69 and 1.65 ms.
+constexpr int kWinCarry = 448;
+__device__ __forceinline__ int win_block(int entries) { return entries <= kWave ? 4 : (entries <= kWinCarry ? 2 : 1); }
 
 // One launch for every class of the numeric (or adjoint) phase: which part
 // (class 0..4, or kNumClasses for the spill windows) this workgroup serves, -1

@@ -483,7 +483,8 @@ constexpr int kBwdWinDepth = 2;    // batches of 64 pairs whose B loads are issu
 // first pair, and the entries' dA parts
 constexpr int bwd_win_bytes(int CAP) { return CAP * 12 + kWave * 16 + (kWave + 1) * 4 + kWave * 8; }
 
-// Windows of the spill rows come from k_win_scan (same rule: ceil(nnz(W_i) / M)).
+// Tasks of the spill rows come from k_win_scan, one window (of M positions of
+// W_i) each.
 // A window's (entry, B position) pairs are flattened, 64 per step: each pair
 // adds a_ik W_ij into dB with a device atomic and W_ij b_kj into its entry's
 // dA part in LDS; the parts go to dA with one device atomic per entry.
@@ -677,7 +678,7 @@ __global__ __launch_bounds__(kWG) void k_bwd_all(Batch b, Sched sc, double *dA, 
 
 void launch_backward_small(const Batch &b, const Sched &sc, double *dA, double *dB, hipStream_t s)
 {
-    launch_bin_small(b, sc, kBwdWinCap / 2, s);
+    launch_bin_small(b, sc, kBwdWinCap / 2, 0, s);
     ProfScope ps("bwd_all", s);
     hipLaunchKernelGGL(k_bwd_all, dim3(small_rows_grid(b.na)), dim3(kWG), 0, s, b, sc, dA, dB);
 }
@@ -735,7 +736,7 @@ void launch_backward(const Batch &b, const Sched &sc, const double *wval, double
     constexpr int NWW = BwdWinShape<kBwdWinCap>::NW;
     static int win_grid = bwd_grid(k_bwd_win<kBwdWinCap>, NWW * kWave);
     ProfScope ps("bwd_spill", s);
-    hipLaunchKernelGGL(k_win_scan, dim3(1), dim3(kWG), 0, s, b, sc, kBwdWinCap / 2);
+    hipLaunchKernelGGL(k_win_scan, dim3(1), dim3(kWinScanWG), 0, s, b, sc, kBwdWinCap / 2, 0);
     hipLaunchKernelGGL(k_bwd_win<kBwdWinCap>, dim3(win_grid), dim3(NWW * kWave), 0, s, b, sc, dA, dB);
 }
 

@@ -691,67 +691,84 @@ __device__ __forceinline__ int lower_col(const MLS_G int32_t *cols, int lo, int 
     return lo;
 }
 
-// Windows of the spill rows: wstart[r] = first window of the r-th row of the
-// spill bin (ceil(nc / m) windows per row), wstart[n] = the total. One
-// workgroup.
-__global__ __launch_bounds__(kWG) void k_win_scan(Batch b, Sched sc, int m)
+// the same, expected near lo: steps that double from lo on, then a search
+// between the last two (their reads stay in the lines that the window's pairs
+// are read from)
+__device__ __forceinline__ int lower_col_near(const MLS_G int32_t *cols, int lo, int hi, int j)
 {
-    __shared__ int s_red[kWG / kWave];
-    __shared__ int s_carry;
+    int step = 8;
+    while (lo + step < hi && cols[lo + step] < j) {
+        lo += step + 1;
+        step *= 2;
+    }
+    return lower_col(cols, lo, min(lo + step, hi), j);
+}
+
+// Tasks of the spill rows, one workgroup: wstart[r] = first task of the r-th
+// row of the spill bin, wstart[n] = the total. A row has ceil(nc / m) windows,
+// one per task or (blocks) win_block of its entries. Latency bound (perm, then
+// the row's size and entries): four rows per thread in flight. 20400 spill
+// rows of the R-MAT 16 square: 87 us with 256 rows per step, 31 us.
+__global__ __launch_bounds__(kWinScanWG) void k_win_scan(Batch b, Sched sc, int m, int blocks)
+{
+    constexpr int NW = kWinScanWG / kWave, R = 4;
+    __shared__ int s_red[NW];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = gp(sc.bin_count)[kBinSpill];
     const int start = bin_start(sc.bin_count, kBinSpill);
     MLS_G int32_t *ws = gpw(sc.wstart);
-    if (threadIdx.x == 0) s_carry = 0;
-    __syncthreads();
-    for (int r0 = 0; r0 < n; r0 += kWG) {
-        const int r = r0 + (int)threadIdx.x;
-        int c = 0;
-        if (r < n) {
-            const int g = bin_row(sc.perm, sc.err, b.na, start + r);
-            if (g >= 0) c = (gp(sc.val)[g] + m - 1) / m;
-        }
-        int incl = c;
+    ProbCache pc;
+    int carry = 0;
+    for (int r0 = 0; r0 < n; r0 += kWinScanWG * R) {
+        const int r = r0 + (int)threadIdx.x * R;
+        int g[R], c[R], sum = 0;
 #pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int y = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += y;
+        for (int x = 0; x < R; ++x) g[x] = r + x < n ? bin_row(sc.perm, sc.err, b.na, start + r + x) : -1;
+#pragma unroll
+        for (int x = 0; x < R; ++x) {
+            c[x] = g[x] >= 0 ? (gp(sc.val)[g[x]] + m - 1) / m : 0;
+            if (blocks && g[x] >= 0) {
+                const int t = b.nprob == 1 ? 0 : find_prob_cached(b.abase, b.nprob, g[x], pc);
+                const MLS_G int32_t *arp = gp(get_prob(b, t).arp) + (g[x] - (b.nprob == 1 ? 0 : pc.lo));
+                const int per = win_block(arp[1] - arp[0]);
+                c[x] = (c[x] + per - 1) / per;
+            }
         }
+#pragma unroll
+        for (int x = 0; x < R; ++x) sum += c[x];
+        const int incl = group_scan_incl<kWave>(sum, lane);
         if (lane == kWave - 1) s_red[wave] = incl;
         __syncthreads();
-        int before = s_carry, all = 0;
+        int off = carry + incl - sum;
 #pragma unroll
-        for (int x = 0; x < kWG / kWave; ++x) {
-            before += x < wave ? s_red[x] : 0;
-            all += s_red[x];
+        for (int x = 0; x < NW; ++x) {
+            off += x < wave ? s_red[x] : 0;
+            carry += s_red[x];
         }
-        if (r < n) ws[r] = before + incl - c;
-        __syncthreads();
-        if (threadIdx.x == 0) s_carry += all;
+#pragma unroll
+        for (int x = 0; x < R; ++x) {
+            if (r + x < n) ws[r + x] = off;
+            off += c[x];
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) ws[n] = s_carry;
+    if (threadIdx.x == 0) ws[n] = carry;
 }
 
-// Consecutive windows a wave takes per counter grab: one, so that heavy rows'
-// windows spread over all waves, unless there are so many that the grabs (14
-// ns each, one address) would bound the launch. R-MAT squares of 16384 / 65536
-// rows, 40000 / 330000 windows: one each 638 us / 4.62 ms, two 792 us / 3.92 ms.
-constexpr int kWinMany = 131072;
-
-// LDS of one spill window: table, accumulators, staged entries and the start
-// bits of their pairs
+// LDS of one spill window: table, accumulators, staged entries, the start bits
+// of their pairs and where the window ended in the entries' rows of B
 constexpr int win_bytes(int CAP, bool PACK)
 {
-    return CAP * (PACK ? 4 : 8) + (CAP / 2) * 8 + kWave * 16 + kFlatWords * 4;
+    return CAP * (PACK ? 4 : 8) + (CAP / 2) * 8 + kWave * 16 + kFlatWords * 4 + kWinCarry * 2;
 }
 
 // A window streams the whole row of A, its rows of B narrowed to the window's
-// columns, as flattened pairs (flat_chunk). What bounds it: every window
-// stages the whole row of A, with two binary searches in B per entry and
-// window. R-MAT 16 square, whole numeric phase: 6.85 ms with a binary search
-// per pair for its entry and the adds ordered by an LDS minimum per output
-// position, 3.9 ms so.
+// columns, as flattened pairs (flat_chunk). What bounds it: the latency of the
+// dependent loads per window (a third of the issue slots are used, 4 waves per
+// SIMD by LDS): the task's row, the entries of A, their rows of B and the
+// searches in them, then the pairs. R-MAT 16 square, 306000 windows: 4.06 ms
+// with a window per task, 2.78 ms with win_block windows per task, where the
+// first column of a window needs no search and its last is searched from there.
 template <int CAP, bool PACK, int MAXLDS = 65536>
 struct WinShape {
     static constexpr int M = CAP / 2;   // positions of C per window
@@ -760,7 +777,8 @@ struct WinShape {
     static constexpr int LDS_PAR = NW * TW * 4;
     static constexpr int LDS_ACC = LDS_PAR + NW * kWave * 16;
     static constexpr int LDS_FLAGS = LDS_ACC + NW * M * 8;
-    static constexpr int LDS = LDS_FLAGS + NW * kFlatWords * 4;
+    static constexpr int LDS_OFF = LDS_FLAGS + NW * kFlatWords * 4;
+    static constexpr int LDS = LDS_OFF + NW * kWinCarry * 2;
 };
 
 // lds: WinShape::LDS bytes of this workgroup
@@ -787,45 +805,47 @@ __device__ __forceinline__ void num_win_rows(const Batch &b, const Sched &sc, ch
     const int n_bin = gp(sc.bin_count)[kBinSpill];
     const int start = bin_start(sc.bin_count, kBinSpill);
     const MLS_G int32_t *wst = gp(sc.wstart);
-    const int nwin = n_bin > 0 ? wst[n_bin] : 0;
-    // one counter over all windows: their work varies too much (a hub row's
+    const int ntasks = n_bin > 0 ? wst[n_bin] : 0;
+    uint16_t *off = (uint16_t *)(lds + Shape::LDS_OFF) + wave * kWinCarry;
+    // one counter over all tasks: their work varies too much (a hub row's
     // windows are consecutive and long) for per-XCD slabs
-    if (nwin == 0) return;
+    if (ntasks == 0) return;
     int32_t *cursor = sc.task_cursor + kBinSpill * kXcd;
-    const int block = nwin > kWinMany ? 2 : 1;
     ProbCache pcache;
     for (;;) {
-        int u0 = 0;
-        if (lane == 0) u0 = atomicAdd(cursor, 1) * block;
-        u0 = __builtin_amdgcn_readlane(u0, 0);
-        if (u0 >= nwin) break;
-        int r = find_last_wave(wst, n_bin, u0);   // the row holding window u0
-        const int u1 = min(u0 + block, nwin);
-        for (int u = u0; u < u1; ++u) {
-            while (wst[r + 1] <= u) ++r;
-            const int g = bin_row(sc.perm, sc.err, b.na, start + r);
-            if (g < 0) continue;
-            int t = 0, i = g;
-            if (MULTI) {
-                t = find_prob_cached(b.abase, b.nprob, g, pcache);
-                i = g - pcache.lo;
-            }
-            const Prob P = prob_of<MULTI>(b, t);
-            const MLS_G int32_t *__restrict__ aci = gp(P.aci);
-            const MLS_G double *__restrict__ aval = gp(P.aval);
-            const MLS_G int32_t *__restrict__ brp = gp(P.brp);
-            const MLS_G int32_t *__restrict__ bci = gp(P.bci);
-            const MLS_G double *__restrict__ bval = gp(P.bval);
-            const MLS_G int32_t *__restrict__ cci = gp(P.cci);
-            MLS_G double *__restrict__ cval = gpw(P.cval);
-            const int b_off = P.b_off, k_lo = P.k_lo, k_hi = P.k_hi;
-            const bool accumulate = P.accumulate != 0;
-            const int nc = gp(sc.val)[g];
-            const int c0 = (u - wst[r]) * M;   // first position of the window in the row
-            const int cs = gp(P.crp)[i] - P.c_off + c0;
+        int u = 0;
+        if (lane == 0) u = atomicAdd(cursor, 1);
+        u = __builtin_amdgcn_readlane(u, 0);
+        if (u >= ntasks) break;
+        const int r = find_last_wave(wst, n_bin, u);   // the row of task u
+        const int g = bin_row(sc.perm, sc.err, b.na, start + r);
+        if (g < 0) continue;
+        int t = 0, i = g;
+        if (MULTI) {
+            t = find_prob_cached(b.abase, b.nprob, g, pcache);
+            i = g - pcache.lo;
+        }
+        const Prob P = prob_of<MULTI>(b, t);
+        const MLS_G int32_t *__restrict__ aci = gp(P.aci);
+        const MLS_G double *__restrict__ aval = gp(P.aval);
+        const MLS_G int32_t *__restrict__ brp = gp(P.brp);
+        const MLS_G int32_t *__restrict__ bci = gp(P.bci);
+        const MLS_G double *__restrict__ bval = gp(P.bval);
+        const MLS_G int32_t *__restrict__ cci = gp(P.cci);
+        MLS_G double *__restrict__ cval = gpw(P.cval);
+        const int b_off = P.b_off, k_lo = P.k_lo, k_hi = P.k_hi;
+        const bool accumulate = P.accumulate != 0;
+        const int nc = gp(sc.val)[g];
+        const int cr = gp(P.crp)[i] - P.c_off;
+        const int ps = gp(P.arp)[i] - P.a_off, pe = gp(P.arp)[i + 1] - P.a_off;
+        const int per = win_block(pe - ps);
+        const bool narrow = nc > M;
+        bool bad = false;
+        // first positions of the task's windows in the row
+        const int cb = (u - wst[r]) * per * M, ce = min(nc, cb + per * M);
+        for (int c0 = cb; c0 < ce; c0 += M) {
+            const int cs = cr + c0;
             const int n = min(M, nc - c0);
-            const int ps = gp(P.arp)[i] - P.a_off, pe = gp(P.arp)[i + 1] - P.a_off;
-            const bool narrow = nc > M;
             // columns the window takes: from its first to its last column, open
             // below for the row's first window and above for its last, so that
             // a column outside the whole row still fails the lookup
@@ -835,10 +855,10 @@ __device__ __forceinline__ void num_win_rows(const Batch &b, const Sched &sc, ch
             nwave_sync();
             insert_row<G>(tab, acc, cci, cval, cs, n, lane, accumulate);
             nwave_sync();
-            bool bad = false;
             for (int pc = ps; pc < pe; pc += G) {
                 // stage the chunk: entry pc + lane's row of B, narrowed to the
-                // window's columns when it is long, and its pair count
+                // window's columns when it is long, and its pair count; the
+                // task's next window starts where this one ends
                 int sq0 = 0, sq1 = 0;
                 double sa = 0.0;
                 if (pc + lane < pe) {
@@ -848,17 +868,21 @@ __device__ __forceinline__ void num_win_rows(const Batch &b, const Sched &sc, ch
                         sq0 = brp[ka - k_lo] - b_off;
                         sq1 = brp[ka - k_lo + 1] - b_off;
                         if (narrow && sq1 - sq0 > 32) {
-                            if (jlo != INT_MIN) sq0 = lower_col(bci, sq0, sq1, jlo);
-                            if (jhi != INT_MAX) sq1 = lower_col(bci, sq0, sq1, jhi + 1);
+                            const int q = sq0, e = pc - ps + lane;
+                            const int at = c0 > cb ? (int)off[e] : 0xffff;
+                            if (at != 0xffff) sq0 += at;
+                            else if (jlo != INT_MIN) sq0 = lower_col(bci, sq0, sq1, jlo);
+                            if (jhi != INT_MAX) sq1 = lower_col_near(bci, sq0, sq1, jhi + 1);
+                            if (c0 + M < ce) off[e] = (uint16_t)min(sq1 - q, 0xffff);
                         }
                     }
                 }
                 bad |= flat_chunk<kWinDepth>(tab, acc, par, flags, lane, sq0, sq1, sa, bci, bval, jlo, jhi);
             }
-            if (bad) atomicOr(sc.err, kErrStructure);
             for (int e = lane; e < n; e += G) cval[cs + e] = acc[e];
             nwave_sync();
         }
+        if (bad) atomicOr(sc.err, kErrStructure);
     }
 }
 
@@ -954,7 +978,7 @@ static void launch_num_win(const Batch &b, const Sched &sc, hipStream_t s)
     static char name[64];
     if (!name[0]) snprintf(name, sizeof(name), "num_spill_C%d%s%s", CAP, PACK ? "_p" : "", MULTI ? "_b" : "");
     ProfScope ps(name, s);
-    hipLaunchKernelGGL(k_win_scan, dim3(1), dim3(kWG), 0, s, b, sc, CAP / 2);
+    hipLaunchKernelGGL(k_win_scan, dim3(1), dim3(kWinScanWG), 0, s, b, sc, CAP / 2, 1);
     hipLaunchKernelGGL((k_num_win<CAP, PACK, MULTI>), dim3(grid), dim3(NW * kWave), 0, s, b, sc);
 }
 
@@ -1007,7 +1031,7 @@ int small_rows_grid(int na)
 
 void launch_numeric_small(const Batch &b, const Sched &sc, hipStream_t s)
 {
-    launch_bin_small(b, sc, kNumWinCap / 2, s);
+    launch_bin_small(b, sc, kNumWinCap / 2, 1, s);
     ProfScope ps("num_all", s);
     hipLaunchKernelGGL(k_num_all, dim3(small_rows_grid(b.na)), dim3(kWG), 0, s, b, sc);
 }

@@ -632,7 +632,7 @@ __device__ __forceinline__ int small_class(int nc)
     return c == kNumClasses - 1 ? kBinSpill : c;
 }
 
-__global__ __launch_bounds__(kSmallWG) void k_bin_small(Batch b, Sched sc, int m)
+__global__ __launch_bounds__(kSmallWG) void k_bin_small(Batch b, Sched sc, int m, int blocks)
 {
     constexpr int NW = kSmallWG / kWave;
     __shared__ int s_cnt[NW][kNumBins];
@@ -688,7 +688,7 @@ __global__ __launch_bounds__(kSmallWG) void k_bin_small(Batch b, Sched sc, int m
     if (nspill == 0) return;
     __threadfence_block();
     __syncthreads();
-    // windows of the spill rows, as k_win_scan numbers them
+    // tasks of the spill rows, as k_win_scan numbers them
     MLS_G int32_t *ws = gpw(sc.wstart);
     int carry = 0;
     for (int q0 = 0; q0 < nspill; q0 += kSmallWG) {
@@ -697,6 +697,10 @@ __global__ __launch_bounds__(kSmallWG) void k_bin_small(Batch b, Sched sc, int m
         if (q < nspill) {
             const int i = __hip_atomic_load(sc.perm + spill0 + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             c = (crp[i + 1] - crp[i] + m - 1) / m;
+            if (blocks) {
+                const int per = win_block(gp(b.p0.arp)[i + 1] - gp(b.p0.arp)[i]);
+                c = (c + per - 1) / per;
+            }
         }
         const int incl = group_scan_incl<kWave>(c, lane);
         if (lane == kWave - 1) s_red[wave] = incl;
@@ -892,10 +896,10 @@ void launch_scatter(int na, const Sched &sc, hipStream_t s)
     hipLaunchKernelGGL(k_scatter, dim3(nb), dim3(kWG), 0, s, na, sc, nb, fold);
 }
 
-void launch_bin_small(const Batch &b, const Sched &sc, int m, hipStream_t s)
+void launch_bin_small(const Batch &b, const Sched &sc, int m, int blocks, hipStream_t s)
 {
     ProfScope ps("bin_small", s);
-    hipLaunchKernelGGL(k_bin_small, dim3(1), dim3(kSmallWG), 0, s, b, sc, m);
+    hipLaunchKernelGGL(k_bin_small, dim3(1), dim3(kSmallWG), 0, s, b, sc, m, blocks);
 }
 
 int scan_tiles(int n) { return nblk(n > 0 ? n : 1, kScanTile); }

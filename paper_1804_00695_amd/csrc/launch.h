@@ -45,9 +45,11 @@ void launch_rowptr_small(const Batch &b, const int32_t *val, int64_t *total, uin
 // Fill pass from the count pass's scratch words (rows with scnt >= 0).
 void launch_sym_expand(const Batch &b, const Sched &sc, hipStream_t s);
 
-// Windows of the spill bin's rows, ceil(size / m) per row: sc.wstart[r] = the
-// first window of the r-th spill row, sc.wstart[n] = their total (one workgroup).
-__global__ void k_win_scan(Batch b, Sched sc, int m);
+// Tasks of the spill bin's rows, ceil(size / m) windows per row, one per task
+// or (blocks) win_block of the row's entries: sc.wstart[r] = the first task of
+// the r-th spill row, sc.wstart[n] = their total (one workgroup).
+constexpr int kWinScanWG = 1024;
+__global__ void k_win_scan(Batch b, Sched sc, int m, int blocks);
 
 // Products of at most kSmallRows rows (one product, columns that fit the
 // packed tables): the numeric phase as two launches, one workgroup that bins
@@ -62,7 +64,7 @@ constexpr int kSmallRows = 20480;
 constexpr int kSmallGrid = 1280;   // five workgroups per CU
 bool small_rows_fit(const Batch &b);
 int small_rows_grid(int na);
-void launch_bin_small(const Batch &b, const Sched &sc, int m, hipStream_t s);
+void launch_bin_small(const Batch &b, const Sched &sc, int m, int blocks, hipStream_t s);
 void launch_numeric_small(const Batch &b, const Sched &sc, hipStream_t s);
 void launch_backward_small(const Batch &b, const Sched &sc, double *dA, double *dB, hipStream_t s);
 
