@@ -375,6 +375,90 @@ __device__ __forceinline__ int group_scan_incl(int v, int lane)
     return v;
 }
 
+// The elements of a group's entries (entry l of lane l: a run of a row of B)
+// laid end to end in one sequence. seq_compact: the first element of every
+// entry that has any, less its place in the sequence (q), in lane r of the
+// group for the r-th such entry.
+template <int G>
+__device__ __forceinline__ int seq_compact(bool nonempty, int q, int slot, int lane)
+{
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    constexpr unsigned long long kAll = G == kWave ? ~0ull : (1ull << (G & 63)) - 1ull;
+    const unsigned long long ne = (__ballot(nonempty) >> (slot * G)) & kAll;
+    const int rank = nonempty ? __popcll(ne & lt) : __popcll(ne) + __popcll(~ne & kAll & lt);
+    return __builtin_amdgcn_ds_permute((slot * G + rank) * 4, q);
+}
+
+// Starts in a wave's tile handed over by compares (2 to 3 instructions per step
+// each, no cross-lane chain) rather than by start bits: the rows set aside of the
+// dense-bitmap count and fill, R-MAT 16 square, 492 and 657 us, with bits
+// always 719 and 876 us; their short rows, 230 and 523, with compares always
+// 230 and 578 us.
+constexpr int kSeqFew = 6;
+
+// One tile of that sequence, SB elements per lane, loads in flight together:
+// lane l of the group takes elements base + d * G + l. A bit per element tells
+// where an entry starts (OR-ed over the group without LDS), so an element's
+// entry is the count of the bits up to it; eb is the lane (of the wave) of the
+// last entry that started before the tile. Elements past the sequence (ok
+// false) load its last one.
+template <int G, int SB, typename T>
+__device__ __forceinline__ void seq_tile(const MLS_G T *src, int lane, int base, int total, int first, bool nonempty,
+                                         int qd, int &eb, T (&v)[SB], bool (&ok)[SB])
+{
+    static_assert(SB * G % 32 == 0, "whole 32-bit words of start bits");
+    constexpr int SW = G < 32 ? 32 / G : 1;   // steps per word of start bits
+    constexpr int WS = G > 32 ? G / 32 : 1;   // words of start bits per step
+    if constexpr (G == kWave) {
+        unsigned long long st = __ballot(nonempty && (uint32_t)(first - base) < (uint32_t)(SB * kWave));
+        if (__popcll(st) <= kSeqFew) {
+            int qv[SB];
+            const int q = __builtin_amdgcn_readlane(qd, eb > 0 ? eb : 0);
+#pragma unroll
+            for (int d = 0; d < SB; ++d) qv[d] = q;
+            for (; st; st &= st - 1ull) {
+                const int f = __builtin_amdgcn_readlane(first, __ffsll((long long)st) - 1);
+                const int qn = __builtin_amdgcn_readlane(qd, ++eb);
+#pragma unroll
+                for (int d = 0; d < SB; ++d) qv[d] = base + d * kWave + lane >= f ? qn : qv[d];
+            }
+#pragma unroll
+            for (int d = 0; d < SB; ++d) {
+                const int pp = base + d * kWave + lane;
+                ok[d] = pp < total;
+                v[d] = src[qv[d] + min(pp, total - 1)];
+            }
+            return;
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < SB / SW; ++h) {
+        uint32_t m[WS];
+#pragma unroll
+        for (int x = 0; x < WS; ++x) {
+            const int at = first - base - 32 * (WS * h + x);
+            m[x] = group_or<G>(nonempty && (uint32_t)at < 32u ? 1u << at : 0u);
+        }
+#pragma unroll
+        for (int d4 = 0; d4 < SW; ++d4) {
+            const int d = SW * h + d4;
+            int en = eb;
+            if constexpr (WS == 1) {
+                en += __popc(m[0] & ((2u << (G * d4 + lane)) - 1u));
+            } else {
+                en += __popc(m[0] & (lane < 31 ? (2u << lane) - 1u : ~0u));
+                en += lane >= 32 ? __popc(m[1] & ((2u << (lane - 32)) - 1u)) : 0;
+            }
+            const int pp = base + d * G + lane;
+            ok[d] = pp < total;
+            const int q = __builtin_amdgcn_ds_bpermute(en * 4, qd) + min(pp, total - 1);
+            v[d] = src[q];
+        }
+#pragma unroll
+        for (int x = 0; x < WS; ++x) eb += __popc(m[x]);
+    }
+}
+
 // Row at position pos of perm, or -1 (and an error bit) when the position or
 // the row lies outside the batch -- which consistent bins never produce; the
 // kernels then skip the row instead of dereferencing a bad index.

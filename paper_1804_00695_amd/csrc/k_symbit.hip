@@ -7,7 +7,8 @@
 //
 // What bounds it: latency for small products (each launch of the binned path
 // costs its 2-20 us run or at least 4.7 us of stream time, and there are 14
-// in a count pass), LDS atomics for large ones. Whole products, binned path
+// in a count pass), the issue of the pairs' instructions and LDS atomics for
+// large ones. Whole products, binned path
 // against this one: 64x64 Laplacian square 273 / 143 us, 3000 x 2000 x 2500
 // random rows 372 / 144 us, R-MAT 16 square 12.9 / 9.6 ms.
 #include <cstdio>
@@ -21,8 +22,8 @@ namespace mls {
 constexpr int kBitTile = 4 * kWave;        // words a wave reads per step of a bitmap scan (16 bytes per lane)
 constexpr int kBitRowWork = 4096;          // multiply-adds of a row one wave takes; longer rows are set aside
 constexpr int kBitLongWG = 512;            // threads per set-aside row
-constexpr int kBitPieceLanes = 16;         // lanes per piece of a row of B in those
-constexpr int kBitPiece = 4 * kBitPieceLanes;   // columns per piece: four loads in flight per lane
+constexpr int kBitDepth = 4;               // columns of B in flight per lane
+constexpr int kBitStage = 32;              // words of a bitmap written out per step of a wave
 
 __device__ __forceinline__ void bit_sync()
 {
@@ -41,7 +42,9 @@ __device__ __forceinline__ void bit_set(uint32_t *bm, int words, int j, bool ok,
 
 // Rows of at most 64 entries of A and kBitRowWork multiply-adds, one per wave
 // (rows dealt round-robin: their sizes vary); the others go to the list in
-// sc.perm, counted in the spill bin's count.
+// sc.perm, counted in the spill bin's count. R-MAT 16 square, count and fill:
+// 297 and 525 us with a bisection per pair and no row in flight, 230 and 481
+// us; 60000 random rows of 64 outputs: 85 and 175 us, 59 and 128 us.
 template <bool FILL>
 __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
 {
@@ -61,18 +64,42 @@ __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
     bool bad = false;
     const int stride = (int)gridDim.x * (kWG / kWave);
     int g = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (kWG / kWave) + wave);
+    // three rows in flight: this one's rows of B are located, the next one's
+    // entries of A load during its pairs and their rows of B before its bitmap
+    // is read (and so before its stores, which a later load's wait would cover),
+    // the one after has its row pointers loading
+    int s1 = 0, e1 = 0, cs1 = 0, ce1 = 0, s2 = 0, e2 = 0, cs2 = 0, ce2 = 0;
+    int k1 = -1, q1 = 0, n1 = 0;
+    auto row_ptrs = [&](int at, int &s, int &e, int &cs, int &ce) {
+        const int r = min(at, b.na - 1);
+        s = arp[r];
+        e = arp[r + 1];
+        if (FILL) { cs = crp[r]; ce = crp[r + 1]; }
+    };
+    auto entries = [&](int s, int e) {
+        const int x = s - P.a_off + lane;
+        k1 = *(x < e - P.a_off ? aci + x : (const MLS_G int32_t *)k_ones4);
+    };
+    auto rows_b = [&]() {
+        const bool in = k1 >= P.k_lo && k1 < P.k_hi;
+        const MLS_G int32_t *pb = in ? brp + (k1 - P.k_lo) : (const MLS_G int32_t *)k_zeros4;
+        q1 = pb[0];
+        n1 = pb[1] - q1;
+        if (!in) n1 = 0;
+    };
+    if (g < b.na) {
+        row_ptrs(g, s1, e1, cs1, ce1);
+        row_ptrs(g + stride, s2, e2, cs2, ce2);
+        entries(s1, e1);
+        rows_b();
+    }
     for (; g < b.na; g += stride) {
-        const int s = arp[g] - P.a_off, e = arp[g + 1] - P.a_off;
-        const int cs = FILL ? crp[g] - P.c_off : 0, ce = FILL ? crp[g + 1] - P.c_off : 0;
-        const int len = e - s;
-        int q0 = 0, n = 0;
-        if (lane < len) {
-            const int k = aci[s + lane];
-            if (k >= P.k_lo && k < P.k_hi) {
-                q0 = brp[k - P.k_lo] - P.b_off;
-                n = brp[k - P.k_lo + 1] - P.b_off - q0;
-            }
-        }
+        const int len = e1 - s1;
+        const int cs = FILL ? cs1 - P.c_off : 0, ce = FILL ? ce1 - P.c_off : 0;
+        const int q0 = q1 - P.b_off, n = n1;
+        s1 = s2; e1 = e2; cs1 = cs2; ce1 = ce2;
+        entries(s1, e1);
+        row_ptrs(g + 2 * stride, s2, e2, cs2, ce2);
         const int incl = group_scan_incl<kWave>(n, lane);
         const int total = group_total<kWave>(n, incl);
         if (len > kWave || total > kBitRowWork) {
@@ -80,38 +107,21 @@ __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
                 const int at = atomicAdd(sc.bin_count + kBinSpill, 1);
                 if (at < b.na) gpw(sc.perm)[at] = g;
             }
+            rows_b();
             continue;
         }
-        // the (entry, position in B_k) pairs, flattened, four per lane in flight;
-        // a pair's entry is the last one that starts at or before it, found by
-        // bisecting the lanes' first pairs
+        // the (entry, position in B_k) pairs as one sequence, four per lane in flight
         const int first = incl - n;
-        int top = 1;
-        while (top < len) top <<= 1;
-        for (int base = 0; base < total; base += 4 * kWave) {
-            int jv[4];
-            bool ok[4];
+        const int qd = seq_compact<kWave>(n > 0, q0 - first, 0, lane);
+        int eb = -1;
+        for (int base = 0; base < total; base += kBitDepth * kWave) {
+            int jv[kBitDepth];
+            bool ok[kBitDepth];
+            seq_tile<kWave, kBitDepth>(bci, lane, base, total, first, n > 0, qd, eb, jv, ok);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int pp = base + u * kWave + lane;
-                int at = 0;
-                for (int step = top >> 1; step > 0; step >>= 1) {
-                    const int c = at + step;
-                    const int f = __shfl(first, c & 63, kWave);
-                    if (c < len && f <= pp) at = c;
-                }
-                const int qa = __shfl(q0, at, kWave), fa = __shfl(first, at, kWave);
-                ok[u] = pp < total;
-                jv[u] = *(ok[u] ? bci + (qa + (pp - fa)) : (const MLS_G int32_t *)k_zeros4);
-                if (base + (u + 1) * kWave >= total) {
-#pragma unroll
-                    for (int v = u + 1; v < 4; ++v) ok[v] = false;
-                    break;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) bit_set(bm, words, jv[u], ok[u], bad);
+            for (int u = 0; u < kBitDepth; ++u) bit_set(bm, words, jv[u], ok[u], bad);
         }
+        rows_b();
         bit_sync();
         // the bitmap in column order, cleared for the next row as it is read
         int c = 0, at = cs;
@@ -128,12 +138,12 @@ __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
                 const int in = group_scan_incl<kWave>(pc, lane);
                 int pos = at + in - pc;
                 at += group_total<kWave>(pc, in);
-                const uint32_t wv[4] = {w.x, w.y, w.z, w.w};
+                const uint64_t wv[2] = {((uint64_t)w.y << 32) | w.x, ((uint64_t)w.w << 32) | w.z};
 #pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    uint32_t m = wv[d];
+                for (int d = 0; d < 2; ++d) {
+                    uint64_t m = wv[d];
                     while (m) {
-                        if (pos < ce) cci[pos] = (x + d) * 32 + (__ffs(m) - 1);
+                        if (pos < ce) cci[pos] = x * 32 + d * 64 + (__ffsll((unsigned long long)m) - 1);
                         else bad = true;
                         ++pos;
                         m &= m - 1u;
@@ -152,14 +162,17 @@ __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
     if (bad) atomicOr(sc.err, kErrStructure);
 }
 
-// The rows set aside, a workgroup each: their rows of B are cut into pieces
-// of kBitPiece columns, dealt to groups of kBitPieceLanes lanes.
+// The rows set aside, a workgroup each: the columns of their rows of B as one
+// sequence, an equal share of it per wave. R-MAT 16 square, count and fill: 750
+// and 1011 us with 64-column pieces found by bisection and a thread writing a
+// run of columns, 492 and 657 us.
 template <bool FILL>
 __global__ __launch_bounds__(kBitLongWG) void k_bit_long(Batch b, Sched sc, int words)
 {
     constexpr int NT = kBitLongWG, NWV = NT / kWave;
     extern __shared__ __attribute__((aligned(16))) uint32_t s_bm[];   // words
-    __shared__ int s_first[NT + 1], s_q0[NT], s_n[NT], s_red[NWV];
+    __shared__ int s_first[NT + 1], s_qd[NT], s_red[NWV];
+    __shared__ uint16_t s_col[NWV][kBitStage * 32];
     __shared__ int s_row;
     const int n_rows = min(gp(sc.bin_count)[kBinSpill], b.na);
     if ((int)blockIdx.x >= n_rows) return;
@@ -203,51 +216,70 @@ __global__ __launch_bounds__(kBitLongWG) void k_bit_long(Batch b, Sched sc, int 
                 }
             }
             int all;
-            s_first[tid] = scan((n + kBitPiece - 1) / kBitPiece, all);
-            s_q0[tid] = q0;
-            s_n[tid] = n;
+            const int first = scan(n, all);
+            s_first[tid] = first;
+            s_qd[tid] = q0 - first;
             if (tid == 0) s_first[NT] = all;
             __syncthreads();
-            const int gl = tid % kBitPieceLanes;
-            for (int p = tid / kBitPieceLanes; p < all; p += NT / kBitPieceLanes) {
-                int lo = 0, hi = NT - 1;   // largest entry whose first piece is at or before p
+            // the chunk's columns as one sequence, an equal share of it per wave
+            const int share = ((all + NWV - 1) / NWV + kWave - 1) / kWave * kWave;
+            int base = wave * share;
+            const int end = min(all, base + share);
+            if (base < end) {
+                int lo = 0, hi = NT - 1;   // largest entry that starts at or before base
                 while (lo < hi) {
                     const int mid = (lo + hi + 1) >> 1;
-                    if (s_first[mid] <= p) lo = mid; else hi = mid - 1;
+                    if (s_first[mid] <= base) lo = mid; else hi = mid - 1;
                 }
-                const int off = (p - s_first[lo]) * kBitPiece + gl;
-                const MLS_G int32_t *src = bci + s_q0[lo];
-                const int nn = s_n[lo];
-                int jv[4];
+                for (int e0 = lo; base < end; e0 += kWave) {
+                    const int f = s_first[min(e0 + lane, NT)], fn = s_first[min(e0 + lane + 1, NT)];
+                    const int stop = min(end, s_first[min(e0 + kWave, NT)]);
+                    const bool any = fn > f;
+                    const int qd = seq_compact<kWave>(any, s_qd[min(e0 + lane, NT - 1)], 0, lane);
+                    int eb = __builtin_amdgcn_readlane(f, 0) < base ? 0 : -1;
+                    for (; base < stop; base += kBitDepth * kWave) {
+                        int jv[kBitDepth];
+                        bool ok[kBitDepth];
+                        seq_tile<kWave, kBitDepth>(bci, lane, base, stop, f, any, qd, eb, jv, ok);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int o = off + u * kBitPieceLanes;
-                    jv[u] = *(o < nn ? src + o : (const MLS_G int32_t *)k_zeros4);
+                        for (int u = 0; u < kBitDepth; ++u) bit_set(s_bm, words, jv[u], ok[u], bad);
+                    }
+                    base = stop;
                 }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) bit_set(s_bm, words, jv[u], off + u * kBitPieceLanes < nn, bad);
             }
             __syncthreads();
         }
         if (s >= e) __syncthreads();   // (the bitmap is cleared)
-        // thread tid owns a run of consecutive words
-        const int run = (words + NT - 1) / NT;
-        const int x0 = tid * run, x1 = min(x0 + run, words);
+        // wave w owns a run of consecutive words
+        const int run = (words / kBitStage + NWV - 1) / NWV * kBitStage;
+        const int x0 = wave * run, x1 = min(x0 + run, words);
         int c = 0;
-        for (int x = x0; x < x1; ++x) c += __popc(s_bm[x]);
+        for (int x = x0 + lane; x < x1; x += kWave) c += __popc(s_bm[x]);
         int all;
-        const int before = scan(c, all);
+        const int mine = scan(c, all);
         if constexpr (FILL) {
             const int cs = g >= 0 ? gp(P.crp)[g] - P.c_off : 0, ce = g >= 0 ? gp(P.crp)[g + 1] - P.c_off : 0;
-            int pos = cs + before;
-            for (int x = x0; x < x1; ++x) {
-                uint32_t m = s_bm[x];
+            int pos = cs + __builtin_amdgcn_readlane(mine, 0);
+            // kBitStage words per step, half a word per lane: the lanes place their
+            // columns in LDS, then the wave writes them out in order
+            for (int x = x0; x < x1; x += kBitStage) {
+                uint32_t m = (s_bm[x + (lane >> 1)] >> ((lane & 1) * 16)) & 0xffffu;
+                const int pc = __popc(m);
+                const int in = group_scan_incl<kWave>(pc, lane);
+                const int tot = group_total<kWave>(pc, in);
+                if (tot == 0) continue;
+                int at = in - pc;
                 while (m) {
-                    if (pos < ce) cci[pos] = x * 32 + (__ffs(m) - 1);
-                    else bad = true;
-                    ++pos;
+                    s_col[wave][at++] = (uint16_t)(lane * 16 + (__ffs(m) - 1));
                     m &= m - 1u;
                 }
+                bit_sync();
+                for (int o = lane; o < tot; o += kWave) {
+                    if (pos + o < ce) cci[pos + o] = x * 32 + (int)s_col[wave][o];
+                    else bad = true;
+                }
+                pos += tot;
+                bit_sync();
             }
             if (cs + all != ce) bad = true;
         } else if (tid == 0 && g >= 0) {
@@ -325,7 +357,7 @@ void launch_symbit(const Batch &b, const Sched &sc, int fill, hipStream_t s)
     per_cu = per_cu > 8 ? 8 : (per_cu < 1 ? 1 : per_cu);
     const int want = (b.na + nw - 1) / nw;
     const int grid = want < cus * per_cu ? want : cus * per_cu;
-    int long_per_cu = (int)(163840 / (wave_bytes + 16384));
+    int long_per_cu = (int)(163840 / (wave_bytes + (fill ? 21504 : 4608)));
     long_per_cu = long_per_cu > 4 ? 4 : (long_per_cu < 1 ? 1 : long_per_cu);
     const int long_grid = b.na < cus * long_per_cu ? b.na : cus * long_per_cu;
     ProfScope ps(fill ? "sym_bit_fill" : "sym_bit_count", s);

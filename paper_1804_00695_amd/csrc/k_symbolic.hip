@@ -151,46 +151,6 @@ __device__ __forceinline__ void sym_first_b(const Batch &b, const SymRow &m, Sym
 // few rows. 27-point stencil square on 128^3, 256- and 512-slot rows: 1520 and
 // 414 us so, 1057 and 334 us now (with 32 instead of 16 lanes for the first,
 // and the table read back four slots a lane without loops over them).
-//
-// One tile of a chunk's word sequence, SB words per lane, loads in flight
-// together: lane l of the group takes words base + d * G + l. A bit per word
-// tells where an entry starts (OR-ed over the group without LDS), so a word's
-// entry is the count of the bits up to it. Words past the sequence (ok false)
-// load its last one.
-template <int G, int SB>
-__device__ __forceinline__ void word_tile(const MLS_G u32x2 *bw, int lane, int base, int total, int first,
-                                          bool nonempty, int qd, int &eb, u32x2 (&wd)[SB], bool (&ok)[SB])
-{
-    static_assert(SB * G % 32 == 0, "whole 32-bit words of start bits");
-    constexpr int SW = G < 32 ? 32 / G : 1;   // steps per word of start bits
-    constexpr int WS = G > 32 ? G / 32 : 1;   // words of start bits per step
-#pragma unroll
-    for (int h = 0; h < SB / SW; ++h) {
-        uint32_t m[WS];
-#pragma unroll
-        for (int x = 0; x < WS; ++x) {
-            const int at = first - base - 32 * (WS * h + x);
-            m[x] = group_or<G>(nonempty && (uint32_t)at < 32u ? 1u << at : 0u);
-        }
-#pragma unroll
-        for (int d4 = 0; d4 < SW; ++d4) {
-            const int d = SW * h + d4;
-            int en = eb;
-            if constexpr (WS == 1) {
-                en += __popc(m[0] & ((2u << (G * d4 + lane)) - 1u));
-            } else {
-                en += __popc(m[0] & (lane < 31 ? (2u << lane) - 1u : ~0u));
-                en += lane >= 32 ? __popc(m[1] & ((2u << (lane - 32)) - 1u)) : 0;
-            }
-            const int pp = base + d * G + lane;
-            ok[d] = pp < total;
-            const int q = __builtin_amdgcn_ds_bpermute(en * 4, qd) + min(pp, total - 1);
-            wd[d] = bw[q];
-        }
-#pragma unroll
-        for (int x = 0; x < WS; ++x) eb += __popc(m[x]);
-    }
-}
 
 // Waves per SIMD that the count kernel's LDS leaves resident (160 KB per CU,
 // 4 SIMDs), at most 6 for 64 lanes per row and 5 otherwise, one fewer for
@@ -295,23 +255,16 @@ void k_sym_lds(Batch b, Sched sc, int bin)
                 const int pn = pc + G + lane;
                 const int kn = *(pn < pe ? aci + pn : (const MLS_G int32_t *)k_ones4);
                 int q0n = 0, nwn = 0;
-                // the chunk's words in one sequence, entry after entry: the first
-                // word of an entry with words, less its place in the sequence, in
-                // lane r of the group for the r-th such entry
+                // the chunk's words in one sequence, entry after entry
                 const int incl = group_scan_incl<G>(nw, lane);
                 const int total = group_total<G>(nw, incl);
                 const int first = incl - nw;
-                const unsigned long long lt = (1ull << lane) - 1ull;
-                const unsigned long long ne = __ballot(nw > 0) >> (slot * G);
-                const unsigned long long em = __ballot(nw <= 0) >> (slot * G);
-                constexpr unsigned long long kAll = G == kWave ? ~0ull : (1ull << (G & 63)) - 1ull;
-                const int rank = nw > 0 ? __popcll(ne & lt) : __popcll(ne & kAll) + __popcll(em & lt);
-                const int qd = __builtin_amdgcn_ds_permute((slot * G + rank) * 4, q0 - first);
+                const int qd = seq_compact<G>(nw > 0, q0 - first, slot, lane);
                 int eb = slot * G - 1;   // lane of the last entry that started before the tile
                 for (int base = 0; base < total; base += SB * G) {
                     u32x2 wd[SB];
                     bool ok[SB];
-                    word_tile<G, SB>(bw, lane, base, total, first, nw > 0, qd, eb, wd, ok);
+                    seq_tile<G, SB>(bw, lane, base, total, first, nw > 0, qd, eb, wd, ok);
                     if (base == 0) {
                         const bool in = kn >= k_lo && kn < k_hi;
                         q0n = *(in ? brp + (kn - k_lo) : (const MLS_G int32_t *)k_zeros4);

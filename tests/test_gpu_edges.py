@@ -272,3 +272,22 @@ def test_symbolic_fill_clumps(clump, group):
         check(A, B)
     finally:
         mls.set_option(mls._abi.OPT_GROUP_SIZE, 0)
+
+
+# dense-bitmap rows set aside: A rows around one and several chunks of a
+# workgroup, rows of B empty, of one column and of several tiles (no, few and
+# many entries starting in a tile; shares of a wave that end inside them)
+@pytest.mark.parametrize("mean_b", [0, 1, 5, 60, 300])
+@pytest.mark.parametrize("ncols", [300, 5000, 65536])
+def test_bitmap_long_rows(ncols, mean_b):
+    g = synth.rng(mean_b + ncols)
+    lens_b = [min(int(n), ncols) for n in g.poisson(mean_b, 1100)]
+    lens_b[3], lens_b[700] = min(ncols, 4500), 0
+    B = rows_of(lens_b, ncols, 1)
+    A = rows_of([1, 63, 64, 65, 511, 512, 513, 1024, 1025, 1100, 0, 3], 1100, 2)
+    check(A, B)
+
+
+@pytest.mark.parametrize("rows", [16383, 16384, 16385])
+def test_row_pointers_small(rows):
+    check(synth.poisson_csr(rows, 400, 2.0, seed=rows), synth.poisson_csr(400, 300, 3.0, seed=1))
