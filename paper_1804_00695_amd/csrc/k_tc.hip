@@ -6,8 +6,8 @@
 // step is a bitwise AND and a popcount.
 //
 // LDS path: G lanes own row i. The (set, mask) words of compressed row i go
-// into an LDS hash keyed by set; each lane takes entries k of row i and, for
-// every word (s, m) of compressed row k, adds popcount(m & mask_i[s]).
+// into an LDS hash keyed by set; for every word (s, m) of the compressed rows k
+// of row i, dealt to the lanes in sequence, popcount(m & mask_i[s]) is added.
 // Spill path: rows whose own word count exceeds the largest LDS class use a
 // dense bitmap of row i in global memory, one workgroup per row.
 #include <cstdio>
@@ -76,19 +76,16 @@ __device__ __forceinline__ void tc_row_entry(TcRow &r, const MLS_G int32_t *lrp,
     }
 }
 
-// LDS per row: the own-word table (key, mask) and the staged entries
-constexpr int tc_row_bytes(int CAP, int G) { return CAP * 8 + G * 12 + 4; }
+// LDS per row: the own-word table (key, mask)
+constexpr int tc_row_bytes(int CAP) { return CAP * 8; }
 
-template <int G, int CAP, int PW, int PP, int WPE>
+template <int G, int CAP, int SB, int WPE>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE))) void k_tc_lds(Batch b, Sched sc, int bin, int64_t *counts)
 {
     constexpr int W = kWave / G;
-    constexpr int NW = nw_tc(tc_row_bytes(CAP, G), W);
+    constexpr int NW = nw_tc(tc_row_bytes(CAP), W);
     __shared__ uint32_t s_key[NW * W * CAP];
     __shared__ uint32_t s_msk[NW * W * CAP];
-    __shared__ int s_poff[NW * W * (G + 1)];   // first piece of each staged entry, then the total
-    __shared__ int s_st[NW * W * G];           // word offset of each staged entry's row
-    __shared__ int s_nk[NW * W * G];           // its word count
 
     const int wave = threadIdx.x >> 6;
     if (wave >= NW) return;
@@ -97,9 +94,6 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE))) void
     const int rs = wave * W + slot;
     uint32_t *key = s_key + rs * CAP;
     uint32_t *msk = s_msk + rs * CAP;
-    int *poff = s_poff + rs * (G + 1);
-    int *pst = s_st + rs * G;
-    int *pnk = s_nk + rs * G;
 
     const Prob P = b.p0;
     const MLS_G int32_t *__restrict__ lrp = gp(P.arp);
@@ -120,7 +114,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE))) void
     // Rows are software-pipelined: while a row is counted, the next row's
     // index, sizes, first own word per lane and first staged entry per lane
     // (its row of comp(L): offset and word count) are loaded, so a row starts
-    // with only its pieces' words to fetch.
+    // with only its entries' words to fetch.
     int task = next_task_wave(sc.task_cursor + bin * kXcd, ntasks, it);
     int gi = (task >= 0 && task * W + slot < n_bin) ? bin_row(sc.perm, sc.err, b.na, start + task * W + slot) : -1;
     TcRow cur = tc_row(lrp, val, gi);
@@ -154,12 +148,13 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE))) void
         TcRow nxt = tc_row(lrp, val, gn);
         tc_sync();
         uint32_t cnt = 0;
-        // Entries k of row i are staged G at a time; the words of row k of
-        // comp(L) are cut into pieces of PW words, and the pieces of the
-        // chunk are dealt round-robin to the lanes, so that one long row of L
-        // does not hold up the group. A piece's entry is found by binary
-        // search over the staged first-piece offsets. Pieces hold PW words; PP
-        // pieces per lane are in flight at once.
+        // Entries k of row i are taken G at a time, one per lane, and the words of
+        // their rows of comp(L) laid end to end (seq_tile): G per step, so that one
+        // long row of L does not hold up the group and neighbouring lanes read
+        // neighbouring words; SB steps per lane are in flight at once, their home
+        // slots read together. (Pieces of 8 words per lane, found by a bisection in
+        // LDS: 169 and 199 us for the first two classes of the R-MAT
+        // 18 graph, 138 and 179 us so.)
         bool first = true;
         for (int pc = ps; pc < pe; pc += G) {   // ps == pe for inactive rows
             int st = 0, nk = 0;
@@ -174,53 +169,33 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WPE))) void
                 st = lrp[k];
                 nk = bwc[k];
             }
-            const int np = (nk + PW - 1) / PW;
-            int incl = group_scan_incl<G>(np, lane);
-            const int npieces = group_total<G>(np, incl);
-            poff[lane] = incl - np;
-            pst[lane] = st;
-            pnk[lane] = nk;
-            if (lane == 0) poff[G] = npieces;
-            tc_sync();
-            for (int q0 = lane; q0 < npieces; q0 += G * PP) {
-                // PP pieces per round: their entries are found, their words loaded,
-                // and only then looked up
-                u32x2 wd[PP][PW];
-                int len[PP];
+            const int incl = group_scan_incl<G>(nk, lane);
+            const int total = group_total<G>(nk, incl), q0 = incl - nk;
+            const int qd = seq_compact<G>(nk > 0, st - q0, slot, lane);
+            int eb = slot * G - 1;
+            for (int base = 0; base < total; base += SB * G) {
+                u32x2 wd[SB];
+                bool ok[SB];
+                seq_tile<G, SB>(bw, lane, base, total, q0, nk > 0, qd, eb, wd, ok);
+                uint32_t hv[SB], kv[SB], mv[SB];
 #pragma unroll
-                for (int r = 0; r < PP; ++r) {
-                    const int q = q0 + r * G;
-                    len[r] = 0;
-                    if (q < npieces) {
-                        int lo = 0, hi = G - 1;   // largest e with poff[e] <= q
-                        while (lo < hi) {
-                            const int mid = (lo + hi + 1) >> 1;
-                            if (poff[mid] <= q) lo = mid; else hi = mid - 1;
-                        }
-                        const int first = (q - poff[lo]) * PW;
-                        len[r] = min(PW, pnk[lo] - first);
-                        const MLS_G u32x2 *wk = bw + pst[lo] + first;
-#pragma unroll
-                        for (int d = 0; d < PW; ++d)
-                            if (d < len[r]) wd[r][d] = wk[d];
-                    }
+                for (int d = 0; d < SB; ++d) {
+                    hv[d] = hslot(wd[d].x, logcap);
+                    kv[d] = key[hv[d]];
+                    mv[d] = msk[hv[d]];
                 }
 #pragma unroll
-                for (int r = 0; r < PP; ++r) {
-#pragma unroll
-                    for (int d = 0; d < PW; ++d) {
-                        if (d >= len[r]) continue;
-                        uint32_t h = hslot(wd[r][d].x, logcap);
-                        for (uint32_t probe = 0; probe <= cmask; ++probe) {
-                            uint32_t kk = key[h];
-                            if (kk == wd[r][d].x) { cnt += __popc(wd[r][d].y & msk[h]); break; }
-                            if (kk == kTcEmpty) break;
-                            h = (h + 1u) & cmask;
-                        }
+                for (int d = 0; d < SB; ++d) {
+                    if (!ok[d]) continue;
+                    uint32_t h = hv[d], kk = kv[d], mm = mv[d];
+                    for (uint32_t probe = 0; kk != wd[d].x && kk != kTcEmpty && probe < cmask; ++probe) {
+                        h = (h + 1u) & cmask;
+                        kk = key[h];
+                        mm = msk[h];
                     }
+                    cnt += kk == wd[d].x ? (uint32_t)__popc(wd[d].y & mm) : 0u;
                 }
             }
-            tc_sync();
         }
         if (first) tc_row_words(nxt, lrp, lci, bw, lane);
         tc_row_entry(nxt, lrp, bwc);
@@ -338,16 +313,16 @@ static int tc_grid(K kernel, int threads)
     return cus * per_cu;
 }
 
-template <int G, int CAP, int P, int PP, int WPE = 8>
+template <int G, int CAP, int SB, int WPE>
 static void launch_tc_class(const Batch &b, const Sched &sc, int bin, int64_t *counts, hipStream_t s)
 {
     constexpr int W = kWave / G;
-    constexpr int NW = nw_tc(tc_row_bytes(CAP, G), W);
-    static int grid = tc_grid(k_tc_lds<G, CAP, P, PP, WPE>, NW * kWave);
+    constexpr int NW = nw_tc(tc_row_bytes(CAP), W);
+    static int grid = tc_grid(k_tc_lds<G, CAP, SB, WPE>, NW * kWave);
     static char name[64];
     if (!name[0]) snprintf(name, sizeof(name), "tc_lds_G%d_C%d", G, CAP);
     ProfScope ps(name, s);
-    hipLaunchKernelGGL((k_tc_lds<G, CAP, P, PP, WPE>), dim3(grid), dim3(NW * kWave), 0, s, b, sc, bin, counts);
+    hipLaunchKernelGGL((k_tc_lds<G, CAP, SB, WPE>), dim3(grid), dim3(NW * kWave), 0, s, b, sc, bin, counts);
 }
 
 void launch_tc_bin(const Batch &b, const Sched &sc, int force, hipStream_t s)
@@ -365,12 +340,16 @@ void launch_tc(const Batch &b, const Sched &sc, int64_t *counts, unsigned long l
                int spill_slots, int64_t spill_words, hipStream_t s)
 {
     if (b.na <= 0) return;
-    // lanes per row, words per piece, pieces in flight per lane: measured on R-MAT
-    launch_tc_class<32, kTcCap[0], 8, 1>(b, sc, 0, counts, s);
-    launch_tc_class<64, kTcCap[1], 8, 1>(b, sc, 1, counts, s);
-    launch_tc_class<64, kTcCap[2], 8, 1>(b, sc, 2, counts, s);
-    launch_tc_class<64, kTcCap[3], 8, 1>(b, sc, 3, counts, s);
-    launch_tc_class<64, kTcCap[4], 8, 1>(b, sc, 4, counts, s);
+    // Lanes per row, steps in flight per lane, waves per SIMD. R-MAT 18, 8 entries
+    // per row of the graph, first and second class: 32 lanes with 4 steps at 8
+    // (spills) and 7 waves 146 and 138 us, with 2 steps 158; 16 lanes 177, 64
+    // 265. 64 lanes with 2, 4, 8 steps 179, 184, 231; 4 steps at 7 and 6 waves
+    // 192 and 208.
+    launch_tc_class<32, kTcCap[0], 4, 7>(b, sc, 0, counts, s);
+    launch_tc_class<64, kTcCap[1], 2, 8>(b, sc, 1, counts, s);
+    launch_tc_class<64, kTcCap[2], 2, 8>(b, sc, 2, counts, s);
+    launch_tc_class<64, kTcCap[3], 2, 8>(b, sc, 3, counts, s);
+    launch_tc_class<64, kTcCap[4], 2, 8>(b, sc, 4, counts, s);
     {
         ProfScope ps("tc_spill", s);
         hipLaunchKernelGGL(k_tc_spill, dim3(spill_slots), dim3(kWG), 0, s, b, sc, counts, spill_bitmaps, spill_words);

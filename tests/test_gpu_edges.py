@@ -291,3 +291,25 @@ def test_bitmap_long_rows(ncols, mean_b):
 @pytest.mark.parametrize("rows", [16383, 16384, 16385])
 def test_row_pointers_small(rows):
     check(synth.poisson_csr(rows, 400, 2.0, seed=rows), synth.poisson_csr(400, 300, 3.0, seed=1))
+
+
+# triangle counting: rows of L around one and several chunks of a group's
+# lanes, the rows they name empty, of one word and of several tiles of words
+@pytest.mark.parametrize("cls", [-1, 1, 3])
+@pytest.mark.parametrize("deg", [1, 31, 32, 33, 63, 64, 65, 129, 200])
+def test_triangle_word_sequences(deg, cls):
+    n, g = 4000, synth.rng(deg)
+    rows = [np.sort(g.choice(i, min(i, [0, 1, 3, 40, 150][i % 5]), replace=False)) if i else np.zeros(0, np.int64)
+            for i in range(n - 5)]
+    rows += [np.sort(g.choice(n - 5, deg, replace=False)) for _ in range(5)]
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    ci = np.concatenate(rows).astype(np.int32)
+    mls.set_option(mls._abi.OPT_FORCE_CLASS, cls)
+    try:
+        counts, total = mls.triangle_count(mls.DeviceCsr.from_host(synth.Csr(n, n, rp, ci, None)))
+    finally:
+        mls.set_option(mls._abi.OPT_FORCE_CLASS, -1)
+    D = np.zeros((n, n), np.float32)
+    D[np.repeat(np.arange(n), np.diff(rp)), ci] = 1
+    ref = ((D @ D) * D).sum(axis=1).astype(np.int64)   # whole numbers below 2^24: exact in any order
+    assert np.array_equal(counts.cpu().numpy(), ref) and total == int(ref.sum())
