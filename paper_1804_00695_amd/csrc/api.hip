@@ -382,7 +382,8 @@ spgemm_status run_symbolic(BatchHost &bh, char *ws, int fill, int64_t *nnz_host,
         launch_symbit(bh.batch, sc, fill, s);
     } else {
         if (!reuse) launch_compress(bh.batch, bh.zb, sc.err, s);
-        launch_bin(bh.batch, fill ? kModeFill : kModeCount, sc, bin_force(), nullptr, s);
+        if (fill) launch_bin(bh.batch, kModeFill, sc, bin_force(), nullptr, s);
+        else launch_bin_count(bh.batch, bh.za, sc, bin_force(), s);
         if (fill) launch_sym_expand(bh.batch, sc, s);
         launch_symbolic(bh.batch, sc, fill, choose_group(bh.avg_a), s);
     }

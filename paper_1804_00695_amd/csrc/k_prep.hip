@@ -301,6 +301,7 @@ __global__ __launch_bounds__(kWG) void k_compress(Batch b, int rw, const uint32_
 //   kModeFill   : size = min(that bound, nnz(C_i))
 //   kModeNumeric: size = nnz(C_i)
 //   kModeWork   : size = sum over in-range k of nnz(B_k) (multiply-adds)
+//   kModeSized  : kModeCount with the sizes in val (k_work)
 // Threshold classes: kCountCap for count, kFillCap/2 for fill and numeric.
 
 // force < 0: natural class; force = kBinSpill: every non-empty row spills;
@@ -366,6 +367,72 @@ __device__ __forceinline__ void bin_place(int mode, const Sched &sc, int force, 
     atomicAdd(&cnt[c], 1);
 }
 
+// Sizes of the rows of A for the count pass (kModeCount) as an entry stream:
+// the word counts of the entries' rows of B, their running sum over a tile in
+// LDS, of which every row takes the difference at its ends. Words of a row past
+// kWorkMax, which no class holds, count as kWorkMax, so that a tile's sum fits.
+// Bound by the gathers. 27-point stencil 128^3, sizes and bins: 158 us with 4
+// lanes per row, 113 us; 20 Galerkin setups 104 and 52 us.
+constexpr int kWorkMax = 1 << 22;
+static_assert(kWorkMax > kCountCap[kNumClasses - 1] && (int64_t)kTileEntries * kWorkMax <= (1ll << 31), "tile sums");
+
+__global__ __launch_bounds__(kWG) void k_work(Batch b, int rw, Sched sc)
+{
+    if (bad_csr(sc.err)) return;
+    constexpr int NWV = kWG / kWave;
+    __shared__ uint32_t s_sum[NWV][kTileEntries];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t *sum = s_sum[wave];
+    const int g0 = ((int)blockIdx.x * NWV + wave) * rw, g = g0 + lane;
+    const bool row = lane < rw && g < b.na;
+    const int gw = g0 < b.na ? g0 : b.na - 1;
+    const int t = b.nprob == 1 ? 0 : find_prob_rows(b.abase, b.nprob, gw, row ? g : gw);
+    int s = 0, e = 0;
+    if (row) {
+        const Prob P = get_prob_any(b, t);
+        const int i = g - (b.nprob == 1 ? 0 : gp(b.abase)[t]);
+        s = gp(P.arp)[i] - P.a_off;
+        e = gp(P.arp)[i + 1] - P.a_off;
+    }
+    int64_t size = 0;
+    unsigned long long todo = __ballot(row);
+    while (todo) {
+        const int l0 = __ffsll((long long)todo) - 1;
+        const int t0 = __builtin_amdgcn_readlane(t, l0);
+        const bool mine = row && t == t0;
+        const unsigned long long seg = __ballot(mine);
+        const int l1 = 63 - __clzll((long long)seg);
+        todo &= ~seg;
+        const Prob P = get_prob_any(b, t0);
+        const MLS_G int32_t *aci = gp(P.aci), *bwc = gp(P.bwc);
+        const int k_lo = P.k_lo, k_hi = P.k_hi;
+        const int q0 = __builtin_amdgcn_readlane(s, l0), q1 = __builtin_amdgcn_readlane(e, l1);
+        for (int tb = q0; tb < q1; tb += kTileEntries) {
+            int cv[kTileSteps];
+#pragma unroll
+            for (int u = 0; u < kTileSteps; ++u) {
+                const int q = tb + u * kWave + lane;
+                cv[u] = *(q < q1 ? aci + q : (const MLS_G int32_t *)k_ones4);
+            }
+#pragma unroll
+            for (int u = 0; u < kTileSteps; ++u)
+                cv[u] = *(cv[u] >= k_lo && cv[u] < k_hi ? bwc + (cv[u] - k_lo) : (const MLS_G int32_t *)k_zeros4);
+            uint32_t before = 0;
+#pragma unroll
+            for (int u = 0; u < kTileSteps; ++u) {
+                const int incl = group_scan_incl<kWave>(min(cv[u], kWorkMax), lane);
+                sum[u * kWave + lane] = before + (uint32_t)incl;
+                before += (uint32_t)__builtin_amdgcn_readlane(incl, 63);
+            }
+            prep_sync();
+            const int lo = max(s, tb) - tb, hi = min(e, tb + kTileEntries) - tb;
+            if (mine && lo < hi) size += (int64_t)(sum[hi - 1] - (lo > 0 ? sum[lo - 1] : 0u));
+            prep_sync();
+        }
+    }
+    if (row) gpw(sc.val)[g] = size >= 0x7fffffffLL ? 0x7fffffff : (int32_t)size;
+}
+
 __global__ __launch_bounds__(kWG) void k_bin(Batch b, int mode, Sched sc, int force,
                                              unsigned long long *total)
 {
@@ -373,10 +440,12 @@ __global__ __launch_bounds__(kWG) void k_bin(Batch b, int mode, Sched sc, int fo
     __shared__ unsigned long long tsum;
     __shared__ int s_long[kBinMaxLong];
     __shared__ int s_nlong;
+    __shared__ uint16_t s_todo[kBinRowsPerWG];   // fill pass: rows without scratch words
+    __shared__ int s_ntodo;
     __shared__ int64_t s_red[kWG / kWave];
     if (bad_csr(sc.err)) return;
     if (threadIdx.x < kNumBins) cnt[threadIdx.x] = 0;
-    if (threadIdx.x == 0) { tsum = 0; s_nlong = 0; }
+    if (threadIdx.x == 0) { tsum = 0; s_nlong = 0; s_ntodo = 0; }
     __syncthreads();
     const int g0 = blockIdx.x * kBinRowsPerWG;
     ProbCache pc;
@@ -386,6 +455,18 @@ __global__ __launch_bounds__(kWG) void k_bin(Batch b, int mode, Sched sc, int fo
         pc.t = find_prob_wave(b.abase, b.nprob, g0);
         pc.lo = gp(b.abase)[pc.t];
         pc.hi = gp(b.abase)[pc.t + 1];
+    }
+    if (mode == kModeSized) {   // size left in val by k_work: one thread per row
+        for (int r = threadIdx.x; r < kBinRowsPerWG; r += kWG) {
+            const int g = g0 + r;
+            if (g >= b.na) break;
+            const int t = b.nprob == 1 ? 0 : find_prob_cached(b.abase, b.nprob, g, pc);
+            const Prob P = get_prob_any(b, t);
+            bin_place(kModeCount, sc, force, P, g, g - (b.nprob == 1 ? 0 : pc.lo), false, gp(sc.val)[g], cnt, &tsum);
+        }
+        __syncthreads();
+        bin_write_counts(sc, cnt);
+        return;
     }
     if (mode == kModeNumeric) {   // size = nnz(C_i): one thread per row
         for (int r = threadIdx.x; r < kBinRowsPerWG; r += kWG) {
@@ -404,50 +485,61 @@ __global__ __launch_bounds__(kWG) void k_bin(Batch b, int mode, Sched sc, int fo
         bin_write_counts(sc, cnt);
         return;
     }
+    // fill pass: rows whose words the count pass kept are expanded, not binned,
+    // a thread each (with 4 lanes each 28 us of 2.1M rows, 13 us)
+    const bool scratch = mode == kModeFill && sc.scr;
+    int nrows = min(kBinRowsPerWG, b.na - g0);
+    if (scratch) {
+        const int all = nrows;
+        for (int r = threadIdx.x; r < all; r += kWG) {
+            const int g = g0 + r;
+            if (gp(sc.scnt)[g] < 0) { s_todo[atomicAdd(&s_ntodo, 1)] = (uint16_t)r; continue; }
+            const int t = b.nprob == 1 ? 0 : find_prob_cached(b.abase, b.nprob, g, pc);
+            bin_place(mode, sc, force, get_prob_any(b, t), g, g - (b.nprob == 1 ? 0 : pc.lo), true, 0, cnt, &tsum);
+        }
+        __syncthreads();
+        nrows = s_ntodo;
+    }
     const int slot = threadIdx.x / kBinRG, lane = threadIdx.x % kBinRG;
-    for (int r = slot; r < kBinRowsPerWG; r += kBinSlots) {
+    for (int x = slot; x < nrows; x += kBinSlots) {   // uniform per row group
+        const int r = scratch ? (int)s_todo[x] : x;
         const int g = g0 + r;
-        if (g >= b.na) break;   // uniform per row group
         const int t = b.nprob == 1 ? 0 : find_prob_cached(b.abase, b.nprob, g, pc);
         const Prob P = get_prob_any(b, t);
         const int i = g - (b.nprob == 1 ? 0 : pc.lo);
-        // fill pass: rows whose words the count pass kept are expanded, not binned
-        const bool from_scratch = mode == kModeFill && sc.scr && gp(sc.scnt)[g] >= 0;
         int64_t size = 0;
-        if (!from_scratch) {
-            const int s = gp(P.arp)[i] - P.a_off, e = gp(P.arp)[i + 1] - P.a_off;
-            if (e - s > kBinLongRow) {
-                // long row: gathered below by the whole workgroup, unless the list is full
-                int at = 0;
-                if (lane == 0) {
-                    at = atomicAdd(&s_nlong, 1);
-                    if (at < kBinMaxLong) s_long[at] = r;
-                }
-                at = __shfl(at, 0, kBinRG);
-                if (at < kBinMaxLong) continue;
+        const int s = gp(P.arp)[i] - P.a_off, e = gp(P.arp)[i + 1] - P.a_off;
+        if (e - s > kBinLongRow) {
+            // long row: gathered below by the whole workgroup, unless the list is full
+            int at = 0;
+            if (lane == 0) {
+                at = atomicAdd(&s_nlong, 1);
+                if (at < kBinMaxLong) s_long[at] = r;
             }
-            const MLS_G int32_t *__restrict__ aci = gp(P.aci);
-            const MLS_G int32_t *__restrict__ brp = gp(P.brp);
-            const MLS_G int32_t *__restrict__ bwc = gp(P.bwc);
-            const int k_lo = P.k_lo, k_hi = P.k_hi;
-            // four entries per lane in flight: their columns, then the gathers
-            for (int p0 = s + lane; p0 < e; p0 += 4 * kBinRG) {
-                int kv[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int p = p0 + u * kBinRG;
-                    kv[u] = p < e ? aci[p] : -1;
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (kv[u] < k_lo || kv[u] >= k_hi) continue;
-                    const int kl = kv[u] - k_lo;
-                    size += mode == kModeWork ? (int64_t)(brp[kl + 1] - brp[kl]) : (int64_t)bwc[kl];
-                }
-            }
-            size = group_sum<kBinRG>(size);
+            at = __shfl(at, 0, kBinRG);
+            if (at < kBinMaxLong) continue;
         }
-        if (lane == 0) bin_place(mode, sc, force, P, g, i, from_scratch, size, cnt, &tsum);
+        const MLS_G int32_t *__restrict__ aci = gp(P.aci);
+        const MLS_G int32_t *__restrict__ brp = gp(P.brp);
+        const MLS_G int32_t *__restrict__ bwc = gp(P.bwc);
+        const int k_lo = P.k_lo, k_hi = P.k_hi;
+        // four entries per lane in flight: their columns, then the gathers
+        for (int p0 = s + lane; p0 < e; p0 += 4 * kBinRG) {
+            int kv[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int p = p0 + u * kBinRG;
+                kv[u] = p < e ? aci[p] : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (kv[u] < k_lo || kv[u] >= k_hi) continue;
+                const int kl = kv[u] - k_lo;
+                size += mode == kModeWork ? (int64_t)(brp[kl + 1] - brp[kl]) : (int64_t)bwc[kl];
+            }
+        }
+        size = group_sum<kBinRG>(size);
+        if (lane == 0) bin_place(mode, sc, force, P, g, i, false, size, cnt, &tsum);
     }
     __syncthreads();
     // the deferred long rows, one at a time across the workgroup
@@ -872,6 +964,17 @@ void launch_compress(const Batch &b, int64_t nnz_b, const uint32_t *err, hipStre
     ProfScope ps("compress", s);
     const int rw = stream_rows(b.nb, nnz_b);
     hipLaunchKernelGGL(k_compress, dim3(nblk(b.nb, kWG / kWave * rw)), dim3(kWG), 0, s, b, rw, err);
+}
+
+void launch_bin_count(const Batch &b, int64_t nnz_a, const Sched &sc, int force, hipStream_t s)
+{
+    if (b.na <= 0) return;
+    {
+        ProfScope ps("work", s);
+        const int rw = stream_rows(b.na, nnz_a);
+        hipLaunchKernelGGL(k_work, dim3(nblk(b.na, kWG / kWave * rw)), dim3(kWG), 0, s, b, rw, sc);
+    }
+    launch_bin(b, kModeSized, sc, force, nullptr, s);
 }
 
 void launch_bin(const Batch &b, int mode, const Sched &sc, int force, unsigned long long *total,

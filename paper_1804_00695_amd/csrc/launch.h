@@ -8,7 +8,7 @@
 
 namespace mls {
 
-enum { kModeCount = 0, kModeFill = 1, kModeNumeric = 2, kModeWork = 3 };
+enum { kModeCount = 0, kModeFill = 1, kModeNumeric = 2, kModeWork = 3, kModeSized = 4 };
 
 void launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 void launch_fill_f64(double *p, double v, int64_t n, hipStream_t s);
@@ -22,6 +22,8 @@ void launch_validate(const Batch &b, int which, const int64_t *nnz_tab, int64_t 
 // nnz_b: entries of all B. err (may be NULL): the error word of a CSR check
 // queued before.
 void launch_compress(const Batch &b, int64_t nnz_b, const uint32_t *err, hipStream_t s);
+// Binning of a count pass; nnz_a: entries of all A.
+void launch_bin_count(const Batch &b, int64_t nnz_a, const Sched &sc, int force, hipStream_t s);
 void launch_bin(const Batch &b, int mode, const Sched &sc, int force, unsigned long long *total,
                 hipStream_t s);
 int scan_tiles(int n);

@@ -313,3 +313,22 @@ def test_triangle_word_sequences(deg, cls):
     D[np.repeat(np.arange(n), np.diff(rp)), ci] = 1
     ref = ((D @ D) * D).sum(axis=1).astype(np.int64)   # whole numbers below 2^24: exact in any order
     assert np.array_equal(counts.cpu().numpy(), ref) and total == int(ref.sum())
+
+
+# sizes of wide rows as a stream: rows of A that end at, before and past a tile
+# of 512 entries, empty ones between them; alone and as one of a batch
+@pytest.mark.parametrize("batch", [False, True])
+@pytest.mark.parametrize("lens", [[512, 0, 512], [511, 1, 513, 0, 0, 3], [1500, 2, 0, 1024, 700],
+                                  [1] * 700, [8] * 129 + [0] * 70 + [40] * 13])
+def test_row_sizes_stream(lens, batch):
+    B = rows_of([n % 7 for n in range(1500)], 90000, 5)
+    A = rows_of(lens, 1500, 6)
+    check(A, B)
+    if batch:
+        A2 = rows_of([3, 0, 700], 1500, 7)
+        dA, dB = [mls.DeviceCsr.from_host(M) for M in (A2, A, A2)], [mls.DeviceCsr.from_host(B)] * 3
+        for M, C in zip((A2, A, A2), mls.batch_numeric(dA, dB, mls.batch_symbolic(dA, dB))):
+            rp, ci, v = C.numpy()
+            R, _ = oracle.spgemm(M, B)
+            assert np.array_equal(rp, R.row_ptr) and np.array_equal(ci, R.col_idx)
+            assert np.array_equal(v, R.values)
