@@ -322,9 +322,9 @@ struct NumShape {
     static constexpr int DEPTH = OCC <= 4 ? 2 * kNumDepth : kNumDepth;
     // waves per SIMD the kernel is compiled for: the LDS bound, capped so the
     // row pipeline's registers fit without spills (a reload from scratch
-    // would wait for every load issued before it): 7 waves (72 VGPRs), 5
-    // (96) for the flattened steps or for batches
-    static constexpr int OCC_CAP = (FLAT || MULTI) ? 5 : 7;
+    // would wait for every load issued before it): 7 waves (72 VGPRs), 6
+    // (80) where a wave owns a row, 5 (96) for the flattened steps or for batches
+    static constexpr int OCC_CAP = (FLAT || MULTI) ? 5 : (G == kWave ? 6 : 7);
     static constexpr int OCC_R = OCC < OCC_CAP ? OCC : OCC_CAP;
     // the next row's first chunk is prefetched where registers allow (at
     // most 5 waves per SIMD); otherwise a row loads its first chunk when it
@@ -352,7 +352,7 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
     // entries, chain a load, a lookup and a load per step. Numeric phase of the
     // restriction times the 81-point elasticity operator on 48^3 nodes: 1050 us
     // with one step at a time, 711 us in steps of one entry,
-    // 611 us flattened.
+    // 452 us flattened.
     constexpr bool LONG = G == kWave && !FLAT;
     static_assert(FLAT || G % kNumDepth == 0, "the staged entries are read kNumDepth at a time");
     constexpr int W = kWave / G;
@@ -368,9 +368,13 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
     const int lw = threadIdx.x & 63;
     const int slot = lw / G, lane = lw % G;
     const int rs = wave * W + slot;
-    // 2-slot buckets where 32 or more lanes own a row (measured on the
-    // 27-point stencil square), 4-slot ones for narrower groups
-    PosTab<CAP, PACK, (G >= 32 ? 2 : 4)> tab{s_tab + rs * TW};
+    // 2-slot buckets where 32 lanes own a row, else 4-slot ones. A 4-slot bucket
+    // costs more instructions, a 2-slot one more probes past it, in which one
+    // lane holds up the others: restriction times the 81-point elasticity
+    // operator, 64 lanes and tables 43 % full, 559 us with 2 and 452 with 4
+    // slots; 27-point stencil square on 128^3, 32 lanes, 2377 with 2 and 2632
+    // with 4.
+    PosTab<CAP, PACK, (G == 32 ? 2 : 4)> tab{s_tab + rs * TW};
     double *acc = s_acc + rs * (CAP / 2);
     int4 *par = s_par + rs * G;
     uint32_t *flags = s_tab + NW * W * TW + rs * XW;   // LONG only
