@@ -90,6 +90,7 @@ struct SymMemo {
     const void *ws = nullptr;
     std::vector<uint64_t> key;
     bool valid = false;
+    unsigned seen = 0;   // sizes of rows among the kept words (bits kSeen*)
 } g_memo;
 }  // namespace
 
@@ -112,6 +113,7 @@ Sched make_sched(char *ws, const Layout &L)
     sc.perm = (int32_t *)(ws + L.perm);
     sc.scr = L.has_scratch ? (uint2 *)(ws + L.scr) : nullptr;
     sc.scnt = L.has_scratch ? (int32_t *)(ws + L.scnt) : nullptr;
+    sc.seen = (uint32_t *)(ws + L.hdr + kHdrSeen);
     sc.wstart = (int32_t *)(ws + L.prefix);   // the row-pointer scan's array, idle outside the symbolic phase
     return sc;
 }
@@ -339,7 +341,7 @@ static void queue_validate(const BatchHost &bh, char *ws, uint32_t *err, hipStre
 
 // Waits for a count pass: error word and nnz of every product, in one copy
 // (the header, which begins with the error word, and the totals behind it).
-static spgemm_status read_counts(BatchHost &bh, char *ws, int64_t *nnz_host, hipStream_t s)
+static spgemm_status read_counts(BatchHost &bh, char *ws, int64_t *nnz_host, unsigned &seen, hipStream_t s)
 {
     const Layout &L = bh.layout;
     const int np = bh.batch.nprob;
@@ -350,6 +352,10 @@ static spgemm_status read_counts(BatchHost &bh, char *ws, int64_t *nnz_host, hip
     if (st != SPGEMM_OK) return st;
     uint32_t err = 0;
     std::memcpy(&err, got.data(), sizeof(err));
+    uint32_t sizes[kNumSeen];
+    std::memcpy(sizes, (const char *)got.data() + kHdrSeen, sizeof(sizes));
+    seen = 0;
+    for (int x = 0; x < kNumSeen; ++x) seen |= sizes[x] ? 1u << x : 0u;
     if (err & kErrBadCsr) return err_status(err);
     int64_t *tot = got.data() + words;
     // products with no rows never write their total
@@ -366,9 +372,11 @@ spgemm_status run_symbolic(BatchHost &bh, char *ws, int fill, int64_t *nnz_host,
 {
     Layout &L = bh.layout;
     bool reuse = false;
+    unsigned seen = 0;
     {
         std::lock_guard<std::mutex> lk(g_memo_mu);
         reuse = fill && g_memo.valid && g_memo.ws == ws && g_memo.key == bh.key;
+        seen = g_memo.seen;
         if (g_memo.ws == ws) g_memo.valid = false;
     }
     // few columns: dense bitmaps in place of compression, binning and hash
@@ -382,17 +390,22 @@ spgemm_status run_symbolic(BatchHost &bh, char *ws, int fill, int64_t *nnz_host,
         launch_symbit(bh.batch, sc, fill, s);
     } else {
         if (!reuse) launch_compress(bh.batch, bh.zb, sc.err, s);
-        if (fill) launch_bin(bh.batch, kModeFill, sc, bin_force(), nullptr, s);
-        else launch_bin_count(bh.batch, bh.za, sc, bin_force(), s);
-        if (fill) launch_sym_expand(bh.batch, sc, s);
-        launch_symbolic(bh.batch, sc, fill, choose_group(bh.avg_a), s);
+        // the fill of a count whose words were all kept has nothing to bin and
+        // no row to recompute, and only the sizes of rows seen to expand (an
+        // empty launch costs at least 4.5 us of stream time; 20 Galerkin setups
+        // 1.75 -> 1.68 ms)
+        const bool again = !fill || !reuse || !sc.scr || (seen >> kSeenMore & 1u);
+        if (!fill) launch_bin_count(bh.batch, bh.za, sc, bin_force(), s);
+        else if (again) launch_bin(bh.batch, kModeFill, sc, bin_force(), nullptr, s);
+        if (fill) launch_sym_expand(bh.batch, sc, seen, s);
+        if (again) launch_symbolic(bh.batch, sc, fill, choose_group(bh.avg_a), s);
     }
     spgemm_status st = check_launch();
     if (st != SPGEMM_OK) return st;
     if (fill) {
         if (reuse) {   // the words stay valid for another fill pass on the same operands
             std::lock_guard<std::mutex> lk(g_memo_mu);
-            g_memo.ws = ws; g_memo.key = bh.key; g_memo.valid = true;
+            g_memo.ws = ws; g_memo.key = bh.key; g_memo.valid = true; g_memo.seen = seen;
         }
         return SPGEMM_OK;
     }
@@ -407,10 +420,10 @@ spgemm_status run_symbolic(BatchHost &bh, char *ws, int fill, int64_t *nnz_host,
     }
     st = check_launch();
     if (st != SPGEMM_OK) return st;
-    st = read_counts(bh, ws, nnz_host, s);
+    st = read_counts(bh, ws, nnz_host, seen, s);
     if (st == SPGEMM_OK && !bits) {
         std::lock_guard<std::mutex> lk(g_memo_mu);
-        g_memo.ws = ws; g_memo.key = bh.key; g_memo.valid = true;
+        g_memo.ws = ws; g_memo.key = bh.key; g_memo.valid = true; g_memo.seen = seen;
     }
     return st;
 }

@@ -78,6 +78,8 @@ struct Batch {
 };
 
 // Per-phase device state inside the workspace.
+enum { kSeenSmall = 0, kSeenMid = 1, kSeenLarge = 2, kSeenMore = 3, kNumSeen = 4 };   // up to 16, 32, 64 words, more
+
 struct Sched {
     uint32_t *err;
     int32_t *bin_count;     // [kNumBins]
@@ -93,6 +95,9 @@ struct Sched {
     // and the fill pass expands them instead of recomputing the union
     uint2 *scr;             // nullptr when the workspace has no room for it
     int32_t *scnt;
+    // set by the count pass where any row has that many words (kSeen*): which
+    // launches the fill pass needs, read back with the counts
+    uint32_t *seen;
     // numeric / adjoint spill path: first task of each spill row (position in
     // the spill bin), then the total; per-row scratch of na + 1 entries
     int32_t *wstart;

@@ -32,6 +32,7 @@ constexpr size_t kHdrErr = 0;
 constexpr size_t kHdrBinCount = 64;
 constexpr size_t kHdrTaskCursor = 192;   // kNumBins * kXcd int32 (up to 224 bytes)
 constexpr size_t kHdrTotal = 512;        // uint64
+constexpr size_t kHdrSeen = 576;         // kNumSeen uint32 (Sched::seen)
 
 struct Layout {
     size_t hdr = 0, totals = 0, nnz_tab = 0, probs = 0, abase = 0, bbase = 0;

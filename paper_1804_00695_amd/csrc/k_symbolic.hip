@@ -30,6 +30,8 @@ constexpr uint32_t kEmptyKey = 0xffffffffu;
 template <int G, bool FILL, bool MULTI>
 constexpr int sym_batch() { return !FILL && MULTI ? (G == 8 ? 8 : (G == 16 ? 6 : 4)) : 4; }
 
+constexpr int kExpandSmall = 16;   // rows with at most this many words take the 16-lane kernel
+constexpr int kExpandMid = 32;     // rows with at most this many words take the 32-lane kernel
 constexpr int kBucketMax = 32;   // words of a fill bucket ranked by counting the smaller ones
 
 __device__ __forceinline__ void wave_sync()
@@ -220,6 +222,7 @@ void k_sym_lds(Batch b, Sched sc, int bin)
     // no prologue load is left pending into the loop (the wait counts at its
     // top are computed over both ways into it)
     asm volatile("" ::"v"(f.q0), "v"(f.nw), "v"(g_n), "v"(mr.size), "v"(mr.ps), "v"(mr.pe));
+    uint32_t seen = 0;   // sizes of the rows counted (bits kSeen*)
     while (task >= 0) {
         const int task_x = task_n >= 0 ? next_task_wave(sc.task_cursor + bin * kXcd, ntasks, it) : -1;
         const bool h_x = task_x >= 0 && task_x * W + slot < n_bin;
@@ -340,6 +343,9 @@ void k_sym_lds(Batch b, Sched sc, int bin)
             }
             c = group_sum<G>(c);
             sym_first_b<MULTI>(b, mn, f);
+            if (active && base > 0) seen |= base > kScratchWords ? 1u << kSeenMore :
+                                            (base > kExpandMid ? 1u << kSeenLarge :
+                                             (base > kExpandSmall ? 1u << kSeenMid : 1u << kSeenSmall));
             if (active && lane == 0) {
                 val[g] = c;
                 if (sc.scr) gpw(sc.scnt)[g] = base <= kScratchWords ? base : -1;
@@ -480,6 +486,12 @@ void k_sym_lds(Batch b, Sched sc, int bin)
         g_n = g_x;
         h_n = h_x;
         mr = mr_n;
+    }
+    if (!FILL && sc.scr) {
+        static_assert(kSeenSmall == 0 && kSeenMid == 1 && kSeenLarge == 2 && kSeenMore == 3, "bits of seen");
+#pragma unroll
+        for (int x = 0; x < kNumSeen; ++x)
+            if (__ballot(seen >> x & 1u) && lw == 0) gpw(sc.seen)[x] = 1u;
     }
 }
 
@@ -649,7 +661,10 @@ __global__ __launch_bounds__(kWG) void k_sym_spill(Batch b, Sched sc, int fill, 
         if (bad) atomicOr(sc.err, kErrStructure);
         if (!fill && tid == 0) {
             gpw(sc.val)[g] = total;
-            if (sc.scr) gpw(sc.scnt)[g] = -1;   // recomputed by the fill pass
+            if (sc.scr) {   // recomputed by the fill pass
+                gpw(sc.scnt)[g] = -1;
+                gpw(sc.seen)[kSeenMore] = 1u;
+            }
         }
         if (fill && tid == 0 && cs + total != ce) atomicOr(sc.err, kErrStructure);
     }
@@ -661,8 +676,6 @@ __global__ __launch_bounds__(kWG) void k_sym_spill(Batch b, Sched sc, int fill, 
 // (no LDS); its bits then expand into ascending columns. Rows without scratch
 // words (scnt < 0) are left to the recomputing fill kernels.
 static_assert(kScratchWords == kWave, "one scratch word per lane");
-constexpr int kExpandSmall = 16;   // rows with at most this many words take the 16-lane kernel
-constexpr int kExpandMid = 32;     // rows with at most this many words take the 32-lane kernel
 constexpr int kExpandStage = 256;  // columns of a row staged in LDS before the ordered write-out
 
 struct ExpandRow {
@@ -846,16 +859,19 @@ __global__ __launch_bounds__(kWG) void k_sym_expand_small(Batch b, Sched sc)
     }
 }
 
-void launch_sym_expand(const Batch &b, const Sched &sc, hipStream_t s)
+void launch_sym_expand(const Batch &b, const Sched &sc, unsigned seen, hipStream_t s)
 {
     if (b.na <= 0 || !sc.scr) return;
     static int cus = device_cu_count();
     {
         // rows of 1-16 words take 16 lanes each (4 rows per step), rows of 17-32 words 32 lanes
         ProfScope ps("sym_expand_small", s);
-        hipLaunchKernelGGL((k_sym_expand_small<kExpandSmall, 0>), dim3(cus * 8), dim3(kWG), 0, s, b, sc);
-        hipLaunchKernelGGL((k_sym_expand_small<kExpandMid, kExpandSmall>), dim3(cus * 8), dim3(kWG), 0, s, b, sc);
+        if (seen >> kSeenSmall & 1u)
+            hipLaunchKernelGGL((k_sym_expand_small<kExpandSmall, 0>), dim3(cus * 8), dim3(kWG), 0, s, b, sc);
+        if (seen >> kSeenMid & 1u)
+            hipLaunchKernelGGL((k_sym_expand_small<kExpandMid, kExpandSmall>), dim3(cus * 8), dim3(kWG), 0, s, b, sc);
     }
+    if (!(seen >> kSeenLarge & 1u)) return;
     ProfScope ps("sym_expand", s);
     hipLaunchKernelGGL(k_sym_expand, dim3(cus * 8), dim3(kWG), 0, s, b, sc);
 }

@@ -46,8 +46,9 @@ void launch_symbit(const Batch &b, const Sched &sc, int fill, hipStream_t s);
 constexpr int kRowptrSmallRows = 16384;
 void launch_rowptr_small(const Batch &b, const int32_t *val, int64_t *total, uint32_t *err, hipStream_t s);
 
-// Fill pass from the count pass's scratch words (rows with scnt >= 0).
-void launch_sym_expand(const Batch &b, const Sched &sc, hipStream_t s);
+// Fill pass from the count pass's scratch words (rows with scnt >= 0); seen: the
+// sizes that any row has (bits kSeen*).
+void launch_sym_expand(const Batch &b, const Sched &sc, unsigned seen, hipStream_t s);
 
 // Tasks of the spill bin's rows, ceil(size / m) windows per row, one per task
 // or (blocks) win_block of the row's entries: sc.wstart[r] = the first task of

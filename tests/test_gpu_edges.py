@@ -332,3 +332,25 @@ def test_row_sizes_stream(lens, batch):
             R, _ = oracle.spgemm(M, B)
             assert np.array_equal(rp, R.row_ptr) and np.array_equal(ci, R.col_idx)
             assert np.array_equal(v, R.values)
+
+
+# the fill pass launches what the count pass saw: products whose rows all have
+# the same number of words, around the expansion's sizes and past the kept ones
+@pytest.mark.parametrize("batch", [False, True])
+@pytest.mark.parametrize("words", [[0], [1], [16], [17], [32], [33], [64], [65], [0, 40], [16, 33], [5, 70, 20]])
+def test_symbolic_fill_sizes(words, batch):
+    ncols, g = 70000, synth.rng(sum(words))
+    rows = [32 * np.sort(g.choice(ncols // 32, words[i % len(words)], replace=False)) for i in range(60)]
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    B = synth.Csr(60, ncols, rp, np.concatenate(rows).astype(np.int32), g.standard_normal(int(rp[-1])))
+    A = synth.Csr(60, 60, np.arange(61, dtype=np.int32), g.permutation(60).astype(np.int32), g.standard_normal(60))
+    check(A, B)
+    if batch:
+        B1 = rows_of([3] * 60, ncols, 1)   # smaller rows in the same batch
+        dA = [mls.DeviceCsr.from_host(A)] * 3
+        dB = [mls.DeviceCsr.from_host(M) for M in (B1, B, B1)]
+        for M, C in zip((B1, B, B1), mls.batch_numeric(dA, dB, mls.batch_symbolic(dA, dB))):
+            rp, ci, v = C.numpy()
+            R, _ = oracle.spgemm(A, M)
+            assert np.array_equal(rp, R.row_ptr) and np.array_equal(ci, R.col_idx)
+            assert np.array_equal(v, R.values)
