@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
     int s1 = 0, e1 = 0, cs1 = 0, ce1 = 0, s2 = 0, e2 = 0, cs2 = 0, ce2 = 0;
     int k1 = -1, q1 = 0, n1 = 0;
     auto row_ptrs = [&](int at, int &s, int &e, int &cs, int &ce) {
-        const int r = min(at, b.na - 1);
+        const int r = (uint32_t)at < (uint32_t)b.na ? at : b.na - 1;   // (past the rows, or past an int)
         s = arp[r];
         e = arp[r + 1];
         if (FILL) { cs = crp[r]; ce = crp[r + 1]; }
@@ -93,13 +93,13 @@ __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
         entries(s1, e1);
         rows_b();
     }
-    for (; g < b.na; g += stride) {
+    for (; g < b.na; g = g < b.na - stride ? g + stride : b.na) {
         const int len = e1 - s1;
         const int cs = FILL ? cs1 - P.c_off : 0, ce = FILL ? ce1 - P.c_off : 0;
         const int q0 = q1 - P.b_off, n = n1;
         s1 = s2; e1 = e2; cs1 = cs2; ce1 = ce2;
         entries(s1, e1);
-        row_ptrs(g + 2 * stride, s2, e2, cs2, ce2);
+        row_ptrs((int)((uint32_t)g + 2u * (uint32_t)stride), s2, e2, cs2, ce2);
         const int incl = group_scan_incl<kWave>(n, lane);
         const int total = group_total<kWave>(n, incl);
         if (len > kWave || total > kBitRowWork) {
