@@ -833,13 +833,14 @@ __global__ __launch_bounds__(kWG) void k_bwd_det_da(int32_t m, int64_t nnz_b, in
     if (!row) return;
     const int top = det_top(wn);
     bool bad = false;
-    const int pe = gp(arp)[i + 1];
-    for (int p = gp(arp)[i] + l; p < pe; p += G) {
+    // (unsigned positions: the last step may end past the largest int)
+    const uint32_t pe = (uint32_t)gp(arp)[i + 1];
+    for (uint32_t p = (uint32_t)(gp(arp)[i] + l); p < pe; p += G) {
         const int k = gp(aci)[p];
-        const int qs = gp(brp)[k], qe = gp(brp)[k + 1];
+        const uint32_t qs = (uint32_t)gp(brp)[k], qe = (uint32_t)gp(brp)[k + 1];
         double sum = 0.0;
         if (staged) {
-            for (int q = qs; q < qe; q += kDetAhead) {
+            for (uint32_t q = qs; q < qe; q += kDetAhead) {
                 int j[kDetAhead], at[kDetAhead];
                 double bv[kDetAhead];
                 load4(gp(bci), q, nnz_b, j);
@@ -859,7 +860,7 @@ __global__ __launch_bounds__(kWG) void k_bwd_det_da(int32_t m, int64_t nnz_b, in
             }
         } else {
             int lo = 0;   // the columns of B_k ascend, so each search starts past the last hit
-            for (int q = qs; q < qe; ++q) {
+            for (uint32_t q = qs; q < qe; ++q) {
                 const int j = gp(bci)[q];
                 lo = lower_col_w(wc, lo, wn, j);
                 if (lo >= wn || wc[lo] != j) { bad = true; break; }
@@ -889,15 +890,16 @@ __global__ __launch_bounds__(kWG) void k_bwd_det_db(int32_t kb, int64_t nnz_w, c
     const int64_t k = (int64_t)blockIdx.x * (kWG / G) + grp;
     if (k >= kb) return;   // whole groups: a group exchanges with itself alone
     int *c = s_c[grp];
-    const int rs = gp(trp)[k], re = gp(trp)[k + 1];
-    const int qs = gp(brp)[k], qe = gp(brp)[k + 1];
+    // (unsigned positions: the last step may end past the largest int)
+    const uint32_t rs = (uint32_t)gp(trp)[k], re = (uint32_t)gp(trp)[k + 1];
+    const uint32_t qs = (uint32_t)gp(brp)[k], qe = (uint32_t)gp(brp)[k + 1];
     bool bad = false;
-    for (int q0 = qs; q0 < qe; q0 += G * kDetOwn) {
+    for (uint32_t q0 = qs; q0 < qe; q0 += G * kDetOwn) {
         int j[kDetOwn];
         double sum[kDetOwn];
 #pragma unroll
         for (int u = 0; u < kDetOwn; ++u) {
-            const int q = q0 + u * G + l;
+            const uint32_t q = q0 + (uint32_t)(u * G + l);
             j[u] = q < qe ? gp(bci)[q] : -1;
             sum[u] = 0.0;
         }
@@ -906,12 +908,12 @@ __global__ __launch_bounds__(kWG) void k_bwd_det_db(int32_t kb, int64_t nnz_w, c
         bool ph[kDetOwn];
 #pragma unroll
         for (int u = 0; u < kDetOwn; ++u) { pw[u] = 0.0; ph[u] = false; }
-        for (int rb = rs; rb < re; rb += G) {   // rows i of column k of A, ascending, G located together
+        for (uint32_t rb = rs; rb < re; rb += G) {   // rows i of column k of A, ascending, G located together
             const bool in = rb + l < re;
             const int i = in ? gp(tci)[rb + l] : 0;
             const double al = in ? gp(tv)[rb + l] : 0.0;
             const int wsl = gp(wrp)[i], wnl = in ? gp(wrp)[i + 1] - wsl : 0;
-            const int nr = min(G, re - rb);
+            const int nr = (int)min((uint32_t)G, re - rb);
             int w[NV][4];
             int w0 = __shfl(wsl, 0, G), n = __shfl(wnl, 0, G);
             auto next_row = [&]() {   // the row's columns x, 4 at a time, lane by lane
@@ -961,7 +963,7 @@ __global__ __launch_bounds__(kWG) void k_bwd_det_db(int32_t kb, int64_t nnz_w, c
             if (ph[u]) sum[u] += pa * pw[u];
 #pragma unroll
         for (int u = 0; u < kDetOwn; ++u) {
-            const int q = q0 + u * G + l;
+            const uint32_t q = q0 + (uint32_t)(u * G + l);
             if (q < qe) gpw(dB)[q] = sum[u];
         }
     }
@@ -1026,8 +1028,8 @@ __global__ __launch_bounds__(kWG) void k_tr_scatter(int32_t nrows, const int32_t
     const int64_t t = (int64_t)blockIdx.x * kWG + threadIdx.x;
     const int64_t i = t / kTrLanes;
     if (i >= nrows) return;
-    const int e = gp(rp)[i + 1];
-    for (int p = gp(rp)[i] + (int)(t % kTrLanes); p < e; p += kTrLanes) {
+    const uint32_t e = (uint32_t)gp(rp)[i + 1];   // (unsigned: the last step may end past the largest int)
+    for (uint32_t p = (uint32_t)(gp(rp)[i] + (int)(t % kTrLanes)); p < e; p += kTrLanes) {
         const int c = gp(ci)[p];
         const int pos = gp(trp)[c] + atomicAdd(cursor + c, 1);
         gpw(tci)[pos] = (int32_t)i;

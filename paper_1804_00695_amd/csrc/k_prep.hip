@@ -36,6 +36,8 @@ __global__ void k_zero2_f64(double *p, int64_t n, double *q, int64_t m)
 // to 64) hold one contiguous run of entries, which the wave walks 64 at a time
 // whatever the rows' lengths, with the loads of a tile of kTileSteps steps in
 // flight. A bit per entry of the tile tells where a (non-empty) row starts.
+// Positions in the stream are unsigned: a tile's end, and a lane's position
+// behind the run's end, may lie past the largest int (the entry limit).
 constexpr int kTileSteps = 8;
 constexpr int kTileEntries = kTileSteps * kWave;
 
@@ -48,13 +50,13 @@ __device__ __forceinline__ void prep_sync()
 
 // Row starts of the tile [tb, tb + kTileEntries) from the lanes' rows [s, e),
 // as a bitmap in flags (kTileEntries bits).
-__device__ __forceinline__ void tile_starts(uint32_t *flags, int lane, int tb, int s, int e)
+__device__ __forceinline__ void tile_starts(uint32_t *flags, int lane, uint32_t tb, int s, int e)
 {
     static_assert(kTileEntries / 32 <= kWave, "one word per lane");
     if (lane < kTileEntries / 32) flags[lane] = 0u;
     prep_sync();
-    const int at = s - tb;
-    if (s < e && (uint32_t)at < (uint32_t)kTileEntries) atomicOr(flags + (at >> 5), 1u << (at & 31));
+    const uint32_t at = (uint32_t)s - tb;
+    if (s < e && at < (uint32_t)kTileEntries) atomicOr(flags + (at >> 5), 1u << (at & 31));
     prep_sync();
 }
 
@@ -125,22 +127,22 @@ __global__ __launch_bounds__(kWG) void k_validate(Batch b, int which, const int6
         todo &= ~seg;
         const bool mine = row && t == t0;
         const int nc = __builtin_amdgcn_readlane(ncols, l0);
-        const int q0 = __builtin_amdgcn_readlane(s, l0), q1 = __builtin_amdgcn_readlane(e, l1);
+        const uint32_t q0 = (uint32_t)__builtin_amdgcn_readlane(s, l0), q1 = (uint32_t)__builtin_amdgcn_readlane(e, l1);
         const uint64_t pa = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)((uint64_t)ci >> 32), l0) << 32) |
                             (uint32_t)__builtin_amdgcn_readlane((int)(uint64_t)ci, l0);
         const MLS_G int32_t *c = (const MLS_G int32_t *)pa;
         int carry = -1;
-        for (int tb = q0; tb < q1; tb += kTileEntries) {
+        for (uint32_t tb = q0; tb < q1; tb += kTileEntries) {
             int cv[kTileSteps];
 #pragma unroll
             for (int u = 0; u < kTileSteps; ++u) {
-                const int q = tb + u * kWave + lane;
+                const uint32_t q = tb + (uint32_t)(u * kWave + lane);
                 cv[u] = *(q < q1 ? c + q : (const MLS_G int32_t *)k_zeros4);
             }
             tile_starts(flags, lane, tb, mine ? s : 0, mine ? e : 0);
 #pragma unroll
             for (int u = 0; u < kTileSteps; ++u) {
-                const int q = tb + u * kWave + lane;
+                const uint32_t q = tb + (uint32_t)(u * kWave + lane);
                 const bool start = ((flags[2 * u + (lane >> 5)] >> (lane & 31)) & 1u) != 0u;
                 const int prev = lane_before(cv[u], carry);
                 bad |= q < q1 && (cv[u] < 0 || cv[u] >= nc || (!start && cv[u] <= prev));
@@ -207,17 +209,17 @@ __global__ __launch_bounds__(kWG) void k_compress(Batch b, int rw, const uint32_
         };
         const MLS_G int32_t *c = (const MLS_G int32_t *)rl64(ci);
         MLS_G u32x2 *out = (MLS_G u32x2 *)rl64(bw);
-        const int q0 = __builtin_amdgcn_readlane(s, l0), q1 = __builtin_amdgcn_readlane(e, l1);
+        const uint32_t q0 = (uint32_t)__builtin_amdgcn_readlane(s, l0), q1 = (uint32_t)__builtin_amdgcn_readlane(e, l1);
         const unsigned long long full = __ballot(mine && s < e);
         // the open word (set, mask, its place), the latest row start's q - H,
         // and the heads and row starts of the stream so far
         uint32_t open_set = kNone, open_msk = 0u;
         int open_pos = 0, shift = 0, nheads = 0, nrows = 0;
-        for (int tb = q0; tb < q1; tb += kTileEntries) {
+        for (uint32_t tb = q0; tb < q1; tb += kTileEntries) {
             uint32_t cv[kTileSteps];
 #pragma unroll
             for (int u = 0; u < kTileSteps; ++u) {
-                const int q = tb + u * kWave + lane;
+                const uint32_t q = tb + (uint32_t)(u * kWave + lane);
                 cv[u] = (uint32_t)*(q < q1 ? c + q : (const MLS_G int32_t *)k_zeros4);
             }
             tile_starts(flags, lane, tb, mine ? s : 0, mine ? e : 0);
@@ -232,7 +234,7 @@ __global__ __launch_bounds__(kWG) void k_compress(Batch b, int rw, const uint32_
                 lw[u] = 0;
                 at[u] = -1;
                 if (tb + u * kWave >= q1) continue;
-                const int q = tb + u * kWave + lane;
+                const uint32_t q = tb + (uint32_t)(u * kWave + lane);
                 const bool valid = q < q1;
                 const bool start = valid && ((flags[2 * u + (lane >> 5)] >> (lane & 31)) & 1u) != 0u;
                 const uint32_t set = valid ? cv[u] >> 5 : kNone;
@@ -244,7 +246,7 @@ __global__ __launch_bounds__(kWG) void k_compress(Batch b, int rw, const uint32_
                 if (start) heads[nrows + __popcll(sm & upto) - 1] = h;
                 // q - H of the latest row start at or before this lane
                 const unsigned long long sb = sm & upto;
-                const int sh = __shfl(q - h, sb ? 63 - __clzll((long long)sb) : 0, kWave);
+                const int sh = __shfl((int)q - h, sb ? 63 - __clzll((long long)sb) : 0, kWave);
                 const int place = (sb ? sh : shift) + h;
                 if (head) at[u] = place;
                 if (valid) atomicOr(&wmsk[lw[u]], 1u << (cv[u] & 31u));
@@ -253,7 +255,7 @@ __global__ __launch_bounds__(kWG) void k_compress(Batch b, int rw, const uint32_
                     last_set = (uint32_t)__builtin_amdgcn_readlane((int)set, lh);
                     last_pos = __builtin_amdgcn_readlane(place, lh);
                 }
-                if (sm) shift = __builtin_amdgcn_readlane(q - h, 63 - __clzll((long long)sm));
+                if (sm) shift = __builtin_amdgcn_readlane((int)q - h, 63 - __clzll((long long)sm));
                 carry = (uint32_t)__builtin_amdgcn_readlane((int)set, 63);
                 th += __popcll(hm);
                 nrows += __popcll(sm);
@@ -406,12 +408,12 @@ __global__ __launch_bounds__(kWG) void k_work(Batch b, int rw, Sched sc)
         const Prob P = get_prob_any(b, t0);
         const MLS_G int32_t *aci = gp(P.aci), *bwc = gp(P.bwc);
         const int k_lo = P.k_lo, k_hi = P.k_hi;
-        const int q0 = __builtin_amdgcn_readlane(s, l0), q1 = __builtin_amdgcn_readlane(e, l1);
-        for (int tb = q0; tb < q1; tb += kTileEntries) {
+        const uint32_t q0 = (uint32_t)__builtin_amdgcn_readlane(s, l0), q1 = (uint32_t)__builtin_amdgcn_readlane(e, l1);
+        for (uint32_t tb = q0; tb < q1; tb += kTileEntries) {
             int cv[kTileSteps];
 #pragma unroll
             for (int u = 0; u < kTileSteps; ++u) {
-                const int q = tb + u * kWave + lane;
+                const uint32_t q = tb + (uint32_t)(u * kWave + lane);
                 cv[u] = *(q < q1 ? aci + q : (const MLS_G int32_t *)k_ones4);
             }
 #pragma unroll
@@ -425,7 +427,7 @@ __global__ __launch_bounds__(kWG) void k_work(Batch b, int rw, Sched sc)
                 before += (uint32_t)__builtin_amdgcn_readlane(incl, 63);
             }
             prep_sync();
-            const int lo = max(s, tb) - tb, hi = min(e, tb + kTileEntries) - tb;
+            const int lo = max(s - (int)tb, 0), hi = min(e - (int)tb, kTileEntries);   // (tb < q1 is an int)
             if (mine && lo < hi) size += (int64_t)(sum[hi - 1] - (lo > 0 ? sum[lo - 1] : 0u));
             prep_sync();
         }
