@@ -15,6 +15,7 @@
 // Also here: CSR transpose (count, scan, scatter, per-row sort) and a masked
 // gather out[e] = X(row(e), col(e)) over a pattern, used by the unfused
 // per-call adjoint (W B^T masked to pat(A), A^T W masked to pat(B)).
+#include <algorithm>
 #include <climits>
 #include <cstdio>
 
@@ -1022,18 +1023,27 @@ __global__ void k_tr_rowptr(int32_t n, const int64_t *prefix, int32_t *trp)
 
 constexpr int kTrLanes = 8;   // lanes per row of the scatter (their atomics are independent)
 
+// Workgroups of the kernels with several lanes per row: at most 2^23, as a
+// launch holds less than 2^32 threads; they go on to further rows.
+constexpr int64_t kTrMaxGrid = 1 << 23;
+static unsigned tr_grid(int64_t rows, int lanes)
+{
+    const int64_t per = kWG / lanes;
+    return (unsigned)std::min<int64_t>((rows + per - 1) / per, kTrMaxGrid);
+}
+
 __global__ __launch_bounds__(kWG) void k_tr_scatter(int32_t nrows, const int32_t *rp, const int32_t *ci, const double *v,
                                                     const int32_t *trp, int32_t *cursor, int32_t *tci, double *tv)
 {
     const int64_t t = (int64_t)blockIdx.x * kWG + threadIdx.x;
-    const int64_t i = t / kTrLanes;
-    if (i >= nrows) return;
-    const uint32_t e = (uint32_t)gp(rp)[i + 1];   // (unsigned: the last step may end past the largest int)
-    for (uint32_t p = (uint32_t)(gp(rp)[i] + (int)(t % kTrLanes)); p < e; p += kTrLanes) {
-        const int c = gp(ci)[p];
-        const int pos = gp(trp)[c] + atomicAdd(cursor + c, 1);
-        gpw(tci)[pos] = (int32_t)i;
-        if (v) gpw(tv)[pos] = gp(v)[p];
+    for (int64_t i = t / kTrLanes; i < nrows; i += (int64_t)gridDim.x * (kWG / kTrLanes)) {
+        const uint32_t e = (uint32_t)gp(rp)[i + 1];   // (unsigned: the last step may end past the largest int)
+        for (uint32_t p = (uint32_t)(gp(rp)[i] + (int)(t % kTrLanes)); p < e; p += kTrLanes) {
+            const int c = gp(ci)[p];
+            const int pos = gp(trp)[c] + atomicAdd(cursor + c, 1);
+            gpw(tci)[pos] = (int32_t)i;
+            if (v) gpw(tv)[pos] = gp(v)[p];
+        }
     }
 }
 
@@ -1047,12 +1057,11 @@ constexpr int kTrGroup = 16;
 constexpr int kTrPer = 8;                       // entries per lane of a wave's row
 constexpr int kTrSortMax = kTrPer * kWave;
 
-__global__ __launch_bounds__(kWG) void k_tr_sort(int32_t n, const int32_t *trp, int32_t *tci, double *tv)
+// the group's row r (none: r >= n); all lanes of the wave active
+__device__ __forceinline__ void tr_sort_row(int64_t r, int32_t n, const int32_t *trp, int32_t *tci, double *tv,
+                                            int lane, int *c)
 {
-    __shared__ int s_c[kWG / kWave][kTrSortMax];
-    const int lane = threadIdx.x & 63, l = lane % kTrGroup;
-    int *c = s_c[threadIdx.x >> 6];
-    const int64_t r = ((int64_t)blockIdx.x * kWG + threadIdx.x) / kTrGroup;
+    const int l = lane % kTrGroup;
     const int s = r < n ? gp(trp)[r] : 0, e = r < n ? gp(trp)[r + 1] : 0;
     const int len = e - s;
     const bool mine = len <= kTrGroup && l < len;
@@ -1115,6 +1124,15 @@ __global__ __launch_bounds__(kWG) void k_tr_sort(int32_t n, const int32_t *trp, 
     }
 }
 
+__global__ __launch_bounds__(kWG) void k_tr_sort(int32_t n, const int32_t *trp, int32_t *tci, double *tv)
+{
+    __shared__ int s_c[kWG / kWave][kTrSortMax];
+    constexpr int per = kWG / kTrGroup;
+    const int g = (int)threadIdx.x / kTrGroup;
+    for (int64_t r0 = (int64_t)blockIdx.x * per; r0 < n; r0 += (int64_t)gridDim.x * per)
+        tr_sort_row(r0 + g, n, trp, tci, tv, (int)(threadIdx.x & 63), s_c[threadIdx.x >> 6]);
+}
+
 void launch_transpose(int32_t nrows, int32_t ncols, int64_t nnz, const int32_t *rp, const int32_t *ci, const double *v,
                       int32_t *trp, int32_t *tci, double *tv, int32_t *cursor, int64_t *tile_sum, int64_t *prefix,
                       int32_t *cnt, hipStream_t s)
@@ -1124,12 +1142,11 @@ void launch_transpose(int32_t nrows, int32_t ncols, int64_t nnz, const int32_t *
     if (nnz > 0) hipLaunchKernelGGL(k_tr_count, dim3((unsigned)((nnz + kWG - 1) / kWG)), dim3(kWG), 0, s, nnz, ci, cnt);
     launch_scan(cnt, ncols, tile_sum, prefix, s);
     hipLaunchKernelGGL(k_tr_rowptr, dim3((ncols + kWG) / kWG), dim3(kWG), 0, s, ncols, prefix, trp);
-    constexpr int srows = kWG / kTrLanes, trows = kWG / kTrGroup;
     if (nrows > 0)
-        hipLaunchKernelGGL(k_tr_scatter, dim3((nrows + srows - 1) / srows), dim3(kWG), 0, s, nrows, rp, ci, v, trp,
-                           cursor, tci, tv);
+        hipLaunchKernelGGL(k_tr_scatter, dim3(tr_grid(nrows, kTrLanes)), dim3(kWG), 0, s, nrows, rp, ci, v, trp, cursor,
+                           tci, tv);
     if (ncols > 0)
-        hipLaunchKernelGGL(k_tr_sort, dim3((ncols + trows - 1) / trows), dim3(kWG), 0, s, ncols, trp, tci, tv);
+        hipLaunchKernelGGL(k_tr_sort, dim3(tr_grid(ncols, kTrGroup)), dim3(kWG), 0, s, ncols, trp, tci, tv);
 }
 
 // out[e] = X(r, c) for the e-th entry (r, c) of pattern P, else 0.0

@@ -74,3 +74,20 @@ def test_fixed_order_adjoint_near_the_limit():
     gA, gB = mls.backward(A, B, W, deterministic=True)
     assert gA.tolist() == [730.0] and gB[-2:].tolist() == [20.0, 200.0]
     assert int(torch.count_nonzero(gB)) == 2
+
+
+# several lanes per row (scatter) and per column (sort): 2^32 threads and more
+@pytest.mark.parametrize("nrows,ncols", [(4000, (1 << 28) + 3), ((1 << 29) + 3, 7)])
+def test_transpose_of_many_rows(nrows, ncols):
+    need(48)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    k = 3000   # the first k rows and the last one end in the last column
+    rp = torch.full((nrows + 1,), k, **i32)
+    rp[:k], rp[nrows:] = torch.arange(k, **i32), k + 2
+    ci = torch.full((k + 2,), ncols - 1, **i32)
+    ci[k] = 0
+    v = torch.arange(k + 2, dtype=torch.float64, device="cuda")
+    T = mls.transpose(mls.DeviceCsr(nrows, ncols, rp, ci, v))
+    assert T.row_ptr[0] == 0 and T.row_ptr[1:ncols].eq(1).all() and T.row_ptr[ncols] == k + 2
+    assert T.col_idx.tolist() == [nrows - 1] + list(range(k)) + [nrows - 1]
+    assert T.values.tolist() == [float(k)] + [float(x) for x in range(k)] + [k + 1.0]
