@@ -36,8 +36,8 @@ __global__ void k_zero2_f64(double *p, int64_t n, double *q, int64_t m)
 // to 64) hold one contiguous run of entries, which the wave walks 64 at a time
 // whatever the rows' lengths, with the loads of a tile of kTileSteps steps in
 // flight. A bit per entry of the tile tells where a (non-empty) row starts.
-// Positions in the stream are unsigned: a tile's end, and a lane's position
-// behind the run's end, may lie past the largest int (the entry limit).
+// Positions in the stream are unsigned, and a lane counts from its tile on: a tile's
+// end may lie past the largest int (the entry limit).
 constexpr int kTileSteps = 8;
 constexpr int kTileEntries = kTileSteps * kWave;
 
@@ -133,19 +133,20 @@ __global__ __launch_bounds__(kWG) void k_validate(Batch b, int which, const int6
         const MLS_G int32_t *c = (const MLS_G int32_t *)pa;
         int carry = -1;
         for (uint32_t tb = q0; tb < q1; tb += kTileEntries) {
+            const MLS_G int32_t *ct = c + tb;
+            const uint32_t left = q1 - tb;
             int cv[kTileSteps];
 #pragma unroll
             for (int u = 0; u < kTileSteps; ++u) {
-                const uint32_t q = tb + (uint32_t)(u * kWave + lane);
-                cv[u] = *(q < q1 ? c + q : (const MLS_G int32_t *)k_zeros4);
+                const uint32_t x = (uint32_t)(u * kWave + lane);
+                cv[u] = *(x < left ? ct + x : (const MLS_G int32_t *)k_zeros4);
             }
             tile_starts(flags, lane, tb, mine ? s : 0, mine ? e : 0);
 #pragma unroll
             for (int u = 0; u < kTileSteps; ++u) {
-                const uint32_t q = tb + (uint32_t)(u * kWave + lane);
                 const bool start = ((flags[2 * u + (lane >> 5)] >> (lane & 31)) & 1u) != 0u;
                 const int prev = lane_before(cv[u], carry);
-                bad |= q < q1 && (cv[u] < 0 || cv[u] >= nc || (!start && cv[u] <= prev));
+                bad |= (uint32_t)(u * kWave + lane) < left && (cv[u] < 0 || cv[u] >= nc || (!start && cv[u] <= prev));
                 carry = __builtin_amdgcn_readlane(cv[u], 63);
             }
             prep_sync();
@@ -216,11 +217,13 @@ __global__ __launch_bounds__(kWG) void k_compress(Batch b, int rw, const uint32_
         uint32_t open_set = kNone, open_msk = 0u;
         int open_pos = 0, shift = 0, nheads = 0, nrows = 0;
         for (uint32_t tb = q0; tb < q1; tb += kTileEntries) {
+            const MLS_G int32_t *ct = c + tb;
+            const uint32_t left = q1 - tb;
             uint32_t cv[kTileSteps];
 #pragma unroll
             for (int u = 0; u < kTileSteps; ++u) {
-                const uint32_t q = tb + (uint32_t)(u * kWave + lane);
-                cv[u] = (uint32_t)*(q < q1 ? c + q : (const MLS_G int32_t *)k_zeros4);
+                const uint32_t x = (uint32_t)(u * kWave + lane);
+                cv[u] = (uint32_t)*(x < left ? ct + x : (const MLS_G int32_t *)k_zeros4);
             }
             tile_starts(flags, lane, tb, mine ? s : 0, mine ? e : 0);
             // the tile's heads and their words' masks: every step's ORs before
@@ -233,9 +236,9 @@ __global__ __launch_bounds__(kWG) void k_compress(Batch b, int rw, const uint32_
             for (int u = 0; u < kTileSteps; ++u) {
                 lw[u] = 0;
                 at[u] = -1;
-                if (tb + u * kWave >= q1) continue;
-                const uint32_t q = tb + (uint32_t)(u * kWave + lane);
-                const bool valid = q < q1;
+                if ((uint32_t)(u * kWave) >= left) continue;
+                const int q = (int)(tb + (uint32_t)(u * kWave + lane));
+                const bool valid = (uint32_t)(u * kWave + lane) < left;
                 const bool start = valid && ((flags[2 * u + (lane >> 5)] >> (lane & 31)) & 1u) != 0u;
                 const uint32_t set = valid ? cv[u] >> 5 : kNone;
                 const uint32_t prev = (uint32_t)lane_before((int)set, (int)carry);
@@ -246,7 +249,7 @@ __global__ __launch_bounds__(kWG) void k_compress(Batch b, int rw, const uint32_
                 if (start) heads[nrows + __popcll(sm & upto) - 1] = h;
                 // q - H of the latest row start at or before this lane
                 const unsigned long long sb = sm & upto;
-                const int sh = __shfl((int)q - h, sb ? 63 - __clzll((long long)sb) : 0, kWave);
+                const int sh = __shfl(q - h, sb ? 63 - __clzll((long long)sb) : 0, kWave);
                 const int place = (sb ? sh : shift) + h;
                 if (head) at[u] = place;
                 if (valid) atomicOr(&wmsk[lw[u]], 1u << (cv[u] & 31u));
@@ -255,7 +258,7 @@ __global__ __launch_bounds__(kWG) void k_compress(Batch b, int rw, const uint32_
                     last_set = (uint32_t)__builtin_amdgcn_readlane((int)set, lh);
                     last_pos = __builtin_amdgcn_readlane(place, lh);
                 }
-                if (sm) shift = __builtin_amdgcn_readlane((int)q - h, 63 - __clzll((long long)sm));
+                if (sm) shift = __builtin_amdgcn_readlane(q - h, 63 - __clzll((long long)sm));
                 carry = (uint32_t)__builtin_amdgcn_readlane((int)set, 63);
                 th += __popcll(hm);
                 nrows += __popcll(sm);
@@ -410,11 +413,13 @@ __global__ __launch_bounds__(kWG) void k_work(Batch b, int rw, Sched sc)
         const int k_lo = P.k_lo, k_hi = P.k_hi;
         const uint32_t q0 = (uint32_t)__builtin_amdgcn_readlane(s, l0), q1 = (uint32_t)__builtin_amdgcn_readlane(e, l1);
         for (uint32_t tb = q0; tb < q1; tb += kTileEntries) {
+            const MLS_G int32_t *at = aci + tb;
+            const uint32_t left = q1 - tb;
             int cv[kTileSteps];
 #pragma unroll
             for (int u = 0; u < kTileSteps; ++u) {
-                const uint32_t q = tb + (uint32_t)(u * kWave + lane);
-                cv[u] = *(q < q1 ? aci + q : (const MLS_G int32_t *)k_ones4);
+                const uint32_t x = (uint32_t)(u * kWave + lane);
+                cv[u] = *(x < left ? at + x : (const MLS_G int32_t *)k_ones4);
             }
 #pragma unroll
             for (int u = 0; u < kTileSteps; ++u)
