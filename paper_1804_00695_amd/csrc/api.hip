@@ -91,6 +91,7 @@ struct SymMemo {
     std::vector<uint64_t> key;
     bool valid = false;
     unsigned seen = 0;   // sizes of rows among the kept words (bits kSeen*)
+    SymBits bits = kBitsNone;   // what the count pass ran as
 } g_memo;
 }  // namespace
 
@@ -371,23 +372,25 @@ static spgemm_status read_counts(BatchHost &bh, char *ws, int64_t *nnz_host, uns
 spgemm_status run_symbolic(BatchHost &bh, char *ws, int fill, int64_t *nnz_host, hipStream_t s)
 {
     Layout &L = bh.layout;
+    // few columns: dense bitmaps in place of binning and hash tables, by rule (the
+    // test knobs that choose a path or class keep those)
+    const SymBits bits = g_opt.force_spill || g_opt.force_class >= 0 ? kBitsNone
+                                                                     : symbit_choose(bh.batch, bh.avg_a, bh.avg_b);
     bool reuse = false;
     unsigned seen = 0;
     {
         std::lock_guard<std::mutex> lk(g_memo_mu);
-        reuse = fill && g_memo.valid && g_memo.ws == ws && g_memo.key == bh.key;
+        reuse = fill && g_memo.valid && g_memo.ws == ws && g_memo.bits == bits && g_memo.key == bh.key;
         seen = g_memo.seen;
         if (g_memo.ws == ws) g_memo.valid = false;
     }
-    // few columns: dense bitmaps in place of compression, binning and hash
-    // tables (the test knobs that choose a path or class keep those)
-    const bool bits = symbit_fits(bh.batch) && !g_opt.force_spill && g_opt.force_class < 0;
     if (fill && !reuse) L.has_scratch = false;   // nothing to expand: recompute every row
     Sched sc = make_sched(ws, L);
     reset_header(ws, L, s);
     if (!fill && g_opt.validate) queue_validate(bh, ws, sc.err, s);
-    if (bits) {
-        launch_symbit(bh.batch, sc, fill, s);
+    if (bits != kBitsNone) {
+        if (bits == kBitsWords && !reuse) launch_compress(bh.batch, bh.zb, sc.err, s);
+        launch_symbit(bh.batch, sc, fill, bits == kBitsWords, s);
     } else {
         if (!reuse) launch_compress(bh.batch, bh.zb, sc.err, s);
         // the fill of a count whose words were all kept has nothing to bin and
@@ -406,12 +409,13 @@ spgemm_status run_symbolic(BatchHost &bh, char *ws, int fill, int64_t *nnz_host,
         if (reuse) {   // the words stay valid for another fill pass on the same operands
             std::lock_guard<std::mutex> lk(g_memo_mu);
             g_memo.ws = ws; g_memo.key = bh.key; g_memo.valid = true; g_memo.seen = seen;
+            g_memo.bits = bits;
         }
         return SPGEMM_OK;
     }
     for (int t = 0; t < bh.batch.nprob; ++t)
         if (bh.probs[t].nrows == 0) launch_fill_i32(bh.probs[t].crp, 0, 1, s);
-    if (bits && bh.batch.na > 0 && bh.batch.na <= kRowptrSmallRows) {
+    if (bits != kBitsNone && bh.batch.na > 0 && bh.batch.na <= kRowptrSmallRows) {
         launch_rowptr_small(bh.batch, sc.val, (int64_t *)(ws + L.totals), sc.err, s);
     } else {
         int64_t *prefix = (int64_t *)(ws + L.prefix);
@@ -421,9 +425,10 @@ spgemm_status run_symbolic(BatchHost &bh, char *ws, int fill, int64_t *nnz_host,
     st = check_launch();
     if (st != SPGEMM_OK) return st;
     st = read_counts(bh, ws, nnz_host, seen, s);
-    if (st == SPGEMM_OK && !bits) {
+    if (st == SPGEMM_OK && bits != kBitsColumns) {
         std::lock_guard<std::mutex> lk(g_memo_mu);
         g_memo.ws = ws; g_memo.key = bh.key; g_memo.valid = true; g_memo.seen = seen;
+        g_memo.bits = bits;
     }
     return st;
 }

@@ -1,9 +1,9 @@
 // k_symbit.hip -- symbolic phase (Sec. 2.1) of products whose C has few
 // columns: the union of the rows B_k, k in row i of A, as a dense bitmap over
-// C's columns in LDS, one wave per row and straight from B's column indices.
-// No compression of B, no binning and no hash tables: the count pass is one
-// launch over the rows and one over the rows set aside, the fill pass the
-// same two, and columns come out of the bitmap in ascending order.
+// C's columns in LDS, one wave per row, straight from B's column indices or,
+// where rows are long, from compressed B. No binning and no hash tables: the
+// count pass is one launch over the rows and one over the rows set aside, the
+// fill pass the same two, and columns come out of the bitmap in ascending order.
 //
 // What bounds it: latency for small products (each launch of the binned path
 // costs its 2-20 us run or at least 4.7 us of stream time, and there are 14
@@ -32,20 +32,37 @@ __device__ __forceinline__ void bit_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// ORs columns j (those >= 0) into the wave's bitmap of `words` words.
-__device__ __forceinline__ void bit_set(uint32_t *bm, int words, int j, bool ok, bool &bad)
-{
-    if (!ok) return;
-    if ((uint32_t)j < 32u * (uint32_t)words) atomicOr(bm + (j >> 5), 1u << (j & 31));
-    else bad = true;
-}
+// What is OR-ed into a bitmap of `words` words: B's columns, or (WORDS) the
+// (set, mask) words of compressed B, where rows of B are long: a stencil's
+// columns share words, and random ones cost little more as words.
+template <bool WORDS> struct BitSrc {
+    using T = int32_t;
+    __device__ __forceinline__ static const MLS_G T *base(const Prob &P) { return gp(P.bci); }
+    __device__ __forceinline__ static void set(uint32_t *bm, int words, T j, bool ok, bool &bad)
+    {
+        if (!ok) return;
+        if ((uint32_t)j < 32u * (uint32_t)words) atomicOr(bm + (j >> 5), 1u << (j & 31));
+        else bad = true;
+    }
+};
+template <> struct BitSrc<true> {
+    using T = u32x2;
+    __device__ __forceinline__ static const MLS_G T *base(const Prob &P) { return (const MLS_G T *)P.bw; }
+    __device__ __forceinline__ static void set(uint32_t *bm, int words, T w, bool ok, bool &bad)
+    {
+        if (!ok) return;
+        if (w.x < (uint32_t)words) atomicOr(bm + w.x, w.y);
+        else bad = true;
+    }
+};
 
-// Rows of at most 64 entries of A and kBitRowWork multiply-adds, one per wave
-// (rows dealt round-robin: their sizes vary); the others go to the list in
-// sc.perm, counted in the spill bin's count. R-MAT 16 square, count and fill:
-// 297 and 525 us with a bisection per pair and no row in flight, 230 and 481
-// us; 60000 random rows of 64 outputs: 85 and 175 us, 59 and 128 us.
-template <bool FILL>
+// Rows of at most kBitRowWork multiply-adds (and entries of A), one per wave (dealt
+// round-robin: their sizes vary), 64 entries of A at a time; the others go to
+// the list in sc.perm, counted in the spill bin's count (a wave lists up to 64
+// with one atomic: on one address they take some 10 ns each). R-MAT 16 square,
+// count and fill: 297 and 525 us with a bisection per pair and no row in flight,
+// 230 and 481 us; 60000 random rows of 64 outputs: 85 and 175 us, 59 and 128 us.
+template <bool FILL, bool WORDS>
 __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t s_bm[];   // words per wave, a multiple of kBitTile
@@ -56,7 +73,9 @@ __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
     const MLS_G int32_t *__restrict__ arp = gp(P.arp);
     const MLS_G int32_t *__restrict__ aci = gp(P.aci);
     const MLS_G int32_t *__restrict__ brp = gp(P.brp);
-    const MLS_G int32_t *__restrict__ bci = gp(P.bci);
+    using Src = BitSrc<WORDS>;
+    const MLS_G typename Src::T *__restrict__ src = Src::base(P);
+    const MLS_G int32_t *__restrict__ bwc = gp(P.bwc);   // (WORDS)
     const MLS_G int32_t *__restrict__ crp = gp(P.crp);
     MLS_G int32_t *__restrict__ cci = gpw(P.cci);
     for (int x = 4 * lane; x < words; x += kBitTile) *(uint4 *)(bm + x) = make_uint4(0u, 0u, 0u, 0u);
@@ -80,12 +99,17 @@ __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
         const int x = s - P.a_off + lane;
         k1 = *(x < e - P.a_off ? aci + x : (const MLS_G int32_t *)k_ones4);
     };
+    // row k of B (none for k < 0): its start before b_off, and its elements
+    auto row_b = [&](int k, int &q, int &n) {
+        const bool in = k >= P.k_lo && k < P.k_hi;
+        const MLS_G int32_t *zero = (const MLS_G int32_t *)k_zeros4;
+        const MLS_G int32_t *pb = in ? brp + (k - P.k_lo) : zero;
+        q = pb[0];
+        if (WORDS) n = *(in ? bwc + (k - P.k_lo) : zero);
+        else n = in ? pb[1] - q : 0;
+    };
     auto rows_b = [&]() {
-        const bool in = k1 >= P.k_lo && k1 < P.k_hi;
-        const MLS_G int32_t *pb = in ? brp + (k1 - P.k_lo) : (const MLS_G int32_t *)k_zeros4;
-        q1 = pb[0];
-        n1 = pb[1] - q1;
-        if (!in) n1 = 0;
+        row_b(k1, q1, n1);
     };
     if (g < b.na) {
         row_ptrs(g, s1, e1, cs1, ce1);
@@ -93,33 +117,59 @@ __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
         entries(s1, e1);
         rows_b();
     }
+    int aside = 0, n_aside = 0;   // lane l: the l-th row set aside and not yet listed
+    auto list = [&]() {
+        int at = 0;
+        if (lane == 0) at = atomicAdd(sc.bin_count + kBinSpill, n_aside);
+        at = __builtin_amdgcn_readlane(at, 0) + lane;
+        if (lane < n_aside && at < b.na) gpw(sc.perm)[at] = aside;
+        n_aside = 0;
+    };
     for (; g < b.na; g = g < b.na - stride ? g + stride : b.na) {
-        const int len = e1 - s1;
+        const int len = e1 - s1, ps = s1 - P.a_off;
         const int cs = FILL ? cs1 - P.c_off : 0, ce = FILL ? ce1 - P.c_off : 0;
-        const int q0 = q1 - P.b_off, n = n1;
+        int q0 = q1 - P.b_off, n = n1;
         s1 = s2; e1 = e2; cs1 = cs2; ce1 = ce2;
         entries(s1, e1);
         row_ptrs((int)((uint32_t)g + 2u * (uint32_t)stride), s2, e2, cs2, ce2);
-        const int incl = group_scan_incl<kWave>(n, lane);
-        const int total = group_total<kWave>(n, incl);
-        if (len > kWave || total > kBitRowWork) {
-            if (lane == 0) {
-                const int at = atomicAdd(sc.bin_count + kBinSpill, 1);
-                if (at < b.na) gpw(sc.perm)[at] = g;
-            }
-            rows_b();
-            continue;
-        }
-        // the (entry, position in B_k) pairs as one sequence, four per lane in flight
-        const int first = incl - n;
-        const int qd = seq_compact<kWave>(n > 0, q0 - first, 0, lane);
-        int eb = -1;
-        for (int base = 0; base < total; base += kBitDepth * kWave) {
-            int jv[kBitDepth];
-            bool ok[kBitDepth];
-            seq_tile<kWave, kBitDepth>(bci, lane, base, total, first, n > 0, qd, eb, jv, ok);
+        // the (entry, position in B_k) pairs of 64 entries of A as one sequence, four
+        // per lane in flight
+        auto set_columns = [&](int total, int incl) {
+            const int first = incl - n;
+            const int qd = seq_compact<kWave>(n > 0, q0 - first, 0, lane);
+            int eb = -1;
+            for (int base = 0; base < total; base += kBitDepth * kWave) {
+                typename Src::T v[kBitDepth];
+                bool ok[kBitDepth];
+                seq_tile<kWave, kBitDepth>(src, lane, base, total, first, n > 0, qd, eb, v, ok);
 #pragma unroll
-            for (int u = 0; u < kBitDepth; ++u) bit_set(bm, words, jv[u], ok[u], bad);
+                for (int u = 0; u < kBitDepth; ++u) Src::set(bm, words, v[u], ok[u], bad);
+            }
+        };
+        const int incl = group_scan_incl<kWave>(n, lane);
+        int work = group_total<kWave>(n, incl);
+        bool over = work > kBitRowWork || len > kBitRowWork;   // (entries of empty rows of B take time too)
+        if (!over) set_columns(work, incl);
+        for (int pc = kWave; !over && pc < len; pc += kWave) {   // a longer row's other entries
+            const int k = *(lane < len - pc ? aci + ps + pc + lane : (const MLS_G int32_t *)k_ones4);
+            row_b(k, q0, n);
+            q0 -= P.b_off;
+            const int more = group_scan_incl<kWave>(n, lane);
+            const int total = group_total<kWave>(n, more);
+            work += total;
+            over = work > kBitRowWork;
+            if (!over) set_columns(total, more);
+        }
+        if (over) {
+            if (len > kWave) {   // (the chunks before have set columns)
+                bit_sync();
+                for (int x = 4 * lane; x < words; x += kBitTile) *(uint4 *)(bm + x) = make_uint4(0u, 0u, 0u, 0u);
+            }
+            if (lane == n_aside) aside = g;
+            if (++n_aside == kWave) list();
+            rows_b();
+            bit_sync();
+            continue;
         }
         rows_b();
         bit_sync();
@@ -159,6 +209,7 @@ __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
         }
         bit_sync();
     }
+    if (n_aside) list();
     if (bad) atomicOr(sc.err, kErrStructure);
 }
 
@@ -166,7 +217,7 @@ __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
 // sequence, an equal share of it per wave. R-MAT 16 square, count and fill: 750
 // and 1011 us with 64-column pieces found by bisection and a thread writing a
 // run of columns, 492 and 657 us.
-template <bool FILL>
+template <bool FILL, bool WORDS>
 __global__ __launch_bounds__(kBitLongWG) void k_bit_long(Batch b, Sched sc, int words)
 {
     constexpr int NT = kBitLongWG, NWV = NT / kWave;
@@ -180,7 +231,9 @@ __global__ __launch_bounds__(kBitLongWG) void k_bit_long(Batch b, Sched sc, int 
     const Prob &P = b.p0;
     const MLS_G int32_t *__restrict__ aci = gp(P.aci);
     const MLS_G int32_t *__restrict__ brp = gp(P.brp);
-    const MLS_G int32_t *__restrict__ bci = gp(P.bci);
+    using Src = BitSrc<WORDS>;
+    const MLS_G typename Src::T *__restrict__ src = Src::base(P);
+    const MLS_G int32_t *__restrict__ bwc = gp(P.bwc);   // (WORDS)
     MLS_G int32_t *__restrict__ cci = gpw(P.cci);
     // exclusive scan over the workgroup; returns the thread's prefix, all = the total
     auto scan = [&](int v, int &all) -> int {
@@ -198,11 +251,8 @@ __global__ __launch_bounds__(kBitLongWG) void k_bit_long(Batch b, Sched sc, int 
         return before + incl - v;
     };
     bool bad = false;
-    for (;;) {
-        if (tid == 0) s_row = atomicAdd(sc.task_cursor + kBinSpill * kXcd, 1);
-        __syncthreads();
-        const int r = s_row;
-        if (r >= n_rows) break;
+    // the first row by the workgroup's index, the others from a counter
+    for (int r = (int)blockIdx.x; r < n_rows;) {
         const int g = bin_row(sc.perm, sc.err, b.na, r);
         for (int x = tid; x < words; x += NT) s_bm[x] = 0u;
         const int s = g >= 0 ? gp(P.arp)[g] - P.a_off : 0, e = g >= 0 ? gp(P.arp)[g + 1] - P.a_off : 0;
@@ -212,7 +262,7 @@ __global__ __launch_bounds__(kBitLongWG) void k_bit_long(Batch b, Sched sc, int 
                 const int k = aci[pb + tid];
                 if (k >= P.k_lo && k < P.k_hi) {
                     q0 = brp[k - P.k_lo] - P.b_off;
-                    n = brp[k - P.k_lo + 1] - P.b_off - q0;
+                    n = WORDS ? bwc[k - P.k_lo] : brp[k - P.k_lo + 1] - P.b_off - q0;
                 }
             }
             int all;
@@ -238,11 +288,11 @@ __global__ __launch_bounds__(kBitLongWG) void k_bit_long(Batch b, Sched sc, int 
                     const int qd = seq_compact<kWave>(any, s_qd[min(e0 + lane, NT - 1)], 0, lane);
                     int eb = __builtin_amdgcn_readlane(f, 0) < base ? 0 : -1;
                     for (; base < stop; base += kBitDepth * kWave) {
-                        int jv[kBitDepth];
+                        typename Src::T v[kBitDepth];
                         bool ok[kBitDepth];
-                        seq_tile<kWave, kBitDepth>(bci, lane, base, stop, f, any, qd, eb, jv, ok);
+                        seq_tile<kWave, kBitDepth>(src, lane, base, stop, f, any, qd, eb, v, ok);
 #pragma unroll
-                        for (int u = 0; u < kBitDepth; ++u) bit_set(s_bm, words, jv[u], ok[u], bad);
+                        for (int u = 0; u < kBitDepth; ++u) Src::set(s_bm, words, v[u], ok[u], bad);
                     }
                     base = stop;
                 }
@@ -285,7 +335,10 @@ __global__ __launch_bounds__(kBitLongWG) void k_bit_long(Batch b, Sched sc, int 
         } else if (tid == 0 && g >= 0) {
             gpw(sc.val)[g] = all;
         }
+        if (n_rows <= (int)gridDim.x) break;
+        if (tid == 0) s_row = (int)gridDim.x + atomicAdd(sc.task_cursor + kBinSpill * kXcd, 1);
         __syncthreads();
+        r = s_row;
     }
     if (bad) atomicOr(sc.err, kErrStructure);
 }
@@ -338,14 +391,48 @@ __global__ __launch_bounds__(kRowptrWG) void k_rowptr_small(Batch b, const int32
 
 // ---------------------------------------------------------------------------
 
-bool symbit_fits(const Batch &b)
+// Bitmaps or hash tables, by the product's rows and its multiply-adds per row (the
+// mean row of A times the mean row of B). Symbolic phase in us, binned / columns
+// / words; random: uniform columns, the others on grids; A P: the operator
+// times a multigrid prolongator.
+//   More than kBitRowWork multiply-adds: words. Stencils' columns share words
+//   (elasticity, 27 neighbours of 3 unknowns, 59049 rows squared: 1166 / 1590 /
+//   450; 6 unknowns, 63888 rows: 1994 / 5143 / 864), random ones do not and cost
+//   little more as words (40000 rows, 100 times 100 in 60000 columns: 2912 / 1522
+//   / 1669).
+//   Up to kBitFewRows rows: columns. The launches decide (20000 rows in 16384
+//   columns, 2 times 2: 113 / 89, 20 times 20: 338 / 108).
+//   Fewer than 1024 columns: the adds of a step meet in few words, and compressed
+//   rows are short (200000 rows, 20 times 20 in 256 columns: 308 / 825; 60000,
+//   30 times 30 in 512: 280 / 364; 30000, 60 times 60: 672 / 318).
+//   Few multiply-adds leave most of a wave idle, a group of lanes less so, and
+//   the more the more rows there are: 64000 rows of the 5-point Laplacian's
+//   square, 25: 111 / 158; 80000 random rows, 36 in 16384 columns: 211 / 151;
+//   200000, 36: 273 / 276, 64: 424 / 310, and 64 in 65536 columns, where LDS
+//   leaves 20 waves per CU: 448 / 605, 144: 1144 / 650; 2 million rows, 9: 545 /
+//   1912. 27-point A P, 262144 rows, 32768 columns, 102: 320 / 411, 493039 rows,
+//   64000 columns, 104: 439 / 1106.
+//   Rows of A past a wave's 64 entries, many of them: 81-point A P, 331776 rows:
+//   662 / 924 (59049 rows: 206 / 209; 40000 random rows of 100 times 4: 588 / 238).
+constexpr int kBitFewRows = 32768, kBitManyRows = 131072;
+
+SymBits symbit_choose(const Batch &b, double avg_a, double avg_b)
 {
-    return b.nprob == 1 && b.p0.ncols <= kBitMaxCols;
+    if (b.nprob != 1 || b.p0.ncols > kBitMaxCols) return kBitsNone;
+    const int ncols = b.p0.ncols;
+    const double work = avg_a * avg_b;
+    if (work > kBitRowWork) return kBitsWords;
+    if (b.na <= kBitFewRows) return kBitsColumns;
+    bool bits;
+    if (ncols < 1024) bits = work >= 2048.0;
+    else if (b.na <= kBitManyRows) bits = work >= 32.0;
+    else bits = avg_a <= kWave && work >= (ncols <= 32768 ? 48.0 : 128.0);
+    return bits ? kBitsColumns : kBitsNone;
 }
 
-void launch_symbit(const Batch &b, const Sched &sc, int fill, hipStream_t s)
+template <bool FILL, bool WORDS>
+static void launch_bits(const Batch &b, const Sched &sc, hipStream_t s)
 {
-    if (b.na <= 0) return;
     int words = (b.p0.ncols + 31) / 32;
     words = (words + kBitTile - 1) / kBitTile * kBitTile;
     if (words < kBitTile) words = kBitTile;
@@ -357,16 +444,23 @@ void launch_symbit(const Batch &b, const Sched &sc, int fill, hipStream_t s)
     per_cu = per_cu > 8 ? 8 : (per_cu < 1 ? 1 : per_cu);
     const int want = (b.na + nw - 1) / nw;
     const int grid = want < cus * per_cu ? want : cus * per_cu;
-    int long_per_cu = (int)(163840 / (wave_bytes + (fill ? 21504 : 4608)));
+    int long_per_cu = (int)(163840 / (wave_bytes + (FILL ? 21504 : 4608)));
     long_per_cu = long_per_cu > 4 ? 4 : (long_per_cu < 1 ? 1 : long_per_cu);
     const int long_grid = b.na < cus * long_per_cu ? b.na : cus * long_per_cu;
-    ProfScope ps(fill ? "sym_bit_fill" : "sym_bit_count", s);
-    if (fill) {
-        hipLaunchKernelGGL(k_bit_rows<true>, dim3(grid), dim3(kWG), nw * wave_bytes, s, b, sc, words);
-        hipLaunchKernelGGL(k_bit_long<true>, dim3(long_grid), dim3(kBitLongWG), wave_bytes, s, b, sc, words);
+    ProfScope ps(FILL ? "sym_bit_fill" : "sym_bit_count", s);
+    hipLaunchKernelGGL((k_bit_rows<FILL, WORDS>), dim3(grid), dim3(kWG), nw * wave_bytes, s, b, sc, words);
+    hipLaunchKernelGGL((k_bit_long<FILL, WORDS>), dim3(long_grid), dim3(kBitLongWG), wave_bytes, s, b, sc, words);
+}
+
+void launch_symbit(const Batch &b, const Sched &sc, int fill, bool words, hipStream_t s)
+{
+    if (b.na <= 0) return;
+    if (words) {
+        if (fill) launch_bits<true, true>(b, sc, s);
+        else launch_bits<false, true>(b, sc, s);
     } else {
-        hipLaunchKernelGGL(k_bit_rows<false>, dim3(grid), dim3(kWG), nw * wave_bytes, s, b, sc, words);
-        hipLaunchKernelGGL(k_bit_long<false>, dim3(long_grid), dim3(kBitLongWG), wave_bytes, s, b, sc, words);
+        if (fill) launch_bits<true, false>(b, sc, s);
+        else launch_bits<false, false>(b, sc, s);
     }
 }
 

@@ -34,12 +34,15 @@ void launch_write_rowptr(const Batch &b, const int64_t *prefix, int64_t *totals,
 // G = lanes per row for the LDS classes.
 void launch_symbolic(const Batch &b, const Sched &sc, int fill, int G, hipStream_t s);
 
-// Symbolic phase by dense bitmaps: one product of at most kBitMaxCols columns.
-// A wave's bitmap then takes at most 8 KB of LDS, which leaves 20 waves per
-// CU resident; each doubling halves them.
+// Symbolic phase by dense bitmaps, of B's columns or of compressed B's words: one
+// product of at most kBitMaxCols columns. A wave's bitmap then takes at most 8
+// KB of LDS, which leaves 20 waves per CU resident; each doubling halves them
+// (60000 random rows of 30 times 30, binned / bitmaps: 1573 / 349 us in 8192
+// columns, 1606 / 305 in 32768, 1598 / 443 in 65536).
 constexpr int kBitMaxCols = 65536;
-bool symbit_fits(const Batch &b);
-void launch_symbit(const Batch &b, const Sched &sc, int fill, hipStream_t s);
+enum SymBits { kBitsNone, kBitsColumns, kBitsWords };
+SymBits symbit_choose(const Batch &b, double avg_a, double avg_b);
+void launch_symbit(const Batch &b, const Sched &sc, int fill, bool words, hipStream_t s);
 // Row pointers and nnz(C) of one product of few rows in one launch of one
 // workgroup (17 us for 16384 rows, 30 for 30000, 61 for 65536; the four
 // launches that take more rows, 20 us for all of these).

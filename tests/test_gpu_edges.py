@@ -354,3 +354,123 @@ def test_symbolic_fill_sizes(words, batch):
             R, _ = oracle.spgemm(A, M)
             assert np.array_equal(rp, R.row_ptr) and np.array_equal(ci, R.col_idx)
             assert np.array_equal(v, R.values)
+
+
+# dense bitmaps: rows of A of several 64-entry chunks that one wave takes (up to
+# 4096 multiply-adds and entries), that it gives up part of the way, and that it
+# sets aside at once; rows of B empty, of one column and longer
+@pytest.mark.parametrize("len_b", [0, 1, 30, 63, 64])
+def test_bitmap_rows_of_several_chunks(len_b):
+    lens_b = [len_b] * 4200
+    lens_b[64:128] = [1] * 64          # a light first chunk
+    lens_b[200] = 4000
+    B = rows_of(lens_b, 9000, len_b)
+    A = rows_of([0, 1, 64, 65, 66, 127, 128, 129, 192, 4095, 4096, 4097, 4200] + [3] * 900, 4200, 3)
+    check(A, B)
+
+
+# dense bitmaps from compressed B (mean rows of more than 4096 multiply-adds):
+# neighbouring columns that share words, and spread ones; rows of A within and
+# past a chunk of 64 and of 512, rows of B empty and full
+@pytest.mark.parametrize("spread", [False, True])
+@pytest.mark.parametrize("ncols", [200, 8192, 8193, 65536])
+def test_bitmap_words(ncols, spread):
+    g = synth.rng(ncols)
+    lens_b = np.minimum(ncols, g.integers(60, 190, 700))
+    lens_b[::50] = 0
+    rows = [np.sort(g.choice(ncols, n, replace=False)) if spread
+            else g.integers(0, ncols - n + 1) + np.arange(n) for n in lens_b]
+    rows[7] = np.arange(ncols)
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    B = synth.Csr(700, ncols, rp, np.concatenate(rows).astype(np.int32), g.standard_normal(int(rp[-1])))
+    A = rows_of([0, 1, 63, 64, 65, 128, 511, 512, 513, 700] + [60, 100] * 30, 700, 5)
+    assert A.nnz / A.nrows * B.nnz / B.nrows > 4096
+    check(A, B)
+    dA, dB = mls.DeviceCsr.from_host(A), mls.DeviceCsr.from_host(B)
+    dA.col_idx[3] = 700
+    with pytest.raises(mls.SpgemmError):
+        mls.symbolic(dA, dB)
+
+
+# a fill pass that takes another path than the count pass before it uses nothing
+# that the count left behind
+@pytest.mark.parametrize("first,second", [(-1, 0), (0, -1)])
+def test_fill_on_another_path(first, second):
+    import ctypes
+    A, B = rows_of([70] * 50, 90, 1), rows_of([80] * 90, 3000, 2)
+    dA, dB = mls.DeviceCsr.from_host(A), mls.DeviceCsr.from_host(B)
+    R, _ = oracle.spgemm(A, B)
+    n = mls.workspace_size(dA, dB)
+    ws = mls.Workspace()
+    p, s, nnz = ws.get(n), mls.stream_handle(), ctypes.c_int64(0)
+    crp = torch.empty(51, dtype=torch.int32, device="cuda")
+    cci = torch.full((R.nnz,), -1, dtype=torch.int32, device="cuda")
+    ha, hb = ctypes.byref(dA.handle()), ctypes.byref(dB.handle())
+    try:
+        mls.set_option(mls._abi.OPT_FORCE_CLASS, first)
+        assert mls.lib.spgemm_symbolic(ha, hb, crp.data_ptr(), None, ctypes.byref(nnz), p, n, s) == 0
+        mls.set_option(mls._abi.OPT_FORCE_CLASS, second)
+        assert mls.lib.spgemm_symbolic(ha, hb, crp.data_ptr(), cci.data_ptr(), None, p, n, s) == 0
+    finally:
+        mls.set_option(mls._abi.OPT_FORCE_CLASS, -1)
+    assert nnz.value == R.nnz and np.array_equal(cci.cpu().numpy(), R.col_idx)
+
+
+# more set-aside rows than a wave lists at once: every second row past 4096
+# multiply-adds; the binned path finds the same structure
+def test_bitmap_rows_set_aside_in_bulk():
+    m, full = 1200000, 17
+    rp = torch.arange(m + 1, device="cuda") // 2 * (full + 1) + torch.arange(m + 1, device="cuda") % 2 * full
+    ci = torch.arange(int(rp[-1]), device="cuda") % (full + 1) % full
+    A = mls.DeviceCsr(m, full, rp.to(torch.int32), ci.to(torch.int32), None)
+    B = mls.DeviceCsr.from_host(rows_of([256] * full, 256, 1), values=False)
+    C = mls.symbolic(A, B, with_values=False)
+    assert torch.equal(C.row_ptr, torch.arange(m + 1, dtype=torch.int32, device="cuda") * 256)
+    assert torch.equal(C.col_idx.view(m, 256), torch.arange(256, dtype=torch.int32, device="cuda").expand(m, 256))
+
+
+# on either side of the lines between bitmaps and hash tables: rows, columns and
+# multiply-adds per row
+@pytest.mark.parametrize("rows,ncols,len_a,len_b", [
+    (32768, 70, 2, 2), (32769, 70, 2, 2), (32769, 1024, 4, 8), (32769, 1023, 4, 8), (32769, 1024, 4, 7),
+    (131072, 2000, 4, 8), (131073, 2000, 4, 8), (131073, 2000, 6, 8), (131073, 40000, 6, 8), (40000, 900, 40, 60),
+    (400, 5000, 64, 64), (400, 5000, 64, 65)])
+def test_bitmap_rule(rows, ncols, len_a, len_b):
+    g = synth.rng(rows + ncols)
+    step = 500 // len_a
+    ci = np.arange(len_a) * step + g.integers(0, step, (rows, len_a))
+    A = synth.Csr(rows, 500, (np.arange(rows + 1) * len_a).astype(np.int32), ci.astype(np.int32).ravel(),
+                  g.standard_normal(rows * len_a))
+    check(A, rows_of([len_b] * 500, ncols, 1))
+
+
+# time of symbolic phases whose rows of A are long (few multiply-adds in each) or
+# whose rows are many and short, against the binned path, which they fell
+# behind 5 to 20 times when every such row was set aside or took a wave
+@pytest.mark.parametrize("rows,len_a,len_b,ncols", [(40000, 81, 4, 41472), (2000000, 3, 3, 65536)])
+def test_symbolic_time(rows, len_a, len_b, ncols):
+    def regular(m, n, k, seed):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(seed)
+        step = n // k
+        c = torch.arange(k, device="cuda") * step + torch.randint(0, step, (m, k), generator=g, device="cuda")
+        return mls.DeviceCsr(m, n, (torch.arange(m + 1, device="cuda") * k).to(torch.int32),
+                             c.to(torch.int32).view(-1), None)
+    A, B = regular(rows, 30000, len_a, 1), regular(30000, ncols, len_b, 2)
+
+    def best():
+        t = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            mls.symbolic(A, B, with_values=False)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return min(t[1:])
+    now = best()
+    mls.set_option(mls._abi.OPT_FORCE_CLASS, 0)
+    try:
+        assert now < 2.0 * best()
+    finally:
+        mls.set_option(mls._abi.OPT_FORCE_CLASS, -1)
