@@ -513,8 +513,12 @@ __device__ __forceinline__ int bin_start(const int32_t *bin_count, int bin)
 // at a time, as theirs are long and have to spread over all waves. R-MAT 16
 // square, windows of rows of up to 64 and 448 entries: 4 and 2 in turn 2.78 ms,
 // 2 and 2 2.92 ms, 8 and 4 2.75 ms; R-MAT 15 with 12 entries per row: 1.61,
-// 1.69 and 1.65 ms.
+// 1.69 and 1.65 ms. Up to kWinSpread windows in all, one for each wave that stays
+// resident, every window is a task of its own: larger ones would leave waves idle
+// (16, 250 and 1000 rows of 6000 outputs, 60 entries of A each: 134, 148 and 186
+// us with tasks of 4 windows, 92, 127 and 246 with tasks of one).
 constexpr int kWinCarry = 448;
+constexpr int kWinSpread = 4096;
 __device__ __forceinline__ int win_block(int entries) { return entries <= kWave ? 4 : (entries <= kWinCarry ? 2 : 1); }
 
 // One launch for every class of the numeric (or adjoint) phase: which part

@@ -710,7 +710,8 @@ __device__ __forceinline__ int lower_col_near(const MLS_G int32_t *cols, int lo,
 
 // Tasks of the spill rows, one workgroup: wstart[r] = first task of the r-th
 // row of the spill bin, wstart[n] = the total. A row has ceil(nc / m) windows,
-// one per task or (blocks) win_block of its entries. Latency bound (perm, then
+// one per task or (blocks, and more than kWinSpread windows) win_block of its
+// entries. Latency bound (perm, then
 // the row's size and entries): four rows per thread in flight. 20400 spill
 // rows of the R-MAT 16 square: 87 us with 256 rows per step, 31 us.
 __global__ __launch_bounds__(kWinScanWG) void k_win_scan(Batch b, Sched sc, int m, int blocks)
@@ -723,6 +724,22 @@ __global__ __launch_bounds__(kWinScanWG) void k_win_scan(Batch b, Sched sc, int 
     MLS_G int32_t *ws = gpw(sc.wstart);
     ProbCache pc;
     int carry = 0;
+    // (one step's rows may have few windows; more spill rows have at least 5 each)
+    if (blocks && n <= kWinScanWG * R) {
+        int w = 0;
+        for (int r = (int)threadIdx.x; r < n; r += kWinScanWG) {
+            const int g = bin_row(sc.perm, sc.err, b.na, start + r);
+            w += g >= 0 ? (gp(sc.val)[g] + m - 1) / m : 0;
+        }
+        w = group_sum<kWave>(w);
+        if (lane == 0) s_red[wave] = w;
+        __syncthreads();
+        int all = 0;
+#pragma unroll
+        for (int x = 0; x < NW; ++x) all += s_red[x];
+        blocks = all > kWinSpread;
+        __syncthreads();
+    }
     for (int r0 = 0; r0 < n; r0 += kWinScanWG * R) {
         const int r = r0 + (int)threadIdx.x * R;
         int g[R], c[R], sum = 0;
@@ -842,11 +859,13 @@ __device__ __forceinline__ void num_win_rows(const Batch &b, const Sched &sc, ch
         const int nc = gp(sc.val)[g];
         const int cr = gp(P.crp)[i] - P.c_off;
         const int ps = gp(P.arp)[i] - P.a_off, pe = gp(P.arp)[i + 1] - P.a_off;
-        const int per = win_block(pe - ps);
+        // (one window per task where k_win_scan gave the row as many tasks)
+        const int w0 = wst[r];
+        const int per = wst[r + 1] - w0 == (nc + M - 1) / M ? 1 : win_block(pe - ps);
         const bool narrow = nc > M;
         bool bad = false;
         // first positions of the task's windows in the row
-        const int cb = (u - wst[r]) * per * M, ce = min(nc, cb + per * M);
+        const int cb = (u - w0) * per * M, ce = min(nc, cb + per * M);
         for (int c0 = cb; c0 < ce; c0 += M) {
             const int cs = cr + c0;
             const int n = min(M, nc - c0);

@@ -790,6 +790,20 @@ __global__ __launch_bounds__(kSmallWG) void k_bin_small(Batch b, Sched sc, int m
     // tasks of the spill rows, as k_win_scan numbers them
     MLS_G int32_t *ws = gpw(sc.wstart);
     int carry = 0;
+    if (blocks) {
+        int w = 0;
+        for (int q = tid; q < nspill; q += kSmallWG) {
+            const int i = __hip_atomic_load(sc.perm + spill0 + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            w += (crp[i + 1] - crp[i] + m - 1) / m;
+        }
+        w = group_sum<kWave>(w);
+        if (lane == 0) s_red[wave] = w;
+        __syncthreads();
+        int all = 0;
+        for (int x = 0; x < NW; ++x) all += s_red[x];
+        blocks = all > kWinSpread;
+        __syncthreads();
+    }
     for (int q0 = 0; q0 < nspill; q0 += kSmallWG) {
         const int q = q0 + tid;
         int c = 0;

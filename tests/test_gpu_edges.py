@@ -474,3 +474,25 @@ def test_symbolic_time(rows, len_a, len_b, ncols):
         assert now < 2.0 * best()
     finally:
         mls.set_option(mls._abi.OPT_FORCE_CLASS, -1)
+
+
+# spill windows: every window a task of its own up to 4096 windows in all, 4, 2 or
+# 1 of a row (by its entries of A: 64, 448 and more) past that
+@pytest.mark.parametrize("entries", [3, 64, 65, 448, 449])
+@pytest.mark.parametrize("rows", [1, 819, 820])   # 5 windows each
+def test_window_tasks(rows, entries):
+    n, wide = 500, 2100
+    B = rows_of([wide // 3] * 3 + [1] * (n - 3), 60000, 1)
+    for k in range(3):
+        B.col_idx[B.row_ptr[k]:B.row_ptr[k + 1]] = 5 + 3 * np.arange(wide // 3) + k   # 2100 outputs in three rows
+    B.col_idx[B.row_ptr[3]:] = 5 + np.arange(n - 3) % wide
+    tail = synth.rng(entries).permuted(np.tile(np.arange(3, n), (rows, 1)), axis=1)[:, :entries - 3]
+    ci = np.concatenate([np.tile(np.arange(3), (rows, 1)), np.sort(tail, axis=1)], axis=1)
+    A = synth.Csr(rows, n, (np.arange(rows + 1) * entries).astype(np.int32), ci.astype(np.int32).ravel(),
+                  synth.normal_values(rows * entries, 2))
+    mls.set_option(mls._abi.OPT_GROUP_SIZE, 32)   # by class
+    try:
+        check(A, B)
+    finally:
+        mls.set_option(mls._abi.OPT_GROUP_SIZE, 0)
+    check(A, B)
