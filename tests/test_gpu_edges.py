@@ -496,3 +496,18 @@ def test_window_tasks(rows, entries):
     finally:
         mls.set_option(mls._abi.OPT_GROUP_SIZE, 0)
     check(A, B)
+
+
+# windows that start where the one before ended in a row of B: up to and past the
+# 65534 entries that the carried place holds, for rows of A of up to 448 entries
+# and one more
+@pytest.mark.parametrize("entries", [4, 64, 65, 448, 449])
+def test_window_carry(entries):
+    B = rows_of([65534, 65535, 65536, 85000, 33, 32] + [1, 40, 0, 3] * 120, 90000, 9)
+    A = rows_of([entries] * 30, B.nrows, entries)
+    for i in range(30):   # the long rows of B, each row of A with another set of them
+        a = A.col_idx[i * entries:(i + 1) * entries]
+        long_rows = [x for x in range(4) if (i + 1) >> x & 1 or x == 3]
+        rest = np.setdiff1d(a, np.arange(4))
+        a[:] = np.sort(np.concatenate([long_rows, rest, np.setdiff1d(np.arange(10, B.nrows), rest)])[:entries])
+    check(A, B)
