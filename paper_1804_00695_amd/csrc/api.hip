@@ -280,6 +280,8 @@ spgemm_status prepare_batch(int32_t nbatch, const spgemm_csr *A, const spgemm_cs
     bt.probs = (const Prob *)(ws + out.layout.probs);
     bt.abase = (const int32_t *)(ws + out.layout.abase);
     bt.bbase = (const int32_t *)(ws + out.layout.bbase);
+    out.zc = 0;
+    for (int t = 0; C && t < nbatch; ++t) out.zc += C[t].nnz;
     out.za = za;
     out.zb = zb;
     out.avg_a = na > 0 ? (double)za / (double)na : 1.0;
@@ -440,8 +442,8 @@ spgemm_status run_numeric(BatchHost &bh, char *ws, hipStream_t s)
     Sched sc = make_sched(ws, L);
     // few rows: two launches in all (the test knobs that choose classes, lanes
     // or table layouts keep the launches by class)
-    if (small_rows_fit(bh.batch) && bin_force() < 0 && !g_opt.group_size) {
-        launch_numeric_small(bh.batch, sc, s);
+    if (num_small_fit(bh.batch, bh.zc) && bin_force() < 0 && !g_opt.group_size) {
+        launch_numeric_small(bh.batch, sc, bh.zc, s);
         return check_launch();
     }
     reset_header(ws, L, s);

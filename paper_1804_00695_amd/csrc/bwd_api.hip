@@ -90,8 +90,8 @@ spgemm_status spgemm_backward(const spgemm_csr *A, const spgemm_csr *B, const sp
     char *ws = (char *)ws_v;
     Sched sc = make_sched(ws, bh.layout);
     launch_zero2_f64(dA, A->nnz, dB, B->nnz, s);
-    if (small_rows_fit(bh.batch) && bin_force() < 0 && !g_opt.group_size) {
-        launch_backward_small(bh.batch, sc, dA, dB, s);
+    if (bwd_small_fit(bh.batch, bh.zc) && bin_force() < 0 && !g_opt.group_size) {
+        launch_backward_small(bh.batch, sc, dA, dB, bh.zc, s);
         return check_launch();
     }
     reset_header(ws, bh.layout, s);

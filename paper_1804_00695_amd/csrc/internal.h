@@ -53,7 +53,7 @@ struct BatchHost {
     std::vector<Prob> probs;
     std::vector<int32_t> abase, bbase;
     std::vector<int64_t> nnz_tab;
-    int64_t za = 0, zb = 0;     // entries of all A and of all B
+    int64_t za = 0, zb = 0, zc = 0;   // entries of all A, B and C
     double avg_a = 1.0, avg_b = 1.0;
     std::vector<uint64_t> key;  // operands and shapes of the call, verbatim
 };

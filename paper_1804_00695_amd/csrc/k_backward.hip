@@ -677,11 +677,23 @@ __global__ __launch_bounds__(kWG) void k_bwd_all(Batch b, Sched sc, double *dA, 
     }
 }
 
-void launch_backward_small(const Batch &b, const Sched &sc, double *dA, double *dB, hipStream_t s)
+// As num_small_fit; the adjoint's windows hold one wave per workgroup there. By
+// class / two launches in us: 20000 x 100 (17 x 6) 75 / 66; 4000 x 250 (12 x 20) 50 /
+// 46, 10000 x 250 74 / 86, 1000 x 900 (45 x 20) 60 / 38, 4000 x 900 93 / 101, 250 x 1500
+// (15 x 100) 61 / 52, 1000 x 1500 70 / 109; 1000 x 2500 (25 x 100) 160 / 137, 4000 x 2500
+// 363 / 411, 64 x 20000 (200 x 100) 155 / 114, 250 x 20000 295 / 315.
+bool bwd_small_fit(const Batch &b, int64_t outputs)
+{
+    if (!small_rows_fit(b)) return false;
+    const int64_t mean = outputs / b.na;
+    return outputs <= (mean <= 128 ? 1ll << 21 : (mean <= 2048 ? 1ll << 20 : 1ll << 22));
+}
+
+void launch_backward_small(const Batch &b, const Sched &sc, double *dA, double *dB, int64_t outputs, hipStream_t s)
 {
     launch_bin_small(b, sc, kBwdWinCap / 2, 0, s);
     ProfScope ps("bwd_all", s);
-    hipLaunchKernelGGL(k_bwd_all, dim3(small_rows_grid(b.na)), dim3(kWG), 0, s, b, sc, dA, dB);
+    hipLaunchKernelGGL(k_bwd_all, dim3(small_rows_grid(b.na, 2 * outputs)), dim3(kWG), 0, s, b, sc, dA, dB);
 }
 
 template <typename K>

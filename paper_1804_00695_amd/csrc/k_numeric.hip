@@ -921,9 +921,8 @@ __global__ __launch_bounds__(kWG) void k_num_win(Batch b, Sched sc)
 // least one). The classes' own launches cost at least 4.7 us of stream time
 // each, empty or not, and seven of them (with the window scan) are saved. A
 // workgroup has as many waves per class as kAllLds holds, and the rows of the
-// largest class (33 KB each) run as windows, so that five workgroups (20
-// waves, what the registers allow) stay resident per CU, as in the launches
-// by class. Numeric phase of 5000 random rows of 36 outputs 46 -> 22 us, of
+// largest class (33 KB each) run as windows, so that LDS leaves six workgroups
+// resident per CU (registers leave four). Numeric phase of 5000 random rows of 36 outputs 46 -> 22 us, of
 // the 64x64 Laplacian square 36 -> 15 us.
 constexpr int kAllLds = 24576;
 
@@ -1046,17 +1045,39 @@ bool small_rows_fit(const Batch &b)
            (uint32_t)b.max_ncols <= PackBits<kFillCap[4]>::kMaxCols;
 }
 
-int small_rows_grid(int na)
+// Two launches or one per class, by the outputs and their mean per row. Numeric
+// phase in us, by class / two launches (rows x outputs, entries of A times of B):
+//   up to 512 outputs, always two: 4 x 450 (22 x 20) 44 / 19, 20000 x 450 139 / 130
+//   up to 2048, 2^20 outputs: 1000 x 900 (45 x 20) 54 / 34, 4000 x 900 82 / 96, 4 x
+//     1500 (15 x 100) 50 / 26, 1000 x 1500 59 / 98; and, past 1024, from 2^24 on,
+//     where their windows overtake the 4096-slot class again: 4000 x 1500 138 / 169,
+//     10000 x 1500 287 / 300, 20000 x 1500 573 / 541, 20000 x 1776 (30 x 60) 723 / 632
+//   more (windows either way), 2^24: 4 x 2500 (25 x 100) 90 / 26, 4000 x 2500 239 / 218,
+//     10000 x 2500 402 / 451, 16 x 20000 (200 x 100) 109 / 51, 250 x 20000 260 / 220,
+//     1000 x 20000 590 / 661
+bool num_small_fit(const Batch &b, int64_t outputs)
 {
-    const int want = na / 2 + kNumBins;   // two rows per workgroup in the larger classes
-    return want < kSmallGrid ? want : kSmallGrid;
+    if (!small_rows_fit(b)) return false;
+    const int64_t mean = outputs / b.na;
+    if (mean <= 512) return true;
+    if (mean <= 2048) return outputs <= 1ll << 20 || (mean > 1024 && outputs >= 1ll << 24);
+    return outputs <= 1ll << 24;
 }
 
-void launch_numeric_small(const Batch &b, const Sched &sc, hipStream_t s)
+// Two rows per workgroup in the larger classes, and two windows of 512 outputs in
+// the spill bin: from the rows alone, a few long ones had too few workgroups (16
+// rows of 20000 outputs: 658 us).
+int small_rows_grid(int na, int64_t outputs)
+{
+    const int64_t want = na / 2 + kNumBins + outputs / kNumWinCap;
+    return want < kSmallGrid ? (int)want : kSmallGrid;
+}
+
+void launch_numeric_small(const Batch &b, const Sched &sc, int64_t outputs, hipStream_t s)
 {
     launch_bin_small(b, sc, kNumWinCap / 2, 1, s);
     ProfScope ps("num_all", s);
-    hipLaunchKernelGGL(k_num_all, dim3(small_rows_grid(b.na)), dim3(kWG), 0, s, b, sc);
+    hipLaunchKernelGGL(k_num_all, dim3(small_rows_grid(b.na, outputs)), dim3(kWG), 0, s, b, sc);
 }
 
 void launch_numeric(const Batch &b, const Sched &sc, int G, hipStream_t s)

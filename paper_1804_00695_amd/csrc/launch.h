@@ -68,13 +68,22 @@ __global__ void k_win_scan(Batch b, Sched sc, int m, int blocks);
 // (random rows of 36 outputs, numeric / adjoint in us by class and in two
 // launches: 12000 rows 55/57 and 32/39, 20000 rows 50/58 and 46/55, 32000
 // rows 66/77 and 67/80).
+// Its workgroups hold few waves where rows are long, so products with many outputs
+// go by class: thresholds and figures at num_small_fit and bwd_small_fit
+// (outputs: entries of C, or of W).
 constexpr int kSmallRows = 20480;
-constexpr int kSmallGrid = 1280;   // five workgroups per CU
+// Five workgroups per CU; four stay resident (104 and 112 vector registers).
+// Compiled for five, with 4 and 36 registers spilled, the kernels take as long
+// (20000 rows of 36 to 450 outputs within 1 %); 1024 workgroups, 1280: numeric
+// 20000 rows of 36 outputs 39, 44 us, of 100 61, 70, of 250 113, 101, of 450 149, 131.
+constexpr int kSmallGrid = 1280;
+bool num_small_fit(const Batch &b, int64_t outputs);
+bool bwd_small_fit(const Batch &b, int64_t outputs);
 bool small_rows_fit(const Batch &b);
-int small_rows_grid(int na);
+int small_rows_grid(int na, int64_t outputs);
 void launch_bin_small(const Batch &b, const Sched &sc, int m, int blocks, hipStream_t s);
-void launch_numeric_small(const Batch &b, const Sched &sc, hipStream_t s);
-void launch_backward_small(const Batch &b, const Sched &sc, double *dA, double *dB, hipStream_t s);
+void launch_numeric_small(const Batch &b, const Sched &sc, int64_t outputs, hipStream_t s);
+void launch_backward_small(const Batch &b, const Sched &sc, double *dA, double *dB, int64_t outputs, hipStream_t s);
 
 // Numeric phase (row-range fused multiply-add) over the binned rows.
 void launch_numeric(const Batch &b, const Sched &sc, int G, hipStream_t s);

@@ -511,3 +511,63 @@ def test_window_carry(entries):
         rest = np.setdiff1d(a, np.arange(4))
         a[:] = np.sort(np.concatenate([long_rows, rest, np.setdiff1d(np.arange(10, B.nrows), rest)])[:entries])
     check(A, B)
+
+
+# few long rows of C, alone and with short ones that hide them in the mean: values
+# and adjoint on either side of the lines between two launches and one per class
+@pytest.mark.parametrize("rows,len_a,len_b,short", [
+    (1, 1, 4000, 0), (1, 3, 30000, 0), (3, 9, 7000, 0), (40, 8, 60, 0), (40, 9, 60, 0), (40, 16, 130, 0),
+    (40, 17, 130, 0), (600, 20, 100, 0), (2200, 8, 64, 0), (9000, 2, 64, 0), (17000, 2, 64, 0), (2, 9, 7000, 700)])
+def test_few_long_rows(rows, len_a, len_b, short):
+    inner, ncols = 60, 66000
+    B = rows_of([len_b] * inner, ncols, len_b)
+    if short:
+        B = rows_of([len_b] * (inner - 1) + [1], ncols, len_b)   # its last row for the short ones
+    A = rows_of([len_a] * rows + [0, 1] * short, inner, rows)
+    for i in range(rows + 1, A.nrows, 2):
+        A.col_idx[A.row_ptr[i]] = inner - 1
+    R = check(A, B)
+    W = synth.Csr(R.nrows, R.ncols, R.row_ptr, R.col_idx, synth.normal_values(R.nnz, 3))
+    gA, gB = mls.backward(*[mls.DeviceCsr.from_host(M) for M in (A, B, W)])
+    rA, rB, aA, aB = oracle.backward(A, B, W)
+    assert np.all(np.abs(gA.cpu().numpy() - rA) <= 1e-10 * aA)
+    assert np.all(np.abs(gB.cpu().numpy() - rB) <= 1e-10 * aB)
+
+
+# and their time against the launches by class, which they fell behind 4 to 20
+# times while the grid came from the rows alone
+@pytest.mark.parametrize("what", ["numeric", "adjoint"])
+@pytest.mark.parametrize("rows,len_a", [(16, 40), (16, 400)])
+def test_few_long_rows_time(rows, len_a, what):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+
+    def regular(m, n, k):
+        step = n // k
+        c = torch.arange(k, device="cuda") * step + torch.randint(0, step, (m, k), generator=g, device="cuda")
+        return mls.DeviceCsr(m, n, (torch.arange(m + 1, device="cuda") * k).to(torch.int32), c.to(torch.int32).view(-1),
+                             torch.randn(m * k, generator=g, dtype=torch.float64, device="cuda"))
+    A, B = regular(rows, 20000, len_a), regular(20000, 65536, 1500 if len_a == 40 else 200)
+    C = mls.symbolic(A, B)
+    W = mls.numeric(A, B, C)
+
+    def best():
+        t = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(3):
+                if what == "numeric":
+                    mls.numeric(A, B, C)
+                else:
+                    mls.backward(A, B, W, check_structure=False)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return min(t[1:])
+    now = best()
+    mls.set_option(mls._abi.OPT_GROUP_SIZE, 32)
+    try:
+        assert now < 2.0 * best()
+    finally:
+        mls.set_option(mls._abi.OPT_GROUP_SIZE, 0)
