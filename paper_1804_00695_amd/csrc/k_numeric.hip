@@ -25,6 +25,7 @@
 // step go in rounds so that every c_ij still gets its terms in ascending k.
 #include <climits>
 #include <cstdio>
+#include <type_traits>
 
 #include "common.h"
 #include "launch.h"
@@ -212,7 +213,18 @@ __device__ __forceinline__ void first_b(const Prob &P, FirstChunk &f)
 // entry (one wave's LDS adds take effect in program order), which keeps every
 // c_ij's terms in ascending k. Columns outside [jlo, jhi] are another
 // window's. Returns whether a column was not found.
-template <int D, typename TAB>
+// A step's rounds of adds: one per entry that has pairs in it, or (FEW) per entry
+// that has an output in the window. Short rows of B make many entries per step,
+// and a window takes few of their pairs, as rows of up to 32 are not narrowed:
+// chunks of kWinRounds entries per step and more are taken so. Rows of 6000
+// outputs, rows of B of 1, 2, 4, 8 and 16 entries: 4139, 2231, 1471, 911 and 691 us
+// with a round for each, 2021, 1301, 1079, 844 and 601 us so (one add per collision, which needs a word of
+// LDS per output and three passes over it: 1915, 1356, 1183, 1126 and 1077). Rows of
+// 1500 outputs in one table, whose pairs all hit, lose by it: rows of B of 1
+// entry 3336, 4626 us (8978 by collisions).
+constexpr int kWinRounds = 8;
+
+template <int D, bool FEW, typename TAB>
 __device__ __forceinline__ bool flat_tile(const TAB &tab, double *acc, const int4 *par, uint32_t *flags,
                                           int lane, int base, int first, bool nonempty, int total, int &eb,
                                           const MLS_G int32_t *bci, const MLS_G double *bval, int jlo, int jhi)
@@ -257,15 +269,23 @@ __device__ __forceinline__ bool flat_tile(const TAB &tab, double *acc, const int
         const bool hit = ok[d] && posv[d] <= TAB::kMaxPos;
         bad |= ok[d] && !hit;
         const double t = av[d] * bv[d];
-        for (int r = 0; r <= more[d]; ++r)
-            if (hit && rel[d] == r) atomicAdd(acc + posv[d], t);
+        if constexpr (!FEW) {
+            for (int r = 0; r <= more[d]; ++r)
+                if (hit && rel[d] == r) atomicAdd(acc + posv[d], t);
+        } else {
+            for (unsigned long long pend = __ballot(hit); pend;) {
+                const bool mine = hit && rel[d] == __builtin_amdgcn_readlane(rel[d], __ffsll((long long)pend) - 1);
+                if (mine) atomicAdd(acc + posv[d], t);
+                pend &= ~__ballot(mine);
+            }
+        }
     }
     return bad;
 }
 
 constexpr int kFlatWords = 16;   // start bits of a tile of 8 steps
 
-template <int DEPTH, typename TAB>
+template <int DEPTH, bool WIN, typename TAB>
 __device__ __forceinline__ bool flat_chunk(const TAB &tab, double *acc, int4 *par, uint32_t *flags,
                                            int lane, int q0, int q1, double a, const MLS_G int32_t *bci,
                                            const MLS_G double *bval, int jlo, int jhi)
@@ -280,19 +300,24 @@ __device__ __forceinline__ bool flat_chunk(const TAB &tab, double *acc, int4 *pa
         par[__popcll(ne & ((1ull << lane) - 1ull))] = make_int4(q0 - first, 0, __double2loint(a), __double2hiint(a));
     bool bad = false;
     int eb = -1;
-    for (int base = 0; base < total;) {
-        // (the tail in smaller tiles: a step past the pairs costs as much as any)
-        const int steps = (total - base + kWave - 1) / kWave;
-        if (steps > DEPTH / 2) {
-            bad |= flat_tile<DEPTH>(tab, acc, par, flags, lane, base, first, np > 0, total, eb, bci, bval,
-                                    jlo, jhi);
-            base += DEPTH * kWave;
-        } else {
-            bad |= flat_tile<2>(tab, acc, par, flags, lane, base, first, np > 0, total, eb, bci, bval, jlo,
-                                jhi);
-            base += 2 * kWave;
+    auto tiles = [&](auto few) {
+        constexpr bool FEW = decltype(few)::value;
+        for (int base = 0; base < total;) {
+            // (the tail in smaller tiles: a step past the pairs costs as much as any)
+            const int steps = (total - base + kWave - 1) / kWave;
+            if (steps > DEPTH / 2) {
+                bad |= flat_tile<DEPTH, FEW>(tab, acc, par, flags, lane, base, first, np > 0, total, eb, bci, bval,
+                                             jlo, jhi);
+                base += DEPTH * kWave;
+            } else {
+                bad |= flat_tile<2, FEW>(tab, acc, par, flags, lane, base, first, np > 0, total, eb, bci, bval, jlo,
+                                         jhi);
+                base += 2 * kWave;
+            }
         }
-    }
+    };
+    if (WIN && total <= kWave / kWinRounds * __popcll(ne)) tiles(std::true_type{});
+    else tiles(std::false_type{});
     nwave_sync();
     return bad;
 }
@@ -622,7 +647,7 @@ __device__ __forceinline__ void num_lds_rows(const Batch &b, const Sched &sc, in
                 }
             };
             if constexpr (LONG)
-                bad |= flat_chunk<kNumDepth>(tab, acc, par, flags, lane, eq0, eq1, ea, bci, bval,
+                bad |= flat_chunk<kNumDepth, false>(tab, acc, par, flags, lane, eq0, eq1, ea, bci, bval,
                                              INT_MIN, INT_MAX);
             for (int u0 = 0; !LONG && u0 < n; u0 += kNumDepth) {
                 // The staged entries are read together (all G are written every
@@ -900,7 +925,7 @@ __device__ __forceinline__ void num_win_rows(const Batch &b, const Sched &sc, ch
                         }
                     }
                 }
-                bad |= flat_chunk<kWinDepth>(tab, acc, par, flags, lane, sq0, sq1, sa, bci, bval, jlo, jhi);
+                bad |= flat_chunk<kWinDepth, true>(tab, acc, par, flags, lane, sq0, sq1, sa, bci, bval, jlo, jhi);
             }
             for (int e = lane; e < n; e += G) cval[cs + e] = acc[e];
             nwave_sync();

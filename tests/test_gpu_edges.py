@@ -571,3 +571,56 @@ def test_few_long_rows_time(rows, len_a, what):
         assert now < 2.0 * best()
     finally:
         mls.set_option(mls._abi.OPT_GROUP_SIZE, 0)
+
+
+# rows of B of one to many entries under long rows of A, in spill windows (few of a
+# step's pairs hit) and in one table: up to 64 entries in a step, columns that
+# ascend, repeat and descend from entry to entry
+@pytest.mark.parametrize("order", ["ascending", "same", "descending", "random"])
+@pytest.mark.parametrize("len_b", [1, 2, 7, 8, 9, 16, 33])
+@pytest.mark.parametrize("outputs", [1500, 5000])
+def test_short_rows_of_b(outputs, len_b, order):
+    n, g = 3000, synth.rng(len_b)
+    k = np.arange(n)
+    start = {"ascending": k * (outputs - len_b) // n, "same": k % 3, "descending": (n - 1 - k) * (outputs - len_b) // n,
+             "random": g.integers(0, outputs - len_b + 1, n)}[order]
+    ci = start[:, None] + np.arange(len_b)
+    ci[-1] = outputs - len_b + np.arange(len_b)
+    rp = np.arange(n + 1) * len_b
+    B = synth.Csr(n, outputs, rp.astype(np.int32), ci.astype(np.int32).ravel(), g.standard_normal(n * len_b))
+    A = rows_of([n, 1, 63, 64, 65, 900, 2999, n], n, 4)
+    check(A, B)
+    mls.set_option(mls._abi.OPT_GROUP_SIZE, 64)   # by class
+    try:
+        check(A, B)
+    finally:
+        mls.set_option(mls._abi.OPT_GROUP_SIZE, 0)
+
+
+# and the time of such windows against as many pairs of rows of 16 entries, which
+# differ by the entries of A read, 16 times as many, but not by rounds of adds (up
+# to 64 per step were made: 6 times the time)
+def test_short_rows_of_b_time():
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    n = 200000
+
+    def best(k, per):
+        m = 2000
+        c = torch.arange(k, device="cuda") * (n // k) + torch.randint(0, n // k, (m, k), generator=g, device="cuda")
+        A = mls.DeviceCsr(m, n, (torch.arange(m + 1, device="cuda") * k).to(torch.int32), c.to(torch.int32).view(-1),
+                          torch.ones(m * k, dtype=torch.float64, device="cuda"))
+        ci = torch.arange(per, device="cuda") * (n // per) + torch.randint(0, n // per, (n, per), generator=g,
+                                                                            device="cuda")
+        B = mls.DeviceCsr(n, n, (torch.arange(n + 1, device="cuda") * per).to(torch.int32),
+                          ci.to(torch.int32).view(-1), torch.ones(n * per, dtype=torch.float64, device="cuda"))
+        C, t = mls.symbolic(A, B), []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            mls.numeric(A, B, C)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return min(t[1:])
+    assert best(6000, 1) < 4.5 * best(375, 16)
