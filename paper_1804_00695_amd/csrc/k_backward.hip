@@ -46,7 +46,7 @@ constexpr int nw_bwd(int row_bytes, int rows_per_wave, int lds = 65536)
 // values beside them. A column takes the first empty slot at or after the
 // start of its home bucket, so a bucket's filled slots are a prefix of it and
 // a bucket whose last slot is empty ends a search.
-__device__ __forceinline__ uint32_t w_home(int logcap, int j) { return hslot((uint32_t)j, logcap - 2) << 2; }
+__device__ __forceinline__ uint32_t w_home(int logcap, int j) { return hslot32((uint32_t)j, logcap - 2) << 2; }
 
 __device__ __forceinline__ void w_insert(int *key, double *wv, int logcap, int j, double w)
 {

@@ -218,10 +218,10 @@ __device__ __forceinline__ void first_b(const Prob &P, FirstChunk &f)
 // and a window takes few of their pairs, as rows of up to 32 are not narrowed:
 // chunks of kWinRounds entries per step and more are taken so. Rows of 6000
 // outputs, rows of B of 1, 2, 4, 8 and 16 entries: 4139, 2231, 1471, 911 and 691 us
-// with a round for each, 2021, 1301, 1079, 844 and 601 us so (one add per collision, which needs a word of
-// LDS per output and three passes over it: 1915, 1356, 1183, 1126 and 1077). Rows of
-// 1500 outputs in one table, whose pairs all hit, lose by it: rows of B of 1
-// entry 3336, 4626 us (8978 by collisions).
+// with a round for each, 2021, 1301, 1079, 844 and 601 us so (one add per
+// collision, which needs a word of LDS per output and three passes over it: 1915,
+// 1356, 1183, 1126 and 1077). Rows of 1500 outputs in one table, whose pairs all
+// hit, lose by it: rows of B of 1 entry 3336, 4626 us (8978 by collisions).
 constexpr int kWinRounds = 8;
 
 template <int D, bool FEW, typename TAB>

@@ -98,7 +98,7 @@ struct PosTab {
                 h = (h + (4u << LB)) & bm;
             }
         } else {
-            uint32_t h = hslot((uint32_t)j, logcap);
+            uint32_t h = hslot32((uint32_t)j, logcap);
             int2 *tab = (int2 *)t;
             for (uint32_t probe = 0; probe < cap; ++probe) {
                 int old = atomicCAS(&tab[h].x, -1, j);
@@ -135,7 +135,7 @@ struct PosTab {
             return m <= kMaxPos || BT::last(w) == kEmpty ? m : find_more(key, h);
         } else {
             const uint32_t cap = 1u << logcap;
-            uint32_t h = hslot((uint32_t)j, logcap);
+            uint32_t h = hslot32((uint32_t)j, logcap);
             const int2 *tab = (const int2 *)t;
             for (uint32_t probe = 0; probe < cap; ++probe) {
                 const int2 v = tab[h];

@@ -624,3 +624,43 @@ def test_short_rows_of_b_time():
             t.append(a.elapsed_time(b))
         return min(t[1:])
     assert best(6000, 1) < 4.5 * best(375, 16)
+
+
+# columns that lie powers of two apart, in matrices too wide for packed tables:
+# values, and the time against neighbouring columns (all hashed to one slot, the
+# numeric phase took 19 times as long)
+@pytest.mark.parametrize("log_step", [16, 20, 24])
+def test_wide_strides(log_step):
+    n = (1 << 31) - 1
+    k = min(100, n >> log_step)
+    g = synth.rng(log_step)
+    A = synth.poisson_csr(4000, 2000, 3.0, 1)
+    v = g.standard_normal(2000 * k)
+
+    def factor(step):
+        ci = (np.arange(2000) % 500)[:, None] + np.arange(k, dtype=np.int64) * step
+        return synth.Csr(2000, n, (np.arange(2001) * k).astype(np.int32), ci.astype(np.int32).ravel(), v)
+    far, near = factor(1 << log_step), factor(1)
+    dA, dB = mls.DeviceCsr.from_host(A), mls.DeviceCsr.from_host(far)
+    C = mls.spgemm(dA, dB)
+    # columns (base, multiple) of far map one to one to those of a narrow product
+    small = synth.Csr(2000, 500 * k, far.row_ptr, ((np.arange(2000) % 500)[:, None] * k + np.arange(k)).astype(np.int32)
+                      .ravel(), v)
+    R, _ = oracle.spgemm(A, small)
+    wide = (R.col_idx % k).astype(np.int64) << log_step | R.col_idx // k
+    order = np.lexsort((wide, np.repeat(np.arange(4000), np.diff(R.row_ptr))))
+    rp, ci, cv = C.numpy()
+    assert np.array_equal(rp, R.row_ptr) and np.array_equal(ci, wide[order]) and np.array_equal(cv, R.values[order])
+
+    def best(dB):
+        C, t = mls.symbolic(dA, dB), []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            mls.numeric(dA, dB, C)
+            mls.backward(dA, dB, C, check_structure=False)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return min(t[1:])
+    assert best(dB) < 2.5 * best(mls.DeviceCsr.from_host(near))
