@@ -1035,27 +1035,23 @@ __global__ void k_tr_rowptr(int32_t n, const int64_t *prefix, int32_t *trp)
 
 constexpr int kTrLanes = 8;   // lanes per row of the scatter (their atomics are independent)
 
-// Workgroups of the kernels with several lanes per row: at most 2^23, as a
-// launch holds less than 2^32 threads; they go on to further rows.
-constexpr int64_t kTrMaxGrid = 1 << 23;
-static unsigned tr_grid(int64_t rows, int lanes)
-{
-    const int64_t per = kWG / lanes;
-    return (unsigned)std::min<int64_t>((rows + per - 1) / per, kTrMaxGrid);
-}
+// Rows per launch of the kernels with several lanes per row: a launch holds less
+// than 2^32 threads.
+constexpr int64_t kTrSlice = 1 << 27;
 
-__global__ __launch_bounds__(kWG) void k_tr_scatter(int32_t nrows, const int32_t *rp, const int32_t *ci, const double *v,
-                                                    const int32_t *trp, int32_t *cursor, int32_t *tci, double *tv)
+__global__ __launch_bounds__(kWG) void k_tr_scatter(int64_t row0, int32_t nrows, const int32_t *rp, const int32_t *ci,
+                                                    const double *v, const int32_t *trp, int32_t *cursor, int32_t *tci,
+                                                    double *tv)
 {
     const int64_t t = (int64_t)blockIdx.x * kWG + threadIdx.x;
-    for (int64_t i = t / kTrLanes; i < nrows; i += (int64_t)gridDim.x * (kWG / kTrLanes)) {
-        const uint32_t e = (uint32_t)gp(rp)[i + 1];   // (unsigned: the last step may end past the largest int)
-        for (uint32_t p = (uint32_t)(gp(rp)[i] + (int)(t % kTrLanes)); p < e; p += kTrLanes) {
-            const int c = gp(ci)[p];
-            const int pos = gp(trp)[c] + atomicAdd(cursor + c, 1);
-            gpw(tci)[pos] = (int32_t)i;
-            if (v) gpw(tv)[pos] = gp(v)[p];
-        }
+    const int64_t i = row0 + t / kTrLanes;
+    if (i >= nrows) return;
+    const uint32_t e = (uint32_t)gp(rp)[i + 1];   // (unsigned: the last step may end past the largest int)
+    for (uint32_t p = (uint32_t)(gp(rp)[i] + (int)(t % kTrLanes)); p < e; p += kTrLanes) {
+        const int c = gp(ci)[p];
+        const int pos = gp(trp)[c] + atomicAdd(cursor + c, 1);
+        gpw(tci)[pos] = (int32_t)i;
+        if (v) gpw(tv)[pos] = gp(v)[p];
     }
 }
 
@@ -1069,11 +1065,12 @@ constexpr int kTrGroup = 16;
 constexpr int kTrPer = 8;                       // entries per lane of a wave's row
 constexpr int kTrSortMax = kTrPer * kWave;
 
-// the group's row r (none: r >= n); all lanes of the wave active
-__device__ __forceinline__ void tr_sort_row(int64_t r, int32_t n, const int32_t *trp, int32_t *tci, double *tv,
-                                            int lane, int *c)
+__global__ __launch_bounds__(kWG) void k_tr_sort(int64_t row0, int32_t n, const int32_t *trp, int32_t *tci, double *tv)
 {
-    const int l = lane % kTrGroup;
+    __shared__ int s_c[kWG / kWave][kTrSortMax];
+    const int lane = threadIdx.x & 63, l = lane % kTrGroup;
+    int *c = s_c[threadIdx.x >> 6];
+    const int64_t r = row0 + ((int64_t)blockIdx.x * kWG + threadIdx.x) / kTrGroup;
     const int s = r < n ? gp(trp)[r] : 0, e = r < n ? gp(trp)[r + 1] : 0;
     const int len = e - s;
     const bool mine = len <= kTrGroup && l < len;
@@ -1136,15 +1133,6 @@ __device__ __forceinline__ void tr_sort_row(int64_t r, int32_t n, const int32_t 
     }
 }
 
-__global__ __launch_bounds__(kWG) void k_tr_sort(int32_t n, const int32_t *trp, int32_t *tci, double *tv)
-{
-    __shared__ int s_c[kWG / kWave][kTrSortMax];
-    constexpr int per = kWG / kTrGroup;
-    const int g = (int)threadIdx.x / kTrGroup;
-    for (int64_t r0 = (int64_t)blockIdx.x * per; r0 < n; r0 += (int64_t)gridDim.x * per)
-        tr_sort_row(r0 + g, n, trp, tci, tv, (int)(threadIdx.x & 63), s_c[threadIdx.x >> 6]);
-}
-
 void launch_transpose(int32_t nrows, int32_t ncols, int64_t nnz, const int32_t *rp, const int32_t *ci, const double *v,
                       int32_t *trp, int32_t *tci, double *tv, int32_t *cursor, int64_t *tile_sum, int64_t *prefix,
                       int32_t *cnt, hipStream_t s)
@@ -1154,11 +1142,15 @@ void launch_transpose(int32_t nrows, int32_t ncols, int64_t nnz, const int32_t *
     if (nnz > 0) hipLaunchKernelGGL(k_tr_count, dim3((unsigned)((nnz + kWG - 1) / kWG)), dim3(kWG), 0, s, nnz, ci, cnt);
     launch_scan(cnt, ncols, tile_sum, prefix, s);
     hipLaunchKernelGGL(k_tr_rowptr, dim3((ncols + kWG) / kWG), dim3(kWG), 0, s, ncols, prefix, trp);
-    if (nrows > 0)
-        hipLaunchKernelGGL(k_tr_scatter, dim3(tr_grid(nrows, kTrLanes)), dim3(kWG), 0, s, nrows, rp, ci, v, trp, cursor,
+    auto grid = [](int64_t rows, int lanes) {
+        const int64_t per = kWG / lanes;
+        return dim3((unsigned)((std::min(rows, kTrSlice) + per - 1) / per));
+    };
+    for (int64_t r = 0; r < nrows; r += kTrSlice)
+        hipLaunchKernelGGL(k_tr_scatter, grid(nrows - r, kTrLanes), dim3(kWG), 0, s, r, nrows, rp, ci, v, trp, cursor,
                            tci, tv);
-    if (ncols > 0)
-        hipLaunchKernelGGL(k_tr_sort, dim3(tr_grid(ncols, kTrGroup)), dim3(kWG), 0, s, ncols, trp, tci, tv);
+    for (int64_t r = 0; r < ncols; r += kTrSlice)
+        hipLaunchKernelGGL(k_tr_sort, grid(ncols - r, kTrGroup), dim3(kWG), 0, s, r, ncols, trp, tci, tv);
 }
 
 // out[e] = X(r, c) for the e-th entry (r, c) of pattern P, else 0.0

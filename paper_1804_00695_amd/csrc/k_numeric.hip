@@ -7,14 +7,16 @@
 // LDS path: G lanes own a row of C. Its (sorted) columns are loaded once into
 // an LDS hash mapping column -> position in the row, next to an LDS array of
 // fp64 accumulators in row order. When C has few enough columns, a table slot
-// packs column and position into one 32-bit word. The entries of row i of A are taken in
-// stored order; for each, the G lanes take distinct entries of B_k, so no two
-// lanes of a step touch the same accumulator and every c_ij receives its
-// terms in ascending k -- the order of the row-wise formulation. Products are
-// rounded before the add (compiled without contraction), so the result equals
-// a sequential dense-accumulator evaluation bit for bit. The B loads of a
-// batch of steps are all issued, without branches, before the first of them
-// is used, to hide HBM/L2 latency.
+// packs column and position into one 32-bit word. The entries of row i of A are
+// taken in stored order, G at a time. With 8 lanes or a whole wave per row their
+// (entry, position in B_k) pairs are laid end to end, one per lane, and lanes of a
+// step that belong to different entries add entry by entry; with 16 or 32 lanes
+// a step is one entry, whose lanes hold distinct columns of B_k. Either way every
+// c_ij receives its terms in ascending k -- the order of the row-wise
+// formulation. Products are rounded before the add (compiled without
+// contraction), so the result equals a sequential dense-accumulator evaluation bit
+// for bit. The B loads of a batch of steps are all issued, without branches, before
+// the first of them is used, to hide HBM/L2 latency.
 //
 // Spill path (rows with more outputs than the largest LDS class holds): the
 // row's outputs are cut into windows of consecutive positions of C, each a

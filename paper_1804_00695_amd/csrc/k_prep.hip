@@ -36,8 +36,8 @@ __global__ void k_zero2_f64(double *p, int64_t n, double *q, int64_t m)
 // to 64) hold one contiguous run of entries, which the wave walks 64 at a time
 // whatever the rows' lengths, with the loads of a tile of kTileSteps steps in
 // flight. A bit per entry of the tile tells where a (non-empty) row starts.
-// Positions in the stream are unsigned, and a lane counts from its tile on: a tile's
-// end may lie past the largest int (the entry limit).
+// Positions in the stream are unsigned: a tile's end, and a lane's position behind
+// the run's end, may lie past the largest int (the entry limit).
 constexpr int kTileSteps = 8;
 constexpr int kTileEntries = kTileSteps * kWave;
 
@@ -413,13 +413,11 @@ __global__ __launch_bounds__(kWG) void k_work(Batch b, int rw, Sched sc)
         const int k_lo = P.k_lo, k_hi = P.k_hi;
         const uint32_t q0 = (uint32_t)__builtin_amdgcn_readlane(s, l0), q1 = (uint32_t)__builtin_amdgcn_readlane(e, l1);
         for (uint32_t tb = q0; tb < q1; tb += kTileEntries) {
-            const MLS_G int32_t *at = aci + tb;
-            const uint32_t left = q1 - tb;
             int cv[kTileSteps];
 #pragma unroll
             for (int u = 0; u < kTileSteps; ++u) {
-                const uint32_t x = (uint32_t)(u * kWave + lane);
-                cv[u] = *(x < left ? at + x : (const MLS_G int32_t *)k_ones4);
+                const uint32_t q = tb + (uint32_t)(u * kWave + lane);
+                cv[u] = *(q < q1 ? aci + q : (const MLS_G int32_t *)k_ones4);
             }
 #pragma unroll
             for (int u = 0; u < kTileSteps; ++u)

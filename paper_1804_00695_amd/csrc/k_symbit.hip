@@ -344,7 +344,7 @@ __global__ __launch_bounds__(kBitLongWG) void k_bit_long(Batch b, Sched sc, int 
 }
 
 // Row pointers and nnz(C) of one product of few rows from the rows' counts,
-// one workgroup, 8 rows per thread and step (three launches otherwise).
+// one workgroup, 8 rows per thread and step (four launches otherwise).
 constexpr int kRowptrWG = 1024;
 constexpr int kRowptrPer = 8;
 
