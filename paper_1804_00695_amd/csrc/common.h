@@ -401,10 +401,10 @@ __device__ __forceinline__ int seq_compact(bool nonempty, int q, int slot, int l
 }
 
 // Starts in a wave's tile handed over by compares (2 to 3 instructions per step
-// each, no cross-lane chain) rather than by start bits: the rows set aside of the
-// dense-bitmap count and fill, R-MAT 16 square, 492 and 657 us, with bits
-// always 719 and 876 us; their short rows, 230 and 523, with compares always
-// 230 and 578 us.
+// each, no cross-lane chain) rather than by start bits: the dense-bitmap count and
+// fill of the R-MAT 16 square with every row of more than 64 entries set aside,
+// those rows 492 and 657 us, with bits always 719 and 876 us; the short ones 230
+// and 523, with compares always 230 and 578 us.
 constexpr int kSeqFew = 6;
 
 // One tile of that sequence, SB elements per lane, loads in flight together:

@@ -58,10 +58,11 @@ template <> struct BitSrc<true> {
 
 // Rows of at most kBitRowWork multiply-adds (and entries of A), one per wave (dealt
 // round-robin: their sizes vary), 64 entries of A at a time; the others go to
-// the list in sc.perm, counted in the spill bin's count (a wave lists up to 64
-// with one atomic: on one address they take some 10 ns each). R-MAT 16 square,
-// count and fill: 297 and 525 us with a bisection per pair and no row in flight,
-// 230 and 481 us; 60000 random rows of 64 outputs: 85 and 175 us, 59 and 128 us.
+// the list in sc.perm, counted in the spill bin's count, up to 64 of a wave's with
+// one atomic. R-MAT 16 square, count and fill: 297 and 525 us with a bisection
+// per pair and no row in flight, 231 and 467 us with the pairs as a sequence and
+// an atomic per row set aside, 104 and 323 us; 60000 random rows of 64 outputs
+// (none set aside) 85 and 175, 61 and 128, 66 and 120 us.
 template <bool FILL, bool WORDS>
 __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
 {
@@ -216,7 +217,8 @@ __global__ __launch_bounds__(kWG) void k_bit_rows(Batch b, Sched sc, int words)
 // The rows set aside, a workgroup each: the columns of their rows of B as one
 // sequence, an equal share of it per wave. R-MAT 16 square, count and fill: 750
 // and 1011 us with 64-column pieces found by bisection and a thread writing a
-// run of columns, 492 and 657 us.
+// run of columns, 488 and 653 us so, 450 and 638 us with rows of up to
+// kBitRowWork multiply-adds left to the waves.
 template <bool FILL, bool WORDS>
 __global__ __launch_bounds__(kBitLongWG) void k_bit_long(Batch b, Sched sc, int words)
 {

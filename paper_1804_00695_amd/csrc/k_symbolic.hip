@@ -151,7 +151,7 @@ __device__ __forceinline__ void sym_first_b(const Batch &b, const SymRow &m, Sym
 // A lane per row of B (which this replaces) read a line per lane and load, and
 // its longest row of B held up the group; end to end, a load reads the words of
 // few rows. 27-point stencil square on 128^3, 256- and 512-slot rows: 1520 and
-// 414 us so, 1057 and 334 us now (with 32 instead of 16 lanes for the first,
+// 414 us so, 1063 and 338 us now (with 32 instead of 16 lanes for the first,
 // and the table read back four slots a lane without loops over them).
 
 // Waves per SIMD that the count kernel's LDS leaves resident (160 KB per CU,
