@@ -344,12 +344,14 @@ void launch_tc(const Batch &b, const Sched &sc, int64_t *counts, unsigned long l
     // per row of the graph, first and second class: 32 lanes with 4 steps at 8
     // (spills) and 7 waves 146 and 138 us, with 2 steps 158; 16 lanes 177, 64
     // 265. 64 lanes with 2, 4, 8 steps 179, 184, 231; 4 steps at 7 and 6 waves
-    // 192 and 208.
+    // 192 and 208. The two largest tables leave 5 and 2 waves by LDS, and registers
+    // for more steps: uniform graph of 30000 vertices, mean degree 1200, whole count,
+    // 2, 4 and 8 steps 14.1, 10.2 and 8.3 ms (14.6 with pieces of 8 words per lane).
     launch_tc_class<32, kTcCap[0], 4, 7>(b, sc, 0, counts, s);
     launch_tc_class<64, kTcCap[1], 2, 8>(b, sc, 1, counts, s);
     launch_tc_class<64, kTcCap[2], 2, 8>(b, sc, 2, counts, s);
-    launch_tc_class<64, kTcCap[3], 2, 8>(b, sc, 3, counts, s);
-    launch_tc_class<64, kTcCap[4], 2, 8>(b, sc, 4, counts, s);
+    launch_tc_class<64, kTcCap[3], 8, 4>(b, sc, 3, counts, s);
+    launch_tc_class<64, kTcCap[4], 8, 4>(b, sc, 4, counts, s);
     {
         ProfScope ps("tc_spill", s);
         hipLaunchKernelGGL(k_tc_spill, dim3(spill_slots), dim3(kWG), 0, s, b, sc, counts, spill_bitmaps, spill_words);
