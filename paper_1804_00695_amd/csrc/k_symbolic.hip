@@ -22,13 +22,17 @@
 namespace mls {
 
 constexpr uint32_t kEmptyKey = 0xffffffffu;
-// Words per lane loaded before they are inserted. More in a batch's count: its
-// kernels run at fewer waves per SIMD and its rows have few words, most of
-// which one tile then takes (20 Galerkin setups, 64- and 256-slot rows: 140 and
-// 67 us with 4, 128 and 47 with these; a single random product of 300k rows
-// loses, 141 -> 159 and 83 -> 91 us, and past 16 lanes registers spill).
+// Words per lane loaded before they are inserted. More in a batch's count of 16
+// lanes per row, and of 8 in batches of up to kSymManyRows rows: its kernels run
+// at fewer waves per SIMD and its rows have few words, most of which one tile
+// then takes (20 Galerkin setups, 64- and 256-slot rows: 140 and 67 us with 4, 128
+// and 47 with 8 and 6; a single random product of 300k rows loses, 141 -> 159 and 83
+// -> 91 us, and past 16 lanes registers spill). With more rows a wave less per SIMD
+// costs more than the tiles save: A P of 20 grids of 24^3, 32^3 and 40^3, whole
+// symbolic phase, 330, 386 and 580 us with 4 words, 320, 457 and 620 with 8.
 template <int G, bool FILL, bool MULTI>
 constexpr int sym_batch() { return !FILL && MULTI ? (G == 8 ? 8 : (G == 16 ? 6 : 4)) : 4; }
+constexpr int kSymManyRows = 1 << 19;
 
 constexpr int kExpandSmall = 16;   // rows with at most this many words take the 16-lane kernel
 constexpr int kExpandMid = 32;     // rows with at most this many words take the 32-lane kernel
@@ -169,12 +173,11 @@ constexpr int sym_count_waves()
     return w > cap ? cap : (w < 1 ? 1 : w);
 }
 
-template <int G, int CAP, bool FILL, bool MULTI>
+template <int G, int CAP, bool FILL, bool MULTI, int SB = sym_batch<G, FILL, MULTI>()>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(FILL ? 1 : sym_count_waves<G, CAP, MULTI>())))
 void k_sym_lds(Batch b, Sched sc, int bin)
 {
     constexpr int W = kWave / G;
-    constexpr int SB = sym_batch<G, FILL, MULTI>();
     constexpr int ROWB = FILL ? CAP * 12 : CAP * 8;
     constexpr int NW = nw_for(ROWB, W);
     constexpr int LIST = FILL ? CAP / 2 : 1;
@@ -903,6 +906,13 @@ static void launch_sym_class(const Batch &b, const Sched &sc, int bin, hipStream
     if (!name[0]) snprintf(name, sizeof(name), "sym_%s_lds_G%d_C%d", FILL ? "fill" : "count", G, CAP);
     ProfScope ps(name, s);
     if (b.nprob > 1) {
+        if constexpr (G == 8 && !FILL) {
+            if (b.na > kSymManyRows) {
+                static int grid = persistent_grid(k_sym_lds<G, CAP, FILL, true, 4>, NW * kWave);
+                hipLaunchKernelGGL((k_sym_lds<G, CAP, FILL, true, 4>), dim3(grid), dim3(NW * kWave), 0, s, b, sc, bin);
+                return;
+            }
+        }
         static int grid = persistent_grid(k_sym_lds<G, CAP, FILL, true>, NW * kWave);
         hipLaunchKernelGGL((k_sym_lds<G, CAP, FILL, true>), dim3(grid), dim3(NW * kWave), 0, s, b, sc, bin);
     } else {

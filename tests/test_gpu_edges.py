@@ -664,3 +664,16 @@ def test_wide_strides(log_step):
             t.append(a.elapsed_time(b))
         return min(t[1:])
     assert best(dB) < 2.5 * best(mls.DeviceCsr.from_host(near))
+
+
+# batches on either side of 2^19 rows, whose small count class loads its words
+# differently
+@pytest.mark.parametrize("rows", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1])
+def test_batch_rows(rows):
+    As = [synth.poisson_csr(m, 300, 2.5, m) for m in (rows, 1 << 18)]
+    Bs = [synth.poisson_csr(300, 66000 + i, 2.0, 50 + i) for i in range(2)]
+    dA, dB = [[mls.DeviceCsr.from_host(M) for M in Ms] for Ms in (As, Bs)]
+    for A, B, C in zip(As, Bs, mls.batch_numeric(dA, dB, mls.batch_symbolic(dA, dB))):
+        R, _ = oracle.spgemm(A, B)
+        rp, ci, v = C.numpy()
+        assert np.array_equal(rp, R.row_ptr) and np.array_equal(ci, R.col_idx) and np.array_equal(v, R.values)

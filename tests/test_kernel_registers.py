@@ -53,8 +53,9 @@ def waves(vgprs):
 
 
 # the count pass of the 256-slot class with 32 lanes per row: 6 waves per SIMD
-# for one product, 5 for batches, and nothing in scratch memory
-@pytest.mark.parametrize("multi,resident", [(0, 6), (1, 5)])
-def test_count_kernel(kernels, multi, resident):
-    k = kernels[f"_ZN3mls9k_sym_ldsILi32ELi256ELb0ELb{multi}EEEvNS_5BatchENS_5SchedEi"]
+# for one product, 5 for batches; of the 64-slot class in batches of many rows,
+# 5; and nothing in scratch memory
+@pytest.mark.parametrize("lanes,slots,multi,resident", [(32, 256, 0, 6), (32, 256, 1, 5), (8, 64, 1, 5)])
+def test_count_kernel(kernels, lanes, slots, multi, resident):
+    k = kernels[f"_ZN3mls9k_sym_ldsILi{lanes}ELi{slots}ELb0ELb{multi}ELi4EEEvNS_5BatchENS_5SchedEi"]
     assert waves(k[".vgpr_count"]) >= resident and k[".vgpr_spill_count"] == 0
