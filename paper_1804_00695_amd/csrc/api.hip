@@ -281,7 +281,7 @@ spgemm_status prepare_batch(int32_t nbatch, const spgemm_csr *A, const spgemm_cs
     bt.abase = (const int32_t *)(ws + out.layout.abase);
     bt.bbase = (const int32_t *)(ws + out.layout.bbase);
     out.zc = 0;
-    for (int t = 0; C && t < nbatch; ++t) out.zc += C[t].nnz;
+    for (int t = 0; C && t < nbatch; ++t) out.zc += std::max<int64_t>(C[t].nnz, 0);
     out.za = za;
     out.zb = zb;
     out.avg_a = na > 0 ? (double)za / (double)na : 1.0;

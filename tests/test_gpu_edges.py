@@ -677,3 +677,21 @@ def test_batch_rows(rows):
         R, _ = oracle.spgemm(A, B)
         rp, ci, v = C.numpy()
         assert np.array_equal(rp, R.row_ptr) and np.array_equal(ci, R.col_idx) and np.array_equal(v, R.values)
+
+
+# the entry count in C's handle only helps to choose launches: the numeric phase
+# follows C's row pointers whatever it says
+@pytest.mark.parametrize("nnz", [-(1 << 40), -1, 0, 1, 1 << 40])
+def test_entry_count_of_c(nnz):
+    import ctypes
+    A, B = rows_of([300, 5, 0, 64] * 30, 400, 1), rows_of([20, 1, 90, 7] * 100, 9000, 2)
+    dA, dB = mls.DeviceCsr.from_host(A), mls.DeviceCsr.from_host(B)
+    C = mls.symbolic(dA, dB)
+    C.values.fill_(-1.0)
+    h = mls._abi.CsrT(C.nrows, C.ncols, nnz, C.row_ptr.data_ptr(), C.col_idx.data_ptr(), C.values.data_ptr())
+    n = mls.workspace_size(dA, dB)
+    ws = mls.Workspace()
+    assert mls.lib.spgemm_numeric(ctypes.byref(dA.handle()), ctypes.byref(dB.handle()), ctypes.byref(h), ws.get(n), n,
+                                  mls.stream_handle()) == 0
+    R, _ = oracle.spgemm(A, B)
+    assert np.array_equal(C.values.cpu().numpy(), R.values)
