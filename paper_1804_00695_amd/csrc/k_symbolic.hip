@@ -23,16 +23,17 @@ namespace mls {
 
 constexpr uint32_t kEmptyKey = 0xffffffffu;
 // Words per lane loaded before they are inserted. More in a batch's count of 16
-// lanes per row, and of 8 in batches of up to kSymManyRows rows: its kernels run
-// at fewer waves per SIMD and its rows have few words, most of which one tile
-// then takes (20 Galerkin setups, 64- and 256-slot rows: 140 and 67 us with 4, 128
-// and 47 with 8 and 6; a single random product of 300k rows loses, 141 -> 159 and 83
-// -> 91 us, and past 16 lanes registers spill). With more rows a wave less per SIMD
-// costs more than the tiles save: A P of 20 grids of 24^3, 32^3 and 40^3, whole
-// symbolic phase, 330, 386 and 580 us with 4 words, 320, 457 and 620 with 8.
+// lanes per row: its rows have few words, most of which one tile then takes, and
+// its waves are few for their tables (20 Galerkin setups, 256-slot rows: 67 us
+// with 4, 47 with 6; a single random product of 300k rows loses, 83 -> 91 us, and
+// past 16 lanes registers spill). With 8 lanes 8 words cost a wave per SIMD and
+// with it more than the tiles save: A P of 20 grids of 24^3 46 us with 8, 37 with
+// 4, of 32^3 156 and 74 (one round of the resident waves or two), of 64^3 797 and
+// 677; 20 random squares of 20000 rows of 4 77 and 63. Only a batch just past a
+// whole number of rounds takes as long or longer with 4 (20 grids of 16^3 to 64^3,
+// 1.4 million rows: 248 and 268; 10 of them, 780000 rows: 163 and 174).
 template <int G, bool FILL, bool MULTI>
-constexpr int sym_batch() { return !FILL && MULTI ? (G == 8 ? 8 : (G == 16 ? 6 : 4)) : 4; }
-constexpr int kSymManyRows = 1 << 19;
+constexpr int sym_batch() { return !FILL && MULTI && G == 16 ? 6 : 4; }
 
 constexpr int kExpandSmall = 16;   // rows with at most this many words take the 16-lane kernel
 constexpr int kExpandMid = 32;     // rows with at most this many words take the 32-lane kernel
@@ -906,13 +907,6 @@ static void launch_sym_class(const Batch &b, const Sched &sc, int bin, hipStream
     if (!name[0]) snprintf(name, sizeof(name), "sym_%s_lds_G%d_C%d", FILL ? "fill" : "count", G, CAP);
     ProfScope ps(name, s);
     if (b.nprob > 1) {
-        if constexpr (G == 8 && !FILL) {
-            if (b.na > kSymManyRows) {
-                static int grid = persistent_grid(k_sym_lds<G, CAP, FILL, true, 4>, NW * kWave);
-                hipLaunchKernelGGL((k_sym_lds<G, CAP, FILL, true, 4>), dim3(grid), dim3(NW * kWave), 0, s, b, sc, bin);
-                return;
-            }
-        }
         static int grid = persistent_grid(k_sym_lds<G, CAP, FILL, true>, NW * kWave);
         hipLaunchKernelGGL((k_sym_lds<G, CAP, FILL, true>), dim3(grid), dim3(NW * kWave), 0, s, b, sc, bin);
     } else {

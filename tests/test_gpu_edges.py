@@ -666,8 +666,7 @@ def test_wide_strides(log_step):
     assert best(dB) < 2.5 * best(mls.DeviceCsr.from_host(near))
 
 
-# batches on either side of 2^19 rows, whose small count class loads its words
-# differently
+# batches on either side of 2^19 rows
 @pytest.mark.parametrize("rows", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1])
 def test_batch_rows(rows):
     As = [synth.poisson_csr(m, 300, 2.5, m) for m in (rows, 1 << 18)]

@@ -53,9 +53,15 @@ def waves(vgprs):
 
 
 # the count pass of the 256-slot class with 32 lanes per row: 6 waves per SIMD
-# for one product, 5 for batches; of the 64-slot class in batches of many rows,
-# 5; and nothing in scratch memory
+# for one product, 5 for batches; of the 64-slot class in batches, 5; and
+# nothing in scratch memory
 @pytest.mark.parametrize("lanes,slots,multi,resident", [(32, 256, 0, 6), (32, 256, 1, 5), (8, 64, 1, 5)])
 def test_count_kernel(kernels, lanes, slots, multi, resident):
     k = kernels[f"_ZN3mls9k_sym_ldsILi{lanes}ELi{slots}ELb0ELb{multi}ELi4EEEvNS_5BatchENS_5SchedEi"]
     assert waves(k[".vgpr_count"]) >= resident and k[".vgpr_spill_count"] == 0
+
+
+# and no batch takes one that leaves fewer
+def test_count_kernels_of_batches(kernels):
+    ks = [k for n, k in kernels.items() if n.startswith("_ZN3mls9k_sym_ldsILi8ELi64ELb0ELb1E")]
+    assert ks and all(waves(k[".vgpr_count"]) >= 5 for k in ks)
